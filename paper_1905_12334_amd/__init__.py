@@ -2,9 +2,12 @@
 (arXiv 1905.12334): ``quantize_e5m2``, ``gemm_fp8`` and ``sgd_update_fp16_sr``.
 
 Argument marshalling only: every function takes torch tensors that already live on the GPU,
-passes their ``data_ptr()`` and the current HIP stream through the C ABI declared in
+passes their addresses and the current HIP stream through the C ABI declared in
 ``include/mp8.h`` and returns without synchronising.  There is no CPU fallback: if the HIP
 library has not been built, loading it raises.
+
+The functions a training step calls hand their arguments to the extension module ``_binding``
+(``csrc/binding.cpp``), which checks the tensors and makes the call; ctypes serves the rest.
 """
 from __future__ import annotations
 
@@ -143,6 +146,25 @@ def _check(status: int, what: str) -> None:
         raise Mp8Error(f"{what}: {lib().mp8_status_string(status).decode()} (status {status})")
 
 
+_nat = None
+
+
+def _native():
+    """The extension module behind the functions of a training step, bound to lib()."""
+    global _nat
+    if _nat is None:
+        import torch  # noqa: F401  (the extension uses torch's libraries)
+        try:
+            from . import _binding
+        except ImportError as e:
+            raise Mp8Error(f"the extension module _binding cannot be loaded ({e}): build it with "
+                           "`python -m paper_1905_12334_amd.build` (or __graft_entry__.build())") from e
+        L = lib()
+        _binding.init(Mp8Error, {name: C.cast(getattr(L, name), C.c_void_p).value for name in EXPORTS})
+        _nat = _binding
+    return _nat
+
+
 def _ptr(t):
     return None if t is None else C.c_void_p(t.data_ptr())
 
@@ -188,19 +210,7 @@ def read_stats(stats):
 def quantize_e5m2(src, dst, dst_t=None, scale=1.0, round=RNE, flags=0, seed=0, offset=0,
                   stats=None):
     """mp8_quantize_e5m2: dst = Q(fl32(src*scale)); src [rows, cols] float32/float16."""
-    import torch
-    _dev(src, "src", (torch.float32, torch.float16))
-    _dev(dst, "dst", torch.uint8)
-    _dev(dst_t, "dst_t", torch.uint8)
-    if src.dim() != 2:
-        raise Mp8Error("src must be 2-D")
-    rows, cols = src.shape
-    if dst.numel() != rows * cols or (dst_t is not None and dst_t.numel() != rows * cols):
-        raise Mp8Error("dst / dst_t size does not match src")
-    st = lib().mp8_quantize_e5m2(_ptr(src), int(src.dtype == torch.float16), _ptr(dst), _ptr(dst_t),
-                                 rows, cols, float(scale), round, flags, seed, offset,
-                                 _ptr(stats), _stream())
-    _check(st, "mp8_quantize_e5m2")
+    (_nat or _native()).quantize_e5m2(src, dst, dst_t, scale, round, flags, seed, offset, stats)
     return dst
 
 
@@ -233,10 +243,6 @@ def quantize_e5m2_batch(items):
     _check(lib().mp8_quantize_e5m2_batch(arr, len(items), _stream()), "mp8_quantize_e5m2_batch")
 
 
-def _op_dims(op, M, N, K):
-    return {FWD: (M, N, K), BWD_DATA: (M, K, N), WGRAD: (K, N, M)}[op]
-
-
 def gemm_fp8_workspace_bytes(op, M, N, K, tile_config=0, split_k=0) -> int:
     return int(lib().mp8_gemm_fp8_workspace_bytes_tuned(op, M, N, K, tile_config, split_k))
 
@@ -247,41 +253,8 @@ def gemm_fp8(op, M, N, K, a, b, out8=None, out8_t=None, acc=None, acc_mode=0, al
     """mp8_gemm_fp8(_tuned): out[r,c] = sum_j a[r,j]*b[c,j] with the operand orientation of
     include/mp8.h.  All tensors are caller-allocated GPU tensors; workspace is a uint8/any
     tensor of at least gemm_fp8_workspace_bytes(...) bytes when that is non-zero."""
-    import torch
-    _dev(a, "a", torch.uint8)
-    _dev(b, "b", torch.uint8)
-    _dev(out8, "out8", torch.uint8)
-    _dev(out8_t, "out8_t", torch.uint8)
-    _dev(acc, "acc", torch.float32)
-    rows, cols, kc = _op_dims(op, M, N, K)
-    a_km, b_km = bool(flags & FLAG_A_CONTRACTION_MAJOR), bool(flags & FLAG_B_CONTRACTION_MAJOR)
-    if lda is None:
-        lda = rows if a_km else kc
-    if ldb is None:
-        ldb = cols if b_km else kc
-    need_a = ((kc - 1) * lda + rows if a_km else (rows - 1) * lda + kc) if rows > 0 and kc > 0 else 0
-    need_b = ((kc - 1) * ldb + cols if b_km else (cols - 1) * ldb + kc) if cols > 0 and kc > 0 else 0
-    if a.numel() < need_a:
-        raise Mp8Error("a is smaller than its shape and leading dimension require")
-    if b.numel() < need_b:
-        raise Mp8Error("b is smaller than its shape and leading dimension require")
-    for t, name in ((out8, "out8"), (out8_t, "out8_t"), (acc, "acc")):
-        if t is not None and t.numel() < rows * cols:
-            raise Mp8Error(f"{name} is smaller than rows*cols")
-    if static_scratch:
-        if workspace is not None or tile_config or split_k:
-            raise Mp8Error("static_scratch takes no workspace, tile_config or split_k")
-        st = lib().mp8_gemm_fp8_static(op, M, N, K, _ptr(a), lda, _ptr(b), ldb, float(alpha), _ptr(acc),
-                                       acc_mode, _ptr(out8), _ptr(out8_t), round, flags, seed, offset,
-                                       _ptr(stats), _stream())
-        _check(st, "mp8_gemm_fp8_static")
-        return out8
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = lib().mp8_gemm_fp8_tuned(op, M, N, K, _ptr(a), lda, _ptr(b), ldb, float(alpha), _ptr(acc),
-                                  acc_mode, _ptr(out8), _ptr(out8_t), round, flags, seed, offset,
-                                  _ptr(stats), _ptr(workspace), ws_bytes, _stream(), tile_config,
-                                  split_k)
-    _check(st, "mp8_gemm_fp8")
+    (_nat or _native()).gemm_fp8(op, M, N, K, a, b, out8, out8_t, acc, acc_mode, alpha, round, flags, seed, offset,
+                                 stats, workspace, lda, ldb, tile_config, split_k, static_scratch)
     return out8
 
 
@@ -300,28 +273,9 @@ def quantize_gemm_fwd_fp8(M, N, K, x, x8_out, w8, out8=None, out8_t=None, acc=No
                           ldw=None):
     """mp8_quantize_gemm_fwd_fp8: x8_out = Q(x * x_scale) [M, K] and out = x8_out . w8 [K, N] in one
     call (one kernel when N <= 128)."""
-    import torch
-    _dev(x, "x", torch.float32)
-    _dev(x8_out, "x8_out", torch.uint8)
-    _dev(w8, "w8", torch.uint8)
-    _dev(out8, "out8", torch.uint8)
-    _dev(out8_t, "out8_t", torch.uint8)
-    _dev(acc, "acc", torch.float32)
-    ldw = N if ldw is None else ldw
-    if x.numel() != M * K or x8_out.numel() != M * K:
-        raise Mp8Error("x and x8_out must have M*K elements")
-    if K > 0 and N > 0 and w8.numel() < (K - 1) * ldw + N:
-        raise Mp8Error("w8 is smaller than its shape and leading dimension require")
-    for t, name in ((out8, "out8"), (out8_t, "out8_t"), (acc, "acc")):
-        if t is not None and t.numel() < M * N:
-            raise Mp8Error(f"{name} is smaller than M*N")
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = lib().mp8_quantize_gemm_fwd_fp8(M, N, K, _ptr(x), float(x_scale), x_round, x_flags, x_seed,
-                                         x_offset, _ptr(x_stats), _ptr(x8_out), _ptr(w8), ldw,
-                                         float(alpha), _ptr(acc), acc_mode, _ptr(out8), _ptr(out8_t),
-                                         round, flags, seed, offset, _ptr(stats), _ptr(workspace),
-                                         ws_bytes, _stream())
-    _check(st, "mp8_quantize_gemm_fwd_fp8")
+    (_nat or _native()).quantize_gemm_fwd_fp8(M, N, K, x, x8_out, w8, out8, out8_t, acc, acc_mode, x_scale, x_round,
+                                              x_flags, x_seed, x_offset, x_stats, alpha, round, flags, seed, offset,
+                                              stats, workspace, ldw)
     return out8
 
 
@@ -339,11 +293,6 @@ def conv_buffer(prows, channels, W, dtype=None, device="cuda"):
     return store[guard:guard + prows * channels].view(prows, channels)
 
 
-def _has_guard(t, guard_elems):
-    after = t.untyped_storage().nbytes() // t.element_size() - (t.storage_offset() + t.numel())
-    return t.storage_offset() >= guard_elems and after >= guard_elems
-
-
 def conv3x3_fp8_workspace_bytes(op, B, H, W, Cin, Cout, prows=None) -> int:
     prows = conv_prows(B, H, W) if prows is None else prows
     return int(lib().mp8_conv3x3_fp8_workspace_bytes(op, B, H, W, Cin, Cout, prows))
@@ -353,29 +302,8 @@ def conv3x3_fp8(op, B, H, W, Cin, Cout, a, b, out8=None, acc=None, acc_mode=0, a
                 flags=0, seed=0, offset=0, stats=None, workspace=None, prows=None):
     """mp8_conv3x3_fp8 on padded channels-last tensors (see include/mp8.h): a / b are
     [prows, C] views with guard rows around them (conv_buffer), weights are [3, 3, Cin, Cout]."""
-    import torch
-    prows = conv_prows(B, H, W) if prows is None else prows
-    _dev(a, "a", torch.uint8)
-    _dev(b, "b", torch.uint8)
-    _dev(out8, "out8", torch.uint8)
-    _dev(acc, "acc", torch.float32)
-    ca = Cout if op == BWD_DATA else Cin
-    shapes = {FWD: (prows * Cin, 9 * Cin * Cout, prows * Cout),
-              BWD_DATA: (prows * Cout, 9 * Cin * Cout, prows * Cin),
-              WGRAD: (prows * Cin, prows * Cout, 9 * Cin * Cout)}[op]
-    if a.numel() != shapes[0] or b.numel() != shapes[1]:
-        raise Mp8Error("a / b do not have the sizes the operation implies")
-    for t, name in ((out8, "out8"), (acc, "acc")):
-        if t is not None and t.numel() < shapes[2]:
-            raise Mp8Error(f"{name} is smaller than the output")
-    if not _has_guard(a, (W + 3) * ca):
-        raise Mp8Error("the padded tensor `a` needs W+3 readable guard rows before and after "
-                       "(allocate it with conv_buffer)")
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = lib().mp8_conv3x3_fp8(op, B, H, W, Cin, Cout, prows, _ptr(a), _ptr(b), float(alpha), _ptr(acc),
-                               acc_mode, _ptr(out8), round, flags, seed, offset, _ptr(stats),
-                               _ptr(workspace), ws_bytes, _stream())
-    _check(st, "mp8_conv3x3_fp8")
+    (_nat or _native()).conv3x3_fp8(op, B, H, W, Cin, Cout, a, b, out8, acc, acc_mode, alpha, round, flags, seed,
+                                    offset, stats, workspace, prows)
     return out8
 
 
@@ -384,28 +312,9 @@ def conv3x3_wgrad_update_fp16_sr(B, H, W, Cin, Cout, x8, e8, w16, lr, inv_loss_s
                                  w_offset=0, skip_if_nonzero=None, w8_out=None, workspace=None, prows=None):
     """mp8_conv3x3_wgrad_update_fp16_sr: weight gradient of the 3x3 convolution, its rounding to
     8 bits and the update of the FP16 master weights w16 [3, 3, Cin, Cout] in one call."""
-    import torch
-    prows = conv_prows(B, H, W) if prows is None else prows
-    _dev(x8, "x8", torch.uint8)
-    _dev(e8, "e8", torch.uint8)
-    _dev(w16, "w16", (torch.float16, torch.int16, torch.uint16))
-    _dev(g8_out, "g8_out", torch.uint8)
-    _dev(w8_out, "w8_out", torch.uint8)
-    if x8.numel() != prows * Cin or e8.numel() != prows * Cout:
-        raise Mp8Error("x8 / e8 do not have the sizes the operation implies")
-    for t, name in ((w16, "w16"), (g8_out, "g8_out"), (w8_out, "w8_out")):
-        if t is not None and t.numel() != 9 * Cin * Cout:
-            raise Mp8Error(f"{name} must have 9*Cin*Cout elements")
-    if not _has_guard(x8, (W + 3) * Cin):
-        raise Mp8Error("the padded tensor x8 needs W+3 readable guard rows before and after "
-                       "(allocate it with conv_buffer)")
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = lib().mp8_conv3x3_wgrad_update_fp16_sr(B, H, W, Cin, Cout, prows, _ptr(x8), _ptr(e8), float(alpha),
-                                                _ptr(g8_out), g_round, flags, g_seed, g_offset, _ptr(stats),
-                                                _ptr(w16), float(lr), float(inv_loss_scale), w_round, w_seed,
-                                                w_offset, _ptr(skip_if_nonzero), _ptr(w8_out), _ptr(workspace),
-                                                ws_bytes, _stream())
-    _check(st, "mp8_conv3x3_wgrad_update_fp16_sr")
+    (_nat or _native()).conv3x3_wgrad_update_fp16_sr(
+        B, H, W, Cin, Cout, x8, e8, w16, lr, inv_loss_scale, g8_out, alpha, g_round, flags, g_seed, g_offset,
+        stats, w_round, w_seed, w_offset, skip_if_nonzero, w8_out, workspace, prows)
     return w16
 
 
@@ -415,32 +324,9 @@ def wgrad_momentum_fp16_sr(M, N, K, a, b, w16, velocity, lr, inv_loss_scale, mom
                            workspace=None, lda=None, ldb=None):
     """mp8_wgrad_momentum_fp16_sr: wgrad_update_fp16_sr with the momentum optimizer (velocity [K, N]
     FP32 in place) in the finishing pass."""
-    import torch
-    _dev(a, "a", torch.uint8)
-    _dev(b, "b", torch.uint8)
-    _dev(w16, "w16", (torch.float16, torch.int16, torch.uint16))
-    _dev(velocity, "velocity", torch.float32)
-    _dev(g8_out, "g8_out", torch.uint8)
-    _dev(w8_out, "w8_out", torch.uint8)
-    rows, cols, kc = _op_dims(WGRAD, M, N, K)
-    a_km, b_km = bool(flags & FLAG_A_CONTRACTION_MAJOR), bool(flags & FLAG_B_CONTRACTION_MAJOR)
-    lda = (rows if a_km else kc) if lda is None else lda
-    ldb = (cols if b_km else kc) if ldb is None else ldb
-    need_a = ((kc - 1) * lda + rows if a_km else (rows - 1) * lda + kc) if rows > 0 and kc > 0 else 0
-    need_b = ((kc - 1) * ldb + cols if b_km else (cols - 1) * ldb + kc) if cols > 0 and kc > 0 else 0
-    if a.numel() < need_a or b.numel() < need_b:
-        raise Mp8Error("a / b is smaller than its shape and leading dimension require")
-    for t, name in ((w16, "w16"), (velocity, "velocity"), (g8_out, "g8_out"), (w8_out, "w8_out")):
-        if t is not None and t.numel() != rows * cols:
-            raise Mp8Error(f"{name} must have K*N elements")
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = lib().mp8_wgrad_momentum_fp16_sr(M, N, K, _ptr(a), lda, _ptr(b), ldb, float(alpha), _ptr(g8_out),
-                                          g_round, flags, g_seed, g_offset, _ptr(stats), _ptr(w16),
-                                          _ptr(velocity), float(lr), float(inv_loss_scale), float(momentum),
-                                          float(weight_decay), w_round, w_seed, w_offset,
-                                          _ptr(skip_if_nonzero), _ptr(w8_out), _ptr(workspace), ws_bytes,
-                                          _stream())
-    _check(st, "mp8_wgrad_momentum_fp16_sr")
+    (_nat or _native()).wgrad_momentum_fp16_sr(
+        M, N, K, a, b, w16, velocity, lr, inv_loss_scale, momentum, weight_decay, g8_out, alpha, g_round, flags, g_seed, g_offset,
+        stats, w_round, w_seed, w_offset, skip_if_nonzero, w8_out, workspace, lda, ldb)
     return w16
 
 
@@ -450,32 +336,9 @@ def wgrad_adam_fp16_sr(M, N, K, a, b, w16, m, v, lr, inv_loss_scale, step, beta1
                        workspace=None, lda=None, ldb=None):
     """mp8_wgrad_adam_fp16_sr: wgrad_update_fp16_sr with ADAM (m, v [K, N] FP32 in place, step from 1)
     in the finishing pass."""
-    import torch
-    _dev(a, "a", torch.uint8)
-    _dev(b, "b", torch.uint8)
-    _dev(w16, "w16", (torch.float16, torch.int16, torch.uint16))
-    _dev(m, "m", torch.float32)
-    _dev(v, "v", torch.float32)
-    _dev(g8_out, "g8_out", torch.uint8)
-    _dev(w8_out, "w8_out", torch.uint8)
-    rows, cols, kc = _op_dims(WGRAD, M, N, K)
-    a_km, b_km = bool(flags & FLAG_A_CONTRACTION_MAJOR), bool(flags & FLAG_B_CONTRACTION_MAJOR)
-    lda = (rows if a_km else kc) if lda is None else lda
-    ldb = (cols if b_km else kc) if ldb is None else ldb
-    need_a = ((kc - 1) * lda + rows if a_km else (rows - 1) * lda + kc) if rows > 0 and kc > 0 else 0
-    need_b = ((kc - 1) * ldb + cols if b_km else (cols - 1) * ldb + kc) if cols > 0 and kc > 0 else 0
-    if a.numel() < need_a or b.numel() < need_b:
-        raise Mp8Error("a / b is smaller than its shape and leading dimension require")
-    for t, name in ((w16, "w16"), (m, "m"), (v, "v"), (g8_out, "g8_out"), (w8_out, "w8_out")):
-        if t is not None and t.numel() != rows * cols:
-            raise Mp8Error(f"{name} must have K*N elements")
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = lib().mp8_wgrad_adam_fp16_sr(M, N, K, _ptr(a), lda, _ptr(b), ldb, float(alpha), _ptr(g8_out), g_round,
-                                      flags, g_seed, g_offset, _ptr(stats), _ptr(w16), _ptr(m), _ptr(v),
-                                      float(lr), float(inv_loss_scale), float(beta1), float(beta2), float(eps),
-                                      float(weight_decay), int(step), w_round, w_seed, w_offset,
-                                      _ptr(skip_if_nonzero), _ptr(w8_out), _ptr(workspace), ws_bytes, _stream())
-    _check(st, "mp8_wgrad_adam_fp16_sr")
+    (_nat or _native()).wgrad_adam_fp16_sr(
+        M, N, K, a, b, w16, m, v, lr, inv_loss_scale, step, beta1, beta2, eps, weight_decay, g8_out, alpha, g_round, flags, g_seed, g_offset,
+        stats, w_round, w_seed, w_offset, skip_if_nonzero, w8_out, workspace, lda, ldb)
     return w16
 
 
@@ -485,29 +348,9 @@ def conv3x3_wgrad_momentum_fp16_sr(B, H, W, Cin, Cout, x8, e8, w16, velocity, lr
                                    skip_if_nonzero=None, w8_out=None, workspace=None, prows=None):
     """mp8_conv3x3_wgrad_momentum_fp16_sr: conv3x3_wgrad_update_fp16_sr with the momentum optimizer
     (velocity [3, 3, Cin, Cout] FP32 in place) in the finishing pass."""
-    import torch
-    prows = conv_prows(B, H, W) if prows is None else prows
-    _dev(x8, "x8", torch.uint8)
-    _dev(e8, "e8", torch.uint8)
-    _dev(w16, "w16", (torch.float16, torch.int16, torch.uint16))
-    _dev(velocity, "velocity", torch.float32)
-    _dev(g8_out, "g8_out", torch.uint8)
-    _dev(w8_out, "w8_out", torch.uint8)
-    if x8.numel() != prows * Cin or e8.numel() != prows * Cout:
-        raise Mp8Error("x8 / e8 do not have the sizes the operation implies")
-    for t, name in ((w16, "w16"), (velocity, "velocity"), (g8_out, "g8_out"), (w8_out, "w8_out")):
-        if t is not None and t.numel() != 9 * Cin * Cout:
-            raise Mp8Error(f"{name} must have 9*Cin*Cout elements")
-    if not _has_guard(x8, (W + 3) * Cin):
-        raise Mp8Error("the padded tensor x8 needs W+3 readable guard rows before and after "
-                       "(allocate it with conv_buffer)")
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = lib().mp8_conv3x3_wgrad_momentum_fp16_sr(
-        B, H, W, Cin, Cout, prows, _ptr(x8), _ptr(e8), float(alpha), _ptr(g8_out), g_round, flags, g_seed,
-        g_offset, _ptr(stats), _ptr(w16), _ptr(velocity), float(lr), float(inv_loss_scale), float(momentum),
-        float(weight_decay), w_round, w_seed, w_offset, _ptr(skip_if_nonzero), _ptr(w8_out), _ptr(workspace),
-        ws_bytes, _stream())
-    _check(st, "mp8_conv3x3_wgrad_momentum_fp16_sr")
+    (_nat or _native()).conv3x3_wgrad_momentum_fp16_sr(
+        B, H, W, Cin, Cout, x8, e8, w16, velocity, lr, inv_loss_scale, momentum, weight_decay, g8_out, alpha, g_round, flags, g_seed, g_offset,
+        stats, w_round, w_seed, w_offset, skip_if_nonzero, w8_out, workspace, prows)
     return w16
 
 
@@ -537,36 +380,15 @@ def gemm_tile_config_lds_bytes(tile_config, epi):
 def sgd_update_fp16_sr(w16, g8, lr, inv_loss_scale, round=SR, seed=0, offset=0,
                        skip_if_nonzero=None, w8_out=None, stats=None):
     """mp8_sgd_update_fp16_sr: in-place SGD step on float16 master weights from 8-bit grads."""
-    import torch
-    _dev(w16, "w16", (torch.float16, torch.int16, torch.uint16))
-    _dev(g8, "g8", torch.uint8)
-    _dev(w8_out, "w8_out", torch.uint8)
-    n = w16.numel()
-    if g8.numel() != n or (w8_out is not None and w8_out.numel() != n):
-        raise Mp8Error("g8 / w8_out size does not match w16")
-    st = lib().mp8_sgd_update_fp16_sr(_ptr(w16), _ptr(g8), n, float(lr), float(inv_loss_scale),
-                                      round, seed, offset, _ptr(skip_if_nonzero), _ptr(w8_out),
-                                      _ptr(stats), _stream())
-    _check(st, "mp8_sgd_update_fp16_sr")
+    (_nat or _native()).sgd_update_fp16_sr(w16, g8, lr, inv_loss_scale, round, seed, offset, skip_if_nonzero, w8_out, stats)
     return w16
 
 
 def sgd_momentum_fp16_sr(w16, velocity, g8, lr, inv_loss_scale, momentum, weight_decay=0.0, round=SR,
                          seed=0, offset=0, skip_if_nonzero=None, w8_out=None, stats=None):
     """mp8_sgd_momentum_fp16_sr: momentum SGD with L2 regularisation, FP32 velocity in place."""
-    import torch
-    _dev(w16, "w16", (torch.float16, torch.int16, torch.uint16))
-    _dev(velocity, "velocity", torch.float32)
-    _dev(g8, "g8", torch.uint8)
-    _dev(w8_out, "w8_out", torch.uint8)
-    n = w16.numel()
-    if g8.numel() != n or velocity.numel() != n or (w8_out is not None and w8_out.numel() != n):
-        raise Mp8Error("velocity / g8 / w8_out size does not match w16")
-    st = lib().mp8_sgd_momentum_fp16_sr(_ptr(w16), _ptr(velocity), _ptr(g8), n, float(lr),
-                                        float(inv_loss_scale), float(momentum), float(weight_decay),
-                                        round, seed, offset, _ptr(skip_if_nonzero), _ptr(w8_out),
-                                        _ptr(stats), _stream())
-    _check(st, "mp8_sgd_momentum_fp16_sr")
+    (_nat or _native()).sgd_momentum_fp16_sr(w16, velocity, g8, lr, inv_loss_scale, momentum, weight_decay, round, seed,
+                                             offset, skip_if_nonzero, w8_out, stats)
     return w16
 
 
@@ -575,30 +397,9 @@ def wgrad_update_fp16_sr(M, N, K, a, b, w16, lr, inv_loss_scale, g8_out=None, al
                          skip_if_nonzero=None, w8_out=None, workspace=None, lda=None, ldb=None):
     """mp8_wgrad_update_fp16_sr: weight-gradient GEMM, its rounding to 8 bits and the update of the
     FP16 master weights w16 [K, N] in one call (operands as gemm_fp8 with op = WGRAD)."""
-    import torch
-    _dev(a, "a", torch.uint8)
-    _dev(b, "b", torch.uint8)
-    _dev(w16, "w16", (torch.float16, torch.int16, torch.uint16))
-    _dev(g8_out, "g8_out", torch.uint8)
-    _dev(w8_out, "w8_out", torch.uint8)
-    rows, cols, kc = _op_dims(WGRAD, M, N, K)
-    a_km, b_km = bool(flags & FLAG_A_CONTRACTION_MAJOR), bool(flags & FLAG_B_CONTRACTION_MAJOR)
-    lda = (rows if a_km else kc) if lda is None else lda
-    ldb = (cols if b_km else kc) if ldb is None else ldb
-    need_a = ((kc - 1) * lda + rows if a_km else (rows - 1) * lda + kc) if rows > 0 and kc > 0 else 0
-    need_b = ((kc - 1) * ldb + cols if b_km else (cols - 1) * ldb + kc) if cols > 0 and kc > 0 else 0
-    if a.numel() < need_a or b.numel() < need_b:
-        raise Mp8Error("a / b is smaller than its shape and leading dimension require")
-    for t, name in ((w16, "w16"), (g8_out, "g8_out"), (w8_out, "w8_out")):
-        if t is not None and t.numel() != rows * cols:
-            raise Mp8Error(f"{name} must have K*N elements")
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = lib().mp8_wgrad_update_fp16_sr(M, N, K, _ptr(a), lda, _ptr(b), ldb, float(alpha), _ptr(g8_out),
-                                        g_round, flags, g_seed, g_offset, _ptr(stats), _ptr(w16), float(lr),
-                                        float(inv_loss_scale), w_round, w_seed, w_offset,
-                                        _ptr(skip_if_nonzero), _ptr(w8_out), _ptr(workspace), ws_bytes,
-                                        _stream())
-    _check(st, "mp8_wgrad_update_fp16_sr")
+    (_nat or _native()).wgrad_update_fp16_sr(
+        M, N, K, a, b, w16, lr, inv_loss_scale, g8_out, alpha, g_round, flags, g_seed, g_offset,
+        stats, w_round, w_seed, w_offset, skip_if_nonzero, w8_out, workspace, lda, ldb)
     return w16
 
 
@@ -606,20 +407,8 @@ def adam_fp16_sr(w16, m, v, g8, lr, inv_loss_scale, step, beta1=0.9, beta2=0.999
                  weight_decay=0.0, round=SR, seed=0, offset=0, skip_if_nonzero=None, w8_out=None,
                  stats=None):
     """mp8_adam_fp16_sr: ADAM with L2 regularisation, FP32 moments in place (step counts from 1)."""
-    import torch
-    _dev(w16, "w16", (torch.float16, torch.int16, torch.uint16))
-    _dev(m, "m", torch.float32)
-    _dev(v, "v", torch.float32)
-    _dev(g8, "g8", torch.uint8)
-    _dev(w8_out, "w8_out", torch.uint8)
-    n = w16.numel()
-    if g8.numel() != n or m.numel() != n or v.numel() != n or (w8_out is not None and w8_out.numel() != n):
-        raise Mp8Error("m / v / g8 / w8_out size does not match w16")
-    st = lib().mp8_adam_fp16_sr(_ptr(w16), _ptr(m), _ptr(v), _ptr(g8), n, float(lr), float(inv_loss_scale),
-                                float(beta1), float(beta2), float(eps), float(weight_decay), int(step),
-                                round, seed, offset, _ptr(skip_if_nonzero), _ptr(w8_out), _ptr(stats),
-                                _stream())
-    _check(st, "mp8_adam_fp16_sr")
+    (_nat or _native()).adam_fp16_sr(w16, m, v, g8, lr, inv_loss_scale, step, beta1, beta2, eps, weight_decay, round, seed,
+                                     offset, skip_if_nonzero, w8_out, stats)
     return w16
 
 

@@ -1,0 +1,37 @@
+"""The extension module behind the package's functions refuses what it must before anything is
+enqueued (no GPU needed: every call here ends in a check)."""
+import pytest
+import torch
+
+import paper_1905_12334_amd as mp8
+
+
+def test_every_call_refuses_tensors_that_are_not_on_the_gpu():
+    f, u, h = torch.zeros((128, 128)), torch.zeros((128, 128), dtype=torch.uint8), torch.zeros(128 * 128, dtype=torch.float16)
+    calls = [
+        lambda: mp8.quantize_e5m2(f, u),
+        lambda: mp8.gemm_fp8(mp8.FWD, 128, 128, 128, u, u, out8=u),
+        lambda: mp8.gemm_fp8_static(mp8.FWD, 128, 128, 128, u, u, out8=u),
+        lambda: mp8.quantize_gemm_fwd_fp8(128, 128, 128, f, u, u, out8=u),
+        lambda: mp8.conv3x3_fp8(mp8.FWD, 1, 4, 4, 128, 128, u, u, out8=u),
+        lambda: mp8.wgrad_update_fp16_sr(128, 128, 128, u, u, h, 0.1, 1.0),
+        lambda: mp8.wgrad_momentum_fp16_sr(128, 128, 128, u, u, h, f, 0.1, 1.0, 0.9),
+        lambda: mp8.wgrad_adam_fp16_sr(128, 128, 128, u, u, h, f, f, 0.1, 1.0, 1),
+        lambda: mp8.conv3x3_wgrad_update_fp16_sr(1, 4, 4, 128, 128, u, u, h, 0.1, 1.0),
+        lambda: mp8.conv3x3_wgrad_momentum_fp16_sr(1, 4, 4, 128, 128, u, u, h, f, 0.1, 1.0, 0.9),
+        lambda: mp8.sgd_update_fp16_sr(h, u, 0.1, 1.0),
+        lambda: mp8.sgd_momentum_fp16_sr(h, f, u, 0.1, 1.0, 0.9),
+        lambda: mp8.adam_fp16_sr(h, f, f, u, 0.1, 1.0, 1),
+    ]
+    for call in calls:
+        with pytest.raises(mp8.Mp8Error, match="must be a GPU tensor"):
+            call()
+
+
+def test_arguments_of_the_wrong_kind_raise():
+    with pytest.raises(TypeError):
+        mp8.gemm_fp8(mp8.FWD, 1, 1, 1, None, None)
+    with pytest.raises(TypeError):
+        mp8.quantize_e5m2([1.0], None)
+    with pytest.raises(TypeError):
+        mp8.gemm_fp8(mp8.FWD, "1", 1, 1, None, None)
