@@ -132,8 +132,10 @@ mp8_status mp8_quantize_e5m2_batch(const mp8_quantize_item *items, int count, vo
  *              acc_mode 2, for out8_t, and when cols is not a multiple of 16;
  *              mp8_gemm_fp8_workspace_bytes(op, M, N, K) is enough in every case.  A call
  *              that does not need it accepts NULL.
- * Any contraction length >= 1 and any rows/cols >= 1 are accepted (ragged shapes run on a
- * slower kernel); a zero dimension is valid and does nothing.  Partial sums of a split
+ * Any contraction length >= 1 and any rows/cols >= 1 are accepted; a zero dimension is valid and
+ * does nothing.  A contraction that is not a multiple of 128, and operands that are not 16-byte
+ * aligned, never need a workspace; with the one the query asks for they may run faster (a split
+ * contraction).  Partial sums of a split
  * contraction are combined in FP32, in a fixed order, before the single rounding, so results
  * are bit-reproducible run to run.
  */
@@ -144,7 +146,7 @@ mp8_status mp8_gemm_fp8(mp8_op op, int64_t M, int64_t N, int64_t K, const uint8_
                         void *workspace, size_t workspace_bytes, void *stream);
 
 /* Upper bound of the scratch mp8_gemm_fp8 can need for this shape, whatever the options
- * (0 for shapes that take the generic kernel). */
+ * (0 for shapes that are never split). */
 size_t mp8_gemm_fp8_workspace_bytes(mp8_op op, int64_t M, int64_t N, int64_t K);
 
 /*
@@ -187,8 +189,8 @@ mp8_status mp8_gemm_fp8_tuned(mp8_op op, int64_t M, int64_t N, int64_t K, const 
 size_t mp8_gemm_fp8_workspace_bytes_tuned(mp8_op op, int64_t M, int64_t N, int64_t K,
                                           int tile_config, int split_k);
 /* Host only: which kernel an aligned call with these arguments would take -- *tile_out the tile
- * configuration (1-based; 0 = the any-shape kernel), *splits_out the number of contraction
- * slices.  For tests and tuning. */
+ * configuration (1-based), *splits_out the number of contraction slices; 0 and 1 for contractions
+ * that are not a multiple of 128 and other shapes for which the call makes a choice of its own.  For tests and tuning. */
 mp8_status mp8_gemm_fp8_plan(mp8_op op, int64_t M, int64_t N, int64_t K, int flags, int tile_config,
                              int split_k, int *tile_out, int *splits_out);
 int mp8_gemm_num_tile_configs(void);
@@ -300,7 +302,7 @@ mp8_status mp8_adam_fp16_sr(uint16_t *w16, float *m, float *v, const uint8_t *g8
  *   g8_out     nullable [K, N]: the 8-bit weight gradient, if the caller wants to keep it
  *   workspace  at least mp8_gemm_fp8_workspace_bytes(MP8_WGRAD, M, N, K) bytes, always needed
  *              when that is non-zero
- * Shapes that only the any-shape GEMM kernel takes run as the two separate launches and need
+ * Shapes without a finishing pass run as the two separate launches and need
  * g8_out (MP8_ERR_UNSUPPORTED without it).  A weight gradient whose contraction is not split
  * rounds in the GEMM's own epilogue; it is then followed by the update kernel instead of being
  * forced through a finishing pass (cheaper: no FP32 copy of the result is written), with the codes

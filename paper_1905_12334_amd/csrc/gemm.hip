@@ -12,6 +12,7 @@
 //   gemm_shortk.hpp   contractions of one or two stages (all start-up and epilogue)
 //   gemm_wavek.hpp    small outputs with long contractions (contraction divided among waves)
 //   gemm_wave128.hpp  about one 128x128 tile per CU and a long contraction (every wave the whole tile)
+//   gemm_any.hpp      row lengths, leading dimensions, contractions that are not multiples of 16
 //   gemm_finish.hpp   second pass for split contractions and unfused epilogues, optionally with
 //                     the master-weight update; the any-shape fallback kernel
 // Split contraction, FP32 / transposed outputs, ragged column counts: the MFMA kernels write
@@ -28,6 +29,7 @@
 #include <type_traits>
 
 #include "../../include/mp8.h"
+#include "gemm_any.hpp"
 #include "gemm_common.hpp"
 #include "gemm_finish.hpp"
 #include "gemm_mfma.hpp"
@@ -118,8 +120,15 @@ constexpr int kNumTiles = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
 constexpr int kCUs = 256;
 constexpr int kMaxSplits = 64;
 
+// gemm_any_kernel by operand layout (row-major, b contraction-major, both) and epilogue: the FP32
+// tiles of a split contraction, or everything
+static void (*const kAny[3][2])(const GemmArgs) = {
+    {gemm_any_kernel<EPI_PARTIAL, false, false>, gemm_any_kernel<EPI_FULL, false, false>},
+    {gemm_any_kernel<EPI_PARTIAL, false, true>, gemm_any_kernel<EPI_FULL, false, true>},
+    {gemm_any_kernel<EPI_PARTIAL, true, true>, gemm_any_kernel<EPI_FULL, true, true>}};
+
 struct Plan {
-    bool mfma;
+    bool mfma;   // one of kTiles
     int tile;    // index into kTiles
     int splits;
     int tiles_m, tiles_n;
@@ -146,7 +155,9 @@ static Plan make_plan(int64_t rows, int64_t cols, int64_t kc, int tile_config, i
                       int layout = 0,      // bit 0: a contraction-major, bit 1: b
                       bool conv = false) { // a convolution: only the tiles with convolution addressing
     Plan pl{};
-    pl.mfma = (kc % BK) == 0 && kc > 0;
+    // A contraction that ends with an incomplete stage is multiplied by the same kernels (automatic
+    // choice only) as long as whole 16-byte chunks of its row-major operands exist.
+    pl.mfma = kc > 0 && (kc % BK == 0 || (tile_config == 0 && !conv && (layout == 3 || (kc & 15) == 0)));
     // contraction-major operands are fetched in 16-row chunks, by the tiles built for them
     if ((layout & 1) && (rows & 15) != 0) pl.mfma = false;
     if ((layout & 2) && (cols & 15) != 0) pl.mfma = false;
@@ -156,13 +167,13 @@ static Plan make_plan(int64_t rows, int64_t cols, int64_t kc, int tile_config, i
     const bool tn = layout != 0;
     if (layout == 0 && tile_config > 0 && kTiles[tile_config - 1].kernel[0] == nullptr) pl.mfma = false;
     if (tile_config > 0 && kTiles[tile_config - 1].max_ksteps > 0 &&
-        (tn || kc / BK > kTiles[tile_config - 1].max_ksteps))
+        (tn || (kc + BK - 1) / BK > kTiles[tile_config - 1].max_ksteps))
         pl.mfma = false;
     if (!pl.mfma) {
         pl.splits = 1;
         return pl;
     }
-    const int ksteps = (int)(kc / BK);
+    const int ksteps = (int)((kc + BK - 1) / BK);
     auto count = [&](int t) {
         return ((rows + kTiles[t].bm - 1) / kTiles[t].bm) * ((cols + kTiles[t].bn - 1) / kTiles[t].bn);
     };
@@ -223,6 +234,28 @@ static Plan make_plan(int64_t rows, int64_t cols, int64_t kc, int tile_config, i
     return pl;
 }
 
+// Can gemm_any_kernel take it?  (Lane offsets of a tile stay within 32 bits; an edge chunk is read as
+// the last sixteen bytes of its row, so such rows must have sixteen.)
+static bool any_kernel_takes(int64_t rows, int64_t cols, int64_t kc, int64_t lda, int64_t ldb, int layout) {
+    return kc >= 16 && (!(layout & 1) || rows >= 16) && (!(layout & 2) || cols >= 16) && lda < (1 << 24) &&
+           ldb < (1 << 24) && (rows + 63) / 64 * ((cols + 63) / 64) < 0x1000000;
+}
+
+// Contraction slices of gemm_any_kernel: two workgroups fit a CU, so up to 512 run at once, and a
+// slice should keep two stages for each of the four waves.  The finishing pass costs about as much
+// as ANY_FINISH_STAGES stages of one wave, so a split must save more than that.
+constexpr int64_t ANY_FINISH_STAGES = 24;
+static Plan any_plan(int64_t rows, int64_t cols, int64_t kc) {
+    Plan pl{};
+    pl.tiles_m = (int)((rows + 63) / 64);
+    pl.tiles_n = (int)((cols + 63) / 64);
+    const int64_t nt = (int64_t)pl.tiles_m * pl.tiles_n, ksteps = (kc + BK - 1) / BK;
+    int64_t s = std::max<int64_t>(1, std::min<int64_t>({2 * kCUs / nt, ksteps / 8, (int64_t)kMaxSplits}));
+    if (ksteps * (s - 1) <= ANY_FINISH_STAGES * s) s = 1;
+    pl.splits = (int)s;
+    return pl;
+}
+
 // Upper bound of the workspace: one FP32 tile set per contraction slice.  (The MFMA kernel
 // finishes its tiles itself only for an unsplit contraction, a row length that is a multiple
 // of 16 and no FP32 / transposed output; otherwise it writes FP32 tiles and the finishing
@@ -260,8 +293,15 @@ extern "C" size_t mp8_gemm_fp8_workspace_bytes_tuned(mp8_op op, int64_t M, int64
     op_dims(op, M, N, K, rows, cols, kc);
     // enough for every operand layout
     size_t need = 0;
-    for (int layout : {0, 2, 3})
-        need = std::max(need, plan_workspace(make_plan(rows, cols, kc, tile_config, split_k, layout), rows, cols));
+    for (int layout : {0, 2, 3}) {
+        const Plan pl = make_plan(rows, cols, kc, tile_config, split_k, layout);
+        size_t one = plan_workspace(pl, rows, cols);
+        if (!pl.mfma && tile_config == 0) {  // a split contraction of gemm_any_kernel
+            const int splits = any_plan(rows, cols, kc).splits;
+            one = splits > 1 ? (size_t)splits * (size_t)rows * (size_t)cols * sizeof(float) : 0;
+        }
+        need = std::max(need, one);
+    }
     return need;
 }
 
@@ -275,7 +315,9 @@ extern "C" mp8_status mp8_gemm_fp8_plan(mp8_op op, int64_t M, int64_t N, int64_t
     if (atn && !btn) return MP8_ERR_UNSUPPORTED;
     int64_t rows, cols, kc;
     op_dims(op, M, N, K, rows, cols, kc);
-    const Plan pl = make_plan(rows, cols, kc, tile_config, split_k, (atn ? 1 : 0) | (btn ? 2 : 0));
+    Plan pl{};
+    pl.splits = 1;  // (a contraction with an incomplete stage: the call's own choice, reported as 0)
+    if (kc % BK == 0) pl = make_plan(rows, cols, kc, tile_config, split_k, (atn ? 1 : 0) | (btn ? 2 : 0));
     if (tile_out) *tile_out = pl.mfma ? pl.tile + 1 : 0;
     if (splits_out) *splits_out = pl.splits;
     return MP8_OK;
@@ -298,9 +340,10 @@ static mp8_status launch_mfma(GemmArgs ga, const Epilogue &ep, const Plan &pl, i
     const int acc_mode = ep.acc_mode;
     float *acc = ep.acc;
     uint8_t *out8 = ep.out8, *out8_t = ep.out8_t;
-    // Fused epilogue or two passes?  (The master-weight update lives in the finishing pass.)
-    const bool two_pass = pl.splits > 1 || (cols & 15) != 0 || acc_mode != 0 || out8_t != nullptr ||
-                          upd != nullptr;
+    // Fused epilogue or two passes?  (The master-weight update lives in the finishing pass;
+    // gemm_any_kernel's own epilogue does everything else.)
+    const bool two_pass = pl.splits > 1 || upd != nullptr ||
+                          (pl.mfma && ((cols & 15) != 0 || acc_mode != 0 || out8_t != nullptr));
     float *partial = nullptr;
     Epilogue fin = ep;  // what the finishing kernel applies
     fin.want_codes = upd != nullptr;
@@ -310,7 +353,7 @@ static mp8_status launch_mfma(GemmArgs ga, const Epilogue &ep, const Plan &pl, i
             fin.acc = nullptr;
             fin.acc_mode = 0;
         } else {
-            const size_t need = plan_workspace(pl, rows, cols);
+            const size_t need = (size_t)pl.splits * (size_t)rows * (size_t)cols * sizeof(float);
             if (workspace == nullptr || workspace_bytes < need) return MP8_ERR_WORKSPACE;
             partial = (float *)workspace;
         }
@@ -321,7 +364,9 @@ static mp8_status launch_mfma(GemmArgs ga, const Epilogue &ep, const Plan &pl, i
 
     ga.rows = rows;
     ga.cols = cols;
-    ga.ksteps = (int)(kc / BK);
+    ga.ksteps = (int)((kc + BK - 1) / BK);
+    ga.tail = (int)(kc % BK);
+    ga.kc = kc;
     ga.splits = pl.splits;
     ga.tiles_m = pl.tiles_m;
     ga.tiles_n = pl.tiles_n;
@@ -334,9 +379,9 @@ static mp8_status launch_mfma(GemmArgs ga, const Epilogue &ep, const Plan &pl, i
     ga.partial = partial;
     ga.ep = ep;
     const int epi = two_pass ? EPI_PARTIAL
-                             : (ep.sr || ep.sat || ep.stats != nullptr || out8 == nullptr) ? EPI_FULL
-                                                                                            : EPI_RNE;
-    const size_t dyn_lds = (size_t)kTiles[pl.tile].lds_per_stage * (size_t)ga.ksteps;
+                             : (ep.sr || ep.sat || ep.stats != nullptr || out8 == nullptr || !pl.mfma) ? EPI_FULL
+                                                                                                        : EPI_RNE;
+    const size_t dyn_lds = pl.mfma ? (size_t)kTiles[pl.tile].lds_per_stage * (size_t)ga.ksteps : 0;
     hipLaunchKernelGGL(pick[epi], dim3((unsigned)nblocks), dim3(256), dyn_lds, s, ga);
     if (hipGetLastError() != hipSuccess) return MP8_ERR_HIP;
     if (two_pass) {
@@ -401,23 +446,45 @@ static mp8_status gemm_impl(mp8_op op, int64_t M, int64_t N, int64_t K, const ui
     ep.cols = cols;
     hipStream_t s = (hipStream_t)stream;
 
-    Plan pl = make_plan(rows, cols, kc, tile_config, split_k, (atn ? 1 : 0) | (btn ? 2 : 0));
-    // the MFMA kernel wants 16-byte aligned rows and 32-bit offsets inside a 256-row tile
+    const int layout = (atn ? 1 : 0) | (btn ? 2 : 0);
+    Plan pl = make_plan(rows, cols, kc, tile_config, split_k, layout);
+    // the direct-to-LDS kernels want 16-byte aligned rows and 32-bit offsets inside a 256-row tile
     const bool aligned = (((uintptr_t)a | (uintptr_t)b) & 15u) == 0 && (lda & 15) == 0 &&
                          (ldb & 15) == 0 && lda < (1 << 24) && ldb < (1 << 24);
     if (pl.mfma && !aligned) {
         if (tile_config > 0) return MP8_ERR_ALIGNMENT;
         pl.mfma = false;
-        pl.splits = 1;
     }
     if (tile_config > 0 && !pl.mfma) return MP8_ERR_UNSUPPORTED;
+    auto has_workspace = [&](int splits) {
+        return workspace != nullptr && workspace_bytes >= (size_t)splits * (size_t)rows * (size_t)cols * sizeof(float);
+    };
+    // A contraction with an incomplete stage never needs a workspace: without one for the two-pass
+    // form it runs unsplit on the kernel whose epilogue does everything.
+    if (pl.mfma && kc % BK != 0 && (pl.splits > 1 || (cols & 15) != 0 || acc_mode != 0 || out8_t != nullptr || upd != nullptr) &&
+        !has_workspace(pl.splits))
+        pl.mfma = false;
 
+    if (!pl.mfma && any_kernel_takes(rows, cols, kc, lda, ldb, layout)) {
+        pl = any_plan(rows, cols, kc);
+        if (!has_workspace(pl.splits)) pl.splits = 1;
+        // (the update goes with the finishing pass of a split contraction only: otherwise two launches)
+        if (upd != nullptr && pl.splits == 1) return MP8_ERR_UNSUPPORTED;
+        GemmArgs ga{};
+        ga.a = a;
+        ga.b = b;
+        ga.lda = lda;
+        ga.ldb = ldb;
+        void (*const *kern)(const GemmArgs) = kAny[atn ? 2 : btn ? 1 : 0];
+        void (*const pick[3])(const GemmArgs) = {kern[0], nullptr, kern[1]};
+        return launch_mfma(ga, ep, pl, kc, pick, workspace, workspace_bytes, s, upd, validate_only);
+    }
     if (!pl.mfma || kc == 0) {
         if (upd != nullptr) return MP8_ERR_UNSUPPORTED;
         if (validate_only) return MP8_OK;
         int64_t blocks = std::min<int64_t>((rows * cols + 255) / 256, 1 << 20);
         hipLaunchKernelGGL(gemm_generic_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a, lda, b,
-                           ldb, kc, (atn ? 1 : 0) | (btn ? 2 : 0), ep);
+                           ldb, kc, layout, ep);
         return hipGetLastError() == hipSuccess ? MP8_OK : MP8_ERR_HIP;
     }
 
@@ -510,7 +577,7 @@ namespace mp8 {
 // body the three optimizer variants share.  `hook` is the rule as the finishing pass applies it,
 // `update_from(codes)` launches the same rule's stand-alone kernel on codes in memory.  Three ways,
 // all with the same results: the GEMM with its own epilogue followed by the update kernel (unsplit
-// contractions, any-shape kernel, and a skip flag that lives inside `stats` -- see
+// contractions, shapes without a finishing pass, and a skip flag that lives inside `stats` -- see
 // flag_inside_stats), or the update inside the finishing pass of a split contraction.  Whatever
 // can be checked is checked before the first launch.
 template <class UpdateFrom>
@@ -536,7 +603,7 @@ static mp8_status wgrad_with_update(int64_t M, int64_t N, int64_t K, const uint8
                                     g_round, flags, g_seed, g_offset, stats, workspace, workspace_bytes,
                                     stream, 0, 0, &hook);
     if (st != MP8_ERR_UNSUPPORTED || g8_out == nullptr) return st;
-    // shapes that only the any-shape kernel takes: two launches through the 8-bit gradient
+    // no finishing pass to carry the update: two launches through the 8-bit gradient
     return two_launches(g8_out, workspace, workspace_bytes);
 }
 
@@ -677,9 +744,14 @@ extern "C" mp8_status mp8_gemm_fp8_static(mp8_op op, int64_t M, int64_t N, int64
                                           mp8_stats *stats, void *stream) {
     using namespace mp8;
     // the same bound the workspace query gives the callers of mp8_gemm_fp8
-    if (M > 0 && N > 0 && K > 0 && (int)op >= 0 && (int)op <= 2 &&
-        mp8_gemm_fp8_workspace_bytes(op, M, N, K) > kStaticScratchBytes)
-        return MP8_ERR_WORKSPACE;
+    if (M > 0 && N > 0 && K > 0 && (int)op >= 0 && (int)op <= 2) {
+        int64_t rows, cols, kc;
+        op_dims(op, M, N, K, rows, cols, kc);
+        // (a contraction with an incomplete stage runs without a workspace where this one is too small)
+        if (kc % BK == 0 &&
+            mp8_gemm_fp8_workspace_bytes(op, M, N, K) > kStaticScratchBytes)
+            return MP8_ERR_WORKSPACE;
+    }
     void *ws = nullptr;
     const mp8_status ss = static_scratch(&ws);
     if (ss != MP8_OK) return ss;

@@ -1,0 +1,226 @@
+// GEMM kernel on the matrix cores for shapes that the direct-to-LDS kernels cannot take: row
+// lengths, leading dimensions or contraction lengths that are not multiples of 16.
+#pragma once
+
+#include "gemm_common.hpp"
+
+namespace mp8 {
+
+// Direct-to-LDS loads want 16-byte aligned rows and whole chunks, which a matrix with, say, 1000
+// columns does not have.  This kernel fetches its operands through registers instead: sixteen
+// bytes per lane from any address (the hardware takes unaligned vector loads), zeros in place of
+// what lies beyond the contraction, then a 16-byte write into the same swizzled slab images as the
+// other kernels.  64x64 tile, and as in gemm_wavek_kernel the contraction is divided among the four
+// waves: every wave multiplies the whole tile for every fourth stage, from a slab pair of its
+// own, so that nothing in the loop waits for another wave.  The loads of a wave's next stage are
+// issued as soon as its current one has left the registers (64 of them), before the multiplications.
+// Two workgroups fit a CU (70 KB of LDS).  The epilogue takes any row length, so an unsplit call
+// needs no second pass and no workspace.  What bounds it: a 64x64 tile pulls 128 bytes per clock and CU
+// at the full matrix rate, twice what the path from L2 carries; unaligned rows cost more requests.
+// One thread per output element, the form these shapes had before, took 639 us for each GEMM of a
+// layer of 256 x 1000 x 2048; this kernel takes 7 - 9 us.
+// Needs a contraction of at least 16, and 16 rows / columns of a contraction-major operand (an edge
+// chunk is read as the last 16 bytes of its row and shifted into place).
+template <int EPI, bool ATN, bool BTN>
+__global__ __launch_bounds__(256, 2) void gemm_any_kernel(const GemmArgs p) {
+    static_assert(BTN || !ATN, "a alone contraction-major is not built");
+    constexpr int T = 64, SLAB = T * BK, WAVE_LDS = 2 * SLAB;
+    constexpr int RED_LD = T + 4;  // floats per row of a tile parked for the reduction
+    constexpr int RED_BYTES = 4 * T * RED_LD * 4;
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[RED_BYTES > 4 * WAVE_LDS ? RED_BYTES : 4 * WAVE_LDS];
+
+    int split, tm, tn;
+    map_block(p, split, tm, tn);
+    split = __builtin_amdgcn_readfirstlane(split);
+    tm = __builtin_amdgcn_readfirstlane(tm);
+    tn = __builtin_amdgcn_readfirstlane(tn);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t row0 = (int64_t)tm * T, col0 = (int64_t)tn * T;
+    const int per = p.ks_per, extra = p.ks_extra;
+    const int ks_begin = split * per + (split < extra ? split : extra);
+    const int ks_end = ks_begin + per + (split < extra ? 1 : 0);
+
+    // One operand: its tile's first row `first` of `limit`, leading dimension ld.
+    //   row-major: load q brings tile rows 8q .. 8q+7, lane l sixteen contraction bytes of row
+    //   8q + l/8, chunk l%8; rows beyond the matrix are clamped to its last row (never stored)
+    //   contraction-major: load q brings contraction rows 16q .. 16q+15 of 64 bytes, lane l chunk l%4
+    //   of row 16q + l/4; a chunk that would leave the row is read as its last sixteen bytes and
+    //   shifted down by `shift` bytes
+    struct Operand {
+        const uint8_t *base;
+        int64_t kstep;
+        uint32_t off[8];
+        int shift;
+        bool edge;
+    };
+    auto operand = [&](bool km, const uint8_t *x, int64_t ld, int64_t first, int64_t limit) {
+        Operand o;
+        o.kstep = km ? BK * ld : BK;
+        o.shift = 0;
+        o.edge = km && first + T > limit;
+        if (km) {
+            o.base = uniform_ptr(x + first);
+            const int64_t m = 16 * (lane & 3), last = limit - 16 - first;
+            o.shift = m > last ? (int)(m - last < 15 ? m - last : 15) : 0;
+            // (last is negative in a tile narrower than sixteen columns: the sum is not)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) o.off[q] = (uint32_t)((16 * q + (lane >> 2)) * ld + (m > last ? last : m) + 16);
+        } else {
+            o.base = uniform_ptr(x + first * ld);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                int64_t r = 8 * q + (lane >> 3);
+                r = first + r < limit ? r : limit - 1 - first;
+                o.off[q] = (uint32_t)(r * ld) + 16 * (lane & 7) + 16;
+            }
+        }
+        o.base -= 16;  // (what is subtracted from a lane offset leaves it non-negative: they are unsigned)
+        return o;
+    };
+    const Operand oa = operand(ATN, p.a, p.lda, row0, p.rows), ob = operand(BTN, p.b, p.ldb, col0, p.cols);
+
+    // (address space 1: the base pointers have been through integers, and the compiler has to know
+    // that they point to global memory)
+    using Unaligned16 = u32x4 __attribute__((aligned(1)));
+    auto load16 = [](const uint8_t *base, uint32_t off) {
+        const auto *g = (const __attribute__((address_space(1))) uint8_t *)base;
+        return (u32x4) * (const __attribute__((address_space(1))) Unaligned16 *)(g + off);
+    };
+    // x shifted down by 0 .. 15 bytes, zeros above
+    auto shift_down = [](u32x4 x, int bytes) {
+        uint64_t lo = ((uint64_t)x.y << 32) | x.x, hi = ((uint64_t)x.w << 32) | x.z;
+        if (bytes & 8) {
+            lo = hi;
+            hi = 0;
+        }
+        const int s = 8 * (bytes & 7);
+        lo = (lo >> s) | ((hi << 1) << (63 - s));
+        hi >>= s;
+        return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+    };
+    auto load_stage = [&](bool km, const Operand &o, int s, u32x4 x[8]) {
+        const uint8_t *k0 = o.base + (int64_t)s * o.kstep;
+        const int64_t left64 = p.kc - (int64_t)s * BK;
+        if (left64 >= BK) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) x[q] = load16(k0, o.off[q]);
+        } else if (km) {  // the last, incomplete stage: contraction rows beyond it are zero
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                x[q] = u32x4{0, 0, 0, 0};
+                if (16 * q + (lane >> 2) < (int)left64) x[q] = load16(k0, o.off[q]);
+            }
+        } else {  // bytes beyond it are zero; a partial chunk is the row's last sixteen bytes, shifted down
+            const int n = (int)left64 - 16 * (lane & 7), back = n < 16 ? 16 - n : 0;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) x[q] = u32x4{0, 0, 0, 0};
+            if (n > 0) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q) x[q] = shift_down(load16(k0, o.off[q] - back), back);
+            }
+        }
+    };
+    auto store_stage = [&](bool km, const Operand &o, u32x4 x[8], uint8_t *slab) {
+        if (km && o.edge) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) x[q] = shift_down(x[q], o.shift);
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int row = km ? 16 * q + (lane >> 2) : 8 * q + (lane >> 3);
+            const int at = km ? row * 64 + (((lane & 3) ^ (((row >> 2) & 1) << 1)) << 4)
+                              : row * BK + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+            *reinterpret_cast<u32x4 *>(slab + at) = x[q];
+        }
+    };
+
+    f32x16 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+    uint8_t *slab_a = lds + wave * WAVE_LDS, *slab_b = slab_a + SLAB;
+    u32x4 xa[8], xb[8];
+    // stage s is fetched into registers in the round before the one that multiplies it (the rounds
+    // are written so that the code of each step exists once: the incomplete stage makes it long)
+    const int first = ks_begin + wave;
+    for (int s = first; s < ks_end + 4; s += 4) {
+        if (s > first) {
+            store_stage(ATN, oa, xa, slab_a);
+            store_stage(BTN, ob, xb, slab_b);
+        }
+        if (s < ks_end) {
+            load_stage(ATN, oa, s, xa);
+            load_stage(BTN, ob, s, xb);
+        }
+        if (s == first) continue;
+        // the slabs are private to this wave: order its LDS writes before its reads
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub) {
+            i32x8 af[2], bf[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) af[i] = slab64_fragment<ATN>(slab_a, sub, i, lane);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) bf[j] = slab64_fragment<BTN>(slab_b, sub, j, lane);
+            // bf8 x bf8, unscaled; b as the "row" matrix: a lane gets consecutive output columns
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bf[j], af[i], acc[i][j], 1, 1, 0, 0, 0, 0);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+
+    // The four tiles meet in LDS: acc[i][j][4g + e] is row 32i + lane%32, column
+    // 32j + 8g + 4*(lane/32) + e of this wave's tile; each thread then owns sixteen columns of a row.
+    const int frow = lane & 31, fkb = lane >> 5;
+    __syncthreads();
+    float *red = reinterpret_cast<float *>(lds);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                f32x4 o = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+                *reinterpret_cast<f32x4 *>(red + (wave * T + 32 * i + frow) * RED_LD + 32 * j + 8 * g + 4 * fkb) = o;
+            }
+    __syncthreads();
+    StatsAcc st;
+    const int rr = threadIdx.x >> 2, cg = threadIdx.x & 3;
+    const int64_t r = row0 + rr, c = col0 + 16 * cg;
+    float v[16];
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const f32x4 x = *reinterpret_cast<const f32x4 *>(red + (w * T + rr) * RED_LD + 16 * cg + 4 * q);
+            if (w == 0) {
+                v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
+            } else {
+                v[4 * q] += x.x; v[4 * q + 1] += x.y; v[4 * q + 2] += x.z; v[4 * q + 3] += x.w;
+            }
+        }
+    if (r < p.rows && c < p.cols) {
+        if constexpr (EPI == EPI_PARTIAL) {
+            emit16<EPI_PARTIAL>(p, split, r, c, v, st, (p.cols & 15) == 0);
+        } else {
+            if ((p.cols & 15) == 0) finish16(p.ep, r, c, v, st);
+            else finish16_ragged(p.ep, r, c, p.cols - c < 16 ? (int)(p.cols - c) : 16, v, st);
+        }
+    }
+    if constexpr (EPI == EPI_FULL) {
+        if (p.ep.stats != nullptr) st.flush(p.ep.stats);
+    }
+}
+
+}  // namespace mp8

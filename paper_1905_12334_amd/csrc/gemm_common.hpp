@@ -85,7 +85,13 @@ struct GemmArgs {
     const uint8_t *b;
     int64_t lda, ldb;
     int64_t rows, cols;
-    int ksteps;         // contraction length / BK (pipeline stages)
+    int ksteps;         // contraction length / BK, rounded up (pipeline stages)
+    // Contraction indices of a last, incomplete stage (0: the contraction is whole stages).  The
+    // kernels multiply that stage FIRST, so that only their start-up code, and nothing in their
+    // loops, knows of it: global stage 0 is the incomplete one and stage s > 0 covers indices
+    // BK (s - 1) ...  What lies beyond the contraction reads as zero (see dma16_or_zero).
+    int tail;
+    int64_t kc;         // contraction length (gemm_any_kernel)
     int splits;         // number of contraction slices
     int tiles_m, tiles_n;
     // host-side precomputation for the workgroup -> (slice, tile) map, so that the kernel's
@@ -184,6 +190,76 @@ __device__ __forceinline__ void finish16(const Epilogue &ep, int64_t r, int64_t 
     }
 }
 
+// finish16 for any row length and any c: n (1 .. 16) valid columns, addresses without alignment.
+// The random words of sixteen elements that start at halfword h of a Philox block come from three
+// blocks, shifted down by h halfwords.
+__device__ __forceinline__ void finish16_ragged(const Epilogue &ep, int64_t r, int64_t c, int n, float v[16],
+                                                StatsAcc &st) {
+    const int64_t i0 = r * ep.cols + c;
+    if (ep.acc_mode != 0) {
+        float *p = ep.acc + i0;
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            if (e < n) {
+                if (ep.acc_mode == 2) v[e] += p[e];
+                p[e] = v[e];
+            }
+    }
+    if (ep.out8 == nullptr && ep.out8_t == nullptr && ep.stats == nullptr) return;
+    uint32_t rw[12];
+#pragma unroll
+    for (int j = 0; j < 12; ++j) rw[j] = 0;
+    if (ep.sr) {
+        const Philox rng(ep.seed, ep.offset);
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            const uint4 w = rng.block(((uint64_t)i0 >> 3) + b);
+            rw[4 * b] = w.x; rw[4 * b + 1] = w.y; rw[4 * b + 2] = w.z; rw[4 * b + 3] = w.w;
+        }
+        const int h = (int)(i0 & 7);
+        // (bit masks: with `?:` the compiler indexes the array in memory)
+        const uint32_t m4 = (h & 4) ? ~0u : 0u, m2 = (h & 2) ? ~0u : 0u;
+#pragma unroll
+        for (int j = 0; j < 10; ++j) rw[j] = (rw[j + 2] & m4) | (rw[j] & ~m4);
+#pragma unroll
+        for (int j = 0; j < 9; ++j) rw[j] = (rw[j + 1] & m2) | (rw[j] & ~m2);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) rw[j] = __builtin_amdgcn_alignbit(rw[j + 1], rw[j], (h & 1) * 16);
+    }
+    uint32_t pk[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        float y[4] = {v[4 * q] * ep.alpha, v[4 * q + 1] * ep.alpha, v[4 * q + 2] * ep.alpha, v[4 * q + 3] * ep.alpha};
+        pk[q] = e5m2_pack4_rt(y, rw[2 * q], rw[2 * q + 1], ep.sr != 0, ep.sat != 0);
+        if (ep.stats != nullptr) {
+            if (4 * q + 4 <= n) {
+                st.add4(y, pk[q]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if (4 * q + e < n) st.add1(y[e], (pk[q] >> (8 * e)) & 0xFFu);
+            }
+        }
+    }
+    if (ep.out8 != nullptr) {
+        uint8_t *p = ep.out8 + i0;
+        if (n == 16) {
+            const u32x4 o = {pk[0], pk[1], pk[2], pk[3]};
+            __builtin_memcpy(p, &o, 16);  // an unaligned 16-byte store
+        } else {
+#pragma unroll
+            for (int e = 0; e < 15; ++e)
+                if (e < n) p[e] = (uint8_t)(pk[e >> 2] >> (8 * (e & 3)));
+        }
+    }
+    if (ep.out8_t != nullptr) {
+        uint8_t *t = ep.out8_t + c * ep.rows + r;
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            if (e < n) t[e * ep.rows] = (uint8_t)(pk[e >> 2] >> (8 * (e & 3)));
+    }
+}
+
 // Map the linear workgroup id to (slice, tile row, tile column).  Consecutive ids go to
 // different XCDs (round robin), so ids are first regrouped so that each XCD works on a
 // contiguous range of tiles and its L2 sees operand reuse; inside the range, tiles are
@@ -269,12 +345,50 @@ __device__ __forceinline__ void dma16(const uint8_t *gbase, uint32_t lane_off, u
                  : "memory", "m0");
 }
 
+// The same for the incomplete stage of a contraction: a lane whose sixteen bytes lie beyond it
+// fetches zero codes instead, from an array that exists for this, so that every address is valid.
+static __device__ const uint8_t kZeroCodes[16] __attribute__((aligned(16))) = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+__device__ __forceinline__ void dma16_or_zero(const uint8_t *gbase, uint32_t lane_off, bool inside, uint32_t lds_addr) {
+    const uint8_t *src = inside ? gbase + lane_off : kZeroCodes;
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                 :
+                 : "v"(src), "s"(lds_addr)
+                 : "memory", "m0");
+}
+
 // Tell the compiler that a pointer is the same in every lane (keeps it in scalar registers).
 __device__ __forceinline__ const uint8_t *uniform_ptr(const uint8_t *p) {
     const uint64_t v = (uint64_t)(uintptr_t)p;
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
     return (const uint8_t *)(uintptr_t)(((uint64_t)hi << 32) | lo);
+}
+
+// One MFMA operand of half stage `sub` from a 64-row slab: lane l supplies tile row 32 f + l%32 (f = 0,
+// 1) and contraction indices 64*sub + 32*(l/32) .. +31 -- two 16-byte reads of a row-major slab (64
+// rows of 128 bytes), four transposing reads of eight contraction indices each of a
+// contraction-major one (128 contraction rows of 64 bytes); swizzles as in the general kernel.
+template <bool TN>
+__device__ __forceinline__ i32x8 slab64_fragment(const uint8_t *slab, int sub, int f, int lane) {
+    const int frow = lane & 31, fkb = lane >> 5, t16 = lane & 15;
+    if constexpr (TN) {
+        const int mc = (f * 32 + (frow & 16)) >> 4;
+        i32x2 part[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int k = 64 * sub + 32 * fkb + 8 * e + (t16 >> 1);
+            const int off = k * 64 + ((mc ^ (((k >> 2) & 1) << 1)) << 4) + 8 * (t16 & 1);
+            part[e] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((__attribute__((address_space(3))) i32x2 *)(slab + off));
+        }
+        return i32x8{part[0].x, part[0].y, part[1].x, part[1].y, part[2].x, part[2].y, part[3].x, part[3].y};
+    } else {
+        const int row = f * 32 + frow;
+        const uint8_t *rp = slab + row * BK;
+        const int sw = (row >> 1) & 7;
+        const i32x4 h0 = *reinterpret_cast<const i32x4 *>(rp + (((4 * sub + 2 * fkb) ^ sw) << 4));
+        const i32x4 h1 = *reinterpret_cast<const i32x4 *>(rp + (((4 * sub + 2 * fkb + 1) ^ sw) << 4));
+        return __builtin_shufflevector(h0, h1, 0, 1, 2, 3, 4, 5, 6, 7);
+    }
 }
 
 __device__ __forceinline__ uint32_t lds_address(const void *p) {

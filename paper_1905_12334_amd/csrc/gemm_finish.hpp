@@ -224,8 +224,8 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float *__restr
 }
 
 // Any-shape fallback: one thread per output element, operands decoded one by one, FP32 fused
-// multiply-adds in contraction order.  Used when the contraction length is not a multiple of
-// 128 or the operands are not 16-byte aligned.
+// multiply-adds in contraction order.  Used for what gemm_any_kernel cannot take: contractions shorter
+// than 16, contraction-major operands with fewer than 16 rows or columns, enormous leading dimensions.
 __global__ __launch_bounds__(256) void gemm_generic_kernel(const uint8_t *__restrict__ a,
                                                            int64_t lda,
                                                            const uint8_t *__restrict__ b,

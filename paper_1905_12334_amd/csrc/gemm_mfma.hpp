@@ -117,6 +117,12 @@ __global__ __launch_bounds__(256, MINBLOCKS) void gemm_mfma_kernel(const GemmArg
     }
     if constexpr (CONV == 2) b_origin = p.b + col0 * p.ldb;
     else b_origin = BTN ? p.b + (int64_t)ks_begin * b_kstep + col0 : p.b + col0 * p.ldb + (int64_t)ks_begin * BK;
+    // an incomplete stage goes first: the whole ones start one stage later
+    const bool has_tail = CONV == 0 && p.tail != 0;
+    if (has_tail) {
+        a_origin -= a_kstep;
+        b_origin -= b_kstep;
+    }
     const uint8_t *a_tile = uniform_ptr(a_origin);
     const uint8_t *b_tile = uniform_ptr(b_origin);
     // base addresses of stage `kstage` of this workgroup's slice
@@ -211,6 +217,20 @@ __global__ __launch_bounds__(256, MINBLOCKS) void gemm_mfma_kernel(const GemmArg
         for (int q = 0; q < A_DMA; ++q) dma16(ak.base, lane_off(ak, oa[q], HALVES), sa + q * 4096);
 #pragma unroll
         for (int q = 0; q < B_DMA; ++q) dma16(bk.base, lane_off(bk, ob[q], HALVES && CONV == 2), sb + q * 4096);
+    };
+
+    // the incomplete stage (stage 0 of the first slice) into ring slot 0
+    auto issue_tail = [&]() {
+        const uint32_t sa = lds0 + wave * 1024;
+        const uint8_t *ak = a_tile + (int64_t)p.ksteps * a_kstep, *bk = b_tile + (int64_t)p.ksteps * b_kstep;
+        auto inside = [&](bool km, bool narrow, int q) {
+            if (km) return (narrow ? 16 * (wave + 4 * q) + lrow64 : 8 * (wave + 4 * (q & 3)) + lrow) < p.tail;
+            return 16 * lchunk < p.tail;
+        };
+#pragma unroll
+        for (int q = 0; q < A_DMA; ++q) dma16_or_zero(ak, oa[q], inside(ATN, BM == 64, q), sa + q * 4096);
+#pragma unroll
+        for (int q = 0; q < B_DMA; ++q) dma16_or_zero(bk, ob[q], inside(BTN, BN == 64, q), sa + A_BYTES + q * 4096);
     };
 
     // Fragments: lane l supplies row (l % 32) of a 32-row tile and, for sub-step s, the 32
@@ -310,7 +330,10 @@ __global__ __launch_bounds__(256, MINBLOCKS) void gemm_mfma_kernel(const GemmArg
     // prologue: fill the ring, fetch the fragments of (0, 0)
 #pragma unroll
     for (int st = 0; st < NSTAGE; ++st)
-        if (st < ks_count) issue_loads(st);
+        if (st < ks_count) {
+            if (st == 0 && has_tail && ks_begin == 0) issue_tail();
+            else issue_loads(st);
+        }
     wait_stage(-1);
     __syncthreads();
 #pragma unroll

@@ -62,8 +62,11 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(const GemmArgs p) {
         a_origin = ATN ? p.a + row0 : p.a + row0 * p.lda;
     }
     const uint8_t *b_origin = BTN ? p.b + col0 : p.b + col0 * p.ldb;
-    const uint8_t *a_tile = uniform_ptr(a_origin + (int64_t)(ks_begin + wave) * a_kstep);
-    const uint8_t *b_tile = uniform_ptr(b_origin + (int64_t)(ks_begin + wave) * b_kstep);
+    // an incomplete stage goes first (stage 0, wave 0 of the first slice): the others start one later
+    const bool has_tail = CONV == 0 && p.tail != 0;
+    const int64_t ks0 = ks_begin + wave - (has_tail ? 1 : 0);
+    const uint8_t *a_tile = uniform_ptr(a_origin + ks0 * a_kstep);
+    const uint8_t *b_tile = uniform_ptr(b_origin + ks0 * b_kstep);
     // Direct loads, eight per operand and stage.  Row-major operand: load q brings tile rows
     // 8q .. 8q+7, lane i lands at (row i/8, slot i%8) and fetches chunk (i%8) ^ ((row >> 1) & 7);
     // rows beyond the matrix are clamped to its last row.  Contraction-major operand: load q
@@ -103,6 +106,19 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(const GemmArgs p) {
         for (int q = 0; q < QB; ++q) dma16(bk, ob[q], sa + SLAB_A + q * 1024);
     };
 
+    auto issue_tail = [&]() {  // the incomplete stage into buffer 0
+        const uint8_t *ak = a_origin + (int64_t)(p.ksteps - 1) * a_kstep;
+        const uint8_t *bk = b_origin + (int64_t)(p.ksteps - 1) * b_kstep;
+        auto inside = [&](bool km, int q) {
+            if (km) return 16 * q + (lane >> 2) < p.tail;
+            return 16 * ((lane & 7) ^ (((8 * q + (lane >> 3)) >> 1) & 7)) < p.tail;
+        };
+#pragma unroll
+        for (int q = 0; q < QA; ++q) dma16_or_zero(ak, oa[q], inside(ATN, q), ring0 + q * 1024);
+#pragma unroll
+        for (int q = 0; q < QB; ++q) dma16_or_zero(bk, ob[q], inside(BTN, q), ring0 + SLAB_A + q * 1024);
+    };
+
     f32x16 acc[MI][NJ];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
@@ -110,38 +126,12 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(const GemmArgs p) {
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-    const int frow = lane & 31, fkb = lane >> 5, t16 = lane & 15;
-    // fragment f (0, 1: a tile rows 32f ..; 2, 3: b) of half stage `sub` from buffer `s`: lane l
-    // supplies tile row 32f + l%32 and contraction indices 64*sub + 32*(l/32) .. +31 -- two
-    // 16-byte reads of a row-major slab, four transposing reads of eight contraction indices
-    // each of a contraction-major one (see the general kernel)
-    auto fragment = [&](const uint8_t *s, int sub, int f) -> i32x8 {
-        const uint8_t *slab = s + (f >> 1) * SLAB_A;
-        if ((f < 2 && ATN) || (f >= 2 && BTN)) {
-            const int m = (f & 1) * 32 + (frow & 16);
-            const int mc = m >> 4;
-            i32x2 part[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int k = 64 * sub + 32 * fkb + 8 * e + (t16 >> 1);
-                const int off = k * 64 + ((mc ^ (((k >> 2) & 1) << 1)) << 4) + 8 * (t16 & 1);
-                part[e] = __builtin_amdgcn_ds_read_tr8_b64_v2i32(
-                    (__attribute__((address_space(3))) i32x2 *)(slab + off));
-            }
-            return i32x8{part[0].x, part[0].y, part[1].x, part[1].y, part[2].x, part[2].y, part[3].x, part[3].y};
-        } else {
-            const int row = (f & 1) * 32 + frow;
-            const uint8_t *rp = slab + row * BK;
-            const int sw = (row >> 1) & 7;
-            const i32x4 h0 = *reinterpret_cast<const i32x4 *>(rp + (((4 * sub + 2 * fkb) ^ sw) << 4));
-            const i32x4 h1 = *reinterpret_cast<const i32x4 *>(rp + (((4 * sub + 2 * fkb + 1) ^ sw) << 4));
-            return __builtin_shufflevector(h0, h1, 0, 1, 2, 3, 4, 5, 6, 7);
-        }
-    };
+    const int frow = lane & 31, fkb = lane >> 5;
 
     // (Issuing the fragment reads of a half stage ahead of the MFMAs of the one before it, as
     // the general kernel does, was measured and gained nothing here: the loop waits for loads.)
-    if (mine > 0) issue(0);
+    if (has_tail && ks_begin + wave == 0) issue_tail();
+    else if (mine > 0) issue(0);
     if (mine > 1) issue(1);
     for (int j = 0; j < mine; ++j) {
         if (j + 1 < mine) wait_vm_lds<QA + QB>();  // the loads of the next stage may fly
@@ -151,10 +141,10 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(const GemmArgs p) {
         for (int sub = 0; sub < 2; ++sub) {
             i32x8 af[MI];
 #pragma unroll
-            for (int i = 0; i < MI; ++i) af[i] = fragment(s, sub, i);
+            for (int i = 0; i < MI; ++i) af[i] = slab64_fragment<ATN>(s, sub, i, lane);
             i32x8 bf[NJ];
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) bf[j] = fragment(s, sub, 2 + j);
+            for (int j = 0; j < NJ; ++j) bf[j] = slab64_fragment<BTN>(s + SLAB_A, sub, j, lane);
             // bf8 x bf8, unscaled; b as the "row" matrix: a lane gets consecutive output columns
 #pragma unroll
             for (int i = 0; i < MI; ++i)
