@@ -26,6 +26,9 @@ __device__ __forceinline__ float u2f(uint32_t u) { return __uint_as_float(u); }
 // Philox4x32-10.  The key schedule is wave-uniform, so it lives in scalar registers; each
 // round is two 32x32->64 multiplies and two three-input xors per lane.
 // ---------------------------------------------------------------------------------------
+struct Words4 {  // random words of four consecutive elements: (0, 1) and (2, 3)
+    uint32_t r01, r23;
+};
 struct Philox {
     uint32_t k0, k1, off_lo, off_hi;
     __device__ __forceinline__ Philox(uint64_t seed, uint64_t offset)
@@ -50,6 +53,43 @@ struct Philox {
             kb += 0xBB67AE85u;
         }
         return make_uint4(c0, c1, c2, c3);
+    }
+
+    // The words of elements i .. i+3 (i % 4 == 0): half of block i / 8.
+    __device__ __forceinline__ Words4 half_block(uint64_t i) const {
+        const uint4 w = block(i >> 3);
+        return {(i & 4) ? w.z : w.x, (i & 4) ? w.w : w.y};
+    }
+
+    // The words of elements i .. i+3 for any i.
+    __device__ __forceinline__ Words4 words_at(uint64_t i) const {
+        const uint4 a = block(i >> 3);
+        const int h = (int)(i & 7);
+        uint32_t w[6] = {a.x, a.y, a.z, a.w, 0u, 0u};
+        if (h > 4) {  // they go on in the next block
+            const uint4 b = block((i >> 3) + 1);
+            w[4] = b.x;
+            w[5] = b.y;
+        }
+        const uint32_t m4 = (h & 4) ? ~0u : 0u, m2 = (h & 2) ? ~0u : 0u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[j] = (w[j + 2] & m4) | (w[j] & ~m4);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) w[j] = (w[j + 1] & m2) | (w[j] & ~m2);
+        return {__builtin_amdgcn_alignbit(w[1], w[0], (h & 1) * 16), __builtin_amdgcn_alignbit(w[2], w[1], (h & 1) * 16)};
+    }
+
+    // Lanes 2m and 2m + 1 need the first and the second half of block `a`, and of block `b` (the same
+    // for both lanes): the even lane computes a, the odd one b, and each hands over the other's half.
+    // Every lane of the wave must be active.
+    __device__ __forceinline__ void pair_words(uint64_t a, uint64_t b, Words4 &wa, Words4 &wb) const {
+        const bool odd = (threadIdx.x & 1) != 0;
+        const uint4 mine = block(odd ? b : a);
+        // quad_perm [1,0,3,2]: the value of the other lane of the pair
+        const uint32_t got0 = (uint32_t)__builtin_amdgcn_mov_dpp((int)(odd ? mine.x : mine.z), 0xB1, 0xF, 0xF, true);
+        const uint32_t got1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)(odd ? mine.y : mine.w), 0xB1, 0xF, 0xF, true);
+        wa = {odd ? got0 : mine.x, odd ? got1 : mine.y};
+        wb = {odd ? mine.z : got0, odd ? mine.w : got1};
     }
 };
 

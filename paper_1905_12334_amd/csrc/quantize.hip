@@ -9,7 +9,7 @@
 // the codes also go to an LDS tile from which the threads gather 4x4 byte blocks, transpose
 // them in registers and write the transposed copy in whole 128-byte lines (tiles of 128; tiles
 // of 64 only for tensors so small that latency, not traffic, sets the time).
-// Shapes that are not multiples of 4 in both dimensions take a small generic kernel.
+// Row and column counts that are not multiples of 4 take a variant of it with unaligned accesses.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
@@ -44,22 +44,30 @@ __device__ __forceinline__ void load4(const void *src, int64_t i, float v[4]) {
     }
 }
 
-// Scale and round four consecutive elements whose first has linear index i (i % 4 == 0).
+// Scale and round four consecutive elements with their random words.
 template <bool kSR, bool kStats>
-__device__ __forceinline__ uint32_t round4(float v[4], float scale, bool sat, const Philox &rng,
-                                           int64_t i, StatsAcc &st) {
+__device__ __forceinline__ uint32_t round4(float v[4], float scale, bool sat, Words4 r, StatsAcc &st) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) v[j] *= scale;
-    uint32_t r01 = 0, r23 = 0;
-    if constexpr (kSR) {
-        // elements i..i+3 are halfwords (i % 8) .. +3 of Philox block i / 8
-        uint4 w = rng.block((uint64_t)i >> 3);
-        r01 = (i & 4) ? w.z : w.x;
-        r23 = (i & 4) ? w.w : w.y;
-    }
-    uint32_t pk = e5m2_pack4<kSR>(v, r01, r23, sat);
+    uint32_t pk = e5m2_pack4<kSR>(v, r.r01, r.r23, sat);
     if constexpr (kStats) st.add4(v, pk);
     return pk;
+}
+
+// Random words of U groups of four elements per lane, group u starting at element index i(u)
+// (a multiple of 4).  A group is half a Philox block.  With `paired`, lanes 2m and 2m + 1 hold the
+// two halves of the same block for every u (all lanes of the wave are here), and each computes every
+// other block for both: the generator's multiplications are what bounds a stochastic Q node (2^26
+// elements 59.8 us against 51.9 us to nearest, when every lane computed every block it needs half of).
+template <int U, class Index>
+__device__ __forceinline__ void group_words(const Philox &rng, bool paired, Index i, Words4 w[U]) {
+    if (U % 2 == 0 && paired) {
+#pragma unroll
+        for (int u = 0; u + 1 < U; u += 2) rng.pair_words((uint64_t)i(u) >> 3, (uint64_t)i(u + 1) >> 3, w[u], w[u + 1]);
+    } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u) w[u] = rng.half_block((uint64_t)i(u));
+    }
 }
 
 template <bool kSR, bool kStats>
@@ -74,44 +82,60 @@ __device__ __forceinline__ uint32_t round1(float x, float scale, bool sat, const
 }
 
 constexpr int kFlatUnroll = 4;  // 16-byte loads in flight per thread
-constexpr int kStatsBlocks = 512;      // grid limit of the variants that end in atomics
+constexpr int kStatsBlocks = 512;      // grid limit per tensor of a batch with statistics (256 threads)
 // The flat variant with statistics: one workgroup of 1024 threads per CU.  Every workgroup ends with
 // up to three atomics on the one mp8_stats, which the memory side serialises at about 17 ns each
 // (measured: 2048 workgroups 142 us, 512 64 us, 256 57 us for the 67 M elements of the
 // Transformer-big error tensor, against 52 us without statistics).
 constexpr int kFlatStatsBlocks = 256;
+constexpr int64_t kFlatSmall = 256 * 1024;
+constexpr int64_t kTiny = 128 * 1024, kTinyRagged = 256 * 1024;  // transposing: element by element up to here
+constexpr int64_t kTileSwitch = 256;   // transposing: tiles of 128 x 128 from this many on, else of 64 x 64
 constexpr int kStatsThreads = 1024;
 
-// The flat loop of one tensor for workgroup `block` of `nblocks` (NT threads each).
-template <bool kF16, bool kSR, bool kStats, int NT, int U = kFlatUnroll>
+// The flat loop of one tensor for workgroup `block` of `nblocks` (NT threads each).  A workgroup owns a
+// contiguous run of `chunk` groups of four elements (a multiple of 64) and passes over it kFlatUnroll groups
+// per thread at a time -- all loads of a thread in flight before the first is used, no guards -- then two,
+// then one (guarded).  Equal runs: with the grid limit of the stats variants, dealing out whole
+// passes left some workgroups a third pass where others had two (9.1 M elements: 15.1 us, now 11.2).
+template <bool kF16, bool kSR, bool kStats, int NT>
 __device__ __forceinline__ void flat_body(const void *__restrict__ src, uint8_t *__restrict__ dst,
                                           int64_t n, float scale, int sat, uint64_t seed,
                                           uint64_t offset, mp8_stats *stats, int64_t block,
-                                          int64_t nblocks) {
+                                          int64_t chunk) {
     const Philox rng(seed, offset);
     StatsAcc st;
     const int64_t n4 = n >> 2;  // groups of four elements
     uint32_t *dst4 = reinterpret_cast<uint32_t *>(dst);
-    const int64_t stride = nblocks * NT * U;
-    for (int64_t base = block * NT * U + threadIdx.x; base < n4; base += stride) {
+    int64_t at = block * chunk;
+    const int64_t end = at + chunk < n4 ? at + chunk : n4;
+    auto pass = [&](auto unroll, auto guard) {
+        constexpr int U = decltype(unroll)::value;
+        const int64_t base = at + threadIdx.x;
         float v[U][4];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t g = base + u * NT;
-            if (g < n4) load4<kF16>(src, g * 4, v[u]);
+            if (!decltype(guard)::value || g < end) load4<kF16>(src, g * 4, v[u]);
         }
+        Words4 w[U] = {};
+        if constexpr (kSR) group_words<U>(rng, true, [&](int u) { return (base + u * NT) * 4; }, w);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t g = base + u * NT;
-            if (g < n4) {
-                uint32_t pk = round4<kSR, kStats>(v[u], scale, sat != 0, rng, g * 4, st);
+            if (!decltype(guard)::value || g < end) {
+                uint32_t pk = round4<kSR, kStats>(v[u], scale, sat != 0, w[u], st);
                 // a plain store: the codes are what the next kernel (a GEMM) reads, and they are a
                 // quarter of the bytes -- left in the caches they were measured 7 % faster here and
                 // 11 us per step faster for the GEMM that follows than with a non-temporal store
                 dst4[g] = pk;
             }
         }
-    }
+        at += U * NT;
+    };
+    while (at + kFlatUnroll * NT <= end) pass(std::integral_constant<int, kFlatUnroll>{}, std::false_type{});
+    if (at + 2 * NT <= end) pass(std::integral_constant<int, 2>{}, std::false_type{});
+    while (at < end) pass(std::integral_constant<int, 1>{}, std::true_type{});
     // ragged tail (< 4 elements)
     if (block == 0 && threadIdx.x < 4) {
         const int64_t i = (n4 << 2) + threadIdx.x;
@@ -121,14 +145,11 @@ __device__ __forceinline__ void flat_body(const void *__restrict__ src, uint8_t 
     if constexpr (kStats) st.flush(stats);
 }
 
-template <bool kF16, bool kSR, bool kStats>
-__global__ __launch_bounds__(kStats ? kStatsThreads : 256) void quantize_flat_kernel(const void *__restrict__ src,
-                                                            uint8_t *__restrict__ dst, int64_t n,
-                                                            float scale, int sat, uint64_t seed,
-                                                            uint64_t offset, mp8_stats *stats) {
-    // the stats variant runs few, large blocks
-    flat_body<kF16, kSR, kStats, kStats ? kStatsThreads : 256>(src, dst, n, scale, sat, seed, offset, stats,
-                                                      blockIdx.x, gridDim.x);
+template <bool kF16, bool kSR, bool kStats, int NT>
+__global__ __launch_bounds__(NT) void quantize_flat_kernel(const void *__restrict__ src, uint8_t *__restrict__ dst,
+                                                           int64_t n, float scale, int sat, uint64_t seed,
+                                                           uint64_t offset, mp8_stats *stats, int64_t chunk) {
+    flat_body<kF16, kSR, kStats, NT>(src, dst, n, scale, sat, seed, offset, stats, blockIdx.x, chunk);
 }
 
 // Several tensors in one launch: a step that quantises activations and errors (and whatever
@@ -143,6 +164,7 @@ struct BatchItem {
     int f16, sr, sat;
     uint64_t seed, offset;
     mp8_stats *stats;
+    int64_t chunk;  // groups of four elements per workgroup
 };
 struct BatchArgs {
     BatchItem item[kBatchMax];
@@ -161,13 +183,13 @@ __global__ __launch_bounds__(256) void quantize_batch_kernel(const BatchArgs b) 
 #pragma unroll
     for (int i = 1; i < kBatchMax; ++i)
         if (k == i) it = b.item[i];
-    unsigned int lo = b.first[0], hi = b.first[1];
+    unsigned int lo = b.first[0];
 #pragma unroll
     for (int i = 1; i < kBatchMax; ++i)
-        if (k == i) { lo = b.first[i]; hi = b.first[i + 1]; }
-    const int64_t block = blockIdx.x - lo, nblocks = hi - lo;
+        if (k == i) lo = b.first[i];
+    const int64_t block = blockIdx.x - lo;
 #define MP8_B(F16, SR, ST) \
-    flat_body<F16, SR, ST, 256>(it.src, it.dst, it.n, it.scale, it.sat, it.seed, it.offset, it.stats, block, nblocks)
+    flat_body<F16, SR, ST, 256>(it.src, it.dst, it.n, it.scale, it.sat, it.seed, it.offset, it.stats, block, it.chunk)
     const bool st = it.stats != nullptr;
     if (it.f16) {
         if (it.sr) { if (st) MP8_B(true, true, true); else MP8_B(true, true, false); }
@@ -205,17 +227,24 @@ constexpr int kPitch = kTile / 4 + 1;  // LDS row pitch in dwords
 // dwords).  Phase 2: every thread gathers 16 rows x 4 columns, transposes 4x4 byte blocks in
 // registers and writes 16-byte pieces of the transposed copy, eight lanes side by side per
 // 128-byte line.  Requires cols % 4 == 0 and rows % 16 == 0.
+// With statistics two such 256-thread teams, each with tiles of its own, make one workgroup: the
+// workgroups end together, and their atomics on the one mp8_stats then queue up behind the last
+// stores at about 40 ns each (16384 x 1024: 512 of them 39 us, none 21.7 us).
 template <bool kF16, bool kSR, bool kStats>
-__global__ __launch_bounds__(256, 2) void quantize_transpose_kernel(
+__global__ __launch_bounds__(kStats ? 512 : 256, kStats ? 1 : 2) void quantize_transpose_kernel(
     const void *__restrict__ src, uint8_t *__restrict__ dst, uint8_t *__restrict__ dst_t,
     int64_t rows, int64_t cols, float scale, int sat, uint64_t seed, uint64_t offset,
     mp8_stats *stats) {
-    __shared__ uint32_t tiles[2][kTile * kPitch];
+    constexpr int TEAMS = kStats ? 2 : 1;
+    __shared__ uint32_t tiles[TEAMS][2][kTile * kPitch];
     const Philox rng(seed, offset);
     StatsAcc st;
     const int64_t tiles_c = (cols + kTile - 1) / kTile;
     const int64_t ntiles = ((rows + kTile - 1) / kTile) * tiles_c;
-    const int tid = threadIdx.x;
+    const int team = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+    const int64_t teams = (int64_t)gridDim.x * TEAMS;
+    const int tid = threadIdx.x & 255;
+    const bool paired = (cols & 7) == 0;       // neighbouring lanes share their random blocks
     const int cq = tid & 31, tr0 = tid >> 5;   // phase 1: column group, first row (then +8)
     const int k = tid & 7, cg = tid >> 3;      // phase 2: row chunk of 16, column group
     float v[16][4];
@@ -235,14 +264,17 @@ __global__ __launch_bounds__(256, 2) void quantize_transpose_kernel(
     };
     auto phase1 = [&](int64_t t, uint32_t *tile, auto guard) {
         const int64_t r0 = (t / tiles_c) * kTile, c = (t % tiles_c) * kTile + 4 * cq;
+        Words4 w[2] = {};
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
             const int tr = tr0 + 8 * u;
             const int64_t r = r0 + tr;
+            if constexpr (kSR)
+                if (u % 2 == 0) group_words<2>(rng, paired, [&](int d) { return (r + 8 * d) * cols + c; }, w);
             uint32_t pk = 0;
             if (!decltype(guard)::value || (r < rows && c < cols)) {
                 const int64_t i = r * cols + c;
-                pk = round4<kSR, kStats>(v[u], scale, sat != 0, rng, i, st);
+                pk = round4<kSR, kStats>(v[u], scale, sat != 0, w[u % 2], st);
                 __builtin_nontemporal_store(pk, reinterpret_cast<uint32_t *>(dst + i));
             }
             tile[tr * kPitch + cq] = pk;
@@ -274,22 +306,24 @@ __global__ __launch_bounds__(256, 2) void quantize_transpose_kernel(
     };
     using Guarded = std::true_type;
     using Plain = std::false_type;
-    int64_t t = blockIdx.x;
+    int64_t t = (int64_t)blockIdx.x * TEAMS + team;
     if (t < ntiles) {
         if (is_full(t)) load_tile(t, Plain{}); else load_tile(t, Guarded{});
     }
-    for (int buf = 0; t < ntiles; t += gridDim.x, buf ^= 1) {
-        uint32_t *tile = tiles[buf];
-        const bool full = is_full(t);
-        if (full) phase1(t, tile, Plain{}); else phase1(t, tile, Guarded{});
-        const int64_t tn = t + gridDim.x;
+    // (every team passes the barrier as often as the first one, which has the most tiles)
+    int64_t lead = t - team;
+    for (int buf = 0; lead < ntiles; t += teams, lead += teams, buf ^= 1) {
+        uint32_t *tile = tiles[team][buf];
+        const bool here = t < ntiles, full = here && is_full(t);
+        if (full) phase1(t, tile, Plain{}); else if (here) phase1(t, tile, Guarded{});
+        const int64_t tn = t + teams;
         if (tn < ntiles) {
             if (is_full(tn)) load_tile(tn, Plain{}); else load_tile(tn, Guarded{});
         }
         // LDS-only synchronisation (the prefetch just issued must stay in flight); one barrier
         // per tile is enough: the other LDS tile was last read before the previous barrier
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        if (full) phase2(t, tile, Plain{}); else phase2(t, tile, Guarded{});
+        if (full) phase2(t, tile, Plain{}); else if (here) phase2(t, tile, Guarded{});
     }
     if constexpr (kStats) st.flush(stats);
 }
@@ -310,17 +344,21 @@ __global__ __launch_bounds__(256) void quantize_transpose_oneshot_kernel(
     const int64_t r0 = (int64_t)(blockIdx.x / tiles_c) * kTile;
     const int64_t c0 = (int64_t)(blockIdx.x % tiles_c) * kTile;
     // phase 1: 128 rows x 32 column groups of four; item = u * 256 + tid -> (row, group)
+    const bool paired = (cols & 7) == 0;  // neighbouring lanes share their random blocks
+    Words4 w[2] = {};
 #pragma unroll 4
     for (int u = 0; u < 16; ++u) {
         const int item = u * 256 + threadIdx.x;
         const int tr = item >> 5, cq = item & 31;
         const int64_t r = r0 + tr, c = c0 + 4 * cq;
+        if constexpr (kSR)
+            if (u % 2 == 0) group_words<2>(rng, paired, [&](int d) { return (r + 8 * d) * cols + c; }, w);
         uint32_t pk = 0;
         if (r < rows && c < cols) {
             float v[4];
             const int64_t i = r * cols + c;
             load4<kF16>(src, i, v);
-            pk = round4<kSR, kStats>(v, scale, sat != 0, rng, i, st);
+            pk = round4<kSR, kStats>(v, scale, sat != 0, w[u % 2], st);
             *reinterpret_cast<uint32_t *>(dst + i) = pk;
         }
         tile[tr * kPitch + cq] = pk;
@@ -353,14 +391,56 @@ __global__ __launch_bounds__(256) void quantize_transpose_oneshot_kernel(
     if constexpr (kStats) st.flush(stats);
 }
 
+// Four consecutive elements of a row of any length and alignment: `have` (1 .. 4) of them exist.
+template <bool kF16>
+__device__ __forceinline__ void load4_ragged(const void *src, int64_t i, int have, float v[4]) {
+    if (have == 4) {
+        if constexpr (kF16) {
+            __half h[4];
+            __builtin_memcpy(h, reinterpret_cast<const __half *>(src) + i, 8);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = __half2float(h[e]);
+        } else {
+            __builtin_memcpy(v, reinterpret_cast<const float *>(src) + i, 16);
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = e < have ? load_src<kF16>(src, i + e) : 1.0f;
+    }
+}
+
+template <bool kNonTemporal>
+__device__ __forceinline__ void store_dword(uint8_t *dst, uint32_t w) {
+    if constexpr (kNonTemporal) __builtin_nontemporal_store(w, reinterpret_cast<uint32_t *>(dst));
+    else *reinterpret_cast<uint32_t *>(dst) = w;
+}
+
+// Store the first `have` bytes of a dword at any address.
+__device__ __forceinline__ void store4_ragged(uint8_t *dst, uint32_t w, int have) {
+    if (have == 4) {
+        __builtin_memcpy(dst, &w, 4);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+            if (e < have) dst[e] = (uint8_t)(w >> (8 * e));
+    }
+}
+
 // Transposing kernel, tile T x T with (T/4)^2 threads.  Phase 1: every thread converts four
 // groups of four consecutive elements (a wave instruction reads whole rows of the tile), stores
 // the row-major copy from registers and parks the packed codes in an LDS tile.  Phase 2: every
 // thread takes one 4x4 block of bytes from LDS, transposes it in registers and stores four
 // dwords of the transposed copy; T/4 neighbouring lanes complete T contiguous bytes of a
-// transposed row.  Requires cols % 4 == 0 and rows % 4 == 0.  Blocks stride over the tiles,
-// which are numbered super-tile by super-tile (S x S tiles each, row-major inside).
-template <int T, bool kF16, bool kSR, bool kStats>
+// transposed row.  Blocks stride over the tiles, which are numbered super-tile by super-tile
+// (S x S tiles each, row-major inside); a thread's loads of the next tile are issued before the
+// transposed stores of the current one.
+//   kRaggedRows  row and column counts that are not multiples of four: any alignment, partial groups at the
+//                edges; the other forms need both to be
+//   kWholeLines  both are multiples of 64: whole 64-byte pieces go past the caches (2048 x 2048 6.5 us
+//                against 7.5 us with plain stores)
+//   kPartLines   others are put together in the caches (9844 x 924: 16.6 us against 20.5 us)
+enum { kWholeLines, kPartLines, kRaggedRows };
+template <int T, bool kF16, bool kSR, bool kStats, int kForm>
 __global__ __launch_bounds__((T / 4) * (T / 4)) void quantize_tile_kernel(
     const void *__restrict__ src, uint8_t *__restrict__ dst, uint8_t *__restrict__ dst_t,
     int64_t rows, int64_t cols, float scale, int sat, uint64_t seed, uint64_t offset,
@@ -368,6 +448,7 @@ __global__ __launch_bounds__((T / 4) * (T / 4)) void quantize_tile_kernel(
     constexpr int G = T / 4;       // column groups per tile row = threads per tile row
     constexpr int NT = G * G;      // threads
     constexpr int P = G + 1;       // LDS row pitch in dwords
+    constexpr bool kRagged = kForm == kRaggedRows;
     __shared__ uint32_t tile[T * P];
     const Philox rng(seed, offset);
     StatsAcc st;
@@ -376,17 +457,42 @@ __global__ __launch_bounds__((T / 4) * (T / 4)) void quantize_tile_kernel(
     const int64_t ntiles = sup_c * sup_r * S * S;
     const int tid = threadIdx.x;
     const int k = tid % G, cg = tid / G;  // phase 2: rows 4k..4k+3, columns 4cg..4cg+3
-    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    // first row and column of tile t; a super-tile at the edge also numbers tiles that do not exist
+    auto origin = [&](int64_t t, int64_t &r0, int64_t &c0) {
         const int64_t sup = t / (S * S), in = t % (S * S);
-        const int64_t tr_ = (sup / sup_c) * S + in / S, tc_ = (sup % sup_c) * S + in % S;
-        if (tr_ >= tiles_r || tc_ >= tiles_c) continue;
-        const int64_t r0 = tr_ * T, c0 = tc_ * T;
-        float v[4][4];
+        r0 = ((sup / sup_c) * S + in / S) * T;
+        c0 = ((sup % sup_c) * S + in % S) * T;
+        return r0 < rows && c0 < cols;
+    };
+    auto next = [&](int64_t t, int64_t &r0, int64_t &c0) {  // the first tile from t on that exists
+        while (t < ntiles && !origin(t, r0, c0)) t += gridDim.x;
+        return t;
+    };
+    float v[4][4];
+    auto load_tile = [&](int64_t r0, int64_t c0) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int item = u * NT + tid;
             const int64_t r = r0 + item / G, c = c0 + 4 * (item % G);
-            if (r < rows && c < cols) load4<kF16>(src, r * cols + c, v[u]);
+            if (r < rows && c < cols) {
+                if constexpr (kRagged) load4_ragged<kF16>(src, r * cols + c, cols - c < 4 ? (int)(cols - c) : 4, v[u]);
+                else load4<kF16>(src, r * cols + c, v[u]);
+            }
+        }
+    };
+    int64_t r0 = 0, c0 = 0;
+    int64_t t = next(blockIdx.x, r0, c0);
+    if (t < ntiles) load_tile(r0, c0);
+    while (t < ntiles) {
+        Words4 w[4] = {};
+        if constexpr (kSR) {
+            auto index = [&](int u) { return (r0 + (u * NT + tid) / G) * cols + c0 + 4 * (tid % G); };
+            if constexpr (kRagged) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) w[u] = rng.words_at((uint64_t)index(u));
+            } else {
+                group_words<4>(rng, (cols & 7) == 0, index, w);
+            }
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -396,12 +502,31 @@ __global__ __launch_bounds__((T / 4) * (T / 4)) void quantize_tile_kernel(
             uint32_t pk = 0;
             if (r < rows && c < cols) {
                 const int64_t i = r * cols + c;
-                pk = round4<kSR, kStats>(v[u], scale, sat != 0, rng, i, st);
-                __builtin_nontemporal_store(pk, reinterpret_cast<uint32_t *>(dst + i));
+                if constexpr (kRagged) {
+                    const int have = cols - c < 4 ? (int)(cols - c) : 4;
+                    if (have == 4) {
+                        pk = round4<kSR, kStats>(v[u], scale, sat != 0, w[u], st);
+                    } else {
+                        pk = round4<kSR, false>(v[u], scale, sat != 0, w[u], st);
+                        if constexpr (kStats) {
+#pragma unroll
+                            for (int e = 0; e < 3; ++e)
+                                if (e < have) st.add1(v[u][e], (pk >> (8 * e)) & 0xFFu);
+                        }
+                    }
+                    store4_ragged(dst + i, pk, have);
+                } else {
+                    pk = round4<kSR, kStats>(v[u], scale, sat != 0, w[u], st);
+                    store_dword<kForm == kWholeLines>(dst + i, pk);
+                }
             }
             tile[tr * P + cq] = pk;
         }
-        __syncthreads();
+        int64_t rn = 0, cn = 0;
+        const int64_t tn = next(t + gridDim.x, rn, cn);
+        if (tn < ntiles) load_tile(rn, cn);
+        // LDS-only synchronisation: the loads just issued stay in flight
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         uint32_t rr[4], cc[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) rr[j] = tile[(4 * k + j) * P + cg];
@@ -411,17 +536,23 @@ __global__ __launch_bounds__((T / 4) * (T / 4)) void quantize_tile_kernel(
 #pragma unroll
             for (int col = 0; col < 4; ++col) {
                 const int64_t oc = c0 + 4 * cg + col;
-                if (oc < cols)
-                    __builtin_nontemporal_store(cc[col],
-                                                reinterpret_cast<uint32_t *>(dst_t + oc * rows + orow));
+                if (oc < cols) {
+                    uint8_t *to = dst_t + oc * rows + orow;
+                    if constexpr (kRagged) store4_ragged(to, cc[col], rows - orow < 4 ? (int)(rows - orow) : 4);
+                    else store_dword<kForm == kWholeLines>(to, cc[col]);
+                }
             }
         }
-        __syncthreads();  // the tile is rewritten by the next iteration
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // the tile is rewritten by the next iteration
+        t = tn;
+        r0 = rn;
+        c0 = cn;
     }
     if constexpr (kStats) st.flush(stats);
 }
 
-// Any shape: one element per thread and iteration.
+// Any shape: one element per thread and iteration.  For tensors so small that the shortest chain of
+// latencies wins (1001 x 77: 2.6 us, 4.6 us in tiles).
 template <bool kF16, bool kSR, bool kStats>
 __global__ __launch_bounds__(256) void quantize_generic_kernel(
     const void *__restrict__ src, uint8_t *__restrict__ dst, uint8_t *__restrict__ dst_t,
@@ -456,57 +587,67 @@ static hipError_t launch_quantize(const void *src, uint8_t *dst, uint8_t *dst_t,
                                   uint64_t offset, mp8_stats *stats, hipStream_t s) {
     const int64_t n = rows * cols;
     if (dst_t == nullptr) {
-        // Every block of a stats variant ends with atomics on the one mp8_stats; they are
-        // serialised at the memory side, so those variants run at most two 1024-thread blocks
-        // per CU and stride over the tensor.
-        const int nt = kStats ? kStatsThreads : 256;
-        const int64_t per_block = (int64_t)nt * kFlatUnroll;
-        int64_t blocks = ((n >> 2) + per_block - 1) / per_block;
-        if (blocks < 1) blocks = 1;
-        if (blocks > (1 << 22)) blocks = 1 << 22;  // grid-stride beyond 2^34 elements
-        if (kStats && blocks > kFlatStatsBlocks) blocks = kFlatStatsBlocks;
-        hipLaunchKernelGGL((quantize_flat_kernel<kF16, kSR, kStats>), dim3((unsigned)blocks),
-                           dim3(nt), 0, s, src, dst, n, scale, sat, seed, offset, stats);
-    } else if ((cols & 3) == 0 && (rows & 3) == 0) {
+        const int64_t n4 = n >> 2;
+        auto launch = [&](auto threads, int64_t chunk) {
+            constexpr int NT = decltype(threads)::value;
+            const int64_t blocks = std::max<int64_t>(1, (n4 + chunk - 1) / chunk);
+            hipLaunchKernelGGL((quantize_flat_kernel<kF16, kSR, kStats, NT>), dim3((unsigned)blocks), dim3(NT), 0, s, src, dst,
+                               n, scale, sat, seed, offset, stats, chunk);
+        };
+        if constexpr (kStats) {
+            // equal runs for at most kFlatStatsBlocks workgroups; while a run is no longer than
+            // that, 256 threads of the latency-bound small tensors start sooner than 1024
+            const int64_t chunk = std::max<int64_t>(256, ((n4 + kFlatStatsBlocks - 1) / kFlatStatsBlocks + 63) / 64 * 64);
+            if (chunk <= 512) launch(std::integral_constant<int, 256>{}, chunk);
+            else launch(std::integral_constant<int, kStatsThreads>{}, chunk);
+        } else {
+            // one pass per workgroup; tensors of less than kFlatSmall groups take one group per thread, so
+            // that they occupy every CU
+            const int64_t per = n4 <= kFlatSmall ? 256 : 256 * kFlatUnroll;
+            launch(std::integral_constant<int, 256>{}, std::max(per, ((n4 >> 22) + 63) / 64 * 64));
+        }
+    } else {
+        const bool ragged = ((rows | cols) & 3) != 0;
         const int64_t tr128 = (rows + 127) / 128, tc128 = (cols + 127) / 128;
         const int64_t nt = tr128 * tc128;
         const bool wide = tr128 >= 64 && tc128 >= 64;
-        if (!kStats && !wide && (rows & 15) == 0 && nt >= 6144) {
+        auto tiles = [&](auto edge, int S, int64_t limit) {
+            constexpr int T = decltype(edge)::value;
+            const int64_t tr = (rows + T - 1) / T, tc = (cols + T - 1) / T;
+            const int64_t blocks = std::min<int64_t>(((tr + S - 1) / S) * ((tc + S - 1) / S) * S * S, limit);
+            hipLaunchKernelGGL((ragged ? quantize_tile_kernel<T, kF16, kSR, kStats, kRaggedRows>
+                                : ((rows | cols) & 63) == 0 ? quantize_tile_kernel<T, kF16, kSR, kStats, kWholeLines>
+                                                            : quantize_tile_kernel<T, kF16, kSR, kStats, kPartLines>),
+                               dim3((unsigned)blocks), dim3((T / 4) * (T / 4)), 0, s, src, dst, dst_t, rows, cols, scale, sat,
+                               seed, offset, stats, S);
+        };
+        if (n <= (ragged ? kTinyRagged : kTiny)) {
+            hipLaunchKernelGGL((quantize_generic_kernel<kF16, kSR, kStats>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                               src, dst, dst_t, rows, cols, scale, sat, seed, offset, stats);
+        } else if (!ragged && !kStats && !wide && (rows & 15) == 0 && nt >= 6144) {
             // several rounds of blocks: plain one-tile blocks, many per CU
             hipLaunchKernelGGL((quantize_transpose_oneshot_kernel<kF16, kSR, kStats>),
                                dim3((unsigned)nt), dim3(256), 0, s, src, dst, dst_t, rows, cols,
                                scale, sat, seed, offset, stats);
-        } else if (!wide && (rows & 15) == 0 && nt >= 1024) {
-            // a few tiles per CU: about two persistent blocks per CU, the same number of tiles
-            // each, prefetching across tiles
-            const int64_t per = (nt + 511) / 512;
-            const int64_t blocks = (nt + per - 1) / per;
+        } else if (!ragged && !wide && (rows & 15) == 0 && nt >= 1024) {
+            // a few tiles per CU: about two persistent teams of 256 threads per CU, the same number of
+            // tiles each, prefetching across tiles
+            const int64_t per = (nt + 511) / 512, teams = (nt + per - 1) / per;
+            const int64_t blocks = kStats ? (teams + 1) / 2 : teams;
             hipLaunchKernelGGL((quantize_transpose_kernel<kF16, kSR, kStats>),
-                               dim3((unsigned)blocks), dim3(256), 0, s, src, dst, dst_t, rows, cols,
+                               dim3((unsigned)blocks), dim3(kStats ? 512 : 256), 0, s, src, dst, dst_t, rows, cols,
                                scale, sat, seed, offset, stats);
-        } else if (nt >= 64) {
+        } else if (nt >= kTileSwitch) {
             // 1024-thread blocks, all loads of a tile in flight; for a matrix that is wide in
             // both directions, super-tiles of 4x4 keep the lines written by concurrently
-            // running blocks close together in both copies
-            const int S = wide ? 4 : 1;
-            int64_t blocks = ((tr128 + S - 1) / S) * ((tc128 + S - 1) / S) * S * S;
-            if (kStats && blocks > kStatsBlocks) blocks = kStatsBlocks;
-            hipLaunchKernelGGL((quantize_tile_kernel<128, kF16, kSR, kStats>),
-                               dim3((unsigned)blocks), dim3(1024), 0, s, src, dst, dst_t, rows, cols,
-                               scale, sat, seed, offset, stats, S);
+            // running blocks close together in both copies.  With statistics one block per CU:
+            // every block ends in atomics on one address, and blocks that end together wait
+            // for each other there (512 of them: 16384 x 1024 39 us, against 22 us without atomics)
+            tiles(std::integral_constant<int, 128>{}, wide ? 4 : 1, kStats ? kFlatStatsBlocks : (int64_t)1 << 30);
         } else {
             // few tiles: smaller ones shorten the latency chain of the single round of blocks
-            const int64_t blocks = ((rows + 63) / 64) * ((cols + 63) / 64);
-            hipLaunchKernelGGL((quantize_tile_kernel<64, kF16, kSR, kStats>),
-                               dim3((unsigned)blocks), dim3(256), 0, s, src, dst, dst_t, rows, cols,
-                               scale, sat, seed, offset, stats, 1);
+            tiles(std::integral_constant<int, 64>{}, 1, (int64_t)1 << 30);
         }
-    } else {
-        int64_t blocks = (n + 255) / 256;
-        if (blocks > 256 * 32) blocks = 256 * 32;
-        hipLaunchKernelGGL((quantize_generic_kernel<kF16, kSR, kStats>), dim3((unsigned)blocks),
-                           dim3(256), 0, s, src, dst, dst_t, rows, cols, scale, sat, seed, offset,
-                           stats);
     }
     return hipGetLastError();
 }
@@ -587,6 +728,7 @@ extern "C" mp8_status mp8_quantize_e5m2_batch(const mp8_quantize_item *items, in
         it.seed = q.seed;
         it.offset = q.offset;
         it.stats = q.stats;
+        it.chunk = std::max<int64_t>(256, (((q.n >> 2) + nblk[order[j]] - 1) / nblk[order[j]] + 63) / 64 * 64);
         args.first[j] = (unsigned int)total;
         total += nblk[order[j]];
     }

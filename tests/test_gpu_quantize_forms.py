@@ -1,0 +1,67 @@
+"""GPU parity of the Q node's launch forms where they change: runs of a workgroup with statistics (one, two,
+four groups per thread and a rest), one group per thread for small tensors, and transposed copies of
+row and column counts that are not multiples of four (both tile sizes)."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import gpu, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mp8():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    import paper_1905_12334_amd as m
+    m.lib()
+    return m
+
+
+def check(mp8, x, rnd, want_t, with_stats, scale=1.0):
+    import torch
+    rows, cols = x.shape
+    n = rows * cols
+    d = torch.full((n + 64,), 0xAA, dtype=torch.uint8, device="cuda")
+    t = torch.full((n + 64,), 0xAA, dtype=torch.uint8, device="cuda")
+    st = mp8.new_stats() if with_stats else None
+    mp8.quantize_e5m2(gpu(x), d[:n], t[:n] if want_t else None, scale=scale, round=rnd, seed=9, offset=4, stats=st)
+    torch.cuda.synchronize()
+    ost = oracle.Stats()
+    want, _ = oracle.quantize_e5m2(x.astype(np.float32), scale=scale, mode=rnd, seed=9, offset=4, stats=ost)
+    assert np.array_equal(host(d[:n]).reshape(rows, cols), want)
+    assert bool((d[n:] == 0xAA).all()) and bool((t[n if want_t else 0:] == 0xAA).all())
+    if want_t:
+        assert np.array_equal(host(t[:n]).reshape(cols, rows), want.T)
+    if with_stats:
+        assert mp8.read_stats(st) == ost.as_tuple()
+
+
+def data(seed, shape, half):
+    rng = np.random.default_rng(seed)
+    x = rng.standard_normal(shape) * np.exp2(rng.integers(-20, 8, shape))
+    x[rng.random(shape) < 0.01] = 0
+    x.reshape(-1)[rng.integers(0, x.size, 3)] = (np.inf, -np.inf, np.nan)
+    return x.astype(np.float16 if half else np.float32)
+
+
+# groups of four per workgroup of 256: up to 256 (one), 257..512 (two), then 1024-thread blocks with 1, 2, 3, 4, 5, 9 groups
+@pytest.mark.parametrize("n", [4, 252, 4 * 256 * 256 - 4, 4 * 256 * 256 + 4, 4 * 256 * 512 + 260, 4 * 256 * 1024 + 1027,
+                               4 * 256 * 3 * 1024 - 13, 4 * 256 * 5 * 1024 + 3, 4 * 256 * 9 * 1024 + 77])
+@pytest.mark.parametrize("rnd", [oracle.RNE, oracle.SR])
+@pytest.mark.parametrize("with_stats", [False, True])
+def test_flat_run_lengths(mp8, n, rnd, with_stats):
+    check(mp8, data(n, (1, n), False), rnd, False, with_stats)
+
+
+@pytest.mark.parametrize("shape", [(1, 1), (2, 3), (63, 65), (66, 127), (600, 450), (130, 2061), (517, 523), (2049, 2051), (2050, 2052), (2052, 2050)])
+@pytest.mark.parametrize("rnd", [oracle.RNE, oracle.SR])
+@pytest.mark.parametrize("half,with_stats", [(False, True), (True, False)])
+def test_ragged_transposed_copies(mp8, shape, rnd, half, with_stats):
+    check(mp8, data(shape[0], shape, half), rnd, True, with_stats)
+
+
+@pytest.mark.parametrize("shape", [(128, 128), (1024, 2048), (2064, 2052), (2064, 2056), (8208, 8196)])
+def test_transposed_copies_with_statistics_and_shared_random_blocks(mp8, shape):
+    check(mp8, data(shape[1], shape, False), oracle.SR, True, True)
