@@ -64,23 +64,12 @@ struct UpdateHook {
     float b1, b2, omb1, omb2, c1, c2, eps;   // ADAM
 };
 
-// One master weight from its gradient code, with the same arithmetic as the stand-alone update
-// kernels; st points at this element's state words.
-template <int STATES>
-__device__ __forceinline__ uint32_t hook_one(const UpdateHook &u, uint32_t w16, uint32_t code, float *st,
-                                             uint32_t r16) {
-    if constexpr (STATES == 1) {
-        const MomentumRule rule{u.neg_lr, u.mu, u.wd};
-        return u.sr ? rule_one<true>(rule, w16, code, st, u.inv_scale, r16)
-                    : rule_one<false>(rule, w16, code, st, u.inv_scale, 0u);
-    }
-    if constexpr (STATES == 2) {
-        const AdamRule rule{u.neg_lr, u.b1, u.b2, u.omb1, u.omb2, u.c1, u.c2, u.eps, u.wd};
-        return u.sr ? rule_one<true>(rule, w16, code, st, u.inv_scale, r16)
-                    : rule_one<false>(rule, w16, code, st, u.inv_scale, 0u);
-    }
-    return u.sr ? update_one<true>(w16, code, u.neg_lr, u.inv_scale, r16)
-                : update_one<false>(w16, code, u.neg_lr, u.inv_scale, 0u);
+// The hook's update rule: f(rule) with the rule object the stand-alone update kernels use.
+template <int STATES, class F>
+__device__ __forceinline__ void with_rule(const UpdateHook &u, F f) {
+    if constexpr (STATES == 0) f(SgdRule{u.neg_lr});
+    else if constexpr (STATES == 1) f(MomentumRule{u.neg_lr, u.mu, u.wd});
+    else f(AdamRule{u.neg_lr, u.b1, u.b2, u.omb1, u.omb2, u.c1, u.c2, u.eps, u.wd});
 }
 
 template <int STATES>
@@ -88,7 +77,11 @@ __device__ __forceinline__ void update_element(const UpdateHook &u, int64_t i, u
     float st[2] = {0.0f, 0.0f};
     if constexpr (STATES >= 1) st[0] = u.state0[i];
     if constexpr (STATES == 2) st[1] = u.state1[i];
-    const uint32_t h = hook_one<STATES>(u, u.w16[i], code, st, r16);
+    uint32_t h = 0;
+    with_rule<STATES>(u, [&](const auto &rule) {
+        h = u.sr ? update_one<true>(rule, u.w16[i], code, st, u.inv_scale, r16)
+                 : update_one<false>(rule, u.w16[i], code, st, u.inv_scale, 0u);
+    });
     if constexpr (STATES >= 1) u.state0[i] = st[0];
     if constexpr (STATES == 2) u.state1[i] = st[1];
     u.w16[i] = (uint16_t)h;
@@ -113,18 +106,7 @@ __device__ __forceinline__ UpdateOperands4 load_update4(const UpdateHook &u, int
 // Elements i0 .. i0+3 (i0 % 4 == 0) from their four packed gradient codes.
 template <int STATES>
 __device__ __forceinline__ void update4(const UpdateHook &u, int64_t i0, uint32_t pk, const UpdateOperands4 &in) {
-    uint32_t r01 = 0, r23 = 0;
-    if (u.sr) {
-        const Philox rng(u.seed, u.offset);
-        const uint4 w = rng.block((uint64_t)i0 >> 3);
-        r01 = (i0 & 4) ? w.z : w.x;
-        r23 = (i0 & 4) ? w.w : w.y;
-    }
-    u32x2 *wp = reinterpret_cast<u32x2 *>(u.w16 + i0);
-    const u32x2 wr = in.w;
-    uint32_t h[4];
-    const uint32_t w16v[4] = {wr.x & 0xFFFFu, wr.x >> 16, wr.y & 0xFFFFu, wr.y >> 16};
-    const uint32_t r16[4] = {r01 & 0xFFFFu, r01 >> 16, r23 & 0xFFFFu, r23 >> 16};
+    uint32_t w[2] = {in.w.x, in.w.y};
     float st[4][2] = {{0.0f, 0.0f}, {0.0f, 0.0f}, {0.0f, 0.0f}, {0.0f, 0.0f}};
     if constexpr (STATES >= 1) {
         const f32x4 x = in.s0;
@@ -134,11 +116,10 @@ __device__ __forceinline__ void update4(const UpdateHook &u, int64_t i0, uint32_
         const f32x4 x = in.s1;
         st[0][1] = x.x; st[1][1] = x.y; st[2][1] = x.z; st[3][1] = x.w;
     }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const uint32_t code = (pk >> (8 * j)) & 0xFFu;
-        h[j] = hook_one<STATES>(u, w16v[j], code, st[j], r16[j]);
-    }
+    with_rule<STATES>(u, [&](const auto &rule) {
+        if (u.sr) update_four<true>(rule, w, pk, st, u.inv_scale, Philox(u.seed, u.offset).half_block((uint64_t)i0));
+        else update_four<false>(rule, w, pk, st, u.inv_scale, Words4{0u, 0u});
+    });
     if constexpr (STATES >= 1) {
         const f32x4 x = {st[0][0], st[1][0], st[2][0], st[3][0]};
         *reinterpret_cast<f32x4 *>(u.state0 + i0) = x;
@@ -147,11 +128,9 @@ __device__ __forceinline__ void update4(const UpdateHook &u, int64_t i0, uint32_
         const f32x4 x = {st[0][1], st[1][1], st[2][1], st[3][1]};
         *reinterpret_cast<f32x4 *>(u.state1 + i0) = x;
     }
-    const u32x2 o = {h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
-    *wp = o;
-    if (u.w8_out != nullptr)
-        *reinterpret_cast<uint32_t *>(u.w8_out + i0) =
-            e5m2_of_half(h[0]) | (e5m2_of_half(h[1]) << 8) | (e5m2_of_half(h[2]) << 16) | (e5m2_of_half(h[3]) << 24);
+    const u32x2 o = {w[0], w[1]};
+    *reinterpret_cast<u32x2 *>(u.w16 + i0) = o;
+    if (u.w8_out != nullptr) *reinterpret_cast<uint32_t *>(u.w8_out + i0) = e5m2_of_halves(w);
 }
 
 // Sum the FP32 tiles of the contraction slices in slice order and finish: the complete sum is

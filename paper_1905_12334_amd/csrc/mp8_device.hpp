@@ -18,6 +18,7 @@ constexpr int kWave = 64;
 using f32x4 = float __attribute__((ext_vector_type(4)));
 using u32x4 = uint32_t __attribute__((ext_vector_type(4)));
 using u32x2 = uint32_t __attribute__((ext_vector_type(2)));
+using half2v = _Float16 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ uint32_t f2u(float f) { return __float_as_uint(f); }
 __device__ __forceinline__ float u2f(uint32_t u) { return __uint_as_float(u); }
@@ -387,39 +388,53 @@ struct StatsAcc {
 };
 
 // ---------------------------------------------------------------------------------------
-// One element of the master-weight update of Figure 1b (shared by the update kernels and by
-// the weight-gradient finishing pass that applies the update in place).
+// The master-weight update of Figure 1b on four elements (shared by the update kernels and by the
+// weight-gradient finishing pass that applies the update in place).
 // ---------------------------------------------------------------------------------------
-// value(g8) * inv_scale, FP32 weight, one fused multiply-add, rounded to half.
+// FP32 -> half code, from hardware conversions.  RNE: v_cvt_f16_f32 rounds exactly like the
+// bit-level routine for every input that is not a NaN.  SR: v_cvt_sr_f16_f32 adds the top 13 bits of its
+// random operand to the 13 discarded ones, so r16 << 16 gives exactly the bit-level routine's code
+// for every normal (or overflowing) result; for subnormal results it keeps fewer bits, and the integer
+// form replaces it there: |x| in units of 2^-40, truncated, plus r16, over 2^16.  (Both checked
+// against f16_from_f32_bits over all 2^32 inputs.)  NaN is made canonical.
+// r: the element's 16 random bits in the upper half.
 template <bool kSR>
-__device__ __forceinline__ uint32_t update_one(uint32_t w16, uint32_t g8, float neg_lr,
-                                               float inv_scale, uint32_t r16) {
-    float g = e5m2_to_f32(g8) * inv_scale;
-    float w = __half2float(__ushort_as_half((unsigned short)w16));
-    float wn = __builtin_fmaf(neg_lr, g, w);
-    // The update is an FP32 operation whose FP32 result is then converted to half: keep the
-    // compiler from merging the two into one mixed-precision instruction that rounds once.
-    asm volatile("" : "+v"(wn));
+__device__ __forceinline__ uint32_t f16_from_f32(float x, uint32_t r) {
+    uint32_t h;
     if constexpr (kSR) {
-        return f16_from_f32_bits<true>(f2u(wn), r16);
+        const half2v none = {0, 0};
+        h = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_sr_f16_f32(none, x, r, false)) & 0xFFFFu;
+        const float a = __builtin_fabsf(x);
+        const uint32_t quanta = (uint32_t)(a * 0x1p40f);
+        const uint32_t sub = ((quanta + (r >> 16)) >> 16) | ((f2u(x) >> 16) & 0x8000u);
+        h = a < 0x1p-14f ? sub : h;
     } else {
-        // v_cvt_f16_f32 rounds to nearest even exactly like the bit-level routine for every
-        // input that is not a NaN (checked over all 2^32 inputs); NaN is made canonical
-        uint32_t h = __half_as_ushort(__float2half_rn(wn));
-        return (wn != wn) ? 0x7E00u : h;
+        h = __half_as_ushort(__float2half_rn(x));
     }
+    return (x != x) ? 0x7E00u : h;
 }
 
-// The 8-bit (RNE) copy of a half-precision weight: the next step's operand.
-__device__ __forceinline__ uint32_t e5m2_of_half(uint32_t h) {
-    return e5m2_from_f32_bits<false>(f2u(__half2float(__ushort_as_half((unsigned short)h))), 0u,
-                                     false);
+__device__ __forceinline__ float half_bits_to_f32(uint32_t h) {
+    return __half2float(__ushort_as_half((unsigned short)h));
+}
+
+// The 8-bit (RNE) copies of four half-precision weights: the next step's operand.
+__device__ __forceinline__ uint32_t e5m2_of_halves(const uint32_t w[2]) {
+    const float y[4] = {half_bits_to_f32(w[0]), half_bits_to_f32(w[0] >> 16), half_bits_to_f32(w[1]), half_bits_to_f32(w[1] >> 16)};
+    return e5m2_pack4<false>(y, 0u, 0u, false);
 }
 
 // Optimizers with FP32 state in front of the same conversion.  A rule turns the un-scaled
 // gradient g, the weight w and its state words into the new FP32 weight; every operation is a
 // separately rounded FP32 operation in the order written (the build forbids contraction).
 //
+// Plain SGD: w' = w - lr * g.
+struct SgdRule {
+    static constexpr int kStates = 0;
+    float neg_lr;
+    __device__ __forceinline__ float operator()(float w, float g, float *) const { return __builtin_fmaf(neg_lr, g, w); }
+};
+
 // Momentum with the L2 regularisation gradient:   g += wd * w;  v' = mu * v + g;  w' = w - lr * v'
 struct MomentumRule {
     static constexpr int kStates = 1;
@@ -452,19 +467,41 @@ struct AdamRule {
     }
 };
 
-template <bool kSR, class Rule>
-__device__ __forceinline__ uint32_t rule_one(const Rule &rule, uint32_t w16, uint32_t g8, float *st,
-                                             float inv_scale, uint32_t r16) {
-    const float g = e5m2_to_f32(g8) * inv_scale;
-    const float w = __half2float(__ushort_as_half((unsigned short)w16));
-    float wn = rule(w, g, st);
-    asm volatile("" : "+v"(wn));  // keep the conversion a separate, second rounding
-    if constexpr (kSR) {
-        return f16_from_f32_bits<true>(f2u(wn), r16);
-    } else {
-        uint32_t h = __half_as_ushort(__float2half_rn(wn));
-        return (wn != wn) ? 0x7E00u : h;
+// Four weights (two packed pairs of half codes) from their packed gradient codes, in place; st holds
+// kStates words per element.
+template <bool kSR, class Rule, int NS>
+__device__ __forceinline__ void update_four(const Rule &rule, uint32_t w[2], uint32_t g8, float (&st)[4][NS], float inv_scale,
+                                            Words4 r) {
+    static_assert(NS >= Rule::kStates, "state words");
+    const float g[4] = {__builtin_amdgcn_cvt_f32_bf8((int)g8, 0), __builtin_amdgcn_cvt_f32_bf8((int)g8, 1),
+                        __builtin_amdgcn_cvt_f32_bf8((int)g8, 2), __builtin_amdgcn_cvt_f32_bf8((int)g8, 3)};
+    const uint32_t rw[4] = {r.r01 << 16, r.r01 & 0xFFFF0000u, r.r23 << 16, r.r23 & 0xFFFF0000u};
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        uint32_t h[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int j = 2 * p + e;
+            float wn = rule(half_bits_to_f32(w[p] >> (16 * e)), g[j] * inv_scale, st[j]);
+            // The update is an FP32 operation whose FP32 result is then converted to half: keep the
+            // compiler from merging the two into one mixed-precision instruction that rounds once.
+            asm volatile("" : "+v"(wn));
+            h[e] = f16_from_f32<kSR>(wn, rw[j]);
+        }
+        w[p] = h[0] | (h[1] << 16);
     }
+}
+
+// One weight from its gradient code (ragged ends); r16: its random bits.
+template <bool kSR, class Rule>
+__device__ __forceinline__ uint32_t update_one(const Rule &rule, uint32_t w16, uint32_t g8, float *st, float inv_scale,
+                                               uint32_t r16) {
+    float wn = rule(half_bits_to_f32(w16), e5m2_to_f32(g8) * inv_scale, st);
+    asm volatile("" : "+v"(wn));  // as above
+    return f16_from_f32<kSR>(wn, r16 << 16);
+}
+__device__ __forceinline__ uint32_t e5m2_of_half(uint32_t h) {
+    return e5m2_from_f32_bits<false>(f2u(half_bits_to_f32(h)), 0u, false);
 }
 
 }  // namespace mp8

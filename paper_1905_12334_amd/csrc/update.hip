@@ -7,17 +7,19 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <type_traits>
 
 #include "mp8_device.hpp"
 
 namespace mp8 {
 
-constexpr int kUpdUnroll = 2;  // groups of eight elements in flight per thread
-
 // Thread item = eight consecutive elements (16 B of weights, 8 B of gradients, one Philox
 // block); items are wave-interleaved so that every load or store instruction of a wave
-// covers one contiguous run.
-template <bool kSR, bool kW8, bool kStats>
+// covers one contiguous run.  U items in flight per thread: two for tensors that fill the chip,
+// one for small ones (65536 elements: 4.7 us with two, most of it one wave's chain of 16 elements).
+// The loads are issued before the skip flag is looked at: a skipped step reads for nothing, every
+// other one saves the latency of the flag.
+template <bool kSR, bool kW8, bool kStats, int U>
 __global__ __launch_bounds__(256) void sgd_update_kernel(uint16_t *__restrict__ w16,
                                                          const uint8_t *__restrict__ g8,
                                                          int64_t n, float neg_lr,
@@ -27,55 +29,42 @@ __global__ __launch_bounds__(256) void sgd_update_kernel(uint16_t *__restrict__ 
                                                          uint8_t *__restrict__ w8_out,
                                                          mp8_stats *stats) {
     const Philox rng(seed, offset);
+    const SgdRule rule{neg_lr};
     const bool skipping = (skip != nullptr) && (*skip != 0u);
-    if (skipping && !kStats) return;
     uint32_t nonfinite = 0;
     const int64_t n8 = n >> 3;
-    const int64_t stride = (int64_t)gridDim.x * 256 * kUpdUnroll;
-    for (int64_t base = (int64_t)blockIdx.x * 256 * kUpdUnroll + threadIdx.x; base < n8;
-         base += stride) {
-        u32x2 gr[kUpdUnroll];
-        u32x4 wr[kUpdUnroll];
+    const int64_t stride = (int64_t)gridDim.x * 256 * U;
+    for (int64_t base = (int64_t)blockIdx.x * 256 * U + threadIdx.x; base < n8; base += stride) {
+        u32x2 gr[U];
+        u32x4 wr[U];
 #pragma unroll
-        for (int u = 0; u < kUpdUnroll; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int64_t t = base + u * 256;
             if (t < n8) {
                 gr[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(g8) + t);
-                if (!skipping) wr[u] = __builtin_nontemporal_load(reinterpret_cast<u32x4 *>(w16) + t);
+                wr[u] = __builtin_nontemporal_load(reinterpret_cast<u32x4 *>(w16) + t);
             }
         }
+        if (skipping && !kStats) break;
 #pragma unroll
-        for (int u = 0; u < kUpdUnroll; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int64_t t = base + u * 256;
             if (t >= n8) continue;
-            const uint32_t gw[2] = {gr[u].x, gr[u].y};
             if constexpr (kStats) {
-#pragma unroll
-                for (int q = 0; q < 2; ++q)
-                    nonfinite += __builtin_popcount(((gw[q] & 0x7C7C7C7Cu) + 0x04040404u) & 0x80808080u);
+                nonfinite += __builtin_popcount(((gr[u].x & 0x7C7C7C7Cu) + 0x04040404u) & 0x80808080u);
+                nonfinite += __builtin_popcount(((gr[u].y & 0x7C7C7C7Cu) + 0x04040404u) & 0x80808080u);
             }
             if (skipping) continue;
-            uint32_t ww[4] = {wr[u].x, wr[u].y, wr[u].z, wr[u].w};
-            uint32_t rw[4] = {0, 0, 0, 0};
-            if constexpr (kSR) {
-                uint4 r = rng.block((uint64_t)t);
-                rw[0] = r.x; rw[1] = r.y; rw[2] = r.z; rw[3] = r.w;
-            }
-            uint32_t w8[2] = {0, 0};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {  // pair j = elements 2j, 2j+1
-                const uint32_t g_lo = (gw[j >> 1] >> (16 * (j & 1))) & 0xFFu;
-                const uint32_t g_hi = (gw[j >> 1] >> (16 * (j & 1) + 8)) & 0xFFu;
-                const uint32_t h_lo = update_one<kSR>(ww[j] & 0xFFFFu, g_lo, neg_lr, inv_scale, rw[j] & 0xFFFFu);
-                const uint32_t h_hi = update_one<kSR>(ww[j] >> 16, g_hi, neg_lr, inv_scale, rw[j] >> 16);
-                ww[j] = h_lo | (h_hi << 16);
-                if constexpr (kW8)
-                    w8[j >> 1] |= (e5m2_of_half(h_lo) | (e5m2_of_half(h_hi) << 8)) << (16 * (j & 1));
-            }
-            u32x4 o = {ww[0], ww[1], ww[2], ww[3]};
+            uint32_t lo[2] = {wr[u].x, wr[u].y}, hi[2] = {wr[u].z, wr[u].w};
+            uint4 r = make_uint4(0u, 0u, 0u, 0u);
+            if constexpr (kSR) r = rng.block((uint64_t)t);
+            float none[4][1];
+            update_four<kSR>(rule, lo, gr[u].x, none, inv_scale, Words4{r.x, r.y});
+            update_four<kSR>(rule, hi, gr[u].y, none, inv_scale, Words4{r.z, r.w});
+            const u32x4 o = {lo[0], lo[1], hi[0], hi[1]};
             __builtin_nontemporal_store(o, reinterpret_cast<u32x4 *>(w16) + t);
             if constexpr (kW8) {
-                u32x2 o8 = {w8[0], w8[1]};
+                const u32x2 o8 = {e5m2_of_halves(lo), e5m2_of_halves(hi)};
                 reinterpret_cast<u32x2 *>(w8_out)[t] = o8;  // the next step's GEMM operand: stays in the caches
             }
         }
@@ -88,7 +77,7 @@ __global__ __launch_bounds__(256) void sgd_update_kernel(uint16_t *__restrict__ 
             if (!skipping) {
                 uint32_t r16 = 0;
                 if constexpr (kSR) r16 = philox_half(rng.block((uint64_t)i >> 3), (int)(i & 7));
-                const uint32_t h = update_one<kSR>(w16[i], gc, neg_lr, inv_scale, r16);
+                const uint32_t h = update_one<kSR>(rule, w16[i], gc, nullptr, inv_scale, r16);
                 w16[i] = (uint16_t)h;
                 if constexpr (kW8) w8_out[i] = (uint8_t)e5m2_of_half(h);
             }
@@ -118,9 +107,8 @@ __global__ __launch_bounds__(256) void state_update_kernel(uint16_t *__restrict_
     float *const sp[2] = {s0, s1};
     const Philox rng(seed, offset);
     const bool skipping = (skip != nullptr) && (*skip != 0u);
-    if (skipping && stats == nullptr) return;
     uint32_t nonfinite = 0;
-    // Whole units of 512 elements, one per wave and pass: the unit is 128 chunks of four elements
+    // Units of 512 elements, one per wave and pass: the unit is 128 chunks of four elements
     // and lane l owns chunks l and 64 + l, so that every load and store of the wave covers one
     // contiguous run (1 KB of a state array, 512 B of weights, 256 B of gradient codes) -- with
     // eight consecutive elements per lane the 16-byte accesses to the FP32 state would be strided
@@ -128,56 +116,43 @@ __global__ __launch_bounds__(256) void state_update_kernel(uint16_t *__restrict_
     // block; the two lanes of a pair need the same two blocks (one per chunk), each computes one
     // and hands the other lane its half.
     const int lane = threadIdx.x & 63;
-    const int64_t units = n >> 9;
+    // The last unit of a length that is not a multiple of 512 takes a guarded copy of the same code
+    // (its last chunk may be partial: those elements go one by one at the end).
+    const int64_t units = (n + 511) >> 9, n4 = n >> 2;
     const int64_t wave0 = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6), nwaves = (int64_t)gridDim.x * 4;
-    for (int64_t u = wave0; u < units; u += nwaves) {
+    auto unit = [&](int64_t u, auto guard) {
+        constexpr bool kGuard = decltype(guard)::value;
         const int64_t c[2] = {u * 128 + lane, u * 128 + 64 + lane};
-        uint32_t gw[2];
+        // (all loads go out before the skip flag is looked at)
+        uint32_t gw[2] = {0, 0};
+        u32x2 wr[2] = {};
+        f32x4 sr[2][NS] = {};
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
+            if (kGuard && c[h] >= n4) continue;
             gw[h] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(g8) + c[h]);
-            nonfinite += __builtin_popcount(((gw[h] & 0x7C7C7C7Cu) + 0x04040404u) & 0x80808080u);
-        }
-        if (skipping) continue;
-        u32x2 wr[2];
-        f32x4 sr[2][NS];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
             wr[h] = __builtin_nontemporal_load(reinterpret_cast<u32x2 *>(w16) + c[h]);
 #pragma unroll
             for (int k = 0; k < NS; ++k)
                 sr[h][k] = __builtin_nontemporal_load(reinterpret_cast<f32x4 *>(sp[k]) + c[h]);
         }
-        uint32_t rw[2][2] = {{0, 0}, {0, 0}};   // [chunk][word]: 16 random bits per element
-        if constexpr (kSR) {
-            const bool odd = (lane & 1) != 0;
-            const uint4 mine = rng.block((uint64_t)(c[odd ? 1 : 0] >> 1));
-            // quad_perm [1,0,3,2]: the value of the other lane of the pair
-            const uint32_t got0 = (uint32_t)__builtin_amdgcn_mov_dpp((int)(odd ? mine.x : mine.z), 0xB1, 0xF, 0xF, true);
-            const uint32_t got1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)(odd ? mine.y : mine.w), 0xB1, 0xF, 0xF, true);
-            rw[0][0] = odd ? got0 : mine.x;     // first chunk: this lane's half of the even lane's block
-            rw[0][1] = odd ? got1 : mine.y;
-            rw[1][0] = odd ? mine.z : got0;     // second chunk: this lane's half of the odd lane's block
-            rw[1][1] = odd ? mine.w : got1;
-        }
+        Words4 rw[2] = {{0, 0}, {0, 0}};
+        if constexpr (kSR) rng.pair_words((uint64_t)(c[0] >> 1), (uint64_t)(c[1] >> 1), rw[0], rw[1]);
+        if (skipping && stats == nullptr) return;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            nonfinite += __builtin_popcount(((gw[h] & 0x7C7C7C7Cu) + 0x04040404u) & 0x80808080u);
+        if (skipping) return;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
+            if (kGuard && c[h] >= n4) continue;
             uint32_t ww[2] = {wr[h].x, wr[h].y};
             float sv[4][NS];
 #pragma unroll
             for (int k = 0; k < NS; ++k) {
                 sv[0][k] = sr[h][k].x; sv[1][k] = sr[h][k].y; sv[2][k] = sr[h][k].z; sv[3][k] = sr[h][k].w;
             }
-            uint32_t w8 = 0;
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {  // pair j = elements 2j, 2j+1 of the chunk
-                const uint32_t g_lo = (gw[h] >> (16 * j)) & 0xFFu;
-                const uint32_t g_hi = (gw[h] >> (16 * j + 8)) & 0xFFu;
-                const uint32_t h_lo = rule_one<kSR>(rule, ww[j] & 0xFFFFu, g_lo, sv[2 * j], inv_scale, rw[h][j] & 0xFFFFu);
-                const uint32_t h_hi = rule_one<kSR>(rule, ww[j] >> 16, g_hi, sv[2 * j + 1], inv_scale, rw[h][j] >> 16);
-                ww[j] = h_lo | (h_hi << 16);
-                if constexpr (kW8) w8 |= (e5m2_of_half(h_lo) | (e5m2_of_half(h_hi) << 8)) << (16 * j);
-            }
+            update_four<kSR>(rule, ww, gw[h], sv, inv_scale, rw[h]);
             const u32x2 o = {ww[0], ww[1]};
             __builtin_nontemporal_store(o, reinterpret_cast<u32x2 *>(w16) + c[h]);
 #pragma unroll
@@ -186,60 +161,15 @@ __global__ __launch_bounds__(256) void state_update_kernel(uint16_t *__restrict_
                 __builtin_nontemporal_store(a, reinterpret_cast<f32x4 *>(sp[k]) + c[h]);
             }
             if constexpr (kW8)
-                reinterpret_cast<uint32_t *>(w8_out)[c[h]] = w8;  // the next step's GEMM operand: stays in the caches
+                reinterpret_cast<uint32_t *>(w8_out)[c[h]] = e5m2_of_halves(ww);  // the next step's GEMM operand: stays in the caches
         }
+    };
+    for (int64_t u = wave0; u < units; u += nwaves) {
+        if ((u + 1) * 512 <= n) unit(u, std::false_type{});
+        else unit(u, std::true_type{});
     }
-    // what is left of whole items of eight elements (fewer than 64): block 0, one item per thread
-    const int64_t n8 = n >> 3;
-    for (int64_t t = units * 64 + threadIdx.x; blockIdx.x == 0 && t < n8; t += 256) {
-        const u32x2 gr = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(g8) + t);
-        const uint32_t gw[2] = {gr.x, gr.y};
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-            nonfinite += __builtin_popcount(((gw[q] & 0x7C7C7C7Cu) + 0x04040404u) & 0x80808080u);
-        if (skipping) continue;
-        const u32x4 wr = __builtin_nontemporal_load(reinterpret_cast<u32x4 *>(w16) + t);
-        float sv[8][NS];  // [element][state]
-#pragma unroll
-        for (int k = 0; k < NS; ++k) {
-            const f32x4 a = __builtin_nontemporal_load(reinterpret_cast<f32x4 *>(sp[k]) + 2 * t);
-            const f32x4 b = __builtin_nontemporal_load(reinterpret_cast<f32x4 *>(sp[k]) + 2 * t + 1);
-            sv[0][k] = a.x; sv[1][k] = a.y; sv[2][k] = a.z; sv[3][k] = a.w;
-            sv[4][k] = b.x; sv[5][k] = b.y; sv[6][k] = b.z; sv[7][k] = b.w;
-        }
-        uint32_t ww[4] = {wr.x, wr.y, wr.z, wr.w};
-        uint32_t rw[4] = {0, 0, 0, 0};
-        if constexpr (kSR) {
-            uint4 r = rng.block((uint64_t)t);
-            rw[0] = r.x; rw[1] = r.y; rw[2] = r.z; rw[3] = r.w;
-        }
-        uint32_t w8[2] = {0, 0};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {  // pair j = elements 2j, 2j+1
-            const uint32_t g_lo = (gw[j >> 1] >> (16 * (j & 1))) & 0xFFu;
-            const uint32_t g_hi = (gw[j >> 1] >> (16 * (j & 1) + 8)) & 0xFFu;
-            const uint32_t h_lo = rule_one<kSR>(rule, ww[j] & 0xFFFFu, g_lo, sv[2 * j], inv_scale, rw[j] & 0xFFFFu);
-            const uint32_t h_hi = rule_one<kSR>(rule, ww[j] >> 16, g_hi, sv[2 * j + 1], inv_scale, rw[j] >> 16);
-            ww[j] = h_lo | (h_hi << 16);
-            if constexpr (kW8)
-                w8[j >> 1] |= (e5m2_of_half(h_lo) | (e5m2_of_half(h_hi) << 8)) << (16 * (j & 1));
-        }
-        u32x4 o = {ww[0], ww[1], ww[2], ww[3]};
-        __builtin_nontemporal_store(o, reinterpret_cast<u32x4 *>(w16) + t);
-#pragma unroll
-        for (int k = 0; k < NS; ++k) {
-            const f32x4 a = {sv[0][k], sv[1][k], sv[2][k], sv[3][k]};
-            const f32x4 b = {sv[4][k], sv[5][k], sv[6][k], sv[7][k]};
-            __builtin_nontemporal_store(a, reinterpret_cast<f32x4 *>(sp[k]) + 2 * t);
-            __builtin_nontemporal_store(b, reinterpret_cast<f32x4 *>(sp[k]) + 2 * t + 1);
-        }
-        if constexpr (kW8) {
-            u32x2 o8 = {w8[0], w8[1]};
-            reinterpret_cast<u32x2 *>(w8_out)[t] = o8;
-        }
-    }
-    if (blockIdx.x == 0 && threadIdx.x < 8) {  // ragged tail (< 8 elements)
-        const int64_t i = (n8 << 3) + threadIdx.x;
+    if (blockIdx.x == 0 && threadIdx.x < 4) {  // ragged tail (< 4 elements)
+        const int64_t i = (n4 << 2) + threadIdx.x;
         if (i < n) {
             const uint32_t gc = g8[i];
             nonfinite += ((gc & 0x7Cu) == 0x7Cu) ? 1u : 0u;
@@ -249,7 +179,7 @@ __global__ __launch_bounds__(256) void state_update_kernel(uint16_t *__restrict_
                 float st[NS];
 #pragma unroll
                 for (int k = 0; k < NS; ++k) st[k] = sp[k][i];
-                const uint32_t h = rule_one<kSR>(rule, w16[i], gc, st, inv_scale, r16);
+                const uint32_t h = update_one<kSR>(rule, w16[i], gc, st, inv_scale, r16);
 #pragma unroll
                 for (int k = 0; k < NS; ++k) sp[k][i] = st[k];
                 w16[i] = (uint16_t)h;
@@ -276,7 +206,7 @@ static mp8_status launch_state_update(uint16_t *w16, float *s0, float *s1, const
     if (!w16 || !g8 || !s0 || (Rule::kStates > 1 && !s1)) return MP8_ERR_INVALID_ARG;
     if (((uintptr_t)w16 | (uintptr_t)g8 | (uintptr_t)w8_out | (uintptr_t)s0 | (uintptr_t)s1) & 15u)
         return MP8_ERR_ALIGNMENT;
-    int64_t blocks = ((n >> 3) + 255) / 256;
+    int64_t blocks = (n + 2047) / 2048;  // four waves of one 512-element unit each
     if (blocks < 1) blocks = 1;
     if (blocks > (stats != nullptr ? 2048 : (1 << 22))) blocks = stats != nullptr ? 2048 : (1 << 22);
     hipStream_t s = (hipStream_t)stream;
@@ -329,7 +259,8 @@ extern "C" mp8_status mp8_sgd_update_fp16_sr(uint16_t *w16, const uint8_t *g8, i
     if (n == 0) return MP8_OK;
     if (!w16 || !g8) return MP8_ERR_INVALID_ARG;
     if (((uintptr_t)w16 | (uintptr_t)g8 | (uintptr_t)w8_out) & 15u) return MP8_ERR_ALIGNMENT;
-    const int64_t per_block = 256 * kUpdUnroll;
+    const bool small = (n >> 3) <= 2 * 256 * 256;  // one item per thread occupies the chip at most twice
+    const int64_t per_block = small ? 256 : 512;
     int64_t blocks = ((n >> 3) + per_block - 1) / per_block;
     if (blocks < 1) blocks = 1;
     if (blocks > (1 << 22)) blocks = 1 << 22;
@@ -337,9 +268,9 @@ extern "C" mp8_status mp8_sgd_update_fp16_sr(uint16_t *w16, const uint8_t *g8, i
     const float neg_lr = -lr;
     hipStream_t s = (hipStream_t)stream;
 #define MP8_U(SR, W8, ST)                                                                       \
-    hipLaunchKernelGGL((sgd_update_kernel<SR, W8, ST>), dim3((unsigned)blocks), dim3(256), 0, s, \
-                       w16, g8, n, neg_lr, inv_loss_scale, seed, offset, skip_if_nonzero,       \
-                       w8_out, stats)
+    hipLaunchKernelGGL((small ? sgd_update_kernel<SR, W8, ST, 1> : sgd_update_kernel<SR, W8, ST, 2>),  \
+                       dim3((unsigned)blocks), dim3(256), 0, s, w16, g8, n, neg_lr, inv_loss_scale, seed,  \
+                       offset, skip_if_nonzero, w8_out, stats)
     const bool sr = round == MP8_SR, w8 = w8_out != nullptr, st = stats != nullptr;
     if (sr) {
         if (w8) { if (st) MP8_U(true, true, true); else MP8_U(true, true, false); }
