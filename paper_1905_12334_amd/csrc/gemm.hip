@@ -127,6 +127,20 @@ static void (*const kAny[3][2])(const GemmArgs) = {
     {gemm_any_kernel<EPI_PARTIAL, false, true>, gemm_any_kernel<EPI_FULL, false, true>},
     {gemm_any_kernel<EPI_PARTIAL, true, true>, gemm_any_kernel<EPI_FULL, true, true>}};
 
+// Kernels whose epilogue applies the master-weight update: [row-major, contraction-major operands][state
+// words per weight].
+using UpdateKernel = void (*)(const GemmArgs, const UpdateHook);
+static const UpdateKernel kWavekUpdate[2][3] = {
+    {gemm_wavek_update_kernel<0, false, false, 0>, gemm_wavek_update_kernel<1, false, false, 0>,
+     gemm_wavek_update_kernel<2, false, false, 0>},
+    {gemm_wavek_update_kernel<0, true, true, 0>, gemm_wavek_update_kernel<1, true, true, 0>,
+     gemm_wavek_update_kernel<2, true, true, 0>}};
+static const UpdateKernel k64x64Update[2][3] = {
+    {gemm_mfma_update_kernel<64, 64, 2, 2, 2, 4, 0, false, false>, gemm_mfma_update_kernel<64, 64, 2, 2, 2, 4, 1, false, false>,
+     gemm_mfma_update_kernel<64, 64, 2, 2, 2, 4, 2, false, false>},
+    {gemm_mfma_update_kernel<64, 64, 2, 2, 2, 4, 0, true, true>, gemm_mfma_update_kernel<64, 64, 2, 2, 2, 4, 1, true, true>,
+     gemm_mfma_update_kernel<64, 64, 2, 2, 2, 4, 2, true, true>}};
+
 struct Plan {
     bool mfma;   // one of kTiles
     int tile;    // index into kTiles
@@ -256,6 +270,20 @@ static Plan any_plan(int64_t rows, int64_t cols, int64_t kc) {
     return pl;
 }
 
+// The kernel that computes an unsplit weight gradient and applies the update in its epilogue, or null.  Such
+// an update costs neither a launch nor a pass over the gradient codes.  Built for the 64x64 tiles, whose
+// outputs are small: larger ones stream their weights and state faster in a kernel of its own.  Measured
+// against the two kernels (GPU time): 256^3 SGD 5.6 us, was 6.2; 4096 x 2048 x 512 SGD 15.8, was 16.7; ADAM
+// 19.3, was 19.8 there, but with 64 tiles (1024 x 512 x 512) 11.0 against 9.8: its divisions and square
+// roots then run on a quarter of the CUs, so it wants half of them to have a tile.
+static UpdateKernel update_kernel(const Plan &pl, int64_t cols, int layout, int states) {
+    if (!pl.mfma || pl.splits != 1 || (cols & 15) != 0 || (layout != 0 && layout != 3)) return nullptr;
+    if (states == 2 && pl.tiles_m * pl.tiles_n < kCUs / 2) return nullptr;
+    if (pl.tile == T64x64w) return kWavekUpdate[layout != 0][states];
+    if (pl.tile == T64x64s2) return k64x64Update[layout != 0][states];
+    return nullptr;
+}
+
 // Upper bound of the workspace: one FP32 tile set per contraction slice.  (The MFMA kernel
 // finishes its tiles itself only for an unsplit contraction, a row length that is a multiple
 // of 16 and no FP32 / transposed output; otherwise it writes FP32 tiles and the finishing
@@ -335,14 +363,14 @@ namespace mp8 {
 static mp8_status launch_mfma(GemmArgs ga, const Epilogue &ep, const Plan &pl, int64_t kc,
                               void (*const pick[3])(const GemmArgs), void *workspace,
                               size_t workspace_bytes, hipStream_t s, const UpdateHook *upd = nullptr,
-                              bool validate_only = false) {
+                              bool validate_only = false, UpdateKernel with_update = nullptr) {
     const int64_t rows = ep.rows, cols = ep.cols;
     const int acc_mode = ep.acc_mode;
     float *acc = ep.acc;
     uint8_t *out8 = ep.out8, *out8_t = ep.out8_t;
     // Fused epilogue or two passes?  (The master-weight update lives in the finishing pass;
     // gemm_any_kernel's own epilogue does everything else.)
-    const bool two_pass = pl.splits > 1 || upd != nullptr ||
+    const bool two_pass = pl.splits > 1 || (upd != nullptr && with_update == nullptr) ||
                           (pl.mfma && ((cols & 15) != 0 || acc_mode != 0 || out8_t != nullptr));
     float *partial = nullptr;
     Epilogue fin = ep;  // what the finishing kernel applies
@@ -382,6 +410,10 @@ static mp8_status launch_mfma(GemmArgs ga, const Epilogue &ep, const Plan &pl, i
                              : (ep.sr || ep.sat || ep.stats != nullptr || out8 == nullptr || !pl.mfma) ? EPI_FULL
                                                                                                         : EPI_RNE;
     const size_t dyn_lds = pl.mfma ? (size_t)kTiles[pl.tile].lds_per_stage * (size_t)ga.ksteps : 0;
+    if (with_update != nullptr && !two_pass) {
+        hipLaunchKernelGGL(with_update, dim3((unsigned)nblocks), dim3(256), 0, s, ga, *upd);
+        return hipGetLastError() == hipSuccess ? MP8_OK : MP8_ERR_HIP;
+    }
     hipLaunchKernelGGL(pick[epi], dim3((unsigned)nblocks), dim3(256), dyn_lds, s, ga);
     if (hipGetLastError() != hipSuccess) return MP8_ERR_HIP;
     if (two_pass) {
@@ -461,8 +493,9 @@ static mp8_status gemm_impl(mp8_op op, int64_t M, int64_t N, int64_t K, const ui
     };
     // A contraction with an incomplete stage never needs a workspace: without one for the two-pass
     // form it runs unsplit on the kernel whose epilogue does everything.
-    if (pl.mfma && kc % BK != 0 && (pl.splits > 1 || (cols & 15) != 0 || acc_mode != 0 || out8_t != nullptr || upd != nullptr) &&
-        !has_workspace(pl.splits))
+    const UpdateKernel with_update = upd != nullptr ? update_kernel(pl, cols, layout, upd->states) : nullptr;
+    if (pl.mfma && kc % BK != 0 && !has_workspace(pl.splits) &&
+        (pl.splits > 1 || (cols & 15) != 0 || acc_mode != 0 || out8_t != nullptr || (upd != nullptr && with_update == nullptr)))
         pl.mfma = false;
 
     if (!pl.mfma && any_kernel_takes(rows, cols, kc, lda, ldb, layout)) {
@@ -495,7 +528,7 @@ static mp8_status gemm_impl(mp8_op op, int64_t M, int64_t N, int64_t K, const ui
     ga.ldb = ldb;
     const TileConfig &tc = kTiles[pl.tile];
     return launch_mfma(ga, ep, pl, kc, atn ? tc.kernel_tn : btn ? tc.kernel_bt : tc.kernel, workspace,
-                       workspace_bytes, s, upd, validate_only);
+                       workspace_bytes, s, upd, validate_only, with_update);
 }
 
 // The checks of mp8_gemm_fp8 on these arguments without enqueuing anything: what a call made of
@@ -546,13 +579,15 @@ static UpdateHook make_update_hook(uint16_t *w16, uint8_t *w8_out, const uint32_
 // on it just to carry the update would write and re-read the whole FP32 result (measured: 1024 x
 // 4096 from 16384 tokens 91 against 77 us).  Then the codes go to g8_out, or to the workspace if
 // the caller keeps no gradient, and the stand-alone update kernel follows.  Null: use the
-// finishing pass.
+// finishing pass -- or, with own_epilogue, the GEMM kernel whose epilogue carries the update.
 static uint8_t *codes_for_separate_update(int64_t M, int64_t N, int64_t K, int flags, uint8_t *g8_out,
-                                          void *workspace, size_t workspace_bytes) {
+                                          void *workspace, size_t workspace_bytes, bool own_epilogue,
+                                          int states) {
     const bool atn = (flags & MP8_FLAG_A_CONTRACTION_MAJOR) != 0, btn = (flags & MP8_FLAG_B_CONTRACTION_MAJOR) != 0;
     if ((atn && !btn) || (N & 15) != 0 || K > (INT64_MAX / 8) / std::max<int64_t>(N, 1)) return nullptr;
     const Plan pl = make_plan(K, N, M, 0, 0, (atn ? 1 : 0) | (btn ? 2 : 0));
     if (!pl.mfma || pl.splits != 1) return nullptr;
+    if (own_epilogue && update_kernel(pl, N, (atn ? 1 : 0) | (btn ? 2 : 0), states) != nullptr) return nullptr;
     if (g8_out != nullptr) return g8_out;
     return workspace != nullptr && workspace_bytes >= (size_t)(K * N) ? (uint8_t *)workspace : nullptr;
 }
@@ -576,9 +611,10 @@ namespace mp8 {
 // Weight gradient, its rounding, and a master-weight update of the rounded codes (Figure 1b): the
 // body the three optimizer variants share.  `hook` is the rule as the finishing pass applies it,
 // `update_from(codes)` launches the same rule's stand-alone kernel on codes in memory.  Three ways,
-// all with the same results: the GEMM with its own epilogue followed by the update kernel (unsplit
-// contractions, shapes without a finishing pass, and a skip flag that lives inside `stats` -- see
-// flag_inside_stats), or the update inside the finishing pass of a split contraction.  Whatever
+// all with the same results: the update inside the finishing pass of a split contraction, or inside the
+// GEMM's own epilogue (small unsplit outputs, see update_kernel), or the GEMM followed by the
+// update kernel (larger ones, unaligned operands, and a skip flag that lives inside `stats` -- see
+// flag_inside_stats).  Whatever
 // can be checked is checked before the first launch.
 template <class UpdateFrom>
 static mp8_status wgrad_with_update(int64_t M, int64_t N, int64_t K, const uint8_t *a, int64_t lda,
@@ -595,16 +631,20 @@ static mp8_status wgrad_with_update(int64_t M, int64_t N, int64_t K, const uint8
         if (sg != MP8_OK) return sg;
         return update_from(codes);
     };
-    if (uint8_t *codes = codes_for_separate_update(M, N, K, flags, g8_out, workspace, workspace_bytes))
+    const bool late_flag = flag_inside_stats(hook.skip, stats);
+    if (uint8_t *codes = codes_for_separate_update(M, N, K, flags, g8_out, workspace, workspace_bytes, !late_flag,
+                                                   hook.states))
         return two_launches(codes, nullptr, 0);
-    if (flag_inside_stats(hook.skip, stats))
+    if (late_flag)
         return g8_out != nullptr ? two_launches(g8_out, workspace, workspace_bytes) : MP8_ERR_INVALID_ARG;
     const mp8_status st = gemm_impl(MP8_WGRAD, M, N, K, a, lda, b, ldb, alpha, nullptr, 0, g8_out, nullptr,
                                     g_round, flags, g_seed, g_offset, stats, workspace, workspace_bytes,
                                     stream, 0, 0, &hook);
-    if (st != MP8_ERR_UNSUPPORTED || g8_out == nullptr) return st;
-    // no finishing pass to carry the update: two launches through the 8-bit gradient
-    return two_launches(g8_out, workspace, workspace_bytes);
+    if (st != MP8_ERR_UNSUPPORTED) return st;
+    // nothing to carry the update (unaligned operands, ...): two launches through the 8-bit gradient
+    if (uint8_t *codes = codes_for_separate_update(M, N, K, flags, g8_out, workspace, workspace_bytes, false, hook.states))
+        return two_launches(codes, nullptr, 0);
+    return g8_out != nullptr ? two_launches(g8_out, workspace, workspace_bytes) : st;
 }
 
 }  // namespace mp8

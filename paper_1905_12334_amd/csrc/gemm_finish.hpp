@@ -103,9 +103,9 @@ __device__ __forceinline__ UpdateOperands4 load_update4(const UpdateHook &u, int
     return o;
 }
 
-// Elements i0 .. i0+3 (i0 % 4 == 0) from their four packed gradient codes.
+// Elements i0 .. i0+3 (i0 % 4 == 0) from their four packed gradient codes and random words.
 template <int STATES>
-__device__ __forceinline__ void update4(const UpdateHook &u, int64_t i0, uint32_t pk, const UpdateOperands4 &in) {
+__device__ __forceinline__ void update4(const UpdateHook &u, int64_t i0, uint32_t pk, const UpdateOperands4 &in, Words4 r) {
     uint32_t w[2] = {in.w.x, in.w.y};
     float st[4][2] = {{0.0f, 0.0f}, {0.0f, 0.0f}, {0.0f, 0.0f}, {0.0f, 0.0f}};
     if constexpr (STATES >= 1) {
@@ -117,7 +117,7 @@ __device__ __forceinline__ void update4(const UpdateHook &u, int64_t i0, uint32_
         st[0][1] = x.x; st[1][1] = x.y; st[2][1] = x.z; st[3][1] = x.w;
     }
     with_rule<STATES>(u, [&](const auto &rule) {
-        if (u.sr) update_four<true>(rule, w, pk, st, u.inv_scale, Philox(u.seed, u.offset).half_block((uint64_t)i0));
+        if (u.sr) update_four<true>(rule, w, pk, st, u.inv_scale, r);
         else update_four<false>(rule, w, pk, st, u.inv_scale, Words4{0u, 0u});
     });
     if constexpr (STATES >= 1) {
@@ -131,6 +131,73 @@ __device__ __forceinline__ void update4(const UpdateHook &u, int64_t i0, uint32_
     const u32x2 o = {w[0], w[1]};
     *reinterpret_cast<u32x2 *>(u.w16 + i0) = o;
     if (u.w8_out != nullptr) *reinterpret_cast<uint32_t *>(u.w8_out + i0) = e5m2_of_halves(w);
+}
+
+// The update inside a GEMM's own epilogue.  A thread finishes Q groups of four consecutive weights; group
+// q of neighbouring lanes lies side by side (runs of 128 or 256 bytes of FP32 state; sixteen consecutive
+// weights per lane, as the plain epilogues have them, cost 6 us more here for 1 M weights with ADAM).  Lanes
+// 2m and 2m + 1 hold the halves of one random block.  where(q): row, column (a multiple of 4), and whether
+// it exists; value(q, v): the four sums.  `in`: what load_groups fetched, ahead of the contraction.
+struct GroupAt {
+    int64_t r, c;
+    bool valid;
+};
+template <int STATES, int Q, class Where>
+__device__ __forceinline__ void load_groups(const Epilogue &ep, const UpdateHook &u, Where where, UpdateOperands4 (&in)[Q]) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const GroupAt g = where(q);
+        if (g.valid) in[q] = load_update4<STATES>(u, g.r * ep.cols + g.c);
+    }
+}
+// The random words of the two roundings (gradient, weight).  Drawn while the first operands are on their
+// way: one workgroup has nothing else to do then, and 1 - 2 us of multiplications to do after the
+// contraction otherwise.
+template <int Q>
+struct GroupWords {
+    Words4 g[Q], w[Q];
+};
+template <int Q, class Where>
+__device__ __forceinline__ void draw_groups(const Epilogue &ep, const UpdateHook &u, Where where, GroupWords<Q> &out) {
+    static_assert(Q % 2 == 0, "random blocks are shared over pairs of groups");
+    auto draw = [&](uint64_t seed, uint64_t offset, Words4(&w)[Q]) {
+        const Philox rng(seed, offset);
+#pragma unroll
+        for (int q = 0; q < Q; q += 2) {
+            const GroupAt a = where(q), b = where(q + 1);
+            rng.pair_words((uint64_t)(a.r * ep.cols + a.c) >> 3, (uint64_t)(b.r * ep.cols + b.c) >> 3, w[q], w[q + 1]);
+        }
+    };
+    out = GroupWords<Q>{};
+    if (ep.sr) draw(ep.seed, ep.offset, out.g);
+    if (u.sr) draw(u.seed, u.offset, out.w);
+}
+// A rolled loop, the register arrays shifted down by one group per turn: straight-line code for four groups
+// of ADAM is 19 KB that every launch would fetch through a cold instruction cache.
+template <int STATES, int Q, class Where, class Value>
+__device__ __forceinline__ void update_groups(const Epilogue &ep, const UpdateHook &u, bool updating, Where where, Value value,
+                                              StatsAcc &st, UpdateOperands4 (&in)[Q], GroupWords<Q> &words) {
+#pragma unroll 1
+    for (int q = 0; q < Q; ++q) {
+        const GroupAt g = where(q);
+        if (g.valid) {
+            const int64_t i0 = g.r * ep.cols + g.c;
+            float v[4];
+            value(q, v);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] *= ep.alpha;
+            const uint32_t pk = e5m2_pack4_rt(v, words.g[0].r01, words.g[0].r23, ep.sr != 0, ep.sat != 0);
+            if (ep.stats != nullptr) st.add4(v, pk);
+            if (ep.out8 != nullptr) *reinterpret_cast<uint32_t *>(ep.out8 + i0) = pk;
+            if (updating) update4<STATES>(u, i0, pk, in[0], words.w[0]);
+        }
+#pragma unroll
+        for (int k = 0; k + 1 < Q; ++k) {
+            in[k] = in[k + 1];
+            words.g[k] = words.g[k + 1];
+            words.w[k] = words.w[k + 1];
+        }
+    }
 }
 
 // Sum the FP32 tiles of the contraction slices in slice order and finish: the complete sum is
@@ -181,7 +248,8 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float *__restr
                 }
             }
             const uint32_t pk = finish4(ep, r, c, v, st);
-            if (updating) update4<STATES>(upd, i0, pk, uo);
+            if (updating)
+                update4<STATES>(upd, i0, pk, uo, upd.sr ? Philox(upd.seed, upd.offset).half_block((uint64_t)i0) : Words4{0u, 0u});
         }
     } else {
         for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < slice; i += stride) {

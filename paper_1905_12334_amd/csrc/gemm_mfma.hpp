@@ -3,6 +3,7 @@
 #pragma once
 
 #include "gemm_common.hpp"
+#include "gemm_finish.hpp"
 
 namespace mp8 {
 
@@ -38,9 +39,8 @@ namespace mp8 {
 //   2  a[r, (tap, co)] = e[r - shift(tap), co]      a plain, b[ci, (tap, co)] = w[tap][ci][co]
 //   3  a[(tap, ci), r] = x[r + shift(tap), ci]      both contraction-major, tap fixed per tile row
 // so only the base address of a stage (1, 2) or of a tile (3) differs from the plain GEMM.
-template <int BM, int BN, int WGM, int WGN, int NSTAGE, int MINBLOCKS, int EPI, bool ATN = false,
-          bool BTN = false, int CONV_ = 0>
-__global__ __launch_bounds__(256, MINBLOCKS) void gemm_mfma_kernel(const GemmArgs p) {
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI, bool ATN, bool BTN, int CONV_>
+__device__ __forceinline__ void gemm_mfma(const GemmArgs &p, const UpdateHook &upd) {
     // CONV_ 4 / 5: forms 1 / 2 for channel counts that are odd multiples of 64 (HALVES below)
     constexpr int CONV = CONV_ > 3 ? CONV_ - 3 : CONV_;
     constexpr bool HALVES = CONV_ > 3;
@@ -70,6 +70,21 @@ __global__ __launch_bounds__(256, MINBLOCKS) void gemm_mfma_kernel(const GemmArg
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / WGN, wn = wave % WGN;
     const int64_t row0 = (int64_t)tm * BM, col0 = (int64_t)tn * BN;
+
+    // what this thread updates (EPI_UPDATE): four groups of four weights of the wave's 32x32 tile, eight
+    // lanes side by side in a row, fetched before the contraction
+    constexpr int STATES = EPI >= EPI_UPDATE ? EPI - EPI_UPDATE : 0;
+    auto group = [&](int q) {
+        const int64_t r = row0 + wm * WTM + 8 * q + (lane >> 3), c = col0 + wn * WTN + 4 * (lane & 7);
+        return GroupAt{r, c, r < p.rows && c < p.cols};
+    };
+    UpdateOperands4 uo[4];
+    bool updating = false;
+    if constexpr (EPI >= EPI_UPDATE) {
+        static_assert(WTM == 32 && WTN == 32, "one 32x32 tile per wave");
+        load_groups<STATES, 4>(p.ep, upd, group, uo);
+        updating = !(upd.skip != nullptr && *upd.skip != 0u);
+    }
 
     // contraction slice of this workgroup, in stages of 128
     const int per = p.ks_per, extra = p.ks_extra;
@@ -334,6 +349,8 @@ __global__ __launch_bounds__(256, MINBLOCKS) void gemm_mfma_kernel(const GemmArg
             if (st == 0 && has_tail && ks_begin == 0) issue_tail();
             else issue_loads(st);
         }
+    GroupWords<4> words;
+    if constexpr (EPI >= EPI_UPDATE) draw_groups<4>(p.ep, upd, group, words);
     wait_stage(-1);
     __syncthreads();
 #pragma unroll
@@ -504,6 +521,14 @@ __global__ __launch_bounds__(256, MINBLOCKS) void gemm_mfma_kernel(const GemmArg
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if constexpr (EPI >= EPI_UPDATE) {
+            auto sum = [&](int q, float v[4]) {
+                const f32x4 x = *reinterpret_cast<const f32x4 *>(band + (8 * q + (lane >> 3)) * EP_LD + 4 * (lane & 7));
+                v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+            };
+            update_groups<STATES, 4>(p.ep, upd, updating, group, sum, st, uo, words);
+            break;
+        }
         // the RNE-only variant is small enough to unroll: the LDS reads of several items then
         // overlap instead of each item paying the full LDS latency
 #pragma unroll(EPI == EPI_RNE ? 4 : 1)
@@ -526,9 +551,19 @@ __global__ __launch_bounds__(256, MINBLOCKS) void gemm_mfma_kernel(const GemmArg
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    if constexpr (EPI == EPI_FULL) {
+    if constexpr (EPI >= EPI_FULL) {
         if (p.ep.stats != nullptr) st.flush(p.ep.stats);
     }
+}
+
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, int MINBLOCKS, int EPI, bool ATN = false,
+          bool BTN = false, int CONV_ = 0>
+__global__ __launch_bounds__(256, MINBLOCKS) void gemm_mfma_kernel(const GemmArgs p) {
+    gemm_mfma<BM, BN, WGM, WGN, NSTAGE, EPI, ATN, BTN, CONV_>(p, UpdateHook{});
+}
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, int MINBLOCKS, int STATES, bool ATN, bool BTN>
+__global__ __launch_bounds__(256, MINBLOCKS) void gemm_mfma_update_kernel(const GemmArgs p, const UpdateHook upd) {
+    gemm_mfma<BM, BN, WGM, WGN, NSTAGE, EPI_UPDATE + STATES, ATN, BTN, 0>(p, upd);
 }
 
 }  // namespace mp8

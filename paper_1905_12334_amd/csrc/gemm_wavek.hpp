@@ -3,6 +3,7 @@
 #pragma once
 
 #include "gemm_common.hpp"
+#include "gemm_finish.hpp"
 
 namespace mp8 {
 
@@ -20,8 +21,11 @@ namespace mp8 {
 // row), else 0.  BM = 32 / BN = 32 (row-major operand only): half the tile rows / columns, for
 // outputs with so few 64x64 tiles that most CUs would idle while the busy ones wait for their
 // own loads (a CU takes 64 bytes per clock however few of them work).
+// With EPI_UPDATE the master weights and the optimizer's state that a thread will need at the end are
+// fetched before the first stage: one workgroup per CU leaves each lane 512 registers.
 template <int EPI, bool ATN, bool BTN, int CONV, int BM = 64, int BN = 64>
-__global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(const GemmArgs p) {
+__device__ __forceinline__ void gemm_wavek(const GemmArgs &p, const UpdateHook &upd) {
+    constexpr int STATES = EPI >= EPI_UPDATE ? EPI - EPI_UPDATE : 0;
     static_assert(CONV == 0 || (CONV == 3 && ATN && BTN), "plain or convolution weight gradient");
     static_assert(BTN || !ATN, "a alone contraction-major is not built");
     static_assert(BM == 64 || (BM == 32 && !ATN), "the 32-row tile takes a row-major a");
@@ -44,6 +48,19 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(const GemmArgs p) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t row0 = (int64_t)tm * BM, col0 = (int64_t)tn * BN;
+    // what this thread updates: four groups of four weights, 16 lanes side by side in a row of the tile
+    auto group = [&](int q) {
+        const int item = threadIdx.x + 256 * q;
+        const int64_t r = row0 + (item >> 4), c = col0 + 4 * (item & 15);
+        return GroupAt{r, c, r < p.rows && c < p.cols};
+    };
+    UpdateOperands4 uo[4];
+    bool updating = false;
+    if constexpr (EPI >= EPI_UPDATE) {
+        static_assert(BM == 64 && BN == 64, "four groups per thread");
+        load_groups<STATES, 4>(p.ep, upd, group, uo);
+        updating = !(upd.skip != nullptr && *upd.skip != 0u);
+    }
     const int per = p.ks_per, extra = p.ks_extra;
     const int ks_begin = split * per + (split < extra ? split : extra);
     const int ks_count = per + (split < extra ? 1 : 0);
@@ -133,6 +150,8 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(const GemmArgs p) {
     if (has_tail && ks_begin + wave == 0) issue_tail();
     else if (mine > 0) issue(0);
     if (mine > 1) issue(1);
+    GroupWords<4> words;
+    if constexpr (EPI >= EPI_UPDATE) draw_groups<4>(p.ep, upd, group, words);
     for (int j = 0; j < mine; ++j) {
         if (j + 1 < mine) wait_vm_lds<QA + QB>();  // the loads of the next stage may fly
         else wait_vm_lds<0>();
@@ -176,8 +195,20 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(const GemmArgs p) {
             }
     __syncthreads();
     StatsAcc st;
-    const bool fast_cols = (p.cols & 15) == 0;
-    if (BM * BN == 64 * 64 || threadIdx.x < BM * BN / 16) {  // whole waves either way
+    if constexpr (EPI >= EPI_UPDATE) {
+        auto sum = [&](int q, float v[4]) {
+            const int item = threadIdx.x + 256 * q;
+            f32x4 t = {};
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const f32x4 x = *reinterpret_cast<const f32x4 *>(red + (w * BM + (item >> 4)) * RED_LD + 4 * (item & 15));
+                if (w == 0) t = x;
+                else { t.x += x.x; t.y += x.y; t.z += x.z; t.w += x.w; }
+            }
+            v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+        };
+        update_groups<STATES, 4>(p.ep, upd, updating, group, sum, st, uo, words);
+    } else if (BM * BN == 64 * 64 || threadIdx.x < BM * BN / 16) {  // whole waves either way
         constexpr int CG = BN / 16;
         const int rr = threadIdx.x / CG, cg = threadIdx.x % CG;
         const int64_t r = row0 + rr, c = col0 + 16 * cg;
@@ -193,11 +224,20 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(const GemmArgs p) {
                     v[4 * q] += x.x; v[4 * q + 1] += x.y; v[4 * q + 2] += x.z; v[4 * q + 3] += x.w;
                 }
             }
-        if (r < p.rows && c < p.cols) emit16<EPI>(p, split, r, c, v, st, fast_cols);
+        if (r < p.rows && c < p.cols) emit16<EPI>(p, split, r, c, v, st, (p.cols & 15) == 0);
     }
-    if constexpr (EPI == EPI_FULL) {
+    if constexpr (EPI >= EPI_FULL) {
         if (p.ep.stats != nullptr) st.flush(p.ep.stats);
     }
+}
+
+template <int EPI, bool ATN, bool BTN, int CONV, int BM = 64, int BN = 64>
+__global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(const GemmArgs p) {
+    gemm_wavek<EPI, ATN, BTN, CONV, BM, BN>(p, UpdateHook{});
+}
+template <int STATES, bool ATN, bool BTN, int CONV>
+__global__ __launch_bounds__(256, 1) void gemm_wavek_update_kernel(const GemmArgs p, const UpdateHook upd) {
+    gemm_wavek<EPI_UPDATE + STATES, ATN, BTN, CONV>(p, upd);
 }
 
 }  // namespace mp8
