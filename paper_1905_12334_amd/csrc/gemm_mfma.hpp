@@ -310,16 +310,10 @@ __device__ __forceinline__ void gemm_mfma(const GemmArgs &p, const UpdateHook &u
         // ends up with consecutive output columns.
         acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bv, av, acc[i][j], 1, 1, 0, 0, 0, 0);
     };
-    auto issue_one = [&](int kstage, int q) {  // load q (0 .. G-1) of a stage
+    auto issue_one = [&](int kstage, const StageAddr &ak, const StageAddr &bk, int q) {  // load q (0 .. G-1) of a stage
         const uint32_t sa = lds0 + (kstage % NSTAGE) * STAGE + wave * 1024;
-        if (q < A_DMA) {
-            const StageAddr ak = a_stage(kstage);
-            dma16(ak.base, lane_off(ak, oa[q < A_DMA ? q : 0], HALVES), sa + q * 4096);
-        } else {
-            const StageAddr bk = b_stage(kstage);
-            dma16(bk.base, lane_off(bk, ob[q >= A_DMA ? q - A_DMA : 0], HALVES && CONV == 2),
-                  sa + A_BYTES + (q - A_DMA) * 4096);
-        }
+        if (q < A_DMA) dma16(ak.base, lane_off(ak, oa[q < A_DMA ? q : 0], HALVES), sa + q * 4096);
+        else dma16(bk.base, lane_off(bk, ob[q >= A_DMA ? q - A_DMA : 0], HALVES && CONV == 2), sa + A_BYTES + (q - A_DMA) * 4096);
     };
 
     // Wait for this wave's loads of stage t+1 (and for its own LDS reads).  Loads complete in
@@ -392,6 +386,10 @@ __device__ __forceinline__ void gemm_mfma(const GemmArgs &p, const UpdateHook &u
         const bool next = t + 1 < ks_count;
         // the early stage that ends a contraction of an odd number of units: second half only
         const bool skip_first = HALVES && p.cv.odd_units && ks_begin + t == p.ksteps - 1;
+        // The addresses of the stage this one loads, once and before its first MFMA: a tap and a channel
+        // part are some forty scalar instructions, which each load of a convolution's stage used to
+        // repeat between two MFMAs.
+        const StageAddr ak = a_stage(t + NSTAGE), bk = b_stage(t + NSTAGE);
 #pragma unroll
         for (int k = 0; k < 2 * NM; ++k) {
             if (k < NM) {
@@ -416,7 +414,7 @@ __device__ __forceinline__ void gemm_mfma(const GemmArgs &p, const UpdateHook &u
 #pragma unroll
                 for (int r = 0; r < D1; ++r) {
                     const int q = (k - S_BAR) * D1 + r;
-                    if (q < G && more) issue_one(t + NSTAGE, q);
+                    if (q < G && more) issue_one(t + NSTAGE, ak, bk, q);
                 }
             }
             if (k >= NM) {
