@@ -198,10 +198,19 @@ static Plan make_plan(int64_t rows, int64_t cols, int64_t kc, int tile_config, i
         const int64_t n256 = count(T256x256), n128 = count(T128x128s2);
         const double fill256 = (double)n256 / (double)(((n256 + kCUs - 1) / kCUs) * kCUs);
         const int64_t n64 = count(T64x64s2);
-        // 128x128 tiles, one workgroup per CU, long contraction: every wave the whole tile on a
-        // quarter of the contraction (measured 6-17 % faster than the four-stage ring when no CU
-        // gets more than two tiles; with more tiles, or a split contraction, the ring kernels win)
-        const int long128 = (!conv && n128 >= kCUs / 2 && n128 <= 2 * kCUs) ? T128x128p : T128x128s4;
+        // 128x128 tiles.  One round (one tile per CU at most): from 64 stages on every wave takes the whole
+        // tile on a quarter of the contraction, below that the four-stage ring keeps more loads in
+        // flight than the two-stage one (2048 x 2048 x 4096 contraction-major 25.3 -> 23.4 us, 1536 x 2048
+        // 25.3 -> 21.4; with all CUs taken it pays from 24 stages on: 19.7 both, at 16 14.5 against
+        // 15.5).  Two rounds: two workgroups of the two-stage ring per CU beat both, whose second tile
+        // starts when the first has ended (2304 x 2048 x 8192 47.7 us, four stages 69.0, wave-divided
+        // 67.5; 4096 x 2048 x 16384 119.5 / 135.2 / 132.3).  A row-major a with both rounds nearly full is the
+        // exception from 128 stages on (4096 x 2048 x 16384 124.0 us, wave-divided 121.4; x 8192 57.7 and 63.9).
+        const bool one_round = !conv && n128 >= kCUs / 2 && n128 <= kCUs;
+        const int ring128 = one_round && ksteps >= (n128 <= kCUs - kCUs / 8 ? 16 : 24) ? T128x128s4 : T128x128s2;
+        const bool two_rounds = !conv && n128 > kCUs && n128 <= 2 * kCUs;
+        const bool wave_rounds = two_rounds && layout != 3 && n128 >= 2 * kCUs - kCUs / 4 && ksteps >= 128;
+        const int long128 = one_round || wave_rounds ? T128x128p : two_rounds ? T128x128s2 : T128x128s4;
         if (n256 >= 208 && fill256 >= 0.8 && ksteps >= 8) t = T256x256;
         // so few tiles that most CUs would idle and the contraction is too short to split:
         // half the rows per tile, and half the columns too if that still fits one round
@@ -210,10 +219,16 @@ static Plan make_plan(int64_t rows, int64_t cols, int64_t kc, int tile_config, i
         else if (!(layout & 1) && 2 * n64 <= kCUs && ksteps >= 16 && ksteps <= 40 && count(T32x64w) <= kCUs)
             t = T32x64w;
         else if (n64 <= kCUs && ksteps >= 16) t = T64x64w;  // one workgroup per CU, one round
+        // between half and three quarters of the CUs with a 128x128 tile, both operands contraction-major: two
+        // to three 64x64 tiles per CU until the contraction is long enough to pay for an update kernel of its
+        // own, which the 64x64 tiles do not need (2304 x 1024 x 4096 29.0 us, four-stage ring 20.7; 2048 x 1024,
+        // where every CU has two, 20.5 and 20.6, x 6144 31.3 and 26.6)
+        else if (layout == 3 && one_round && n128 < 192 && ksteps <= 64 && ksteps >= (n128 > kCUs / 2 ? 32 : 48))
+            t = T128x128s4;
         else if (tn && (n128 < 16 || (n128 < 192 && ksteps <= 64))) t = T64x64s2;
-        else if (tn) t = ksteps >= 64 ? long128 : T128x128s2;
+        else if (tn) t = ksteps >= 64 ? long128 : ring128;
         else if (n128 >= 192 && ksteps <= 2) t = T128x128k;  // all prologue and epilogue
-        else if (n128 >= 192) t = (ksteps >= 64 && n128 <= 2 * kCUs) ? long128 : T128x128s2;
+        else if (n128 >= 192) t = (ksteps >= 64 && n128 <= 2 * kCUs) ? long128 : ring128;
         else t = T64x64s2;
     }
     pl.tile = t;

@@ -30,6 +30,9 @@ CASES = [
     (512, 512, 2049, TN), (512, 512, 2064, ROW), (128, 1024, 2096, BTN), (128, 512, 2160, ROW),
     (320, 128, 6007, TN), (64, 64, 9001, TN), (1536, 1408, 8200, TN), (1536, 1408, 8208, ROW), (1536, 1408, 8208, BTN),
     (3840, 4096, 1040, ROW), (3840, 4096, 1072, BTN), (3840, 4096, 1025, TN),
+    # one 128x128 tile per CU on the four-stage ring, and two of the two-stage one
+    (1536, 2048, 2065, TN), (2032, 1936, 3100, TN), (2048, 2048, 3088, ROW), (2000, 1552, 2096, BTN), (2288, 1024, 4100, TN),
+    (2304, 2032, 8208, BTN),
     # odd everything
     (17, 33, 16, ROW), (17, 33, 17, BTN), (17, 33, 31, TN), (16, 16, 100, TN), (63, 65, 127, ROW), (65, 63, 128, BTN),
     (129, 1000, 128, BTN), (256, 1000, 2048, BTN), (1000, 2048, 255, TN), (999, 1001, 333, ROW), (81, 79, 1000, TN),
