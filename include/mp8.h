@@ -132,10 +132,13 @@ mp8_status mp8_quantize_e5m2_batch(const mp8_quantize_item *items, int count, vo
  *              acc_mode 2, for out8_t, and when cols is not a multiple of 16;
  *              mp8_gemm_fp8_workspace_bytes(op, M, N, K) is enough in every case.  A call
  *              that does not need it accepts NULL.
- * Any contraction length >= 1 and any rows/cols >= 1 are accepted; a zero dimension is valid and
- * does nothing.  A contraction that is not a multiple of 128, and operands that are not 16-byte
- * aligned, never need a workspace; with the one the query asks for they may run faster (a split
- * contraction).  Partial sums of a split
+ * Any contraction length >= 1, any rows/cols >= 1 and operands without that alignment are accepted; a
+ * zero dimension is valid and does nothing.
+ * Precision: aligned operands with a contraction that is a multiple of 128 (and, for a
+ * contraction-major operand, a multiple of 16 rows resp. columns) run on the 8-bit matrix instruction, which
+ * cuts a product 13 bits below the largest one of its group of eight.  Every other call accumulates at
+ * least as precisely as FP32 multiply-adds do, and never needs a workspace: with the one the query asks
+ * for it may run faster (the slices of a split contraction side by side), to the same bits.  Partial sums of a split
  * contraction are combined in FP32, in a fixed order, before the single rounding, so results
  * are bit-reproducible run to run.
  */

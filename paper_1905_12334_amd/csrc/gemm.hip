@@ -12,7 +12,8 @@
 //   gemm_shortk.hpp   contractions of one or two stages (all start-up and epilogue)
 //   gemm_wavek.hpp    small outputs with long contractions (contraction divided among waves)
 //   gemm_wave128.hpp  about one 128x128 tile per CU and a long contraction (every wave the whole tile)
-//   gemm_any.hpp      row lengths, leading dimensions, contractions that are not multiples of 16
+//   gemm_any.hpp      row lengths and leading dimensions that are not multiples of 16, contractions that
+//                     are not multiples of 128 (half-precision matrix instructions)
 //   gemm_finish.hpp   second pass for split contractions and unfused epilogues, optionally with
 //                     the master-weight update; the any-shape fallback kernel
 // Split contraction, FP32 / transposed outputs, ragged column counts: the MFMA kernels write
@@ -120,12 +121,12 @@ constexpr int kNumTiles = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
 constexpr int kCUs = 256;
 constexpr int kMaxSplits = 64;
 
-// gemm_any_kernel by operand layout (row-major, b contraction-major, both) and epilogue: the FP32
-// tiles of a split contraction, or everything
-static void (*const kAny[3][2])(const GemmArgs) = {
-    {gemm_any_kernel<EPI_PARTIAL, false, false>, gemm_any_kernel<EPI_FULL, false, false>},
-    {gemm_any_kernel<EPI_PARTIAL, false, true>, gemm_any_kernel<EPI_FULL, false, true>},
-    {gemm_any_kernel<EPI_PARTIAL, true, true>, gemm_any_kernel<EPI_FULL, true, true>}};
+// gemm_any_kernel by operand layout (row-major, b contraction-major, both): the FP32 tiles of a split
+// contraction, an unsplit one, a split one slice by slice
+static void (*const kAny[3][3])(const GemmArgs) = {
+    {gemm_any_kernel<EPI_PARTIAL, false, false>, gemm_any_kernel<EPI_FULL, false, false>, gemm_any_slices_kernel<false, false>},
+    {gemm_any_kernel<EPI_PARTIAL, false, true>, gemm_any_kernel<EPI_FULL, false, true>, gemm_any_slices_kernel<false, true>},
+    {gemm_any_kernel<EPI_PARTIAL, true, true>, gemm_any_kernel<EPI_FULL, true, true>, gemm_any_slices_kernel<true, true>}};
 
 // Kernels whose epilogue applies the master-weight update: [row-major, contraction-major operands][state
 // words per weight].
@@ -135,6 +136,9 @@ static const UpdateKernel kWavekUpdate[2][3] = {
      gemm_wavek_update_kernel<2, false, false, 0>},
     {gemm_wavek_update_kernel<0, true, true, 0>, gemm_wavek_update_kernel<1, true, true, 0>,
      gemm_wavek_update_kernel<2, true, true, 0>}};
+static const UpdateKernel kAnyUpdate[2][3] = {
+    {gemm_any_update_kernel<0, false, false>, gemm_any_update_kernel<1, false, false>, gemm_any_update_kernel<2, false, false>},
+    {gemm_any_update_kernel<0, true, true>, gemm_any_update_kernel<1, true, true>, gemm_any_update_kernel<2, true, true>}};
 static const UpdateKernel k64x64Update[2][3] = {
     {gemm_mfma_update_kernel<64, 64, 2, 2, 2, 4, 0, false, false>, gemm_mfma_update_kernel<64, 64, 2, 2, 2, 4, 1, false, false>,
      gemm_mfma_update_kernel<64, 64, 2, 2, 2, 4, 2, false, false>},
@@ -145,6 +149,7 @@ struct Plan {
     bool mfma;   // one of kTiles
     int tile;    // index into kTiles
     int splits;
+    bool in_turn;  // gemm_any_kernel: a workgroup takes all slices of its tile
     int tiles_m, tiles_n;
 };
 
@@ -169,9 +174,7 @@ static Plan make_plan(int64_t rows, int64_t cols, int64_t kc, int tile_config, i
                       int layout = 0,      // bit 0: a contraction-major, bit 1: b
                       bool conv = false) { // a convolution: only the tiles with convolution addressing
     Plan pl{};
-    // A contraction that ends with an incomplete stage is multiplied by the same kernels (automatic
-    // choice only) as long as whole 16-byte chunks of its row-major operands exist.
-    pl.mfma = kc > 0 && (kc % BK == 0 || (tile_config == 0 && !conv && (layout == 3 || (kc & 15) == 0)));
+    pl.mfma = (kc % BK) == 0 && kc > 0;
     // contraction-major operands are fetched in 16-row chunks, by the tiles built for them
     if ((layout & 1) && (rows & 15) != 0) pl.mfma = false;
     if ((layout & 2) && (cols & 15) != 0) pl.mfma = false;
@@ -181,13 +184,13 @@ static Plan make_plan(int64_t rows, int64_t cols, int64_t kc, int tile_config, i
     const bool tn = layout != 0;
     if (layout == 0 && tile_config > 0 && kTiles[tile_config - 1].kernel[0] == nullptr) pl.mfma = false;
     if (tile_config > 0 && kTiles[tile_config - 1].max_ksteps > 0 &&
-        (tn || (kc + BK - 1) / BK > kTiles[tile_config - 1].max_ksteps))
+        (tn || kc / BK > kTiles[tile_config - 1].max_ksteps))
         pl.mfma = false;
     if (!pl.mfma) {
         pl.splits = 1;
         return pl;
     }
-    const int ksteps = (int)((kc + BK - 1) / BK);
+    const int ksteps = (int)(kc / BK);
     auto count = [&](int t) {
         return ((rows + kTiles[t].bm - 1) / kTiles[t].bm) * ((cols + kTiles[t].bn - 1) / kTiles[t].bn);
     };
@@ -272,7 +275,8 @@ static bool any_kernel_takes(int64_t rows, int64_t cols, int64_t kc, int64_t lda
 
 // Contraction slices of gemm_any_kernel: two workgroups fit a CU, so up to 512 run at once, and a
 // slice should keep two stages for each of the four waves.  The finishing pass costs about as much
-// as ANY_FINISH_STAGES stages of one wave, so a split must save more than that.
+// as ANY_FINISH_STAGES stages of one wave, so a split must save more than that.  (The shape alone decides,
+// so that the order of additions does not depend on the workspace.)
 constexpr int64_t ANY_FINISH_STAGES = 24;
 static Plan any_plan(int64_t rows, int64_t cols, int64_t kc) {
     Plan pl{};
@@ -334,16 +338,13 @@ extern "C" size_t mp8_gemm_fp8_workspace_bytes_tuned(mp8_op op, int64_t M, int64
     if (tile_config < 0 || tile_config > kNumTiles || split_k < 0) return 0;
     int64_t rows, cols, kc;
     op_dims(op, M, N, K, rows, cols, kc);
-    // enough for every operand layout
+    // enough for every operand layout and alignment
     size_t need = 0;
-    for (int layout : {0, 2, 3}) {
-        const Plan pl = make_plan(rows, cols, kc, tile_config, split_k, layout);
-        size_t one = plan_workspace(pl, rows, cols);
-        if (!pl.mfma && tile_config == 0) {  // a split contraction of gemm_any_kernel
-            const int splits = any_plan(rows, cols, kc).splits;
-            one = splits > 1 ? (size_t)splits * (size_t)rows * (size_t)cols * sizeof(float) : 0;
-        }
-        need = std::max(need, one);
+    for (int layout : {0, 2, 3})
+        need = std::max(need, plan_workspace(make_plan(rows, cols, kc, tile_config, split_k, layout), rows, cols));
+    if (tile_config == 0) {  // the slices of gemm_any_kernel side by side
+        const Plan pl = any_plan(rows, cols, kc);
+        if (pl.splits > 1) need = std::max(need, (size_t)pl.splits * (size_t)rows * (size_t)cols * sizeof(float));
     }
     return need;
 }
@@ -358,9 +359,7 @@ extern "C" mp8_status mp8_gemm_fp8_plan(mp8_op op, int64_t M, int64_t N, int64_t
     if (atn && !btn) return MP8_ERR_UNSUPPORTED;
     int64_t rows, cols, kc;
     op_dims(op, M, N, K, rows, cols, kc);
-    Plan pl{};
-    pl.splits = 1;  // (a contraction with an incomplete stage: the call's own choice, reported as 0)
-    if (kc % BK == 0) pl = make_plan(rows, cols, kc, tile_config, split_k, (atn ? 1 : 0) | (btn ? 2 : 0));
+    const Plan pl = make_plan(rows, cols, kc, tile_config, split_k, (atn ? 1 : 0) | (btn ? 2 : 0));
     if (tile_out) *tile_out = pl.mfma ? pl.tile + 1 : 0;
     if (splits_out) *splits_out = pl.splits;
     return MP8_OK;
@@ -383,9 +382,9 @@ static mp8_status launch_mfma(GemmArgs ga, const Epilogue &ep, const Plan &pl, i
     const int acc_mode = ep.acc_mode;
     float *acc = ep.acc;
     uint8_t *out8 = ep.out8, *out8_t = ep.out8_t;
-    // Fused epilogue or two passes?  (The master-weight update lives in the finishing pass;
-    // gemm_any_kernel's own epilogue does everything else.)
-    const bool two_pass = pl.splits > 1 || (upd != nullptr && with_update == nullptr) ||
+    // Fused epilogue or two passes?  (The master-weight update lives in the finishing pass or in an
+    // update kernel; gemm_any_kernel's own epilogue does everything else.)
+    const bool two_pass = (pl.splits > 1 && !pl.in_turn) || (upd != nullptr && with_update == nullptr) ||
                           (pl.mfma && ((cols & 15) != 0 || acc_mode != 0 || out8_t != nullptr));
     float *partial = nullptr;
     Epilogue fin = ep;  // what the finishing kernel applies
@@ -401,14 +400,13 @@ static mp8_status launch_mfma(GemmArgs ga, const Epilogue &ep, const Plan &pl, i
             partial = (float *)workspace;
         }
     }
-    const int64_t nblocks = (int64_t)pl.tiles_m * pl.tiles_n * pl.splits;
+    const int64_t nblocks = (int64_t)pl.tiles_m * pl.tiles_n * (pl.in_turn ? 1 : pl.splits);
     if (nblocks > 0x7FFFFFFFLL) return MP8_ERR_UNSUPPORTED;
     if (validate_only) return MP8_OK;  // every check has passed; nothing is enqueued
 
     ga.rows = rows;
     ga.cols = cols;
     ga.ksteps = (int)((kc + BK - 1) / BK);
-    ga.tail = (int)(kc % BK);
     ga.kc = kc;
     ga.splits = pl.splits;
     ga.tiles_m = pl.tiles_m;
@@ -453,7 +451,7 @@ static mp8_status launch_mfma(GemmArgs ga, const Epilogue &ep, const Plan &pl, i
 namespace mp8 {
 
 // mp8_gemm_fp8_tuned, optionally with the master-weight update applied to the rounded result
-// (`upd`; only kernels with a finishing pass carry it: MP8_ERR_UNSUPPORTED otherwise).
+// (`upd`; the finishing pass or an update kernel carries it, MP8_ERR_UNSUPPORTED if the call has neither).
 static mp8_status gemm_impl(mp8_op op, int64_t M, int64_t N, int64_t K, const uint8_t *a, int64_t lda,
                             const uint8_t *b, int64_t ldb, float alpha, float *acc, int acc_mode,
                             uint8_t *out8, uint8_t *out8_t, mp8_round round, int flags, uint64_t seed,
@@ -506,26 +504,22 @@ static mp8_status gemm_impl(mp8_op op, int64_t M, int64_t N, int64_t K, const ui
     auto has_workspace = [&](int splits) {
         return workspace != nullptr && workspace_bytes >= (size_t)splits * (size_t)rows * (size_t)cols * sizeof(float);
     };
-    // A contraction with an incomplete stage never needs a workspace: without one for the two-pass
-    // form it runs unsplit on the kernel whose epilogue does everything.
-    const UpdateKernel with_update = upd != nullptr ? update_kernel(pl, cols, layout, upd->states) : nullptr;
-    if (pl.mfma && kc % BK != 0 && !has_workspace(pl.splits) &&
-        (pl.splits > 1 || (cols & 15) != 0 || acc_mode != 0 || out8_t != nullptr || (upd != nullptr && with_update == nullptr)))
-        pl.mfma = false;
-
     if (!pl.mfma && any_kernel_takes(rows, cols, kc, lda, ldb, layout)) {
         pl = any_plan(rows, cols, kc);
-        if (!has_workspace(pl.splits)) pl.splits = 1;
-        // (the update goes with the finishing pass of a split contraction only: otherwise two launches)
-        if (upd != nullptr && pl.splits == 1) return MP8_ERR_UNSUPPORTED;
+        // it never needs a workspace: without one a split contraction takes its slices in turn
+        const bool side_by_side = pl.splits > 1 && has_workspace(pl.splits);
+        pl.in_turn = !side_by_side;
+        const UpdateKernel any_update = upd != nullptr && !side_by_side && (cols & 15) == 0 && layout != 2
+                                            ? kAnyUpdate[layout != 0][upd->states] : nullptr;
+        if (upd != nullptr && !side_by_side && any_update == nullptr) return MP8_ERR_UNSUPPORTED;
         GemmArgs ga{};
         ga.a = a;
         ga.b = b;
         ga.lda = lda;
         ga.ldb = ldb;
         void (*const *kern)(const GemmArgs) = kAny[atn ? 2 : btn ? 1 : 0];
-        void (*const pick[3])(const GemmArgs) = {kern[0], nullptr, kern[1]};
-        return launch_mfma(ga, ep, pl, kc, pick, workspace, workspace_bytes, s, upd, validate_only);
+        void (*const pick[3])(const GemmArgs) = {kern[0], nullptr, kern[pl.splits > 1 ? 2 : 1]};
+        return launch_mfma(ga, ep, pl, kc, pick, workspace, workspace_bytes, s, upd, validate_only, any_update);
     }
     if (!pl.mfma || kc == 0) {
         if (upd != nullptr) return MP8_ERR_UNSUPPORTED;
@@ -541,6 +535,7 @@ static mp8_status gemm_impl(mp8_op op, int64_t M, int64_t N, int64_t K, const ui
     ga.b = b;
     ga.lda = lda;
     ga.ldb = ldb;
+    const UpdateKernel with_update = upd != nullptr ? update_kernel(pl, cols, layout, upd->states) : nullptr;
     const TileConfig &tc = kTiles[pl.tile];
     return launch_mfma(ga, ep, pl, kc, atn ? tc.kernel_tn : btn ? tc.kernel_bt : tc.kernel, workspace,
                        workspace_bytes, s, upd, validate_only, with_update);
@@ -656,10 +651,11 @@ static mp8_status wgrad_with_update(int64_t M, int64_t N, int64_t K, const uint8
                                     g_round, flags, g_seed, g_offset, stats, workspace, workspace_bytes,
                                     stream, 0, 0, &hook);
     if (st != MP8_ERR_UNSUPPORTED) return st;
-    // nothing to carry the update (unaligned operands, ...): two launches through the 8-bit gradient
-    if (uint8_t *codes = codes_for_separate_update(M, N, K, flags, g8_out, workspace, workspace_bytes, false, hook.states))
-        return two_launches(codes, nullptr, 0);
-    return g8_out != nullptr ? two_launches(g8_out, workspace, workspace_bytes) : st;
+    // nothing to carry the update (a row length that is not a multiple of 16, ...): two launches through the
+    // 8-bit gradient, which lies in the workspace if the caller keeps none
+    if (g8_out != nullptr) return two_launches(g8_out, workspace, workspace_bytes);
+    if (workspace == nullptr || K > (INT64_MAX / 8) / N || workspace_bytes < (size_t)(K * N)) return st;
+    return two_launches((uint8_t *)workspace, nullptr, 0);
 }
 
 }  // namespace mp8
@@ -802,7 +798,7 @@ extern "C" mp8_status mp8_gemm_fp8_static(mp8_op op, int64_t M, int64_t N, int64
     if (M > 0 && N > 0 && K > 0 && (int)op >= 0 && (int)op <= 2) {
         int64_t rows, cols, kc;
         op_dims(op, M, N, K, rows, cols, kc);
-        // (a contraction with an incomplete stage runs without a workspace where this one is too small)
+        // (a contraction that is not whole stages runs without a workspace where this one is too small)
         if (kc % BK == 0 &&
             mp8_gemm_fp8_workspace_bytes(op, M, N, K) > kStaticScratchBytes)
             return MP8_ERR_WORKSPACE;

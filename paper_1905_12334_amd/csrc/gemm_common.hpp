@@ -85,12 +85,7 @@ struct GemmArgs {
     const uint8_t *b;
     int64_t lda, ldb;
     int64_t rows, cols;
-    int ksteps;         // contraction length / BK, rounded up (pipeline stages)
-    // Contraction indices of a last, incomplete stage (0: the contraction is whole stages).  The
-    // kernels multiply that stage FIRST, so that only their start-up code, and nothing in their
-    // loops, knows of it: global stage 0 is the incomplete one and stage s > 0 covers indices
-    // BK (s - 1) ...  What lies beyond the contraction reads as zero (see dma16_or_zero).
-    int tail;
+    int ksteps;         // contraction length / BK (pipeline stages; gemm_any_kernel: rounded up)
     int64_t kc;         // contraction length (gemm_any_kernel)
     int splits;         // number of contraction slices
     int tiles_m, tiles_n;
@@ -351,17 +346,6 @@ __device__ __forceinline__ void dma16(const uint8_t *gbase, uint32_t lane_off, u
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                  :
                  : "v"(lane_off), "s"(gbase), "s"(lds_addr)
-                 : "memory", "m0");
-}
-
-// The same for the incomplete stage of a contraction: a lane whose sixteen bytes lie beyond it
-// fetches zero codes instead, from an array that exists for this, so that every address is valid.
-static __device__ const uint8_t kZeroCodes[16] __attribute__((aligned(16))) = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-__device__ __forceinline__ void dma16_or_zero(const uint8_t *gbase, uint32_t lane_off, bool inside, uint32_t lds_addr) {
-    const uint8_t *src = inside ? gbase + lane_off : kZeroCodes;
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                 :
-                 : "v"(src), "s"(lds_addr)
                  : "memory", "m0");
 }
 

@@ -132,12 +132,6 @@ __device__ __forceinline__ void gemm_mfma(const GemmArgs &p, const UpdateHook &u
     }
     if constexpr (CONV == 2) b_origin = p.b + col0 * p.ldb;
     else b_origin = BTN ? p.b + (int64_t)ks_begin * b_kstep + col0 : p.b + col0 * p.ldb + (int64_t)ks_begin * BK;
-    // an incomplete stage goes first: the whole ones start one stage later
-    const bool has_tail = CONV == 0 && p.tail != 0;
-    if (has_tail) {
-        a_origin -= a_kstep;
-        b_origin -= b_kstep;
-    }
     const uint8_t *a_tile = uniform_ptr(a_origin);
     const uint8_t *b_tile = uniform_ptr(b_origin);
     // base addresses of stage `kstage` of this workgroup's slice
@@ -234,20 +228,6 @@ __device__ __forceinline__ void gemm_mfma(const GemmArgs &p, const UpdateHook &u
         for (int q = 0; q < B_DMA; ++q) dma16(bk.base, lane_off(bk, ob[q], HALVES && CONV == 2), sb + q * 4096);
     };
 
-    // the incomplete stage (stage 0 of the first slice) into ring slot 0
-    auto issue_tail = [&]() {
-        const uint32_t sa = lds0 + wave * 1024;
-        const uint8_t *ak = a_tile + (int64_t)p.ksteps * a_kstep, *bk = b_tile + (int64_t)p.ksteps * b_kstep;
-        auto inside = [&](bool km, bool narrow, int q) {
-            if (km) return (narrow ? 16 * (wave + 4 * q) + lrow64 : 8 * (wave + 4 * (q & 3)) + lrow) < p.tail;
-            return 16 * lchunk < p.tail;
-        };
-#pragma unroll
-        for (int q = 0; q < A_DMA; ++q) dma16_or_zero(ak, oa[q], inside(ATN, BM == 64, q), sa + q * 4096);
-#pragma unroll
-        for (int q = 0; q < B_DMA; ++q) dma16_or_zero(bk, ob[q], inside(BTN, BN == 64, q), sa + A_BYTES + q * 4096);
-    };
-
     // Fragments: lane l supplies row (l % 32) of a 32-row tile and, for sub-step s, the 32
     // bytes k = 64*s + 32*(l/32) .. +31 of the slab, i.e. chunks 4s + 2*(l/32) and the next.
     // A fragment is fetched as two 16-byte LDS reads ("halves").  Fragment f of a sub-step is
@@ -339,10 +319,7 @@ __device__ __forceinline__ void gemm_mfma(const GemmArgs &p, const UpdateHook &u
     // prologue: fill the ring, fetch the fragments of (0, 0)
 #pragma unroll
     for (int st = 0; st < NSTAGE; ++st)
-        if (st < ks_count) {
-            if (st == 0 && has_tail && ks_begin == 0) issue_tail();
-            else issue_loads(st);
-        }
+        if (st < ks_count) issue_loads(st);
     GroupWords<4> words;
     if constexpr (EPI >= EPI_UPDATE) draw_groups<4>(p.ep, upd, group, words);
     wait_stage(-1);

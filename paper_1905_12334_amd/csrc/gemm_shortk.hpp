@@ -31,7 +31,6 @@ __global__ __launch_bounds__(256, EPI == EPI_FULL ? 4 : 5) void gemm_shortk_kern
     const int tn = __builtin_amdgcn_readfirstlane((int)tn_);
     const int64_t row0 = (int64_t)tm * BM, col0 = (int64_t)tn * BN;
     const int ksteps = p.ksteps;  // 1 or 2
-    const bool has_tail = p.tail != 0;  // the incomplete stage goes first
 
     // direct loads: same slab image as the main kernel (chunk c of row r in slot c ^ ((r>>1)&7))
     const int lrow = lane >> 3, lchunk = (lane & 7) ^ ((4 * wave + (lane >> 4)) & 7);
@@ -51,20 +50,10 @@ __global__ __launch_bounds__(256, EPI == EPI_FULL ? 4 : 5) void gemm_shortk_kern
     for (int st = 0; st < 2; ++st) {
         if (st < ksteps) {
             const uint32_t sa = lds0 + st * STAGE + wave * 1024;
-            if (st == 0 && has_tail) {
-                const bool inside = 16 * lchunk < p.tail;
-                const int k0 = (ksteps - 1) * BK;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) dma16_or_zero(a_tile + k0, oa[q], inside, sa + q * 4096);
+            for (int q = 0; q < 4; ++q) dma16(a_tile + st * BK, oa[q], sa + q * 4096);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) dma16_or_zero(b_tile + k0, ob[q], inside, sa + A_BYTES + q * 4096);
-                continue;
-            }
-            const int k0 = (has_tail ? st - 1 : st) * BK;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) dma16(a_tile + k0, oa[q], sa + q * 4096);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) dma16(b_tile + k0, ob[q], sa + A_BYTES + q * 4096);
+            for (int q = 0; q < 4; ++q) dma16(b_tile + st * BK, ob[q], sa + A_BYTES + q * 4096);
         }
     }
 

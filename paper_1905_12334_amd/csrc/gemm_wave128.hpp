@@ -64,11 +64,8 @@ __global__ __launch_bounds__(256, 1) void gemm_wave128_kernel(const GemmArgs p) 
     const int mine = __builtin_amdgcn_readfirstlane(ks_count > wave ? (ks_count - wave + 3) >> 2 : 0);
 
     const int64_t a_kstep = ATN ? (int64_t)BK * p.lda : BK, b_kstep = BTN ? (int64_t)BK * p.ldb : BK;
-    // an incomplete stage goes first (stage 0, wave 0 of the first slice): the others start one later
-    const bool has_tail = p.tail != 0;
-    const int64_t ks0 = ks_begin + wave - (has_tail ? 1 : 0);
-    const uint8_t *a_tile = uniform_ptr((ATN ? p.a + row0 : p.a + row0 * p.lda) + ks0 * a_kstep);
-    const uint8_t *b_tile = uniform_ptr((BTN ? p.b + col0 : p.b + col0 * p.ldb) + ks0 * b_kstep);
+    const uint8_t *a_tile = uniform_ptr((ATN ? p.a + row0 : p.a + row0 * p.lda) + (int64_t)(ks_begin + wave) * a_kstep);
+    const uint8_t *b_tile = uniform_ptr((BTN ? p.b + col0 : p.b + col0 * p.ldb) + (int64_t)(ks_begin + wave) * b_kstep);
     // Direct loads, sixteen per operand and stage (1 KB each).  Row-major operand: load q brings
     // tile rows 8q .. 8q+7, lane i lands at (row i/8, slot i%8) and fetches chunk
     // (i%8) ^ ((row >> 1) & 7); rows beyond the matrix are clamped to its last row.
@@ -136,17 +133,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wave128_kernel(const GemmArgs p) 
         }
     };
 
-    if (has_tail && ks_begin + wave == 0) {
-        const uint8_t *ak = a_tile + (int64_t)p.ksteps * a_kstep, *bk = b_tile + (int64_t)p.ksteps * b_kstep;
-        auto inside = [&](bool km, int q) {
-            const int r = 8 * q + (lane >> 3);
-            return (km ? r : 16 * ((lane & 7) ^ ((r >> 1) & 7))) < p.tail;
-        };
-#pragma unroll
-        for (int q = 0; q < 16; ++q) dma16_or_zero(ak, oa[q], inside(ATN, q), buf0 + q * 1024);
-#pragma unroll
-        for (int q = 0; q < 16; ++q) dma16_or_zero(bk, ob[q], inside(BTN, q), buf0 + SLAB + q * 1024);
-    } else if (mine > 0) {
+    if (mine > 0) {
 #pragma unroll
         for (int q = 0; q < 32; ++q) dma(0, q);
     }

@@ -79,11 +79,8 @@ __device__ __forceinline__ void gemm_wavek(const GemmArgs &p, const UpdateHook &
         a_origin = ATN ? p.a + row0 : p.a + row0 * p.lda;
     }
     const uint8_t *b_origin = BTN ? p.b + col0 : p.b + col0 * p.ldb;
-    // an incomplete stage goes first (stage 0, wave 0 of the first slice): the others start one later
-    const bool has_tail = CONV == 0 && p.tail != 0;
-    const int64_t ks0 = ks_begin + wave - (has_tail ? 1 : 0);
-    const uint8_t *a_tile = uniform_ptr(a_origin + ks0 * a_kstep);
-    const uint8_t *b_tile = uniform_ptr(b_origin + ks0 * b_kstep);
+    const uint8_t *a_tile = uniform_ptr(a_origin + (int64_t)(ks_begin + wave) * a_kstep);
+    const uint8_t *b_tile = uniform_ptr(b_origin + (int64_t)(ks_begin + wave) * b_kstep);
     // Direct loads, eight per operand and stage.  Row-major operand: load q brings tile rows
     // 8q .. 8q+7, lane i lands at (row i/8, slot i%8) and fetches chunk (i%8) ^ ((row >> 1) & 7);
     // rows beyond the matrix are clamped to its last row.  Contraction-major operand: load q
@@ -123,19 +120,6 @@ __device__ __forceinline__ void gemm_wavek(const GemmArgs &p, const UpdateHook &
         for (int q = 0; q < QB; ++q) dma16(bk, ob[q], sa + SLAB_A + q * 1024);
     };
 
-    auto issue_tail = [&]() {  // the incomplete stage into buffer 0
-        const uint8_t *ak = a_origin + (int64_t)(p.ksteps - 1) * a_kstep;
-        const uint8_t *bk = b_origin + (int64_t)(p.ksteps - 1) * b_kstep;
-        auto inside = [&](bool km, int q) {
-            if (km) return 16 * q + (lane >> 2) < p.tail;
-            return 16 * ((lane & 7) ^ (((8 * q + (lane >> 3)) >> 1) & 7)) < p.tail;
-        };
-#pragma unroll
-        for (int q = 0; q < QA; ++q) dma16_or_zero(ak, oa[q], inside(ATN, q), ring0 + q * 1024);
-#pragma unroll
-        for (int q = 0; q < QB; ++q) dma16_or_zero(bk, ob[q], inside(BTN, q), ring0 + SLAB_A + q * 1024);
-    };
-
     f32x16 acc[MI][NJ];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
@@ -147,8 +131,7 @@ __device__ __forceinline__ void gemm_wavek(const GemmArgs &p, const UpdateHook &
 
     // (Issuing the fragment reads of a half stage ahead of the MFMAs of the one before it, as
     // the general kernel does, was measured and gained nothing here: the loop waits for loads.)
-    if (has_tail && ks_begin + wave == 0) issue_tail();
-    else if (mine > 0) issue(0);
+    if (mine > 0) issue(0);
     if (mine > 1) issue(1);
     GroupWords<4> words;
     if constexpr (EPI >= EPI_UPDATE) draw_groups<4>(p.ep, upd, group, words);

@@ -102,6 +102,26 @@ def mfma_error_bound(a8, b8, absref, partial_sums=64):
     return trunc + (kc / MFMA_BLOCK + partial_sums) * 2.0 ** -23 * absref, trunc
 
 
+def fma_chain(a8, b8):
+    """FP32 accumulators of a chain of fused multiply-adds in contraction order (each step is formed in
+    double, where the product of two codes is exact, and rounded to FP32)."""
+    va, vb = (oracle.e5m2_decode_table().astype(np.float64)[x] for x in (a8, b8))
+    acc = np.zeros((a8.shape[0], b8.shape[0]), np.float32)
+    for j in range(a8.shape[1]):
+        acc = (acc + va[:, j, None] * vb[None, :, j]).astype(np.float32)
+    return acc
+
+
+def assert_as_precise_as_fp32(acc, a8, b8, ref, label=""):
+    """GEMMs outside the direct-to-LDS kernels accumulate like FP32 multiply-adds: their rms error against
+    the double reference is at most that of the chain in contraction order, up to one tenth (two
+    independent rounding patterns on this many elements) and one rounding of the result (2^-25 of it)."""
+    rms = lambda x: float(np.sqrt(np.mean(np.square(x.astype(np.float64)))))
+    err, chain = rms(acc - ref), rms(fma_chain(a8, b8) - ref)
+    record_ratios("rms error over that of an FP32 chain " + label, a8.shape[1], model=err / (chain + 1e-300))
+    assert err <= 1.1 * chain + 2.0 ** -25 * rms(ref), (label, err, chain, rms(ref))
+
+
 def acc_tolerance_ok(acc, ref, absref, kc):
     tol, tight = acc_bounds(ref, absref, kc)
     err = np.abs(acc.astype(np.float64) - ref)

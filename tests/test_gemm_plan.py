@@ -18,3 +18,10 @@ def test_plan_of_one_and_two_rounds(tiles, stages, layouts, kernel):
              "bt": (mp8.FLAG_B_CONTRACTION_MAJOR,)}[layouts]
     for f in flags:
         assert mp8.gemm_fp8_plan(mp8.FWD, 128 * tiles[0], 128 * tiles[1], 128 * stages, f) == (kernel, 1)
+
+
+def test_workspace_query_covers_operands_of_any_alignment():
+    """200 tiles of 64x64 and 64 whole stages: unsplit on aligned operands, two slices on others."""
+    rows, cols, kc = 64 * 20, 64 * 10, 8192
+    assert mp8.gemm_fp8_plan(mp8.FWD, rows, cols, kc)[1] == 1
+    assert mp8.gemm_fp8_workspace_bytes(mp8.FWD, rows, cols, kc) >= 2 * 4 * rows * cols

@@ -68,3 +68,27 @@ def test_update_in_the_epilogue_equals_two_calls(mp8, dims, rule, contraction_ma
             res.append([host(t) for t in (w.view(torch.int16), m.view(torch.int32), v.view(torch.int32), w8)] + ([host(g)] if keep else []))
         assert all(np.array_equal(p, q) for p, q in zip(*res)), (keep, skip)
         assert mp8.read_stats(st) == mp8.read_stats(st2)
+
+
+@pytest.mark.parametrize("dims,rule,own", [((256, 64, 64), "sgd", True), ((384, 208, 80), "momentum", True), ((2048, 1040, 976), "sgd", True),
+                                           ((256, 64, 64), "adam", False), ((2048, 1040, 976), "adam", True),
+                                           ((512, 1024, 512), "adam", True), ((512, 1024, 448), "adam", False)])
+def test_which_calls_update_in_the_epilogue(mp8, dims, rule, own):
+    """Only a kernel that applies the update in its own epilogue can do without a gradient buffer and a
+    workspace where the contraction is whole stages: SGD and momentum on any number of 64x64 tiles,
+    ADAM from 128 of them on."""
+    import torch
+    M, N, K = dims
+    a, b = (torch.full(s, 0x38, dtype=torch.uint8, device="cuda") for s in ((M, K), (M, N)))
+    w, m, v = (torch.zeros(K * N, dtype=t, device="cuda") for t in (torch.float16, torch.float32, torch.float32))
+    kw = dict(flags=mp8.FLAG_CONTRACTION_MAJOR)
+    call = {"sgd": lambda: mp8.wgrad_update_fp16_sr(M, N, K, a, b, w, 1e-3, 1.0, **kw),
+            "momentum": lambda: mp8.wgrad_momentum_fp16_sr(M, N, K, a, b, w, m, 1e-3, 1.0, 0.9, **kw),
+            "adam": lambda: mp8.wgrad_adam_fp16_sr(M, N, K, a, b, w, m, v, 1e-3, 1.0, 1, **kw)}[rule]
+    if own:
+        call()
+        torch.cuda.synchronize()
+        assert bool((w < 0).all())
+    else:
+        with pytest.raises(mp8.Mp8Error):
+            call()
