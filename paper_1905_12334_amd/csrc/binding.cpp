@@ -53,6 +53,17 @@ struct Arg {
     explicit operator bool() const { return t != nullptr; }
 };
 
+// Sizes are formed from what the caller passes: they saturate instead of wrapping, so that no product of
+// large dimensions passes for a small one.
+int64_t mul(int64_t a, int64_t b) {
+    int64_t r;
+    return __builtin_mul_overflow(a, b, &r) ? ((a < 0) == (b < 0) ? INT64_MAX : INT64_MIN) : r;
+}
+int64_t add(int64_t a, int64_t b) {
+    int64_t r;
+    return __builtin_add_overflow(a, b, &r) ? (a < 0 ? INT64_MIN : INT64_MAX) : r;
+}
+
 // The arguments of one call, read in order.
 struct Args {
     PyObject *const *at_;
@@ -64,18 +75,35 @@ struct Args {
         }
         return *at_++;
     }
-    // integers wrap to 64 bits, as they do through ctypes
+    // seeds, offsets, enumerations and flags wrap, as they do through ctypes
     uint64_t u64() {
         const uint64_t v = PyLong_AsUnsignedLongLongMask(next());
         if (v == (uint64_t)-1 && PyErr_Occurred()) throw Raised{};
         return v;
     }
-    int64_t i64() { return (int64_t)u64(); }
     int i32() { return (int)u64(); }
+    // dimensions do not: the sizes that are checked are the ones that are passed on
+    int64_t as_i64(PyObject *o) {
+        int overflow = 0;
+        const int64_t v = PyLong_AsLongLongAndOverflow(o, &overflow);
+        if (overflow) fail("%S does not fit 64 bits", o);
+        if (v == -1 && PyErr_Occurred()) throw Raised{};
+        return v;
+    }
+    int64_t i64() { return as_i64(next()); }
     float f32() {
         const double v = PyFloat_AsDouble(next());
         if (v == -1.0 && PyErr_Occurred()) throw Raised{};
         return (float)v;
+    }
+    int op() {
+        PyObject *o = next();
+        const int64_t v = as_i64(o);
+        if (v < 0 || v > 2) {
+            PyErr_SetObject(PyExc_KeyError, o);
+            throw Raised{};
+        }
+        return (int)v;
     }
     int64_t i64_or(int64_t otherwise) {  // None: the default
         if (left > 0 && *at_ == Py_None) {
@@ -159,15 +187,14 @@ mp8_status unlocked(F f) {
 // Elements an operand of `n` rows and contraction length kc spans with leading dimension ld.
 int64_t span(bool contraction_major, int64_t n, int64_t kc, int64_t ld) {
     if (n <= 0 || kc <= 0) return 0;
-    return contraction_major ? (kc - 1) * ld + n : (n - 1) * ld + kc;
+    return contraction_major ? add(mul(kc - 1, ld), n) : add(mul(n - 1, ld), kc);
 }
 
 void op_dims(int op, int64_t M, int64_t N, int64_t K, int64_t &rows, int64_t &cols, int64_t &kc) {
     switch (op) {
         case MP8_FWD: rows = M; cols = N; kc = K; break;
         case MP8_BWD_DATA: rows = M; cols = K; kc = N; break;
-        case MP8_WGRAD: rows = K; cols = N; kc = M; break;
-        default: PyErr_Format(PyExc_KeyError, "%d", op); throw Raised{};
+        default: rows = K; cols = N; kc = M; break;  // MP8_WGRAD
     }
 }
 
@@ -189,7 +216,7 @@ void quantize(Args a) {
     must_be(dst, "dst");
     if (src.t->dim() != 2) fail("src must be 2-D");
     const int64_t rows = src.t->size(0), cols = src.t->size(1);
-    if (dst.n != rows * cols || (dst_t && dst_t.n != rows * cols)) fail("dst / dst_t size does not match src");
+    if (dst.n != src.n || (dst_t && dst_t.n != src.n)) fail("dst / dst_t size does not match src");
     const int f16 = src.t->scalar_type() == at::kHalf;
     void *s = stream();
     check(unlocked([&] {
@@ -199,7 +226,7 @@ void quantize(Args a) {
 }
 
 void gemm(Args a) {
-    const int op = a.i32();
+    const int op = a.op();
     const int64_t M = a.i64(), N = a.i64(), K = a.i64();
     const Arg x = a.tensor("a", kU8), y = a.tensor("b", kU8), out8 = a.tensor("out8", kU8), out8_t = a.tensor("out8_t", kU8),
               acc = a.tensor("acc", kF32);
@@ -218,9 +245,10 @@ void gemm(Args a) {
     must_be(y, "b");
     at_least(x, span(a_km, rows, kc, lda), "a", "its shape and leading dimension require");
     at_least(y, span(b_km, cols, kc, ldb), "b", "its shape and leading dimension require");
-    at_least(out8, rows * cols, "out8", "rows*cols");
-    at_least(out8_t, rows * cols, "out8_t", "rows*cols");
-    at_least(acc, rows * cols, "acc", "rows*cols");
+    const int64_t no = mul(rows, cols);
+    at_least(out8, no, "out8", "rows*cols");
+    at_least(out8_t, no, "out8_t", "rows*cols");
+    at_least(acc, no, "acc", "rows*cols");
     void *s = stream();
     if (fixed) {
         if (ws || tile || split) fail("static_scratch takes no workspace, tile_config or split_k");
@@ -256,11 +284,12 @@ void quantize_gemm_fwd(Args a) {
     must_be(x, "x");
     must_be(x8, "x8_out");
     must_be(w8, "w8");
-    if (x.n != M * K || x8.n != M * K) fail("x and x8_out must have M*K elements");
-    if (K > 0 && N > 0) at_least(w8, (K - 1) * ldw + N, "w8", "its shape and leading dimension require");
-    at_least(out8, M * N, "out8", "M*N");
-    at_least(out8_t, M * N, "out8_t", "M*N");
-    at_least(acc, M * N, "acc", "M*N");
+    const int64_t nx = mul(M, K), no = mul(M, N);
+    if (x.n != nx || x8.n != nx) fail("x and x8_out must have M*K elements");
+    at_least(w8, span(true, N, K, ldw), "w8", "its shape and leading dimension require");
+    at_least(out8, no, "out8", "M*N");
+    at_least(out8_t, no, "out8_t", "M*N");
+    at_least(acc, no, "acc", "M*N");
     void *s = stream();
     const size_t ws_bytes = a.bytes(ws);
     check(unlocked([&] {
@@ -275,7 +304,7 @@ struct ConvDims {
     int64_t B, H, W, Cin, Cout;
     explicit ConvDims(Args &a) : B(a.i64()), H(a.i64()), W(a.i64()), Cin(a.i64()), Cout(a.i64()) {}
     int64_t prows(Args &a) const {  // default: B*(H+2)*(W+2) up to a multiple of 128
-        return a.i64_or((B * (H + 2) * (W + 2) + 127) / 128 * 128);
+        return a.i64_or(mul(add(mul(mul(B, add(H, 2)), add(W, 2)), 127) / 128, 128));
     }
 };
 
@@ -287,7 +316,7 @@ bool has_guard(const Arg &a, int64_t guard) {
 }
 
 void conv(Args a) {
-    const int op = a.i32();
+    const int op = a.op();
     const ConvDims d(a);
     const Arg x = a.tensor("a", kU8), y = a.tensor("b", kU8), out8 = a.tensor("out8", kU8), acc = a.tensor("acc", kF32);
     const int acc_mode = a.i32();
@@ -298,18 +327,17 @@ void conv(Args a) {
     const int64_t prows = d.prows(a);
     must_be(x, "a");
     must_be(y, "b");
-    const int64_t w = 9 * d.Cin * d.Cout, px = prows * d.Cin, py = prows * d.Cout;
+    const int64_t w = mul(mul(9, d.Cin), d.Cout), px = mul(prows, d.Cin), py = mul(prows, d.Cout);
     int64_t na, nb, no;
     switch (op) {
         case MP8_FWD: na = px; nb = w; no = py; break;
         case MP8_BWD_DATA: na = py; nb = w; no = px; break;
-        case MP8_WGRAD: na = px; nb = py; no = w; break;
-        default: PyErr_Format(PyExc_KeyError, "%d", op); throw Raised{};
+        default: na = px; nb = py; no = w; break;  // MP8_WGRAD
     }
     if (x.n != na || y.n != nb) fail("a / b do not have the sizes the operation implies");
     at_least(out8, no, "out8", "the output");
     at_least(acc, no, "acc", "the output");
-    if (!has_guard(x, (d.W + 3) * (op == MP8_BWD_DATA ? d.Cout : d.Cin)))
+    if (!has_guard(x, mul(add(d.W, 3), op == MP8_BWD_DATA ? d.Cout : d.Cin)))
         fail("the padded tensor `a` needs W+3 readable guard rows before and after (allocate it with conv_buffer)");
     void *s = stream();
     const size_t ws_bytes = a.bytes(ws);
@@ -368,11 +396,12 @@ void wgrad_update(Args a) {
     must_be(y, "b");
     if (x.n < span(a_km, K, M, lda) || y.n < span(b_km, N, M, ldb))
         fail("a / b is smaller than its shape and leading dimension require");
-    exactly(w16, K * N, "w16", "K*N");
-    exactly(s0, K * N, RULE == 1 ? "velocity" : "m", "K*N");
-    exactly(s1, K * N, "v", "K*N");
-    exactly(u.g8, K * N, "g8_out", "K*N");
-    exactly(u.w8, K * N, "w8_out", "K*N");
+    const int64_t n = mul(K, N);
+    exactly(w16, n, "w16", "K*N");
+    exactly(s0, n, RULE == 1 ? "velocity" : "m", "K*N");
+    exactly(s1, n, "v", "K*N");
+    exactly(u.g8, n, "g8_out", "K*N");
+    exactly(u.w8, n, "w8_out", "K*N");
     void *s = stream();
     const size_t ws_bytes = a.bytes(u.ws);
     const uint8_t *ap = (const uint8_t *)x.p, *bp = (const uint8_t *)y.p;
@@ -411,15 +440,15 @@ void conv_wgrad_update(Args a) {
     float mu = 0, wd = 0;
     if (RULE == 1) mu = a.f32(), wd = a.f32();
     const UpdateArgs u(a);
-    const int64_t prows = d.prows(a), n = 9 * d.Cin * d.Cout;
+    const int64_t prows = d.prows(a), n = mul(mul(9, d.Cin), d.Cout);
     must_be(x8, "x8");
     must_be(e8, "e8");
-    if (x8.n != prows * d.Cin || e8.n != prows * d.Cout) fail("x8 / e8 do not have the sizes the operation implies");
+    if (x8.n != mul(prows, d.Cin) || e8.n != mul(prows, d.Cout)) fail("x8 / e8 do not have the sizes the operation implies");
     exactly(w16, n, "w16", "9*Cin*Cout");
     exactly(vel, n, "velocity", "9*Cin*Cout");
     exactly(u.g8, n, "g8_out", "9*Cin*Cout");
     exactly(u.w8, n, "w8_out", "9*Cin*Cout");
-    if (!has_guard(x8, (d.W + 3) * d.Cin))
+    if (!has_guard(x8, mul(add(d.W, 3), d.Cin)))
         fail("the padded tensor x8 needs W+3 readable guard rows before and after (allocate it with conv_buffer)");
     void *s = stream();
     const size_t ws_bytes = a.bytes(u.ws);

@@ -1,5 +1,5 @@
 """The extension module behind the package's functions refuses what it must before anything is
-enqueued (no GPU needed: every call here ends in a check)."""
+enqueued, and takes what stands for a number or a pointer."""
 import pytest
 import torch
 
@@ -35,3 +35,41 @@ def test_arguments_of_the_wrong_kind_raise():
         mp8.quantize_e5m2([1.0], None)
     with pytest.raises(TypeError):
         mp8.gemm_fp8(mp8.FWD, "1", 1, 1, None, None)
+
+
+def test_dimensions_and_operations_do_not_wrap():
+    u = torch.zeros((128, 128), dtype=torch.uint8)
+    for dims in ((2 ** 64 + 128, 128, 128), (128, 2 ** 64, 128), (128, 128, -2 ** 64 + 128)):
+        with pytest.raises(mp8.Mp8Error, match="64 bits"):
+            mp8.gemm_fp8(mp8.FWD, *dims, u, u, out8=u)
+    for op in (3, -1, 2 ** 32):
+        with pytest.raises(KeyError):
+            mp8.gemm_fp8(op, 128, 128, 128, u, u, out8=u)
+        with pytest.raises(KeyError):
+            mp8.conv3x3_fp8(op, 1, 4, 4, 128, 128, u, u, out8=u)
+
+
+@pytest.mark.gpu
+def test_sizes_that_overflow_are_refused():
+    """Products of dimensions and leading dimensions that exceed 64 bits are larger than any tensor."""
+    u = torch.zeros((128, 128), dtype=torch.uint8, device="cuda")
+    f, h = torch.zeros((128, 128), device="cuda"), torch.zeros((128, 128), dtype=torch.float16, device="cuda")
+    e8, ef = torch.zeros(0, dtype=torch.uint8, device="cuda"), torch.zeros(0, device="cuda")
+    big = 2 ** 62
+    calls = [
+        lambda: mp8.gemm_fp8(mp8.FWD, 128, 128, 128, u, u, out8=u, lda=big + 1),
+        lambda: mp8.gemm_fp8(mp8.FWD, 128, 128, 128, u, u, out8=u, ldb=big),
+        lambda: mp8.gemm_fp8(mp8.WGRAD, 128, 128, 128, u, u, out8=u, lda=big, flags=mp8.FLAG_CONTRACTION_MAJOR),
+        lambda: mp8.gemm_fp8(mp8.FWD, 2 ** 32, 2 ** 32, 1, u, u, out8=u),
+        lambda: mp8.quantize_gemm_fwd_fp8(128, 128, 128, f, u, u, out8=u, ldw=big),
+        lambda: mp8.quantize_gemm_fwd_fp8(2 ** 32, 128, 2 ** 32, ef, e8, u, out8=u),
+        lambda: mp8.conv3x3_fp8(mp8.FWD, 2 ** 62, 2, 2, 128, 128, e8, u, out8=u),
+        lambda: mp8.conv3x3_fp8(mp8.FWD, 1, 4, 4, 128, 128, e8, u, out8=u, prows=2 ** 57),
+        lambda: mp8.wgrad_update_fp16_sr(128, 128, 128, u, u, h, 0.1, 1.0, lda=big),
+        lambda: mp8.wgrad_update_fp16_sr(128, 2 ** 32, 2 ** 32, u, u, h, 0.1, 1.0),
+    ]
+    for i, call in enumerate(calls):
+        with pytest.raises(mp8.Mp8Error, match="smaller than|elements|sizes"):
+            print("call", i, flush=True)
+            call()
+    torch.cuda.synchronize()
