@@ -44,13 +44,15 @@ struct Raised {};
 }
 
 // What a tensor argument may hold.
-enum Kind { kAny, kF32, kU8, kSource /* float32 or float16 */, kHalf /* float16 or its bits */ };
+enum Kind { kF32, kU8, kSource /* float32 or float16 */, kHalf /* float16 or its bits */ };
 
 struct Arg {
     void *p = nullptr;
-    int64_t n = 0;  // elements
+    int64_t n = 0;         // elements
+    int64_t itemsize = 0;  // bytes of one
     const at::Tensor *t = nullptr;
-    explicit operator bool() const { return t != nullptr; }
+    bool given = false;
+    explicit operator bool() const { return given; }
 };
 
 // Sizes are formed from what the caller passes: they saturate instead of wrapping, so that no product of
@@ -91,9 +93,27 @@ struct Args {
         return v;
     }
     int64_t i64() { return as_i64(next()); }
+    // what int() takes: the step counters that optimizers keep may be floats or tensors
+    int64_t whole() {
+        PyObject *o = PyNumber_Long(next());
+        if (!o) throw Raised{};
+        try {
+            const int64_t v = as_i64(o);
+            Py_DECREF(o);
+            return v;
+        } catch (const Raised &) {
+            Py_DECREF(o);
+            throw;
+        }
+    }
+    // what float() takes
     float f32() {
-        const double v = PyFloat_AsDouble(next());
-        if (v == -1.0 && PyErr_Occurred()) throw Raised{};
+        PyObject *o = next();
+        if (PyFloat_CheckExact(o)) return (float)PyFloat_AS_DOUBLE(o);
+        PyObject *f = PyNumber_Float(o);
+        if (!f) throw Raised{};
+        const double v = PyFloat_AS_DOUBLE(f);
+        Py_DECREF(f);
         return (float)v;
     }
     int op() {
@@ -131,34 +151,56 @@ struct Args {
         if (!t.is_contiguous()) fail("%s must be contiguous", name);
         const at::ScalarType s = t.scalar_type();
         bool ok = true;
+        const char *expected = "";
         switch (kind) {
-            case kAny: break;
-            case kF32: ok = s == at::kFloat; break;
-            case kU8: ok = s == at::kByte; break;
-            case kSource: ok = s == at::kFloat || s == at::kHalf; break;
-            case kHalf: ok = s == at::kHalf || s == at::kShort || s == at::kUInt16; break;
+            case kF32: ok = s == at::kFloat; expected = "torch.float32"; break;
+            case kU8: ok = s == at::kByte; expected = "torch.uint8"; break;
+            case kSource: ok = s == at::kFloat || s == at::kHalf; expected = "(torch.float32, torch.float16)"; break;
+            case kHalf:
+                ok = s == at::kHalf || s == at::kShort || s == at::kUInt16;
+                expected = "(torch.float16, torch.int16, torch.uint16)";
+                break;
         }
-        if (!ok) fail("%s has dtype %s, which it may not have", name, c10::toString(s));
+        if (!ok) {
+            PyObject *d = PyObject_GetAttrString(o, "dtype");
+            if (!d) throw Raised{};
+            PyErr_Format(g_error, "%s has dtype %S, expected %s", name, d, expected);
+            Py_DECREF(d);
+            throw Raised{};
+        }
         a.t = &t;
+        a.given = true;
         a.p = t.data_ptr();
         a.n = t.numel();
+        a.itemsize = t.element_size();
         return a;
     }
-    // a pointer that is passed on as it is (statistics, flags, scratch)
-    Arg raw(const char *name) {
+    // A pointer that is passed on as it is (statistics, flags, scratch): a tensor, or any object with the
+    // methods of one that are needed here.
+    Arg raw(bool sized = false) {
         PyObject *o = next();
         Arg a;
         if (o == Py_None) return a;
-        if (!THPVariable_Check(o)) {
-            PyErr_Format(PyExc_TypeError, "%s must be a tensor or None", name);
-            throw Raised{};
+        a.given = true;
+        if (THPVariable_Check(o)) {
+            a.t = &THPVariable_Unpack(o);
+            a.p = a.t->data_ptr();
+            a.n = a.t->numel();
+            a.itemsize = a.t->element_size();
+            return a;
         }
-        a.t = &THPVariable_Unpack(o);
-        a.p = a.t->data_ptr();
-        a.n = a.t->numel();
+        auto call = [&](const char *method) {
+            PyObject *v = PyObject_CallMethod(o, method, nullptr);
+            const uint64_t x = v ? PyLong_AsUnsignedLongLongMask(v) : 0;
+            Py_XDECREF(v);
+            if (PyErr_Occurred()) throw Raised{};
+            return x;
+        };
+        a.p = (void *)call("data_ptr");
+        if (sized) a.n = (int64_t)call("numel"), a.itemsize = (int64_t)call("element_size");
         return a;
     }
-    size_t bytes(const Arg &a) const { return a ? (size_t)a.n * a.t->element_size() : 0; }
+    size_t bytes(const Arg &a) const { return (size_t)a.n * (size_t)a.itemsize; }
 };
 
 void must_be(const Arg &a, const char *name) {
@@ -211,7 +253,7 @@ void quantize(Args a) {
     const float scale = a.f32();
     const int round = a.i32(), flags = a.i32();
     const uint64_t seed = a.u64(), offset = a.u64();
-    const Arg stats = a.raw("stats");
+    const Arg stats = a.raw();
     must_be(src, "src");
     must_be(dst, "dst");
     if (src.t->dim() != 2) fail("src must be 2-D");
@@ -234,7 +276,7 @@ void gemm(Args a) {
     const float alpha = a.f32();
     const int round = a.i32(), flags = a.i32();
     const uint64_t seed = a.u64(), offset = a.u64();
-    const Arg stats = a.raw("stats"), ws = a.raw("workspace");
+    const Arg stats = a.raw(), ws = a.raw(true);
     int64_t rows, cols, kc;
     op_dims(op, M, N, K, rows, cols, kc);
     const bool a_km = (flags & MP8_FLAG_A_CONTRACTION_MAJOR) != 0, b_km = (flags & MP8_FLAG_B_CONTRACTION_MAJOR) != 0;
@@ -275,11 +317,11 @@ void quantize_gemm_fwd(Args a) {
     const float x_scale = a.f32();
     const int x_round = a.i32(), x_flags = a.i32();
     const uint64_t x_seed = a.u64(), x_offset = a.u64();
-    const Arg x_stats = a.raw("x_stats");
+    const Arg x_stats = a.raw();
     const float alpha = a.f32();
     const int round = a.i32(), flags = a.i32();
     const uint64_t seed = a.u64(), offset = a.u64();
-    const Arg stats = a.raw("stats"), ws = a.raw("workspace");
+    const Arg stats = a.raw(), ws = a.raw(true);
     const int64_t ldw = a.i64_or(N);
     must_be(x, "x");
     must_be(x8, "x8_out");
@@ -323,7 +365,7 @@ void conv(Args a) {
     const float alpha = a.f32();
     const int round = a.i32(), flags = a.i32();
     const uint64_t seed = a.u64(), offset = a.u64();
-    const Arg stats = a.raw("stats"), ws = a.raw("workspace");
+    const Arg stats = a.raw(), ws = a.raw(true);
     const int64_t prows = d.prows(a);
     must_be(x, "a");
     must_be(y, "b");
@@ -366,13 +408,13 @@ struct UpdateArgs {
         flags = a.i32();
         g_seed = a.u64();
         g_offset = a.u64();
-        stats = a.raw("stats");
+        stats = a.raw();
         w_round = a.i32();
         w_seed = a.u64();
         w_offset = a.u64();
-        skip = a.raw("skip_if_nonzero");
+        skip = a.raw();
         w8 = a.tensor("w8_out", kU8);
-        ws = a.raw("workspace");
+        ws = a.raw(true);
     }
 };
 
@@ -388,7 +430,7 @@ void wgrad_update(Args a) {
     float mu = 0, wd = 0, b1 = 0, b2 = 0, eps = 0;
     int64_t step = 0;
     if (RULE == 1) mu = a.f32(), wd = a.f32();
-    if (RULE == 2) step = a.i64(), b1 = a.f32(), b2 = a.f32(), eps = a.f32(), wd = a.f32();
+    if (RULE == 2) step = a.whole(), b1 = a.f32(), b2 = a.f32(), eps = a.f32(), wd = a.f32();
     const UpdateArgs u(a);
     const bool a_km = (u.flags & MP8_FLAG_A_CONTRACTION_MAJOR) != 0, b_km = (u.flags & MP8_FLAG_B_CONTRACTION_MAJOR) != 0;
     const int64_t lda = a.i64_or(a_km ? K : M), ldb = a.i64_or(b_km ? N : M);
@@ -484,10 +526,10 @@ void update(Args a) {
     float mu = 0, wd = 0, b1 = 0, b2 = 0, eps = 0;
     int64_t step = 0;
     if (RULE == 1) mu = a.f32(), wd = a.f32();
-    if (RULE == 2) step = a.i64(), b1 = a.f32(), b2 = a.f32(), eps = a.f32(), wd = a.f32();
+    if (RULE == 2) step = a.whole(), b1 = a.f32(), b2 = a.f32(), eps = a.f32(), wd = a.f32();
     const int round = a.i32();
     const uint64_t seed = a.u64(), offset = a.u64();
-    const Arg skip = a.raw("skip_if_nonzero"), w8 = a.tensor("w8_out", kU8), stats = a.raw("stats");
+    const Arg skip = a.raw(), w8 = a.tensor("w8_out", kU8), stats = a.raw();
     must_be(w16, "w16");
     must_be(g8, "g8");
     if (RULE > 0) must_be(s0, RULE == 1 ? "velocity" : "m");

@@ -73,3 +73,40 @@ def test_sizes_that_overflow_are_refused():
             print("call", i, flush=True)
             call()
     torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
+def test_arguments_that_stand_for_numbers_and_pointers():
+    """A step counter may be what optimizers keep (a float, a tensor); statistics, scratch and flags may be any
+    object with a tensor's methods."""
+    class Wrapped:
+        def __init__(self, t):
+            self.data_ptr, self.numel, self.element_size = t.data_ptr, t.numel, t.element_size
+
+    n = 128 * 128
+    x = torch.full((128, 128), 0x38, dtype=torch.uint8, device="cuda")
+    results = []
+    for step in (7, 7.0, torch.tensor(7.0), torch.tensor(7.0, device="cuda")):
+        w, m, v = (torch.full((n,), 0.5, dtype=t, device="cuda") for t in (torch.float16, torch.float32, torch.float32))
+        w2, m2, v2 = w.clone(), m.clone(), v.clone()
+        mp8.adam_fp16_sr(w, m, v, x, torch.tensor(1e-2), 1.0, step)
+        mp8.wgrad_adam_fp16_sr(128, 128, 128, x, x, w2, m2, v2, 1e-2, 1.0, step, g8_out=torch.empty_like(x),
+                               workspace=Wrapped(torch.empty(4 * n, dtype=torch.uint8, device="cuda")))
+        results.append((w, m, v, w2, m2, v2))
+    assert all(torch.equal(p, q) for r in results[1:] for p, q in zip(results[0], r))
+    src, out = torch.full((128, 128), float("inf"), device="cuda"), torch.zeros_like(x)
+    stats = mp8.new_stats()
+    mp8.quantize_e5m2(src, out, stats=Wrapped(stats))
+    assert mp8.read_stats(stats)[1] == n
+    before = results[0][0].clone()
+    mp8.sgd_update_fp16_sr(results[0][0], x, 1.0, 1.0, skip_if_nonzero=Wrapped(stats[1:2]))
+    assert torch.equal(before, results[0][0])
+
+
+@pytest.mark.gpu
+def test_dtype_errors_say_what_is_expected():
+    u, d = torch.zeros((128, 128), dtype=torch.uint8, device="cuda"), torch.zeros((128, 128), dtype=torch.float64, device="cuda")
+    with pytest.raises(mp8.Mp8Error, match=r"src has dtype torch.float64, expected \(torch.float32, torch.float16\)"):
+        mp8.quantize_e5m2(d, u)
+    with pytest.raises(mp8.Mp8Error, match="b has dtype torch.float64, expected torch.uint8"):
+        mp8.gemm_fp8(mp8.FWD, 128, 128, 128, u, d, out8=u)
