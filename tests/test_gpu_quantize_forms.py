@@ -1,6 +1,6 @@
-"""GPU parity of the Q node's launch forms where they change: runs of a workgroup with statistics (one, two,
-four groups per thread and a rest), one group per thread for small tensors, and transposed copies of
-row and column counts that are not multiples of four (both tile sizes)."""
+"""GPU parity of the Q node's launch forms where they change: how groups are dealt to the workgroups with
+statistics, one group per thread for small tensors, and transposed copies of row and column counts that are not
+multiples of four (both tile sizes)."""
 import numpy as np
 import pytest
 
@@ -46,9 +46,11 @@ def data(seed, shape, half):
     return x.astype(np.float16 if half else np.float32)
 
 
-# groups of four per workgroup of 256: up to 256 (one), 257..512 (two), then 1024-thread blocks with 1, 2, 3, 4, 5, 9 groups
+# with statistics: runs of up to 512 groups for 256 threads, of 2048 to 4096 for 1024 threads, then whole rounds of
+# 2^20 groups over all workgroups and a rest (none, one group, several per thread)
 @pytest.mark.parametrize("n", [4, 252, 4 * 256 * 256 - 4, 4 * 256 * 256 + 4, 4 * 256 * 512 + 260, 4 * 256 * 1024 + 1027,
-                               4 * 256 * 3 * 1024 - 13, 4 * 256 * 5 * 1024 + 3, 4 * 256 * 9 * 1024 + 77])
+                               4 * 256 * 3 * 1024 - 13, 4 * 256 * 5 * 1024 + 3, 4 * 256 * 9 * 1024 + 77,
+                               4 * 32768, 4 * 32768 + 5, 4 * 2 ** 19, 4 * 2 ** 19 + 4, 4 * 2 ** 20, 4 * 2 ** 20 + 6, 4 * (2 ** 21 + 65000) + 1])
 @pytest.mark.parametrize("rnd", [oracle.RNE, oracle.SR])
 @pytest.mark.parametrize("with_stats", [False, True])
 def test_flat_run_lengths(mp8, n, rnd, with_stats):
