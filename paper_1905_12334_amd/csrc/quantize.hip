@@ -90,7 +90,14 @@ constexpr int kStatsBlocks = 512;      // grid limit per tensor of a batch with 
 constexpr int kFlatStatsBlocks = 256;
 constexpr int64_t kFlatSmall = 256 * 1024;
 constexpr int64_t kTiny = 128 * 1024, kTinyRagged = 256 * 1024;  // transposing: element by element up to here
+// The same with statistics: at most 128 workgroups up to 64 K elements (256 x 256 4.7 us; one workgroup per 256
+// elements 5.6, tiles of 64 4.7; 256 x 512 5.7 / 8.8 / 4.8), twice as many elements where tiles need guards
+// (1001 x 77 5.6 / 6.1 / 7.1; 511 x 513 8.0 / 26 / 5.9).
+constexpr int64_t kTinyStats = 64 * 1024;
 constexpr int64_t kTileSwitch = 256;   // transposing: tiles of 128 x 128 from this many on, else of 64 x 64
+// With statistics from the number on at which tiles of 64 become more workgroups than CUs: 1024 x 1280 7.5 us (11.8
+// in tiles of 64), 1920 x 2048 9.6 us (36), while 1024 x 1024 takes 7.2 and 7.5, stochastic 8.5 and 7.9.
+constexpr int64_t kTileSwitchStats = 65;
 constexpr int kStatsThreads = 1024;
 
 // How the groups of four elements of a tensor are dealt to the workgroups: `rounds` rounds of one whole pass
@@ -638,9 +645,10 @@ static hipError_t launch_quantize(const void *src, uint8_t *dst, uint8_t *dst_t,
                                dim3((unsigned)blocks), dim3((T / 4) * (T / 4)), 0, s, src, dst, dst_t, rows, cols, scale, sat,
                                seed, offset, stats, S);
         };
-        if (n <= (ragged ? kTinyRagged : kTiny)) {
-            hipLaunchKernelGGL((quantize_generic_kernel<kF16, kSR, kStats>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                               src, dst, dst_t, rows, cols, scale, sat, seed, offset, stats);
+        if (n <= (kStats ? (ragged ? 2 : 1) * kTinyStats : ragged ? kTinyRagged : kTiny)) {
+            const int64_t limit = kStats ? 128 : 1024;  // (see kTinyStats)
+            hipLaunchKernelGGL((quantize_generic_kernel<kF16, kSR, kStats>), dim3((unsigned)std::min((n + 255) / 256, limit)),
+                               dim3(256), 0, s, src, dst, dst_t, rows, cols, scale, sat, seed, offset, stats);
         } else if (!ragged && !kStats && !wide && (rows & 15) == 0 && nt >= 6144) {
             // several rounds of blocks: plain one-tile blocks, many per CU
             hipLaunchKernelGGL((quantize_transpose_oneshot_kernel<kF16, kSR, kStats>),
@@ -654,7 +662,7 @@ static hipError_t launch_quantize(const void *src, uint8_t *dst, uint8_t *dst_t,
             hipLaunchKernelGGL((quantize_transpose_kernel<kF16, kSR, kStats>),
                                dim3((unsigned)blocks), dim3(kStats ? 512 : 256), 0, s, src, dst, dst_t, rows, cols,
                                scale, sat, seed, offset, stats);
-        } else if (nt >= kTileSwitch) {
+        } else if (nt >= (kStats ? kTileSwitchStats : kTileSwitch)) {
             // 1024-thread blocks, all loads of a tile in flight; for a matrix that is wide in
             // both directions, super-tiles of 4x4 keep the lines written by concurrently
             // running blocks close together in both copies.  With statistics one block per CU:

@@ -67,3 +67,10 @@ def test_ragged_transposed_copies(mp8, shape, rnd, half, with_stats):
 @pytest.mark.parametrize("shape", [(128, 128), (1024, 2048), (2064, 2052), (2064, 2056), (8208, 8196)])
 def test_transposed_copies_with_statistics_and_shared_random_blocks(mp8, shape):
     check(mp8, data(shape[1], shape, False), oracle.SR, True, True)
+
+
+# with statistics: element by element up to 64 K elements (128 K with guards), tiles of 64 up to 64 tiles of 128
+@pytest.mark.parametrize("shape", [(256, 256), (256, 260), (255, 513), (259, 509), (1024, 1024), (1024, 1152), (1020, 1156), (1021, 1155)])
+@pytest.mark.parametrize("rnd", [oracle.RNE, oracle.SR])
+def test_transposed_copies_with_statistics_at_the_changes_of_form(mp8, shape, rnd):
+    check(mp8, data(shape[1], shape, False), rnd, True, True)
