@@ -98,6 +98,7 @@ constexpr int64_t kTileSwitch = 256;   // transposing: tiles of 128 x 128 from t
 // With statistics from the number on at which tiles of 64 become more workgroups than CUs: 1024 x 1280 7.5 us (11.8
 // in tiles of 64), 1920 x 2048 9.6 us (36), while 1024 x 1024 takes 7.2 and 7.5, stochastic 8.5 and 7.9.
 constexpr int64_t kTileSwitchStats = 65;
+constexpr int64_t kMaxTileBlocks = 1 << 21;  // a launch has fewer than 2^32 threads; tiles beyond it by striding
 constexpr int kStatsThreads = 1024;
 
 // How the groups of four elements of a tensor are dealt to the workgroups: `rounds` rounds of one whole pass
@@ -645,10 +646,20 @@ static hipError_t launch_quantize(const void *src, uint8_t *dst, uint8_t *dst_t,
                                dim3((unsigned)blocks), dim3((T / 4) * (T / 4)), 0, s, src, dst, dst_t, rows, cols, scale, sat,
                                seed, offset, stats, S);
         };
-        if (n <= (kStats ? (ragged ? 2 : 1) * kTinyStats : ragged ? kTinyRagged : kTiny)) {
-            const int64_t limit = kStats ? 128 : 1024;  // (see kTinyStats)
+        // Rows or columns so short that most of a tile would be padding go element by element: 10^6 x 1 5.5 us
+        // (251 us in tiles of 128), 300000 x 8 10.8 us (41), 200000 x 17 14.5 us (59), 150001 x 31 19.4 us
+        // (44); with statistics 13 us (241), 25 (54), 42 (73), 52 (59).  Tiles win from 16 columns on where they
+        // need no guards (200000 x 16 14.3 and 14.2 us) and from 16 rows on (31 x 150001 17.7 us, 30.7).
+        const bool narrow = cols < (ragged ? 32 : 16) || rows < 16;
+        const bool tiny = n <= (kStats ? (ragged ? 2 : 1) * kTinyStats : ragged ? kTinyRagged : kTiny);
+        if (narrow || tiny) {
+            // (a grid that strides; with statistics few workgroups, see kTinyStats)
+            const int64_t limit = !kStats ? 256 * 32 : tiny ? 128 : kStatsBlocks;
             hipLaunchKernelGGL((quantize_generic_kernel<kF16, kSR, kStats>), dim3((unsigned)std::min((n + 255) / 256, limit)),
                                dim3(256), 0, s, src, dst, dst_t, rows, cols, scale, sat, seed, offset, stats);
+        } else if (!kStats && std::min(rows, cols) <= 64) {
+            // one tile of 64 across: 100000 x 40 10.0 us (22 in tiles of 128), 100001 x 63 16.8 us (35)
+            tiles(std::integral_constant<int, 64>{}, 1, kMaxTileBlocks);
         } else if (!ragged && !kStats && !wide && (rows & 15) == 0 && nt >= 6144) {
             // several rounds of blocks: plain one-tile blocks, many per CU
             hipLaunchKernelGGL((quantize_transpose_oneshot_kernel<kF16, kSR, kStats>),
@@ -668,10 +679,10 @@ static hipError_t launch_quantize(const void *src, uint8_t *dst, uint8_t *dst_t,
             // running blocks close together in both copies.  With statistics one block per CU:
             // every block ends in atomics on one address, and blocks that end together wait
             // for each other there (512 of them: 16384 x 1024 39 us, against 22 us without atomics)
-            tiles(std::integral_constant<int, 128>{}, wide ? 4 : 1, kStats ? kFlatStatsBlocks : (int64_t)1 << 30);
+            tiles(std::integral_constant<int, 128>{}, wide ? 4 : 1, kStats ? kFlatStatsBlocks : kMaxTileBlocks);
         } else {
             // few tiles: smaller ones shorten the latency chain of the single round of blocks
-            tiles(std::integral_constant<int, 64>{}, 1, (int64_t)1 << 30);
+            tiles(std::integral_constant<int, 64>{}, 1, kMaxTileBlocks);
         }
     }
     return hipGetLastError();

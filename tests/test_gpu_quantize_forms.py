@@ -74,3 +74,28 @@ def test_transposed_copies_with_statistics_and_shared_random_blocks(mp8, shape):
 @pytest.mark.parametrize("rnd", [oracle.RNE, oracle.SR])
 def test_transposed_copies_with_statistics_at_the_changes_of_form(mp8, shape, rnd):
     check(mp8, data(shape[1], shape, False), rnd, True, True)
+
+
+# element by element, one tile of 64 across, tiles of 128
+@pytest.mark.parametrize("shape", [(300001, 1), (20001, 15), (20000, 12), (20000, 16), (10001, 31), (10001, 32), (20000, 64), (6001, 65),
+                                   (1, 300001), (15, 20001), (12, 20000), (16, 20000), (17, 20001), (63, 9001), (64, 9000), (66, 9002)])
+@pytest.mark.parametrize("rnd", [oracle.RNE, oracle.SR])
+@pytest.mark.parametrize("with_stats", [False, True])
+def test_narrow_transposed_copies(mp8, shape, rnd, with_stats):
+    check(mp8, data(shape[0] + shape[1], shape, True), rnd, True, with_stats)
+
+
+@pytest.mark.parametrize("shape", [(2 ** 29 + 5, 1), (2 ** 27 + 64, 16)])
+def test_narrow_transposed_copies_of_more_tiles_than_a_launch_takes(mp8, shape):
+    """Tiles of 128 rows and 1024 threads each would be 2^32 threads and more; one tile of 64 x 64 more than the
+    grid has workgroups."""
+    import torch
+    x = torch.arange(shape[0] * shape[1], device="cuda").remainder_(2039).to(torch.float16).view(shape)
+    d, t, want = (torch.empty(x.numel(), dtype=torch.uint8, device="cuda") for _ in range(3))
+    mp8.quantize_e5m2(x, d, t)
+    mp8.quantize_e5m2(x, want)
+    assert torch.equal(d, want)
+    step = 2 ** 24
+    for i in range(0, shape[0], step):
+        part = want.view(shape)[i:i + step]
+        assert torch.equal(t.view(shape[1], shape[0])[:, i:i + step], part.t())
