@@ -12,8 +12,8 @@
 //   gemm_shortk.hpp   contractions of one or two stages (all start-up and epilogue)
 //   gemm_wavek.hpp    small outputs with long contractions (contraction divided among waves)
 //   gemm_wave128.hpp  about one 128x128 tile per CU and a long contraction (every wave the whole tile)
-//   gemm_any.hpp      row lengths and leading dimensions that are not multiples of 16, contractions that
-//                     are not multiples of 128 (half-precision matrix instructions)
+//   gemm_any.hpp      row lengths, leading dimensions, contractions that are not multiples of 16
+// (contractions that are not multiples of 128: half-precision forms of the general and the wave-split kernel)
 //   gemm_finish.hpp   second pass for split contractions and unfused epilogues, optionally with
 //                     the master-weight update; the any-shape fallback kernel
 // Split contraction, FP32 / transposed outputs, ragged column counts: the MFMA kernels write
@@ -124,31 +124,44 @@ constexpr int kMaxSplits = 64;
 // gemm_any_kernel by operand layout (row-major, b contraction-major, both): the FP32 tiles of a split
 // contraction, an unsplit one, a split one slice by slice
 static void (*const kAny[3][3])(const GemmArgs) = {
-    {gemm_any_kernel<EPI_PARTIAL, false, false>, gemm_any_kernel<EPI_FULL, false, false>, gemm_any_slices_kernel<false, false>},
-    {gemm_any_kernel<EPI_PARTIAL, false, true>, gemm_any_kernel<EPI_FULL, false, true>, gemm_any_slices_kernel<false, true>},
-    {gemm_any_kernel<EPI_PARTIAL, true, true>, gemm_any_kernel<EPI_FULL, true, true>, gemm_any_slices_kernel<true, true>}};
+    {gemm_any_kernel<EPI_PARTIAL, false, false>, gemm_any_kernel<EPI_FULL, false, false>, gemm_any_kernel<EPI_FULL, false, false, true>},
+    {gemm_any_kernel<EPI_PARTIAL, false, true>, gemm_any_kernel<EPI_FULL, false, true>, gemm_any_kernel<EPI_FULL, false, true, true>},
+    {gemm_any_kernel<EPI_PARTIAL, true, true>, gemm_any_kernel<EPI_FULL, true, true>, gemm_any_kernel<EPI_FULL, true, true, true>}};
 
-// Kernels whose epilogue applies the master-weight update: [row-major, contraction-major operands][state
-// words per weight].
+// Half-precision forms of the direct-to-LDS kernels, for contractions that are not whole stages: [64x64, 64x64
+// divided among the waves, 128x128][operand layout as above][EPI_*] (they never write FP32 tiles)
+#define MP8_HALF_64(ATN, BTN)                                                                                    \
+    {nullptr, gemm_mfma_kernel<64, 64, 2, 2, 2, 4, EPI_RNE, ATN, BTN, 0, true>,                                  \
+     gemm_mfma_kernel<64, 64, 2, 2, 2, 4, EPI_FULL, ATN, BTN, 0, true>}
+#define MP8_HALF_WAVEK(ATN, BTN)                                                                                 \
+    {nullptr, gemm_wavek_kernel<EPI_RNE, ATN, BTN, 0, 64, 64, true>, gemm_wavek_kernel<EPI_FULL, ATN, BTN, 0, 64, 64, true>}
+#define MP8_HALF_128(ATN, BTN)                                                                                   \
+    {nullptr, gemm_mfma_kernel<128, 128, 2, 2, 2, 2, EPI_RNE, ATN, BTN, 0, true>,                                \
+     gemm_mfma_kernel<128, 128, 2, 2, 2, 2, EPI_FULL, ATN, BTN, 0, true>}
+static void (*const kHalf[3][3][3])(const GemmArgs) = {
+    {MP8_HALF_64(false, false), MP8_HALF_64(false, true), MP8_HALF_64(true, true)},
+    {MP8_HALF_WAVEK(false, false), MP8_HALF_WAVEK(false, true), MP8_HALF_WAVEK(true, true)},
+    {MP8_HALF_128(false, false), MP8_HALF_128(false, true), MP8_HALF_128(true, true)}};
+
+// Kernels whose epilogue applies the master-weight update: [8-bit, half-precision products][row-major,
+// contraction-major operands][state words per weight].
 using UpdateKernel = void (*)(const GemmArgs, const UpdateHook);
-static const UpdateKernel kWavekUpdate[2][3] = {
-    {gemm_wavek_update_kernel<0, false, false, 0>, gemm_wavek_update_kernel<1, false, false, 0>,
-     gemm_wavek_update_kernel<2, false, false, 0>},
-    {gemm_wavek_update_kernel<0, true, true, 0>, gemm_wavek_update_kernel<1, true, true, 0>,
-     gemm_wavek_update_kernel<2, true, true, 0>}};
-static const UpdateKernel kAnyUpdate[2][3] = {
-    {gemm_any_update_kernel<0, false, false>, gemm_any_update_kernel<1, false, false>, gemm_any_update_kernel<2, false, false>},
-    {gemm_any_update_kernel<0, true, true>, gemm_any_update_kernel<1, true, true>, gemm_any_update_kernel<2, true, true>}};
-static const UpdateKernel k64x64Update[2][3] = {
-    {gemm_mfma_update_kernel<64, 64, 2, 2, 2, 4, 0, false, false>, gemm_mfma_update_kernel<64, 64, 2, 2, 2, 4, 1, false, false>,
-     gemm_mfma_update_kernel<64, 64, 2, 2, 2, 4, 2, false, false>},
-    {gemm_mfma_update_kernel<64, 64, 2, 2, 2, 4, 0, true, true>, gemm_mfma_update_kernel<64, 64, 2, 2, 2, 4, 1, true, true>,
-     gemm_mfma_update_kernel<64, 64, 2, 2, 2, 4, 2, true, true>}};
+#define MP8_WAVEK_UPDATE(KM, HALF)                                                                               \
+    {gemm_wavek_update_kernel<0, KM, KM, 0, HALF>, gemm_wavek_update_kernel<1, KM, KM, 0, HALF>,                 \
+     gemm_wavek_update_kernel<2, KM, KM, 0, HALF>}
+#define MP8_64_UPDATE(KM, HALF)                                                                                  \
+    {gemm_mfma_update_kernel<64, 64, 2, 2, 2, 4, 0, KM, KM, HALF>, gemm_mfma_update_kernel<64, 64, 2, 2, 2, 4, 1, KM, KM, HALF>, \
+     gemm_mfma_update_kernel<64, 64, 2, 2, 2, HALF ? 3 : 4, 2, KM, KM, HALF>}
+static const UpdateKernel kWavekUpdate[2][2][3] = {{MP8_WAVEK_UPDATE(false, false), MP8_WAVEK_UPDATE(true, false)},
+                                                   {MP8_WAVEK_UPDATE(false, true), MP8_WAVEK_UPDATE(true, true)}};
+static const UpdateKernel k64x64Update[2][2][3] = {{MP8_64_UPDATE(false, false), MP8_64_UPDATE(true, false)},
+                                                   {MP8_64_UPDATE(false, true), MP8_64_UPDATE(true, true)}};
 
 struct Plan {
     bool mfma;   // one of kTiles
     int tile;    // index into kTiles
     int splits;
+    bool half;     // the half-precision form of that tile: unsplit, one pass
     bool in_turn;  // gemm_any_kernel: a workgroup takes all slices of its tile
     int tiles_m, tiles_n;
 };
@@ -266,6 +279,31 @@ static Plan make_plan(int64_t rows, int64_t cols, int64_t kc, int tile_config, i
     return pl;
 }
 
+// Can the direct-to-LDS kernels fetch (aligned) operands of a contraction that is not whole stages?  Row-major
+// ones have to end with a whole 16-byte chunk.
+static bool half_takes(int64_t rows, int64_t cols, int64_t kc, int layout) {
+    return kc > 0 && kc % BK != 0 && (layout == 3 || (kc & 15) == 0) && (!(layout & 1) || (rows & 15) == 0) &&
+           (!(layout & 2) || (cols & 15) == 0);
+}
+
+// The half-precision kernel that multiplies them: the tile make_plan names for whole stages, or the nearest that is
+// built -- 128x128 for the large ones, 64x64 for the rest.  Not MFMA if the contraction is to be split: slices
+// need a workspace, and the bits must not depend on one (gemm_any_kernel takes them in turn without).
+// Against gemm_any_kernel: 512 x 2048 from 6007 rows with ADAM 22 us (39), 12972 x 832 x 64 9.1 (34), 2143 x 3840 x 576
+// 13.2 (27).
+static Plan half_plan(int64_t rows, int64_t cols, int64_t kc, int layout) {
+    if (!half_takes(rows, cols, kc, layout)) return Plan{};
+    Plan pl = make_plan(rows, cols, (kc + BK - 1) / BK * BK, 0, 0, layout);
+    if (!pl.mfma || pl.splits != 1) return Plan{};
+    if (kTiles[pl.tile].bm * kTiles[pl.tile].bn > 64 * 64) pl.tile = T128x128s2;
+    else if (pl.tile == T32x64w || pl.tile == T32x32w) pl.tile = T64x64w;
+    else if (pl.tile != T64x64w) pl.tile = T64x64s2;
+    pl.tiles_m = (int)((rows + kTiles[pl.tile].bm - 1) / kTiles[pl.tile].bm);
+    pl.tiles_n = (int)((cols + kTiles[pl.tile].bn - 1) / kTiles[pl.tile].bn);
+    pl.half = true;
+    return pl;
+}
+
 // Can gemm_any_kernel take it?  (Lane offsets of a tile stay within 32 bits; an edge chunk is read as
 // the last sixteen bytes of its row, so such rows must have sixteen.)
 static bool any_kernel_takes(int64_t rows, int64_t cols, int64_t kc, int64_t lda, int64_t ldb, int layout) {
@@ -298,8 +336,8 @@ static Plan any_plan(int64_t rows, int64_t cols, int64_t kc) {
 static UpdateKernel update_kernel(const Plan &pl, int64_t cols, int layout, int states) {
     if (!pl.mfma || pl.splits != 1 || (cols & 15) != 0 || (layout != 0 && layout != 3)) return nullptr;
     if (states == 2 && pl.tiles_m * pl.tiles_n < kCUs / 2) return nullptr;
-    if (pl.tile == T64x64w) return kWavekUpdate[layout != 0][states];
-    if (pl.tile == T64x64s2) return k64x64Update[layout != 0][states];
+    if (pl.tile == T64x64w) return kWavekUpdate[pl.half][layout != 0][states];
+    if (pl.tile == T64x64s2) return k64x64Update[pl.half][layout != 0][states];
     return nullptr;
 }
 
@@ -338,10 +376,13 @@ extern "C" size_t mp8_gemm_fp8_workspace_bytes_tuned(mp8_op op, int64_t M, int64
     if (tile_config < 0 || tile_config > kNumTiles || split_k < 0) return 0;
     int64_t rows, cols, kc;
     op_dims(op, M, N, K, rows, cols, kc);
-    // enough for every operand layout and alignment
+    // enough for every operand layout and alignment (and, with an incomplete stage, for the 8-bit gradient of a
+    // weight gradient with an update)
     size_t need = 0;
-    for (int layout : {0, 2, 3})
-        need = std::max(need, plan_workspace(make_plan(rows, cols, kc, tile_config, split_k, layout), rows, cols));
+    for (int layout : {0, 2, 3}) {
+        const int64_t k = tile_config == 0 && half_takes(rows, cols, kc, layout) ? (kc + BK - 1) / BK * BK : kc;
+        need = std::max(need, plan_workspace(make_plan(rows, cols, k, tile_config, split_k, layout), rows, cols));
+    }
     if (tile_config == 0) {  // the slices of gemm_any_kernel side by side
         const Plan pl = any_plan(rows, cols, kc);
         if (pl.splits > 1) need = std::max(need, (size_t)pl.splits * (size_t)rows * (size_t)cols * sizeof(float));
@@ -383,9 +424,9 @@ static mp8_status launch_mfma(GemmArgs ga, const Epilogue &ep, const Plan &pl, i
     float *acc = ep.acc;
     uint8_t *out8 = ep.out8, *out8_t = ep.out8_t;
     // Fused epilogue or two passes?  (The master-weight update lives in the finishing pass or in an
-    // update kernel; gemm_any_kernel's own epilogue does everything else.)
+    // update kernel; the epilogues of gemm_any_kernel and the half-precision forms do everything else.)
     const bool two_pass = (pl.splits > 1 && !pl.in_turn) || (upd != nullptr && with_update == nullptr) ||
-                          (pl.mfma && ((cols & 15) != 0 || acc_mode != 0 || out8_t != nullptr));
+                          (pl.mfma && !pl.half && ((cols & 15) != 0 || acc_mode != 0 || out8_t != nullptr));
     float *partial = nullptr;
     Epilogue fin = ep;  // what the finishing kernel applies
     fin.want_codes = upd != nullptr;
@@ -407,6 +448,7 @@ static mp8_status launch_mfma(GemmArgs ga, const Epilogue &ep, const Plan &pl, i
     ga.rows = rows;
     ga.cols = cols;
     ga.ksteps = (int)((kc + BK - 1) / BK);
+    ga.tail = (int)(kc % BK);
     ga.kc = kc;
     ga.splits = pl.splits;
     ga.tiles_m = pl.tiles_m;
@@ -419,9 +461,9 @@ static mp8_status launch_mfma(GemmArgs ga, const Epilogue &ep, const Plan &pl, i
     ga.ks_extra = ga.ksteps % pl.splits;
     ga.partial = partial;
     ga.ep = ep;
-    const int epi = two_pass ? EPI_PARTIAL
-                             : (ep.sr || ep.sat || ep.stats != nullptr || out8 == nullptr || !pl.mfma) ? EPI_FULL
-                                                                                                        : EPI_RNE;
+    const bool complete = ep.sr || ep.sat || ep.stats != nullptr || out8 == nullptr || !pl.mfma || (cols & 15) != 0 ||
+                          acc_mode != 0 || out8_t != nullptr;
+    const int epi = two_pass ? EPI_PARTIAL : complete ? EPI_FULL : EPI_RNE;
     const size_t dyn_lds = pl.mfma ? (size_t)kTiles[pl.tile].lds_per_stage * (size_t)ga.ksteps : 0;
     if (with_update != nullptr && !two_pass) {
         hipLaunchKernelGGL(with_update, dim3((unsigned)nblocks), dim3(256), 0, s, ga, *upd);
@@ -501,17 +543,16 @@ static mp8_status gemm_impl(mp8_op op, int64_t M, int64_t N, int64_t K, const ui
         pl.mfma = false;
     }
     if (tile_config > 0 && !pl.mfma) return MP8_ERR_UNSUPPORTED;
+    if (!pl.mfma && aligned) pl = half_plan(rows, cols, kc, layout);
     auto has_workspace = [&](int splits) {
         return workspace != nullptr && workspace_bytes >= (size_t)splits * (size_t)rows * (size_t)cols * sizeof(float);
     };
     if (!pl.mfma && any_kernel_takes(rows, cols, kc, lda, ldb, layout)) {
         pl = any_plan(rows, cols, kc);
         // it never needs a workspace: without one a split contraction takes its slices in turn
-        const bool side_by_side = pl.splits > 1 && has_workspace(pl.splits);
-        pl.in_turn = !side_by_side;
-        const UpdateKernel any_update = upd != nullptr && !side_by_side && (cols & 15) == 0 && layout != 2
-                                            ? kAnyUpdate[layout != 0][upd->states] : nullptr;
-        if (upd != nullptr && !side_by_side && any_update == nullptr) return MP8_ERR_UNSUPPORTED;
+        pl.in_turn = pl.splits == 1 || !has_workspace(pl.splits);
+        // (the update goes with the finishing pass only: otherwise two launches)
+        if (upd != nullptr && pl.in_turn) return MP8_ERR_UNSUPPORTED;
         GemmArgs ga{};
         ga.a = a;
         ga.b = b;
@@ -519,7 +560,7 @@ static mp8_status gemm_impl(mp8_op op, int64_t M, int64_t N, int64_t K, const ui
         ga.ldb = ldb;
         void (*const *kern)(const GemmArgs) = kAny[atn ? 2 : btn ? 1 : 0];
         void (*const pick[3])(const GemmArgs) = {kern[0], nullptr, kern[pl.splits > 1 ? 2 : 1]};
-        return launch_mfma(ga, ep, pl, kc, pick, workspace, workspace_bytes, s, upd, validate_only, any_update);
+        return launch_mfma(ga, ep, pl, kc, pick, workspace, workspace_bytes, s, upd, validate_only);
     }
     if (!pl.mfma || kc == 0) {
         if (upd != nullptr) return MP8_ERR_UNSUPPORTED;
@@ -536,6 +577,11 @@ static mp8_status gemm_impl(mp8_op op, int64_t M, int64_t N, int64_t K, const ui
     ga.lda = lda;
     ga.ldb = ldb;
     const UpdateKernel with_update = upd != nullptr ? update_kernel(pl, cols, layout, upd->states) : nullptr;
+    if (pl.half) {
+        if (upd != nullptr && with_update == nullptr) return MP8_ERR_UNSUPPORTED;  // (two launches)
+        const int form = pl.tile == T64x64s2 ? 0 : pl.tile == T64x64w ? 1 : 2;
+        return launch_mfma(ga, ep, pl, kc, kHalf[form][atn ? 2 : btn ? 1 : 0], nullptr, 0, s, upd, validate_only, with_update);
+    }
     const TileConfig &tc = kTiles[pl.tile];
     return launch_mfma(ga, ep, pl, kc, atn ? tc.kernel_tn : btn ? tc.kernel_bt : tc.kernel, workspace,
                        workspace_bytes, s, upd, validate_only, with_update);
@@ -651,11 +697,14 @@ static mp8_status wgrad_with_update(int64_t M, int64_t N, int64_t K, const uint8
                                     g_round, flags, g_seed, g_offset, stats, workspace, workspace_bytes,
                                     stream, 0, 0, &hook);
     if (st != MP8_ERR_UNSUPPORTED) return st;
-    // nothing to carry the update (a row length that is not a multiple of 16, ...): two launches through the
-    // 8-bit gradient, which lies in the workspace if the caller keeps none
+    // nothing to carry the update (unaligned operands, ...): two launches through the 8-bit gradient, which lies
+    // in the workspace if the caller keeps none
     if (g8_out != nullptr) return two_launches(g8_out, workspace, workspace_bytes);
-    if (workspace == nullptr || K > (INT64_MAX / 8) / N || workspace_bytes < (size_t)(K * N)) return st;
-    return two_launches((uint8_t *)workspace, nullptr, 0);
+    uint8_t *codes = codes_for_separate_update(M, N, K, flags, nullptr, workspace, workspace_bytes, false, hook.states);
+    const int layout = ((flags & MP8_FLAG_A_CONTRACTION_MAJOR) ? 1 : 0) | ((flags & MP8_FLAG_B_CONTRACTION_MAJOR) ? 2 : 0);
+    if (half_takes(K, N, M, layout) && K <= (INT64_MAX / 8) / N && workspace != nullptr && workspace_bytes >= (size_t)(K * N))
+        codes = (uint8_t *)workspace;
+    return codes != nullptr ? two_launches(codes, nullptr, 0) : st;
 }
 
 }  // namespace mp8

@@ -85,7 +85,12 @@ struct GemmArgs {
     const uint8_t *b;
     int64_t lda, ldb;
     int64_t rows, cols;
-    int ksteps;         // contraction length / BK (pipeline stages; gemm_any_kernel: rounded up)
+    int ksteps;         // contraction length / BK, rounded up (pipeline stages)
+    // Contraction indices of a last, incomplete stage (0: the contraction is whole stages).  The half-precision
+    // forms of the direct-to-LDS kernels multiply that stage FIRST, so that only their start-up code, and
+    // nothing in their loops, knows of it: global stage 0 is the incomplete one and stage s > 0 covers
+    // indices BK (s - 1) ...  What lies beyond the contraction reads as zero (see dma16_or_zero).
+    int tail;
     int64_t kc;         // contraction length (gemm_any_kernel)
     int splits;         // number of contraction slices
     int tiles_m, tiles_n;
@@ -347,6 +352,74 @@ __device__ __forceinline__ void dma16(const uint8_t *gbase, uint32_t lane_off, u
                  :
                  : "v"(lane_off), "s"(gbase), "s"(lds_addr)
                  : "memory", "m0");
+}
+
+// The same for the incomplete stage of a contraction: a lane whose sixteen bytes lie beyond it
+// fetches zero codes instead, from an array that exists for this, so that every address is valid.
+static __device__ const uint8_t kZeroCodes[16] __attribute__((aligned(16))) = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+__device__ __forceinline__ void dma16_or_zero(const uint8_t *gbase, uint32_t lane_off, bool inside, uint32_t lds_addr) {
+    const uint8_t *src = inside ? gbase + lane_off : kZeroCodes;
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                 :
+                 : "v"(src), "s"(lds_addr)
+                 : "memory", "m0");
+}
+
+// ---------------------------------------------------------------------------------------
+// Matrix products.  A fragment holds 32 codes per lane: contraction indices 32h .. 32h+31 of one row, h = lane / 32.
+// ---------------------------------------------------------------------------------------
+// Eight 8-bit codes as eight halves: the (1,5,2) format is the upper byte of an IEEE half, so the
+// conversion is exact for every code (subnormals, Inf and NaN among them) and costs four byte permutes.
+using half8 = _Float16 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ half8 halves_of(int lo, int hi) {
+    const u32x4 w = {__builtin_amdgcn_perm(0u, (uint32_t)lo, 0x010C000Cu), __builtin_amdgcn_perm(0u, (uint32_t)lo, 0x030C020Cu),
+                     __builtin_amdgcn_perm(0u, (uint32_t)hi, 0x010C000Cu), __builtin_amdgcn_perm(0u, (uint32_t)hi, 0x030C020Cu)};
+    return __builtin_bit_cast(half8, w);
+}
+
+// acc += x . y over 64 contraction indices.  The 8-bit instruction cuts every product 13 bits below the largest of its
+// group of eight.  HALF: four half-precision ones of sixteen indices (8t .. 8t+7 of both half waves) at half the
+// rate, which keep 24 bits: at least as precise as FP32 multiply-adds, which is what every shape outside the 8-bit
+// kernels' gets.  Error against 64 bits, rms over the rms of the sums, beside a chain of FP32 fused
+// multiply-adds in contraction order: N(0,1) codes, 6007 long, 8-bit 9e-6, half 4.7e-8, chain 6.6e-8; ReLU x uniform, 2047
+// long, 5e-6, 1.5e-8, 1.7e-8; uniform over the finite codes, 2047 long, 2.4e-5, 1.4e-7, 3.5e-7.
+template <bool HALF>
+__device__ __forceinline__ f32x16 mma64(i32x8 x, i32x8 y, f32x16 acc) {
+    if constexpr (HALF) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(halves_of(x[2 * t], x[2 * t + 1]), halves_of(y[2 * t], y[2 * t + 1]), acc, 0, 0, 0);
+        return acc;
+    } else {
+        // cbsz = blgp = 1 selects the (1,5,2) format for both operands; the scale operands are zero, i.e. the
+        // unscaled instruction
+        return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x, y, acc, 1, 1, 0, 0, 0, 0);
+    }
+}
+
+// The same for every pair of MI row and NJ column fragments: the half-precision form converts each of them once
+// (4 % faster on 4091 x 287 x 1088 contraction-major than pair by pair).
+template <bool HALF, int MI, int NJ>
+__device__ __forceinline__ void mma64_tiles(const i32x8 (&x)[NJ], const i32x8 (&y)[MI], f32x16 (&acc)[MI][NJ]) {
+    if constexpr (HALF) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            half8 xh[NJ], yh[MI];
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) xh[j] = halves_of(x[j][2 * t], x[j][2 * t + 1]);
+#pragma unroll
+            for (int i = 0; i < MI; ++i) yh[i] = halves_of(y[i][2 * t], y[i][2 * t + 1]);
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(xh[j], yh[i], acc[i][j], 0, 0, 0);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) acc[i][j] = mma64<false>(x[j], y[i], acc[i][j]);
+    }
 }
 
 // Tell the compiler that a pointer is the same in every lane (keeps it in scalar registers).

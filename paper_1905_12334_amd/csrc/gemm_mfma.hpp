@@ -39,7 +39,9 @@ namespace mp8 {
 //   2  a[r, (tap, co)] = e[r - shift(tap), co]      a plain, b[ci, (tap, co)] = w[tap][ci][co]
 //   3  a[(tap, ci), r] = x[r + shift(tap), ci]      both contraction-major, tap fixed per tile row
 // so only the base address of a stage (1, 2) or of a tile (3) differs from the plain GEMM.
-template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI, bool ATN, bool BTN, int CONV_>
+// HALF: half-precision products (mma64) and any contraction length in whole 16-byte chunks of row-major operands.  Its
+// epilogue takes any row length and every output, so it needs no second pass.
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI, bool ATN, bool BTN, int CONV_, bool HALF = false>
 __device__ __forceinline__ void gemm_mfma(const GemmArgs &p, const UpdateHook &upd) {
     // CONV_ 4 / 5: forms 1 / 2 for channel counts that are odd multiples of 64 (HALVES below)
     constexpr int CONV = CONV_ > 3 ? CONV_ - 3 : CONV_;
@@ -49,6 +51,7 @@ __device__ __forceinline__ void gemm_mfma(const GemmArgs &p, const UpdateHook &u
     static_assert((!ATN || BM % 128 == 0 || BM == 64) && (!BTN || BN % 128 == 0 || BN == 64),
                   "contraction-major operands: panels of 128 (or one of 64) tile rows");
     static_assert(WGM * WGN == 4, "four waves");
+    static_assert(!HALF || CONV_ == 0, "convolutions have whole stages");
     static_assert(NSTAGE >= 2, "ring depth");
     constexpr int WTM = BM / WGM, WTN = BN / WGN;  // wave tile
     constexpr int MT = WTM / 32, NT = WTN / 32;    // 32x32 MFMA tiles per wave
@@ -132,6 +135,12 @@ __device__ __forceinline__ void gemm_mfma(const GemmArgs &p, const UpdateHook &u
     }
     if constexpr (CONV == 2) b_origin = p.b + col0 * p.ldb;
     else b_origin = BTN ? p.b + (int64_t)ks_begin * b_kstep + col0 : p.b + col0 * p.ldb + (int64_t)ks_begin * BK;
+    // an incomplete stage goes first: the whole ones start one stage later
+    const bool has_tail = HALF && p.tail != 0;
+    if (has_tail) {
+        a_origin -= a_kstep;
+        b_origin -= b_kstep;
+    }
     const uint8_t *a_tile = uniform_ptr(a_origin);
     const uint8_t *b_tile = uniform_ptr(b_origin);
     // base addresses of stage `kstage` of this workgroup's slice
@@ -228,6 +237,20 @@ __device__ __forceinline__ void gemm_mfma(const GemmArgs &p, const UpdateHook &u
         for (int q = 0; q < B_DMA; ++q) dma16(bk.base, lane_off(bk, ob[q], HALVES && CONV == 2), sb + q * 4096);
     };
 
+    // the incomplete stage (stage 0 of the first slice) into ring slot 0
+    auto issue_tail = [&]() {
+        const uint32_t sa = lds0 + wave * 1024;
+        const uint8_t *ak = a_tile + (int64_t)p.ksteps * a_kstep, *bk = b_tile + (int64_t)p.ksteps * b_kstep;
+        auto inside = [&](bool km, bool narrow, int q) {
+            if (km) return (narrow ? 16 * (wave + 4 * q) + lrow64 : 8 * (wave + 4 * (q & 3)) + lrow) < p.tail;
+            return 16 * lchunk < p.tail;
+        };
+#pragma unroll
+        for (int q = 0; q < A_DMA; ++q) dma16_or_zero(ak, oa[q], inside(ATN, BM == 64, q), sa + q * 4096);
+#pragma unroll
+        for (int q = 0; q < B_DMA; ++q) dma16_or_zero(bk, ob[q], inside(BTN, BN == 64, q), sa + A_BYTES + q * 4096);
+    };
+
     // Fragments: lane l supplies row (l % 32) of a 32-row tile and, for sub-step s, the 32
     // bytes k = 64*s + 32*(l/32) .. +31 of the slab, i.e. chunks 4s + 2*(l/32) and the next.
     // A fragment is fetched as two 16-byte LDS reads ("halves").  Fragment f of a sub-step is
@@ -285,10 +308,8 @@ __device__ __forceinline__ void gemm_mfma(const GemmArgs &p, const UpdateHook &u
         const i32x8 av = __builtin_shufflevector(fr.h[i][0], fr.h[i][1], 0, 1, 2, 3, 4, 5, 6, 7);
         const i32x8 bv =
             __builtin_shufflevector(fr.h[MT + j][0], fr.h[MT + j][1], 0, 1, 2, 3, 4, 5, 6, 7);
-        // cbsz = blgp = 1 selects the (1,5,2) format for both operands; the scale operands are
-        // zero, i.e. the unscaled instruction.  b goes in as the "row" matrix so that a lane
-        // ends up with consecutive output columns.
-        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bv, av, acc[i][j], 1, 1, 0, 0, 0, 0);
+        // b goes in as the "row" matrix so that a lane ends up with consecutive output columns
+        acc[i][j] = mma64<HALF>(bv, av, acc[i][j]);
     };
     auto issue_one = [&](int kstage, const StageAddr &ak, const StageAddr &bk, int q) {  // load q (0 .. G-1) of a stage
         const uint32_t sa = lds0 + (kstage % NSTAGE) * STAGE + wave * 1024;
@@ -319,7 +340,10 @@ __device__ __forceinline__ void gemm_mfma(const GemmArgs &p, const UpdateHook &u
     // prologue: fill the ring, fetch the fragments of (0, 0)
 #pragma unroll
     for (int st = 0; st < NSTAGE; ++st)
-        if (st < ks_count) issue_loads(st);
+        if (st < ks_count) {
+            if (HALF && st == 0 && has_tail && ks_begin == 0) issue_tail();
+            else issue_loads(st);
+        }
     GroupWords<4> words;
     if constexpr (EPI >= EPI_UPDATE) draw_groups<4>(p.ep, upd, group, words);
     wait_stage(-1);
@@ -519,7 +543,9 @@ __device__ __forceinline__ void gemm_mfma(const GemmArgs &p, const UpdateHook &u
                     f32x4 x = src[q];
                     v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
                 }
-                emit16<EPI>(p, split, r, c, v, st, fast_cols);
+                if (HALF && EPI == EPI_FULL && !fast_cols)
+                    finish16_ragged(p.ep, r, c, p.cols - c < 16 ? (int)(p.cols - c) : 16, v, st);
+                else emit16<EPI>(p, split, r, c, v, st, fast_cols);
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -532,13 +558,13 @@ __device__ __forceinline__ void gemm_mfma(const GemmArgs &p, const UpdateHook &u
 }
 
 template <int BM, int BN, int WGM, int WGN, int NSTAGE, int MINBLOCKS, int EPI, bool ATN = false,
-          bool BTN = false, int CONV_ = 0>
+          bool BTN = false, int CONV_ = 0, bool HALF = false>
 __global__ __launch_bounds__(256, MINBLOCKS) void gemm_mfma_kernel(const GemmArgs p) {
-    gemm_mfma<BM, BN, WGM, WGN, NSTAGE, EPI, ATN, BTN, CONV_>(p, UpdateHook{});
+    gemm_mfma<BM, BN, WGM, WGN, NSTAGE, EPI, ATN, BTN, CONV_, HALF>(p, UpdateHook{});
 }
-template <int BM, int BN, int WGM, int WGN, int NSTAGE, int MINBLOCKS, int STATES, bool ATN, bool BTN>
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, int MINBLOCKS, int STATES, bool ATN, bool BTN, bool HALF = false>
 __global__ __launch_bounds__(256, MINBLOCKS) void gemm_mfma_update_kernel(const GemmArgs p, const UpdateHook upd) {
-    gemm_mfma<BM, BN, WGM, WGN, NSTAGE, EPI_UPDATE + STATES, ATN, BTN, 0>(p, upd);
+    gemm_mfma<BM, BN, WGM, WGN, NSTAGE, EPI_UPDATE + STATES, ATN, BTN, 0, HALF>(p, upd);
 }
 
 }  // namespace mp8

@@ -23,10 +23,11 @@ namespace mp8 {
 // own loads (a CU takes 64 bytes per clock however few of them work).
 // With EPI_UPDATE the master weights and the optimizer's state that a thread will need at the end are
 // fetched before the first stage: one workgroup per CU leaves each lane 512 registers.
-template <int EPI, bool ATN, bool BTN, int CONV, int BM = 64, int BN = 64>
+// HALF: as in the general kernel.
+template <int EPI, bool ATN, bool BTN, int CONV, int BM = 64, int BN = 64, bool HALF = false>
 __device__ __forceinline__ void gemm_wavek(const GemmArgs &p, const UpdateHook &upd) {
     constexpr int STATES = EPI >= EPI_UPDATE ? EPI - EPI_UPDATE : 0;
-    static_assert(CONV == 0 || (CONV == 3 && ATN && BTN), "plain or convolution weight gradient");
+    static_assert(CONV == 0 || (CONV == 3 && ATN && BTN && !HALF), "plain or convolution weight gradient");
     static_assert(BTN || !ATN, "a alone contraction-major is not built");
     static_assert(BM == 64 || (BM == 32 && !ATN), "the 32-row tile takes a row-major a");
     static_assert(BN == 64 || (BN == 32 && !BTN), "the 32-column tile takes a row-major b");
@@ -79,8 +80,11 @@ __device__ __forceinline__ void gemm_wavek(const GemmArgs &p, const UpdateHook &
         a_origin = ATN ? p.a + row0 : p.a + row0 * p.lda;
     }
     const uint8_t *b_origin = BTN ? p.b + col0 : p.b + col0 * p.ldb;
-    const uint8_t *a_tile = uniform_ptr(a_origin + (int64_t)(ks_begin + wave) * a_kstep);
-    const uint8_t *b_tile = uniform_ptr(b_origin + (int64_t)(ks_begin + wave) * b_kstep);
+    // an incomplete stage goes first (stage 0, wave 0 of the first slice): the others start one later
+    const bool has_tail = HALF && p.tail != 0;
+    const int64_t ks0 = ks_begin + wave - (has_tail ? 1 : 0);
+    const uint8_t *a_tile = uniform_ptr(a_origin + ks0 * a_kstep);
+    const uint8_t *b_tile = uniform_ptr(b_origin + ks0 * b_kstep);
     // Direct loads, eight per operand and stage.  Row-major operand: load q brings tile rows
     // 8q .. 8q+7, lane i lands at (row i/8, slot i%8) and fetches chunk (i%8) ^ ((row >> 1) & 7);
     // rows beyond the matrix are clamped to its last row.  Contraction-major operand: load q
@@ -120,6 +124,19 @@ __device__ __forceinline__ void gemm_wavek(const GemmArgs &p, const UpdateHook &
         for (int q = 0; q < QB; ++q) dma16(bk, ob[q], sa + SLAB_A + q * 1024);
     };
 
+    auto issue_tail = [&]() {  // the incomplete stage into buffer 0
+        const uint8_t *ak = a_origin + (int64_t)(p.ksteps - 1) * a_kstep;
+        const uint8_t *bk = b_origin + (int64_t)(p.ksteps - 1) * b_kstep;
+        auto inside = [&](bool km, int q) {
+            if (km) return 16 * q + (lane >> 2) < p.tail;
+            return 16 * ((lane & 7) ^ (((8 * q + (lane >> 3)) >> 1) & 7)) < p.tail;
+        };
+#pragma unroll
+        for (int q = 0; q < QA; ++q) dma16_or_zero(ak, oa[q], inside(ATN, q), ring0 + q * 1024);
+#pragma unroll
+        for (int q = 0; q < QB; ++q) dma16_or_zero(bk, ob[q], inside(BTN, q), ring0 + SLAB_A + q * 1024);
+    };
+
     f32x16 acc[MI][NJ];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
@@ -131,7 +148,8 @@ __device__ __forceinline__ void gemm_wavek(const GemmArgs &p, const UpdateHook &
 
     // (Issuing the fragment reads of a half stage ahead of the MFMAs of the one before it, as
     // the general kernel does, was measured and gained nothing here: the loop waits for loads.)
-    if (mine > 0) issue(0);
+    if (HALF && has_tail && ks_begin + wave == 0) issue_tail();
+    else if (mine > 0) issue(0);
     if (mine > 1) issue(1);
     GroupWords<4> words;
     if constexpr (EPI >= EPI_UPDATE) draw_groups<4>(p.ep, upd, group, words);
@@ -147,12 +165,8 @@ __device__ __forceinline__ void gemm_wavek(const GemmArgs &p, const UpdateHook &
             i32x8 bf[NJ];
 #pragma unroll
             for (int j = 0; j < NJ; ++j) bf[j] = slab64_fragment<BTN>(s + SLAB_A, sub, j, lane);
-            // bf8 x bf8, unscaled; b as the "row" matrix: a lane gets consecutive output columns
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bf[j], af[i], acc[i][j], 1, 1, 0, 0, 0, 0);
+            // b as the "row" matrix: a lane gets consecutive output columns
+            mma64_tiles<HALF>(bf, af, acc);
         }
         if (j + 2 < mine) {
             // the loads below are invisible to the compiler (it could sink the multiplications
@@ -207,20 +221,24 @@ __device__ __forceinline__ void gemm_wavek(const GemmArgs &p, const UpdateHook &
                     v[4 * q] += x.x; v[4 * q + 1] += x.y; v[4 * q + 2] += x.z; v[4 * q + 3] += x.w;
                 }
             }
-        if (r < p.rows && c < p.cols) emit16<EPI>(p, split, r, c, v, st, (p.cols & 15) == 0);
+        if (r < p.rows && c < p.cols) {
+            if (HALF && EPI == EPI_FULL && (p.cols & 15) != 0)
+                finish16_ragged(p.ep, r, c, p.cols - c < 16 ? (int)(p.cols - c) : 16, v, st);
+            else emit16<EPI>(p, split, r, c, v, st, (p.cols & 15) == 0);
+        }
     }
     if constexpr (EPI >= EPI_FULL) {
         if (p.ep.stats != nullptr) st.flush(p.ep.stats);
     }
 }
 
-template <int EPI, bool ATN, bool BTN, int CONV, int BM = 64, int BN = 64>
+template <int EPI, bool ATN, bool BTN, int CONV, int BM = 64, int BN = 64, bool HALF = false>
 __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(const GemmArgs p) {
-    gemm_wavek<EPI, ATN, BTN, CONV, BM, BN>(p, UpdateHook{});
+    gemm_wavek<EPI, ATN, BTN, CONV, BM, BN, HALF>(p, UpdateHook{});
 }
-template <int STATES, bool ATN, bool BTN, int CONV>
+template <int STATES, bool ATN, bool BTN, int CONV, bool HALF = false>
 __global__ __launch_bounds__(256, 1) void gemm_wavek_update_kernel(const GemmArgs p, const UpdateHook upd) {
-    gemm_wavek<EPI_UPDATE + STATES, ATN, BTN, CONV>(p, upd);
+    gemm_wavek<EPI_UPDATE + STATES, ATN, BTN, CONV, 64, 64, HALF>(p, upd);
 }
 
 }  // namespace mp8

@@ -143,12 +143,16 @@ def test_ragged_gemm_special_codes_and_accumulation_across_calls(mp8, rows, cols
     assert all(np.array_equal(x[fin], y[fin]) for x, y in zip(*results))
 
 
-# row-major operands of an odd leading dimension with a split contraction and whole stages; ragged token counts;
-# row lengths that are not multiples of sixteen
-@pytest.mark.parametrize("layout,dims,odd", [(ROW, (5120, 256, 256), 1), (TN, (1000, 128, 64), 0), (TN, (5001, 64, 192), 0),
-                                             (ROW, (4000, 92, 77), 0), (BTN, (2049, 112, 80), 0), (TN, (300, 1008, 2048), 0)])
+# Row-major operands of an odd leading dimension with a split contraction and whole stages; ragged token counts;
+# row lengths that are not multiples of sixteen; 128x128 tiles.  `bare`: the rules that need neither a gradient
+# buffer nor a workspace (the update in the GEMM's own epilogue); `scratch`: the queried workspace stands in for the
+# buffer.
+@pytest.mark.parametrize("layout,dims,odd,bare,scratch", [
+    (ROW, (5120, 256, 256), 1, "", True), (TN, (1000, 128, 64), 0, "sgd momentum", True), (TN, (5001, 64, 192), 0, "sgd momentum", True),
+    (ROW, (4000, 92, 77), 0, "", True), (BTN, (2049, 112, 80), 0, "", False), (TN, (300, 1008, 2048), 0, "sgd momentum adam", True),
+    (ROW, (2064, 1024, 1008), 0, "sgd momentum adam", True), (TN, (300, 2064, 4096), 0, "", True)])
 @pytest.mark.parametrize("rule", ["sgd", "momentum", "adam"])
-def test_ragged_weight_gradient_with_update(mp8, layout, dims, odd, rule):
+def test_ragged_weight_gradient_with_update(mp8, layout, dims, odd, bare, scratch, rule):
     """Weight gradient and update in one call equal the two separate calls bit for bit, whatever workspace
     either of them is given, and with or without a buffer for the gradient."""
     import torch
@@ -163,7 +167,6 @@ def test_ragged_weight_gradient_with_update(mp8, layout, dims, odd, rule):
     exact, large = (torch.empty(k, dtype=torch.uint8, device="cuda") for k in (max(need, 16), 8 * need + 4 * n))
     alpha, inv = scale_for(M), 2.0 ** -6
     grad = dict(flags=layout, lda=lda, ldb=ldb, alpha=alpha)
-    own_epilogue = N % 16 == 0 and layout != BTN
 
     def step(fused, workspace, keep=True):
         wt, mt, vt = gpu(w), gpu(m0), gpu(v0)
@@ -193,8 +196,12 @@ def test_ragged_weight_gradient_with_update(mp8, layout, dims, odd, rule):
     for fused in (False, True):
         for workspace in (None, exact, large):
             assert all(np.array_equal(x, y) for x, y in zip(want, step(fused, workspace))), (fused, workspace is None)
-    for workspace in ([None, exact] if own_epilogue else []) + [large]:
-        assert all(np.array_equal(x, y) for x, y in zip(want, step(True, workspace, keep=False)))
+    for workspace, accepted in ((None, rule in bare.split()), (exact, scratch), (large, scratch)):
+        if accepted:
+            assert all(np.array_equal(x, y) for x, y in zip(want, step(True, workspace, keep=False)))
+        else:
+            with pytest.raises(mp8.Mp8Error):
+                step(True, workspace, keep=False)
     acc = torch.empty((K, N), dtype=torch.float32, device="cuda")
     mp8.gemm_fp8(mp8.WGRAD, M, N, K, ag, bg, acc=acc, acc_mode=1, workspace=exact, **grad)
     ref, absref = oracle.gemm_ref(a, b)
