@@ -289,8 +289,8 @@ static bool half_takes(int64_t rows, int64_t cols, int64_t kc, int layout) {
 // The half-precision kernel that multiplies them: the tile make_plan names for whole stages, or the nearest that is
 // built -- 128x128 for the large ones, 64x64 for the rest.  Not MFMA if the contraction is to be split: slices
 // need a workspace, and the bits must not depend on one (gemm_any_kernel takes them in turn without).
-// Against gemm_any_kernel: 512 x 2048 from 6007 rows with ADAM 22 us (39), 12972 x 832 x 64 9.1 (34), 2143 x 3840 x 576
-// 13.2 (27).
+// Against gemm_any_kernel: 12972 x 832 x 64 9.1 us (34), 2143 x 3840 x 576 13.2 (27), a training step of 6007 x 2048 x 512
+// with ADAM 65.4 (82.5).
 static Plan half_plan(int64_t rows, int64_t cols, int64_t kc, int layout) {
     if (!half_takes(rows, cols, kc, layout)) return Plan{};
     Plan pl = make_plan(rows, cols, (kc + BK - 1) / BK * BK, 0, 0, layout);

@@ -505,3 +505,37 @@ def test_weight_gradient_and_adam_update_in_one_call_against_the_oracle_chain(mp
     torch.cuda.synchronize()
     assert torch.equal(g1, g2.view(-1)) and torch.equal(w1, w2) and torch.equal(q1, q2)
     assert torch.equal(m1.view(torch.int32), m2.view(torch.int32)) and torch.equal(v1.view(torch.int32), v2.view(torch.int32))
+
+
+# the last grid that loads before it looks at the flag, and the first that looks first (2048 workgroups)
+@pytest.mark.parametrize("rule,n", [("sgd", 2047 * 4096), ("sgd", 2047 * 4096 + 9), ("momentum", 2047 * 2048), ("momentum", 2047 * 2048 + 5),
+                                    ("adam", 2047 * 2048), ("adam", 2047 * 2048 + 3)])
+def test_skip_flag_on_both_sides_of_the_grid_that_looks_at_it_first(mp8, rule, n):
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    w0 = (torch.randn(n, generator=gen, device="cuda") * 0.02).half()
+    m0, v0 = torch.randn(n, generator=gen, device="cuda") * 1e-3, torch.rand(n, generator=gen, device="cuda") * 1e-6
+    g8 = torch.randn(n, generator=gen, device="cuda").to(torch.float8_e5m2).view(torch.uint8)
+    g8[n - 1] = 0x7C
+
+    def run(flag, stats):
+        w, m, v, w8 = w0.clone(), m0.clone(), v0.clone(), torch.full((n,), 0x55, dtype=torch.uint8, device="cuda")
+        st = mp8.new_stats() if stats else None
+        kw = dict(round=mp8.SR, seed=3, offset=1, w8_out=w8, stats=st,
+                  skip_if_nonzero=None if flag is None else torch.tensor([flag], dtype=torch.int32, device="cuda"))
+        if rule == "sgd":
+            mp8.sgd_update_fp16_sr(w, g8, 1e-2, 1.0, **kw)
+        elif rule == "momentum":
+            mp8.sgd_momentum_fp16_sr(w, m, g8, 1e-2, 1.0, 0.9, 1e-4, **kw)
+        else:
+            mp8.adam_fp16_sr(w, m, v, g8, 1e-2, 1.0, 5, **kw)
+        if stats:
+            assert mp8.read_stats(st)[1] == 1
+        return [t.view(torch.uint8) for t in (w, m, v, w8)]
+
+    untouched = [t.view(torch.uint8) for t in (w0, m0, v0, torch.full((n,), 0x55, dtype=torch.uint8, device="cuda"))]
+    plain = run(None, False)
+    assert not torch.equal(plain[0], untouched[0])
+    for stats in (False, True):
+        assert all(torch.equal(x, y) for x, y in zip(run(0, stats), plain))
+        assert all(torch.equal(x, y) for x, y in zip(run(2, stats), untouched))
