@@ -539,3 +539,35 @@ def test_skip_flag_on_both_sides_of_the_grid_that_looks_at_it_first(mp8, rule, n
     for stats in (False, True):
         assert all(torch.equal(x, y) for x, y in zip(run(0, stats), plain))
         assert all(torch.equal(x, y) for x, y in zip(run(2, stats), untouched))
+
+
+@pytest.mark.parametrize("rnd", [oracle.RNE, oracle.SR])
+def test_every_fp32_value_is_rounded_to_half_as_defined(mp8, rnd):
+    """All 2^32 inputs of the conversion that ends every update, reached through the momentum rule (velocity = the
+    input, momentum 1, gradient and weight zero, learning rate -1), against its definition in double: the
+    magnitude in units of the half grid at its exponent, rounded to nearest even, or truncated after the
+    element's sixteen random bits have been added below the units."""
+    import torch
+    n = 1 << 26
+    bits, w, g8 = torch.empty(n, dtype=torch.int16, device="cuda"), torch.empty(n, dtype=torch.float16, device="cuda"), \
+        torch.zeros(n, dtype=torch.uint8, device="cuda")
+    index = torch.arange(n, device="cuda")
+    for chunk in range(64):
+        v = (index + (chunk - 32) * n).to(torch.int32).view(torch.float32)
+        x = v.double()
+        w.zero_()
+        mp8.sgd_momentum_fp16_sr(w, v.clone(), g8, -1.0, 1.0, 1.0, 0.0, round=rnd, seed=17, offset=chunk)
+        e = (x.abs().clamp(2.0 ** -14, 2.0 ** 17).view(torch.int64) >> 52) - 1023
+        ulp = ((e - 10 + 1023) << 52).view(torch.float64)
+        q = x.abs() / ulp
+        if rnd == oracle.RNE:
+            q = torch.round(q)
+        else:
+            mp8.sr_bits(bits, 17, chunk)
+            q = torch.floor(q + (bits.to(torch.int32) & 0xFFFF).double() / 65536)
+        y = q * ulp
+        y = torch.where(y > 65504, torch.inf, y).copysign(x)
+        y = torch.where(x == 0, 0.0, y)                              # (-0 + 0 is +0 on the way)
+        want = torch.where(torch.isnan(x), 0x7E00, y.to(torch.float16).view(torch.int16).to(torch.int32) & 0xFFFF)
+        wrong = (w.view(torch.int16).to(torch.int32) & 0xFFFF) != want
+        assert not bool(wrong.any()), (chunk, int(wrong.sum()), v[wrong][:4].tolist())
