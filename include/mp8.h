@@ -118,9 +118,9 @@ mp8_status mp8_quantize_e5m2_batch(const mp8_quantize_item *items, int count, vo
  *     MP8_FWD       a = X8   [M, K]   b = W8^T  [N, K]   out [M, N]   contraction K
  *     MP8_BWD_DATA  a = dY8  [M, N]   b = W8    [K, N]   out [M, K]   contraction N
  *     MP8_WGRAD     a = X8^T [K, M]   b = dY8^T [N, M]   out [K, N]   contraction M
- *   lda, ldb   leading dimensions in elements (>= contraction length, multiples of 16; with
- *              a contraction-major flag: >= rows resp. cols of the output)
- *   a, b       16-byte aligned
+ *   lda, ldb   leading dimensions in elements (>= contraction length; with a contraction-major
+ *              flag: >= rows resp. cols of the output), best multiples of 16
+ *   a, b       best 16-byte aligned
  *   alpha      out8 = Q(fl32(alpha * acc)); acc itself is stored unscaled
  *   acc        nullable FP32 [rows, cols] (16-byte aligned).  acc_mode 0: not touched;
  *              1: receives the FP32 accumulator; 2: acc += accumulator, and out8 is the
@@ -148,8 +148,8 @@ mp8_status mp8_gemm_fp8(mp8_op op, int64_t M, int64_t N, int64_t K, const uint8_
                         int flags, uint64_t seed, uint64_t offset, mp8_stats *stats,
                         void *workspace, size_t workspace_bytes, void *stream);
 
-/* Upper bound of the scratch mp8_gemm_fp8 can need for this shape, whatever the options
- * (0 for shapes that are never split). */
+/* Upper bound of the scratch mp8_gemm_fp8 can use for this shape, whatever the options, and the
+ * weight-gradient calls with an update that take a workspace (0 where none of them uses any). */
 size_t mp8_gemm_fp8_workspace_bytes(mp8_op op, int64_t M, int64_t N, int64_t K);
 
 /*
@@ -191,9 +191,10 @@ mp8_status mp8_gemm_fp8_tuned(mp8_op op, int64_t M, int64_t N, int64_t K, const 
                               void *stream, int tile_config, int split_k);
 size_t mp8_gemm_fp8_workspace_bytes_tuned(mp8_op op, int64_t M, int64_t N, int64_t K,
                                           int tile_config, int split_k);
-/* Host only: which kernel an aligned call with these arguments would take -- *tile_out the tile
- * configuration (1-based), *splits_out the number of contraction slices; 0 and 1 for contractions
- * that are not a multiple of 128 and other shapes for which the call makes a choice of its own.  For tests and tuning. */
+/* Host only: which tile configuration (1-based, *tile_out) and how many contraction slices (*splits_out) an
+ * aligned call with these arguments would take; 0 and 1 where it takes a kernel that is not among the tile
+ * configurations (contractions that are not a multiple of 128, and contraction-major operands whose row length
+ * is not a multiple of 16).  For tests and tuning. */
 mp8_status mp8_gemm_fp8_plan(mp8_op op, int64_t M, int64_t N, int64_t K, int flags, int tile_config,
                              int split_k, int *tile_out, int *splits_out);
 int mp8_gemm_num_tile_configs(void);
@@ -291,26 +292,28 @@ mp8_status mp8_adam_fp16_sr(uint16_t *w16, float *m, float *v, const uint8_t *g8
  * Figure 1b from the weight-gradient GEMM to the next step's weights in one call: the weight
  * gradient is accumulated in FP32 and rounded once to 8 bits (as mp8_gemm_fp8 with MP8_WGRAD:
  * a, lda, b, ldb, alpha, flags incl. the contraction-major ones, g_round / g_seed / g_offset for
- * that rounding, stats), and the finishing pass that rounds it also applies
- * mp8_sgd_update_fp16_sr to the master weights w16 [K, N] with the codes it has just produced
- * (lr, inv_loss_scale, w_round / w_seed / w_offset, skip_if_nonzero, w8_out as there).  The
- * results are bit for bit those of the two separate calls.
- *   skip_if_nonzero  as there.  The finishing pass reads the flag when it starts, so a flag that
- *              earlier work on the stream has written (the overflow count of the error tensor's
- *              Q node) is honoured as it is.  A flag that lies inside *stats would still be
- *              counted by this very call (the gradient's own Inf/NaN codes) while the pass that
- *              reads it runs: such a call runs the weight gradient and the update as two
- *              launches, the update then sees the final count; it needs g8_out
+ * that rounding, stats), and mp8_sgd_update_fp16_sr is applied to the master weights w16 [K, N] with
+ * the codes so produced (lr, inv_loss_scale, w_round / w_seed / w_offset, skip_if_nonzero, w8_out as
+ * there).  The results are bit for bit those of the two separate calls, whatever workspace any of
+ * them is given.  Where the update happens, by shape:
+ *   - the contraction is split: in the finishing pass that adds the slices up and rounds the sum;
+ *   - it is not split and the output takes 64x64 tiles (N a multiple of 16, both operands row-major or
+ *     both contraction-major; with ADAM from 128 tiles on): in the GEMM's own epilogue, without a
+ *     workspace;
+ *   - otherwise in a launch of its own after the GEMM, which is cheaper than a finishing pass that
+ *     writes and reads the FP32 result.  The codes lie in g8_out, or in the first K*N bytes of the
+ *     workspace if the caller passes no g8_out and the workspace is that large.
+ *   skip_if_nonzero  as there.  The kernel that updates reads the flag when it starts (in the second
+ *              case that is the GEMM), so a flag that earlier work on the stream has written (the
+ *              overflow count of the error tensor's Q node) is honoured as it is.  A flag that lies inside
+ *              *stats would still be counted by this very call (the gradient's own Inf/NaN codes)
+ *              while the kernel that reads it runs: such a call runs the weight gradient and the
+ *              update as two launches, the update then sees the final count; it needs g8_out
  *              (MP8_ERR_INVALID_ARG without it).
- *   g8_out     nullable [K, N]: the 8-bit weight gradient, if the caller wants to keep it
- *   workspace  at least mp8_gemm_fp8_workspace_bytes(MP8_WGRAD, M, N, K) bytes, always needed
- *              when that is non-zero
- * Shapes without a finishing pass run as the two separate launches and need
- * g8_out (MP8_ERR_UNSUPPORTED without it).  A weight gradient whose contraction is not split
- * rounds in the GEMM's own epilogue; it is then followed by the update kernel instead of being
- * forced through a finishing pass (cheaper: no FP32 copy of the result is written), with the codes
- * in g8_out, or in the first K*N bytes of the workspace if the caller passes no g8_out and the
- * workspace is that large.
+ *   g8_out     nullable [K, N]: the 8-bit weight gradient, if the caller wants to keep it.  Operands that
+ *              are not 16-byte aligned or whose row length the aligned kernels cannot take, and a
+ *              contraction that is not split, need it (MP8_ERR_UNSUPPORTED without it)
+ *   workspace  mp8_gemm_fp8_workspace_bytes(MP8_WGRAD, M, N, K) bytes are enough in every case
  */
 mp8_status mp8_wgrad_update_fp16_sr(int64_t M, int64_t N, int64_t K, const uint8_t *a, int64_t lda,
                                     const uint8_t *b, int64_t ldb, float alpha, uint8_t *g8_out,

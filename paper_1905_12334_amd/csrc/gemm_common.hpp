@@ -136,28 +136,6 @@ __device__ __forceinline__ uint32_t finish1(const Epilogue &ep, int64_t r, int64
     return code;
 }
 
-// The codes of sixteen consecutive outputs of row r, the first with linear index i0 (a multiple of 16), as
-// four packed words; zero codes in a padding row of a convolution.
-__device__ __forceinline__ void codes16(const Epilogue &ep, int64_t r, int64_t i0, const float v[16], StatsAcc &st,
-                                        uint32_t pk[4]) {
-    const bool padding = ep.mask && conv_padding_row(ep, r);
-    uint32_t rw[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (ep.sr) {
-        const Philox rng(ep.seed, ep.offset);
-        uint4 w0 = rng.block((uint64_t)i0 >> 3), w1 = rng.block(((uint64_t)i0 >> 3) + 1);
-        rw[0] = w0.x; rw[1] = w0.y; rw[2] = w0.z; rw[3] = w0.w;
-        rw[4] = w1.x; rw[5] = w1.y; rw[6] = w1.z; rw[7] = w1.w;
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        float y[4] = {v[4 * q] * ep.alpha, v[4 * q + 1] * ep.alpha, v[4 * q + 2] * ep.alpha,
-                      v[4 * q + 3] * ep.alpha};
-        pk[q] = e5m2_pack4_rt(y, rw[2 * q], rw[2 * q + 1], ep.sr != 0, ep.sat != 0);
-        if (padding) pk[q] = 0;
-        else if (ep.stats != nullptr) st.add4(y, pk[q]);
-    }
-}
-
 // Finish sixteen consecutive columns c .. c+15 (c % 16 == 0) of output row r of an output
 // whose row length is a multiple of 16: 16-byte accesses, two Philox blocks, hardware
 // conversions.  Written to stay small: the rounding mode is a run-time flag and the rare
@@ -178,8 +156,23 @@ __device__ __forceinline__ void finish16(const Epilogue &ep, int64_t r, int64_t 
         }
     }
     if (ep.out8 == nullptr && ep.out8_t == nullptr && ep.stats == nullptr) return;
+    const bool padding = ep.mask && conv_padding_row(ep, r);
+    uint32_t rw[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (ep.sr) {
+        const Philox rng(ep.seed, ep.offset);
+        uint4 w0 = rng.block((uint64_t)i0 >> 3), w1 = rng.block(((uint64_t)i0 >> 3) + 1);
+        rw[0] = w0.x; rw[1] = w0.y; rw[2] = w0.z; rw[3] = w0.w;
+        rw[4] = w1.x; rw[5] = w1.y; rw[6] = w1.z; rw[7] = w1.w;
+    }
     uint32_t pk[4];
-    codes16(ep, r, i0, v, st, pk);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        float y[4] = {v[4 * q] * ep.alpha, v[4 * q + 1] * ep.alpha, v[4 * q + 2] * ep.alpha,
+                      v[4 * q + 3] * ep.alpha};
+        pk[q] = e5m2_pack4_rt(y, rw[2 * q], rw[2 * q + 1], ep.sr != 0, ep.sat != 0);
+        if (padding) pk[q] = 0;
+        else if (ep.stats != nullptr) st.add4(y, pk[q]);
+    }
     if (ep.out8 != nullptr) {
         u32x4 o = {pk[0], pk[1], pk[2], pk[3]};
         *reinterpret_cast<u32x4 *>(ep.out8 + i0) = o;

@@ -1,5 +1,5 @@
-// The general MFMA GEMM kernel (any contraction length that is a multiple of 128 bytes, every
-// operand layout, the three 3x3 convolution forms).
+// The general MFMA GEMM kernel: every operand layout, the three 3x3 convolution forms, contractions that are multiples
+// of 128 bytes on the 8-bit instruction, others in the half-precision form.
 #pragma once
 
 #include "gemm_common.hpp"

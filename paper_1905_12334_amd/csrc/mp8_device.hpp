@@ -255,42 +255,6 @@ __device__ __forceinline__ float e5m2_to_f32(uint32_t code) {
     return __half2float(__ushort_as_half((unsigned short)(code << 8)));
 }
 
-// FP32 bit pattern -> IEEE half code, same two rounding rules (13 discarded bits for normal
-// results).  NaN -> 0x7E00.  Overflow -> Inf.
-template <bool kSR>
-__device__ __forceinline__ uint32_t f16_from_f32_bits(uint32_t u, uint32_t r16) {
-    const uint32_t a = u & 0x7FFFFFFFu;
-    const uint32_t sign = (u >> 16) & 0x8000u;
-    uint32_t mag;
-    if (a >= 0x38800000u) {
-        uint32_t t = a - 0x38000000u;
-        if constexpr (kSR) {
-            uint32_t F = (t & 0x1FFFu) << 3;
-            mag = (t >> 13) + ((F + r16) >> 16);
-        } else {
-            mag = (t + 0x00000FFFu + ((t >> 13) & 1u)) >> 13;
-        }
-    } else {  // subnormal half: count of 2^-24 quanta
-        if constexpr (kSR) {
-            // units of 2^-40: mant * 2^(e-150+40) = mant >> (110 - e); e <= 112 so the shift
-            // may be negative by up to 2 bits
-            uint32_t e = a >> 23;
-            uint32_t mant = (a & 0x007FFFFFu) | (e ? 0x00800000u : 0u);
-            e = e ? e : 1u;
-            int sh = 110 - (int)e;  // >= -2
-            uint32_t v = sh >= 32 ? 0u : sh >= 0 ? (mant >> sh) : (mant << (-sh));
-            mag = (v >> 16) + (((v & 0xFFFFu) + r16) >> 16);
-        } else {
-            // 0.5f has ulp 2^-24: the adder rounds |y| to a multiple of 2^-24, ties to even
-            mag = f2u(u2f(a) + 0.5f) - 0x3F000000u;
-        }
-    }
-    if (a > 0x7F800000u) return 0x7E00u;
-    if (a == 0x7F800000u) return sign | 0x7C00u;
-    if (mag >= 0x7C00u) mag = 0x7C00u;
-    return sign | mag;
-}
-
 // ---------------------------------------------------------------------------------------
 // Statistics: per-thread partials, reduced across the wave with shuffles, then one atomic
 // per wave and field.
@@ -391,12 +355,12 @@ struct StatsAcc {
 // The master-weight update of Figure 1b on four elements (shared by the update kernels and by the
 // weight-gradient finishing pass that applies the update in place).
 // ---------------------------------------------------------------------------------------
-// FP32 -> half code, from hardware conversions.  RNE: v_cvt_f16_f32 rounds exactly like the
-// bit-level routine for every input that is not a NaN.  SR: v_cvt_sr_f16_f32 adds the top 13 bits of its
-// random operand to the 13 discarded ones, so r16 << 16 gives exactly the bit-level routine's code
-// for every normal (or overflowing) result; for subnormal results it keeps fewer bits, and the integer
-// form replaces it there: |x| in units of 2^-40, truncated, plus r16, over 2^16.  (Both checked
-// against f16_from_f32_bits over all 2^32 inputs.)  NaN is made canonical.
+// FP32 -> half code, the same two rounding rules as for the 8-bit format, from hardware conversions.  RNE:
+// v_cvt_f16_f32 for every input that is not a NaN.  SR: v_cvt_sr_f16_f32 adds the top 13 bits of its random operand
+// to the 13 discarded ones, so r16 << 16 gives exactly the rule's code for every normal (or overflowing)
+// result; for subnormal results it keeps fewer bits, and the integer form replaces it there: |x| in units of
+// 2^-40, truncated, plus r16, over 2^16.  (A GPU test compares both with the rule over all 2^32
+// inputs.)  NaN is made canonical.
 // r: the element's 16 random bits in the upper half.
 template <bool kSR>
 __device__ __forceinline__ uint32_t f16_from_f32(float x, uint32_t r) {

@@ -84,9 +84,9 @@ __device__ __forceinline__ uint32_t round1(float x, float scale, bool sat, const
 constexpr int kFlatUnroll = 4;  // 16-byte loads in flight per thread
 constexpr int kStatsBlocks = 512;      // grid limit per tensor of a batch with statistics (256 threads)
 // The flat variant with statistics: one workgroup of 1024 threads per CU.  Every workgroup ends with
-// up to three atomics on the one mp8_stats, which the memory side serialises at about 17 ns each
-// (measured: 2048 workgroups 142 us, 512 64 us, 256 57 us for the 67 M elements of the
-// Transformer-big error tensor, against 52 us without statistics).
+// one to three atomics on the one mp8_stats (the maximum needs none where a larger one has been seen), which
+// the memory side serialises at 10 to 17 ns each: 2048 workgroups 142 us, 512 64 us, 256 57 us for the 67 M
+// elements of the Transformer-big error tensor, against 52 us without statistics.
 constexpr int kFlatStatsBlocks = 256;
 constexpr int64_t kFlatSmall = 256 * 1024;
 constexpr int64_t kTiny = 128 * 1024, kTinyRagged = 256 * 1024;  // transposing: element by element up to here
@@ -253,7 +253,7 @@ constexpr int kPitch = kTile / 4 + 1;  // LDS row pitch in dwords
 // 128-byte line.  Requires cols % 4 == 0 and rows % 16 == 0.
 // With statistics two such 256-thread teams, each with tiles of its own, make one workgroup: the
 // workgroups end together, and their atomics on the one mp8_stats then queue up behind the last
-// stores at about 40 ns each (16384 x 1024: 512 of them 39 us, none 21.7 us).
+// stores (16384 x 1024: 512 workgroups 39 us, 256 34 us, no statistics 21.7 us).
 template <bool kF16, bool kSR, bool kStats>
 __global__ __launch_bounds__(kStats ? 512 : 256, kStats ? 1 : 2) void quantize_transpose_kernel(
     const void *__restrict__ src, uint8_t *__restrict__ dst, uint8_t *__restrict__ dst_t,
@@ -618,10 +618,10 @@ static hipError_t launch_quantize(const void *src, uint8_t *dst, uint8_t *dst_t,
                                n, scale, sat, seed, offset, stats, split);
         };
         if constexpr (kStats) {
-            // Every workgroup adds its atomics to the end of the chain, about 12 ns, so small tensors trade
-            // workgroups against the length of a run: 256 threads on 512 groups, then 1024 threads on 2048
-            // (to nearest 262144 elements in 256 workgroups 5.6 us, in 32 3.6; 2^20 elements 6.0, in 128 4.7;
-            // 2^21 elements 6.4 and 5.7; 2^22 elements 7.7 and 7.6, stochastic 8.6 and 9.6).
+            // Every workgroup adds its atomics to the end of the chain, so small tensors trade workgroups against the
+            // length of a run: 256 threads on 512 groups, then 1024 threads on 2048 (to nearest: 262144 elements in 256
+            // workgroups 5.6 us, in 32 3.6; 2^20 elements in 256 6.0, in 128 4.7; 2^21 elements 6.4 and 5.7;
+            // 2^22 elements 7.7 and 7.6, stochastic 8.6 and 9.6).
             if (n4 <= 32 * 1024) launch(std::integral_constant<int, 256>{}, flat_split(n4, kFlatStatsBlocks, 256, 512));
             else launch(std::integral_constant<int, kStatsThreads>{},
                         flat_split(n4, n4 <= 512 * 1024 ? kFlatStatsBlocks / 2 : kFlatStatsBlocks, kStatsThreads, 2048));

@@ -3,8 +3,9 @@
 Operands are drawn uniformly over all finite codes (all 31 exponents incl. subnormals and zeros,
 both signs), so that inside every group of eight products some lie many binades below the
 largest -- the case in which the matrix cores cut bits off (gpu_util.mfma_error_bound) and in
-which a narrow-range test says nothing.  Every kernel family runs at contraction lengths
-128, 256, 1152, 6400 and 16384 (where it takes them), with RNE and with stochastic rounding, and
+which a narrow-range test says nothing.  Every kernel family on the 8-bit matrix instruction runs at
+contraction lengths 128, 256, 1152, 6400 and 16384 (where it takes them), with RNE and with stochastic
+rounding (what runs on the half-precision one meets the FP32 bar of test_gpu_gemm_ragged.py instead), and
 each result goes through gpu_util.check_outputs with the operands, i.e. against
   - the bound the matrix cores' arithmetic implies (asserted everywhere),
   - the stated tolerance 1e-5 * sqrt(kc) * sum|a||b| (asserted where it is known to hold, recorded
