@@ -90,34 +90,29 @@ constexpr int kStatsBlocks = 512;      // grid limit per tensor of a batch with 
 constexpr int kFlatStatsBlocks = 256;
 constexpr int64_t kFlatSmall = 256 * 1024;
 constexpr int64_t kTiny = 128 * 1024, kTinyRagged = 256 * 1024;  // transposing: element by element up to here
-// The same with statistics: at most 128 workgroups up to 64 K elements (256 x 256 4.7 us; one workgroup per 256
-// elements 5.6, tiles of 64 4.7; 256 x 512 5.7 / 8.8 / 4.8), twice as many elements where tiles need guards
-// (1001 x 77 5.6 / 6.1 / 7.1; 511 x 513 8.0 / 26 / 5.9).
-constexpr int64_t kTinyStats = 64 * 1024;
 constexpr int64_t kTileSwitch = 256;   // transposing: tiles of 128 x 128 from this many on, else of 64 x 64
-// With statistics from the number on at which tiles of 64 become more workgroups than CUs: 1024 x 1280 7.5 us (11.8
-// in tiles of 64), 1920 x 2048 9.6 us (36), while 1024 x 1024 takes 7.2 and 7.5, stochastic 8.5 and 7.9.
-constexpr int64_t kTileSwitchStats = 65;
+// With statistics earlier, where tiles of 64 would be more workgroups than CUs; stochastic rounding, which they speed up
+// more, at two per CU.  (us in tiles of 128 / of 64, where no value of the tensor is flushed to zero, and where
+// every workgroup counts some: to nearest 1024 x 1280 7.0 / 6.9 and 7.5 / 11.8, 1920 x 2048 8.0 / 16.6 and 9.6 / 36;
+// stochastic 1024 x 1280 8.3 / 6.5 and 8.8 / 9.8, 1024 x 2048 8.6 / 8.4 and 9.3 / 13.6.)
+constexpr int64_t kTileSwitchStats = 65, kTileSwitchStatsSR = 128;
 constexpr int64_t kMaxTileBlocks = 1 << 21;  // a launch has fewer than 2^32 threads; tiles beyond it by striding
 constexpr int kStatsThreads = 1024;
 
-// How the groups of four elements of a tensor are dealt to the workgroups: `rounds` rounds of one whole pass
-// (kFlatUnroll groups per thread) for each, in turn, then a contiguous run of `chunk` groups (a multiple of
-// 64) for each.  Equal shares: with the grid limit of the stats variants, whole passes alone leave some
-// workgroups a third pass where others have two (9.1 M elements: 15.1 us, in shares 10.6).
+// How the groups of four elements of a tensor are dealt to the workgroups: a contiguous run of `chunk` groups (a
+// multiple of 64) for each.  Equal runs: with the grid limit of the stats variants, whole passes alone leave
+// some workgroups a third pass where others have two (9.1 M elements: 15.1 us, in runs 10.6).  Tensors of more than
+// a whole pass for every workgroup deal those out in turn first -- `rounds` of `round` groups, so that the
+// workgroups read side by side -- and split the rest into runs (33.6 M elements: 34.2 us in long runs, 31.4).
 struct FlatSplit {
-    int64_t blocks, rounds, chunk;
+    int64_t chunk;
+    int64_t rounds, round, rest;  // rest: the first group behind the rounds
 };
-static FlatSplit flat_split(int64_t n4, int64_t blocks, int threads, int64_t least) {
-    const int64_t round = blocks * threads * kFlatUnroll, rounds = n4 / round, rest = n4 - rounds * round;
-    const int64_t chunk = std::max(least, ((rest + blocks - 1) / blocks + 63) / 64 * 64);
-    return {rounds ? blocks : std::max<int64_t>(1, (rest + chunk - 1) / chunk), rounds, chunk};
-}
 
 // The flat loop of one tensor for workgroup `block` (NT threads each).  In a whole pass all loads of a thread
 // are in flight before the first is used, without guards; the end of a run takes two groups per thread, then
 // one (guarded).
-template <bool kF16, bool kSR, bool kStats, int NT>
+template <bool kF16, bool kSR, bool kStats, int NT, bool kRounds = false>
 __device__ __forceinline__ void flat_body(const void *__restrict__ src, uint8_t *__restrict__ dst,
                                           int64_t n, float scale, int sat, uint64_t seed,
                                           uint64_t offset, mp8_stats *stats, int64_t block,
@@ -126,7 +121,7 @@ __device__ __forceinline__ void flat_body(const void *__restrict__ src, uint8_t 
     StatsAcc st;
     const int64_t n4 = n >> 2;  // groups of four elements
     uint32_t *dst4 = reinterpret_cast<uint32_t *>(dst);
-    int64_t at = block * (NT * kFlatUnroll), end = 0;
+    int64_t at = 0, end = 0;
     auto pass = [&](auto unroll, auto guard) {
         constexpr int U = decltype(unroll)::value;
         const int64_t base = at + threadIdx.x;
@@ -151,11 +146,13 @@ __device__ __forceinline__ void flat_body(const void *__restrict__ src, uint8_t 
         }
         at += U * NT;
     };
-    for (int64_t round = 0; round < split.rounds; ++round) {
-        pass(std::integral_constant<int, kFlatUnroll>{}, std::false_type{});
-        at += (split.blocks - 1) * (NT * kFlatUnroll);
+    if constexpr (kRounds) {
+        for (int64_t round = 0; round < split.rounds; ++round) {
+            at = round * split.round + block * (NT * kFlatUnroll);
+            pass(std::integral_constant<int, kFlatUnroll>{}, std::false_type{});
+        }
     }
-    at = split.rounds * split.blocks * (NT * kFlatUnroll) + block * split.chunk;
+    at = (kRounds ? split.rest : 0) + block * split.chunk;
     end = at + split.chunk < n4 ? at + split.chunk : n4;
     while (at + kFlatUnroll * NT <= end) pass(std::integral_constant<int, kFlatUnroll>{}, std::false_type{});
     if (at + 2 * NT <= end) pass(std::integral_constant<int, 2>{}, std::false_type{});
@@ -169,11 +166,11 @@ __device__ __forceinline__ void flat_body(const void *__restrict__ src, uint8_t 
     if constexpr (kStats) st.flush(stats);
 }
 
-template <bool kF16, bool kSR, bool kStats, int NT>
+template <bool kF16, bool kSR, bool kStats, int NT, bool kRounds>
 __global__ __launch_bounds__(NT) void quantize_flat_kernel(const void *__restrict__ src, uint8_t *__restrict__ dst,
                                                            int64_t n, float scale, int sat, uint64_t seed,
                                                            uint64_t offset, mp8_stats *stats, const FlatSplit split) {
-    flat_body<kF16, kSR, kStats, NT>(src, dst, n, scale, sat, seed, offset, stats, blockIdx.x, split);
+    flat_body<kF16, kSR, kStats, NT, kRounds>(src, dst, n, scale, sat, seed, offset, stats, blockIdx.x, split);
 }
 
 // Several tensors in one launch: a step that quantises activations and errors (and whatever
@@ -612,24 +609,31 @@ static hipError_t launch_quantize(const void *src, uint8_t *dst, uint8_t *dst_t,
     const int64_t n = rows * cols;
     if (dst_t == nullptr) {
         const int64_t n4 = n >> 2;
-        auto launch = [&](auto threads, const FlatSplit &split) {
+        auto launch = [&](auto threads, auto in_rounds, int64_t blocks, const FlatSplit &split) {
             constexpr int NT = decltype(threads)::value;
-            hipLaunchKernelGGL((quantize_flat_kernel<kF16, kSR, kStats, NT>), dim3((unsigned)split.blocks), dim3(NT), 0, s, src, dst,
-                               n, scale, sat, seed, offset, stats, split);
+            hipLaunchKernelGGL((quantize_flat_kernel<kF16, kSR, kStats, NT, decltype(in_rounds)::value>), dim3((unsigned)blocks),
+                               dim3(NT), 0, s, src, dst, n, scale, sat, seed, offset, stats, split);
+        };
+        auto runs = [&](auto threads, int64_t chunk) {
+            launch(threads, std::false_type{}, std::max<int64_t>(1, (n4 + chunk - 1) / chunk), FlatSplit{chunk, 0, 0, 0});
         };
         if constexpr (kStats) {
-            // Every workgroup adds its atomics to the end of the chain, so small tensors trade workgroups against the
-            // length of a run: 256 threads on 512 groups, then 1024 threads on 2048 (to nearest: 262144 elements in 256
-            // workgroups 5.6 us, in 32 3.6; 2^20 elements in 256 6.0, in 128 4.7; 2^21 elements 6.4 and 5.7;
-            // 2^22 elements 7.7 and 7.6, stochastic 8.6 and 9.6).
-            if (n4 <= 32 * 1024) launch(std::integral_constant<int, 256>{}, flat_split(n4, kFlatStatsBlocks, 256, 512));
-            else launch(std::integral_constant<int, kStatsThreads>{},
-                        flat_split(n4, n4 <= 512 * 1024 ? kFlatStatsBlocks / 2 : kFlatStatsBlocks, kStatsThreads, 2048));
+            // At most one workgroup per CU, of 256 threads while a run is no longer than two groups for each.  Every
+            // workgroup adds its atomics to the end of the chain, if it has anything to add: fewer and longer runs
+            // would help where values are flushed to zero all over the tensor (to nearest 524288 elements: 256 runs
+            // 5.7 us, 128 4.6, 64 4.1) and cost where they are not, as after loss scaling (3.2, 3.4, 3.7).
+            constexpr int64_t round = (int64_t)kFlatStatsBlocks * kStatsThreads * kFlatUnroll;
+            const int64_t rounds = n4 / round;
+            const int64_t chunk = std::max<int64_t>(256, ((n4 - rounds * round + kFlatStatsBlocks - 1) / kFlatStatsBlocks + 63) / 64 * 64);
+            if (rounds > 0) launch(std::integral_constant<int, kStatsThreads>{}, std::true_type{}, kFlatStatsBlocks,
+                                   FlatSplit{chunk, rounds, round, rounds * round});
+            else if (chunk <= 512) runs(std::integral_constant<int, 256>{}, chunk);
+            else runs(std::integral_constant<int, kStatsThreads>{}, chunk);
         } else {
             // one pass per workgroup; tensors of less than kFlatSmall groups take one group per thread, so
             // that they occupy every CU
-            const int64_t per = n4 <= kFlatSmall ? 256 : 256 * kFlatUnroll, chunk = std::max(per, ((n4 >> 22) + 63) / 64 * 64);
-            launch(std::integral_constant<int, 256>{}, FlatSplit{std::max<int64_t>(1, (n4 + chunk - 1) / chunk), 0, chunk});
+            const int64_t per = n4 <= kFlatSmall ? 256 : 256 * kFlatUnroll;
+            runs(std::integral_constant<int, 256>{}, std::max(per, ((n4 >> 22) + 63) / 64 * 64));
         }
     } else {
         const bool ragged = ((rows | cols) & 3) != 0;
@@ -651,10 +655,12 @@ static hipError_t launch_quantize(const void *src, uint8_t *dst, uint8_t *dst_t,
         // (44); with statistics 13 us (241), 25 (54), 42 (73), 52 (59).  Tiles win from 16 columns on where they
         // need no guards (200000 x 16 14.3 and 14.2 us) and from 16 rows on (31 x 150001 17.7 us, 30.7).
         const bool narrow = cols < (ragged ? 32 : 16) || rows < 16;
-        const bool tiny = n <= (kStats ? (ragged ? 2 : 1) * kTinyStats : ragged ? kTinyRagged : kTiny);
+        const bool tiny = n <= (ragged ? kTinyRagged : kTiny);
         if (narrow || tiny) {
-            // (a grid that strides; with statistics few workgroups, see kTinyStats)
-            const int64_t limit = !kStats ? 256 * 32 : tiny ? 128 : kStatsBlocks;
+            // (A grid that strides.  With statistics fewer workgroups: 256 x 512 in 512 of them 3.1 us, and 8.8 if each
+            // counts flushed values; in 256 3.6 and 6.2, in tiles of 64 4.6 and 4.8.  Guarded tiles cost more:
+            // 511 x 513 in 1024 workgroups 3.9, in tiles 5.3.)
+            const int64_t limit = !kStats ? 256 * 32 : !tiny ? kStatsBlocks : ragged ? 1024 : kFlatStatsBlocks;
             hipLaunchKernelGGL((quantize_generic_kernel<kF16, kSR, kStats>), dim3((unsigned)std::min((n + 255) / 256, limit)),
                                dim3(256), 0, s, src, dst, dst_t, rows, cols, scale, sat, seed, offset, stats);
         } else if (!kStats && std::min(rows, cols) <= 64) {
@@ -673,7 +679,7 @@ static hipError_t launch_quantize(const void *src, uint8_t *dst, uint8_t *dst_t,
             hipLaunchKernelGGL((quantize_transpose_kernel<kF16, kSR, kStats>),
                                dim3((unsigned)blocks), dim3(kStats ? 512 : 256), 0, s, src, dst, dst_t, rows, cols,
                                scale, sat, seed, offset, stats);
-        } else if (nt >= (kStats ? kTileSwitchStats : kTileSwitch)) {
+        } else if (nt >= (!kStats ? kTileSwitch : kSR ? kTileSwitchStatsSR : kTileSwitchStats)) {
             // 1024-thread blocks, all loads of a tile in flight; for a matrix that is wide in
             // both directions, super-tiles of 4x4 keep the lines written by concurrently
             // running blocks close together in both copies.  With statistics one block per CU:
@@ -764,7 +770,7 @@ extern "C" mp8_status mp8_quantize_e5m2_batch(const mp8_quantize_item *items, in
         it.seed = q.seed;
         it.offset = q.offset;
         it.stats = q.stats;
-        it.split = flat_split(q.n >> 2, nblk[order[j]], 256, 256);
+        it.split.chunk = std::max<int64_t>(256, (((q.n >> 2) + nblk[order[j]] - 1) / nblk[order[j]] + 63) / 64 * 64);
         args.first[j] = (unsigned int)total;
         total += nblk[order[j]];
     }

@@ -46,8 +46,8 @@ def data(seed, shape, half):
     return x.astype(np.float16 if half else np.float32)
 
 
-# with statistics: runs of up to 512 groups for 256 threads, of 2048 to 4096 for 1024 threads, then whole rounds of
-# 2^20 groups over all workgroups and a rest (none, one group, several per thread)
+# with statistics: runs of up to 512 groups for 256 threads, longer ones for 1024 threads, then whole rounds of 2^20
+# groups over all workgroups and a rest (none, one group, several per thread)
 @pytest.mark.parametrize("n", [4, 252, 4 * 256 * 256 - 4, 4 * 256 * 256 + 4, 4 * 256 * 512 + 260, 4 * 256 * 1024 + 1027,
                                4 * 256 * 3 * 1024 - 13, 4 * 256 * 5 * 1024 + 3, 4 * 256 * 9 * 1024 + 77,
                                4 * 32768, 4 * 32768 + 5, 4 * 2 ** 19, 4 * 2 ** 19 + 4, 4 * 2 ** 20, 4 * 2 ** 20 + 6, 4 * (2 ** 21 + 65000) + 1])
@@ -69,8 +69,9 @@ def test_transposed_copies_with_statistics_and_shared_random_blocks(mp8, shape):
     check(mp8, data(shape[1], shape, False), oracle.SR, True, True)
 
 
-# with statistics: element by element up to 64 K elements (128 K with guards), tiles of 64 up to 64 tiles of 128
-@pytest.mark.parametrize("shape", [(256, 256), (256, 260), (255, 513), (259, 509), (1024, 1024), (1024, 1152), (1020, 1156), (1021, 1155)])
+# with statistics: element by element in a capped grid, tiles of 64 up to 64 tiles of 128 (127 when stochastic)
+@pytest.mark.parametrize("shape", [(256, 256), (256, 260), (256, 512), (255, 513), (512, 511), (1024, 1024), (1024, 1152), (1020, 1156), (1021, 1155),
+                                   (1024, 1920), (1024, 2048)])
 @pytest.mark.parametrize("rnd", [oracle.RNE, oracle.SR])
 def test_transposed_copies_with_statistics_at_the_changes_of_form(mp8, shape, rnd):
     check(mp8, data(shape[1], shape, False), rnd, True, True)
