@@ -24,7 +24,8 @@ namespace mp8 {
 //
 // What bounds it: a 64x64 tile pulls 128 bytes per clock and CU at the 8-bit matrix rate and 64 at the
 // half-precision one, which is what the path from L2 carries; unaligned rows cost more requests.  A layer of
-// 256 x 1000 x 2048: forward 10.4 us, backward data 7.1, weight gradient 7.2 (one thread per output element 639 each).
+// 256 x 1000 x 2048, back to back: forward 10.4 us, backward data 7.1, weight gradient 7.2 (one thread per output
+// element 639 each).
 // Needs a contraction of at least 16, and 16 rows / columns of a contraction-major operand (an edge
 // chunk is read as the last 16 bytes of its row and shifted into place).
 template <int EPI, bool ATN, bool BTN, bool SLICES>
