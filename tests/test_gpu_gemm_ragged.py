@@ -1,6 +1,6 @@
 """GPU parity of GEMMs whose contraction is not a whole number of 128-byte stages, or whose rows
-have no 16-byte alignment: the kernel that fetches operands through registers (half-precision matrix
-instructions), its split contractions with and without a workspace, and the fallback for tiny shapes."""
+have no 16-byte alignment: the half-precision forms of the direct-to-LDS kernels, the kernel that fetches
+operands through registers, its split contractions with and without a workspace, and the fallback for tiny shapes."""
 import numpy as np
 import pytest
 
@@ -70,9 +70,9 @@ def test_ragged_gemm(mp8, rows, cols, kc, layout):
     rng = np.random.default_rng(rows * 7919 + cols * 31 + kc + layout)
     big = rows * cols * kc > 3e8
     a, b = codes(int(rng.integers(1 << 30)), (rows, kc)), codes(int(rng.integers(1 << 30)), (cols, kc))
-    pad, shift = 16 * int(rng.integers(0, 2)), int(rng.integers(0, 16))
-    if kc % 128 == 0 and pad + shift == 0:
-        shift = 3
+    # aligned where the direct-to-LDS kernels can take it, any base address elsewhere
+    direct = kc % 128 != 0 and (layout == TN or kc % 16 == 0) and (layout != TN or rows % 16 == 0) and (layout == ROW or cols % 16 == 0)
+    pad, shift = 16 * int(rng.integers(0, 2)), 0 if direct else int(rng.integers(1, 16))
     ag, lda = stored(a, layout == TN, pad, shift)
     bg, ldb = stored(b, layout != ROW, pad)
     sub = rng.choice(rows, 24, replace=False) if big else np.arange(rows)     # rows that are checked
@@ -107,10 +107,16 @@ def test_ragged_gemm(mp8, rows, cols, kc, layout):
         assert mp8.read_stats(s1) == st.as_tuple() == mp8.read_stats(s2)
 
 
-# unsplit, four slices; rows of a multiple of sixteen columns and others
-@pytest.mark.parametrize("rows,cols,kc", [(40, 72, 300), (100, 80, 301), (100, 80, 4100), (41, 71, 5001)])
-@pytest.mark.parametrize("layout", [ROW, BTN, TN])
-def test_ragged_gemm_special_codes_and_accumulation_across_calls(mp8, rows, cols, kc, layout):
+# operands through registers: unsplit, four slices; rows of a multiple of sixteen columns and others
+SPECIAL = [(r, c, k, layout, False) for r, c, k in ((40, 72, 300), (100, 80, 301), (100, 80, 4100), (41, 71, 5001)) for layout in (ROW, BTN, TN)]
+# direct to LDS: 64x64, wave-split and 128x128 tiles; rows of any number of columns where b is row-major
+SPECIAL += [(r, c, k, layout, True) for r, c, k in ((112, 80, 304), (208, 1040, 2064), (2064, 1936, 272)) for layout in (ROW, BTN, TN)]
+SPECIAL += [(99, 71, 304, ROW, True), (207, 1001, 2064, ROW, True), (2061, 1931, 272, ROW, True), (112, 80, 301, TN, True),
+            (208, 1040, 2065, TN, True), (2064, 1936, 257, TN, True)]
+
+
+@pytest.mark.parametrize("rows,cols,kc,layout,aligned", SPECIAL)
+def test_ragged_gemm_special_codes_and_accumulation_across_calls(mp8, rows, cols, kc, layout, aligned):
     """Inf and NaN codes reach exactly the outputs they belong to, also from the last, partial chunk of a
     row; acc_mode 2 adds the accumulator of a call to what is there, once; a workspace changes no bit."""
     import torch
@@ -120,8 +126,8 @@ def test_ragged_gemm_special_codes_and_accumulation_across_calls(mp8, rows, cols
     a[3, kc - 1], a[7, 0], a[rows - 1, kc // 2], b[5, kc - 2], b[cols - 1, 1] = 0x7C, 0xFC, 0x7D, 0x7F, 0x7C
     ref, _ = oracle.gemm_ref(a, b)
     assert np.isnan(ref).any() and np.isinf(ref).any() and np.isfinite(ref).any()
-    ag, lda = stored(a, layout == TN, 0, 5)
-    bg, ldb = stored(b, layout != ROW, 1)
+    ag, lda = stored(a, layout == TN, 0, 0 if aligned else 5)
+    bg, ldb = stored(b, layout != ROW, 0 if aligned else 1)
     alpha = scale_for(kc)
     a0 = (rng.standard_normal((rows, cols)) * np.std(plain)).astype(np.float32)
     ws = torch.empty(max(16, mp8.gemm_fp8_workspace_bytes(mp8.FWD, rows, cols, kc)), dtype=torch.uint8, device="cuda")
