@@ -14,6 +14,8 @@
 //   gemm_wave128.hpp  about one 128x128 tile per CU and a long contraction (every wave the whole tile)
 //   gemm_any.hpp      row lengths, leading dimensions, contractions that are not multiples of 16
 // (contractions that are not multiples of 128: half-precision forms of the general and the wave-split kernel)
+//   gemm_conv.hpp     3x3 convolutions, forward and backward data: a tile's pixel rows in LDS for all taps
+//   gemm_epilogue.hpp  from a tile's accumulators to its outputs
 //   gemm_finish.hpp   second pass for split contractions and unfused epilogues, optionally with
 //                     the master-weight update; the any-shape fallback kernel
 // Split contraction, FP32 / transposed outputs, ragged column counts: the MFMA kernels write
@@ -32,6 +34,7 @@
 #include "../../include/mp8.h"
 #include "gemm_any.hpp"
 #include "gemm_common.hpp"
+#include "gemm_conv.hpp"
 #include "gemm_finish.hpp"
 #include "gemm_mfma.hpp"
 #include "gemm_shortk.hpp"
@@ -163,6 +166,7 @@ struct Plan {
     int splits;
     bool half;     // the half-precision form of that tile: unsplit, one pass
     bool in_turn;  // gemm_any_kernel: a workgroup takes all slices of its tile
+    int conv_rows; // gemm_conv_kernel: output rows per tile (0: another kernel)
     int tiles_m, tiles_n;
 };
 
@@ -971,7 +975,21 @@ static bool conv_dims(mp8_op op, int64_t prows, int64_t Ci, int64_t Co, ConvDims
 // when forward / backward data contract over an odd number of 64-channel units.
 static int64_t conv_kc_stages(const ConvDims &d) { return (d.kc + BK - 1) / BK * BK; }
 
-static Plan conv_plan(mp8_op op, const ConvDims &d, int64_t Ci) {
+static Plan conv_plan(mp8_op op, const ConvDims &d, int64_t Ci, int64_t W) {
+    // Forward and backward data: the kernel that keeps a tile's pixel rows in LDS, while they fit.  256 rows per tile from
+    // one and a half tiles per CU on: 32 x 56 x 56 x 64 (421) 7.7 us, in tiles of 128 8.3, 17 x 33 x 33, 128 to 512 (656) 16.8 and 17.5,
+    // 41 x 17 x 17, 192 to 320 (290) 13.5 and 12.6.
+    if (op != MP8_WGRAD && 2 * (W + 3) <= kConvHalo) {
+        Plan pl{};
+        pl.mfma = true;
+        pl.tile = T128x64s2;
+        pl.conv_rows = (d.rows + 255) / 256 * (d.cols / 64) >= kCUs + kCUs / 2 ? 256 : 128;
+        pl.tiles_m = (int)((d.rows + pl.conv_rows - 1) / pl.conv_rows);
+        pl.tiles_n = (int)(d.cols / 64);
+        pl.splits = 1;
+        return pl;
+    }
+    // Wider images, and the weight gradient, take the general kernels:
     // the tile shapes built for contraction-major operands are the ones built for convolutions
     const int64_t kc = conv_kc_stages(d);
     Plan pl = make_plan(d.rows, d.cols, kc, 0, 0, 3, true);
@@ -989,6 +1007,12 @@ static Plan conv_plan(mp8_op op, const ConvDims &d, int64_t Ci) {
         pl = make_plan(d.rows, d.cols, kc, T128x64s2 + 1, 0, 0, true);
     return pl;
 }
+
+// gemm_conv_kernel: [rows per tile / 128 - 1][op][EPI_*]
+#define MP8_CONV_OP(BM, BTN) \
+    {gemm_conv_kernel<BM, EPI_PARTIAL, BTN>, gemm_conv_kernel<BM, EPI_RNE, BTN>, gemm_conv_kernel<BM, EPI_FULL, BTN>}
+static void (*const kConv[2][2][3])(const GemmArgs) = {{MP8_CONV_OP(128, true), MP8_CONV_OP(128, false)},
+                                                       {MP8_CONV_OP(256, true), MP8_CONV_OP(256, false)}};
 
 // Forward / backward data with the contracted channel count an odd multiple of 64: [op][EPI_*]
 static void (*const kConvHalves[2][3])(const GemmArgs) = {
@@ -1015,7 +1039,7 @@ extern "C" size_t mp8_conv3x3_fp8_workspace_bytes(mp8_op op, int64_t B, int64_t 
     ConvDims d;
     if (B <= 0 || H <= 0 || W <= 0 || Ci <= 0 || Co <= 0 || prows <= 0) return 0;
     if (!conv_dims(op, prows, Ci, Co, d)) return 0;
-    return plan_workspace(conv_plan(op, d, Ci), d.rows, d.cols);
+    return plan_workspace(conv_plan(op, d, Ci, W), d.rows, d.cols);
 }
 
 namespace mp8 {
@@ -1044,7 +1068,7 @@ static mp8_status conv_impl(mp8_op op, int64_t B, int64_t H, int64_t W, int64_t 
     if (op == MP8_WGRAD && (prows & 127) != 0) return MP8_ERR_UNSUPPORTED;
     if (((uintptr_t)a | (uintptr_t)b | (uintptr_t)acc | (uintptr_t)out8 | (uintptr_t)workspace) & 15u)
         return MP8_ERR_ALIGNMENT;
-    const Plan pl = conv_plan(op, d, Ci);
+    const Plan pl = conv_plan(op, d, Ci, W);
     if (!pl.mfma) return MP8_ERR_UNSUPPORTED;
 
     Epilogue ep{};
@@ -1077,6 +1101,9 @@ static mp8_status conv_impl(mp8_op op, int64_t B, int64_t H, int64_t W, int64_t 
     ga.cv.odd_units = op != MP8_WGRAD && (d.kc % BK) != 0;
     ga.cv.b_tap_stride = Ci * Co;
     ga.cv.div_ci = make_fastdiv((uint32_t)Ci);
+    if (pl.conv_rows != 0)  // (a chunk of 64 channels is a stage of its contraction)
+        return launch_mfma(ga, ep, pl, (int64_t)ga.cv.units_per_tap * BK, kConv[pl.conv_rows / 128 - 1][(int)op], workspace,
+                           workspace_bytes, (hipStream_t)stream, upd);
     const bool halves = op != MP8_WGRAD && (ga.cv.units_per_tap & 1) != 0;
     if (halves && pl.tile != T128x128s2 && pl.tile != T128x64s2) return MP8_ERR_UNSUPPORTED;
     return launch_mfma(ga, ep, pl, conv_kc_stages(d),

@@ -76,9 +76,12 @@ struct ConvArgs {
     FastDiv div_cpb;      // by units_per_tap
     int units_per_tap;    // 64-byte units of the contraction per tap (contracted channels / 64)
     int odd_units;        // the contraction has an odd number of units: its last stage starts one early
-    int64_t b_tap_stride; // backward data: bytes between the weight slabs of two taps
+    int64_t b_tap_stride; // bytes between the weight slabs of two taps
     FastDiv div_ci;       // weight gradient: by Cin (tile row -> tap, first channel)
 };
+
+// Pixel rows beyond a tile's own that gemm_conv_kernel holds: 2 (W + 3), so W <= 61.
+constexpr int kConvHalo = 128;
 
 struct GemmArgs {
     const uint8_t *a;
