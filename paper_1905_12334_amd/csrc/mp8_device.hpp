@@ -197,14 +197,10 @@ __device__ __forceinline__ float saturate_finite(float y) {
     return (a > 57344.0f && a < __builtin_inff()) ? __builtin_copysignf(57344.0f, y) : y;
 }
 
-// Four values -> four codes packed little-endian.  r01 / r23 hold the 16 random bits of
-// elements (0: low half, 1: high half) and (2, 3); ignored for RNE.
-template <bool kSR, bool kBranchFree = true>
-__device__ __forceinline__ uint32_t e5m2_pack4(const float y[4], uint32_t r01, uint32_t r23,
-                                               bool sat) {
-    if constexpr (!kBranchFree) {
-        if (any_nan4(y)) return e5m2_pack4_slow(y[0], y[1], y[2], y[3], r01, r23, kSR, sat);
-    }
+// Four values -> four codes packed little-endian, as the instructions give them (NaN: 0xFE).  r01 / r23 hold the
+// 16 random bits of elements (0: low half, 1: high half) and (2, 3); ignored for RNE.
+template <bool kSR>
+__device__ __forceinline__ uint32_t e5m2_pack4_raw(const float y[4], uint32_t r01, uint32_t r23, bool sat) {
     float z[4] = {y[0], y[1], y[2], y[3]};
     if (sat) {
 #pragma unroll
@@ -220,8 +216,19 @@ __device__ __forceinline__ uint32_t e5m2_pack4(const float y[4], uint32_t r01, u
         w = __builtin_amdgcn_cvt_pk_bf8_f32(z[0], z[1], w, false);
         w = __builtin_amdgcn_cvt_pk_bf8_f32(z[2], z[3], w, true);
     }
-    if constexpr (kBranchFree) return canonical_nan_codes((uint32_t)w);
     return (uint32_t)w;
+}
+
+// The same with canonical NaN codes.
+template <bool kSR, bool kBranchFree = true>
+__device__ __forceinline__ uint32_t e5m2_pack4(const float y[4], uint32_t r01, uint32_t r23,
+                                               bool sat) {
+    if constexpr (!kBranchFree) {
+        if (any_nan4(y)) return e5m2_pack4_slow(y[0], y[1], y[2], y[3], r01, r23, kSR, sat);
+    }
+    const uint32_t w = e5m2_pack4_raw<kSR>(y, r01, r23, sat);
+    if constexpr (kBranchFree) return canonical_nan_codes(w);
+    return w;
 }
 
 // The same with the rounding mode chosen at run time.
@@ -263,19 +270,47 @@ struct StatsAcc {
     float amax = 0.0f;      // max |y| over non-NaN values
     uint32_t nan_seen = 0;  // any NaN among the values
     uint32_t nonfinite = 0, zero_codes = 0, zero_inputs = 0;
+    // Bit 7 of the bytes of four packed codes that are zero, Inf or NaN.  In a loss-scaled tensor few groups hold
+    // one, and only those are counted: with everything counted without a branch a Q node with statistics spent 25
+    // instructions per four values on them, as many as on the rest of its work.
+    static __device__ __forceinline__ uint32_t remarkable(uint32_t packed) {
+        const uint32_t top = (packed & 0x7C7C7C7Cu) + 0x04040404u;   // bit 7: the exponent field is all ones
+        const uint32_t some = (packed & 0x7F7F7F7Fu) + 0x7F7F7F7Fu;  // bit 7: the magnitude is not zero
+        return (top | ~some) & 0x80808080u;
+    }
+    __device__ __forceinline__ void add_amax4(const float y[4]) {  // ignores NaN operands
+        amax = __builtin_fmaxf(__builtin_fmaxf(amax, __builtin_fabsf(y[0])), __builtin_fabsf(y[1]));
+        amax = __builtin_fmaxf(__builtin_fmaxf(amax, __builtin_fabsf(y[2])), __builtin_fabsf(y[3]));
+    }
+    __device__ __forceinline__ void count4(const float y[4], uint32_t packed) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) zero_inputs += (y[j] == 0.0f) ? 1u : 0u;
+        nan_seen |= any_nan4(y) ? 1u : 0u;
+        nonfinite += __builtin_popcount(((packed & 0x7C7C7C7Cu) + 0x04040404u) & 0x80808080u);
+        zero_codes += 4u - __builtin_popcount(((packed & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) & 0x80808080u);
+    }
     // four values before rounding and their packed codes
     __device__ __forceinline__ void add4(const float y[4], uint32_t packed) {
+        add_amax4(y);
+        if (remarkable(packed)) count4(y, packed);
+    }
+    // U times four values and their codes as the conversion instructions give them: one test for all, and the NaN codes
+    // made canonical behind it
+    template <int U>
+    __device__ __forceinline__ void add_raw(const float (&y)[U][4], uint32_t (&packed)[U]) {
+        uint32_t any = 0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            amax = __builtin_fmaxf(amax, __builtin_fabsf(y[j]));  // ignores NaN operands
-            zero_inputs += (y[j] == 0.0f) ? 1u : 0u;
+        for (int u = 0; u < U; ++u) {
+            add_amax4(y[u]);
+            any |= remarkable(packed[u]);
         }
-        nan_seen |= any_nan4(y) ? 1u : 0u;
-        // bytes whose exponent field is all ones: (c & 0x7C) + 4 reaches bit 7 only then
-        nonfinite += __builtin_popcount(((packed & 0x7C7C7C7Cu) + 0x04040404u) & 0x80808080u);
-        // bytes whose magnitude is zero
-        const uint32_t z = packed & 0x7F7F7F7Fu;
-        zero_codes += 4u - __builtin_popcount(((z + 0x7F7F7F7Fu) | z) & 0x80808080u);
+        if (any) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                packed[u] = canonical_nan_codes(packed[u]);
+                count4(y[u], packed[u]);
+            }
+        }
     }
     __device__ __forceinline__ void add1(float y, uint32_t code) {
         if (y != y) nan_seen = 1u;
@@ -284,17 +319,20 @@ struct StatsAcc {
         nonfinite += ((code & 0x7Cu) == 0x7Cu) ? 1u : 0u;
         zero_codes += ((code & 0x7Fu) == 0u) ? 1u : 0u;
     }
+    // The running maximum at the destination, for flush: the maximum only grows, so a block whose own does not
+    // exceed a value seen there has nothing to add (an older value only makes the test more conservative).
+    // To be called when the kernel starts: at its end this load would meet the other blocks' additions to the same line,
+    // which then go to and fro between the caches (16384 x 1024, transposed, 256 blocks: 34.0 us, loaded early 25.5).
+    static __device__ __forceinline__ uint32_t peek(const mp8_stats *out) {
+        uint32_t seen = 0;
+        if (threadIdx.x == 0) seen = __hip_atomic_load(&out->amax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return seen;
+    }
     // Reduce over the wave, then over the block's waves through LDS: one atomic per field
     // and block.  Every thread of the block must call this (it contains a barrier).
-    __device__ __forceinline__ void flush(mp8_stats *out) {
+    __device__ __forceinline__ void flush(mp8_stats *out) { flush(out, peek(out)); }
+    __device__ __forceinline__ void flush(mp8_stats *out, uint32_t seen) {
         __shared__ uint32_t part[3][16];
-        // The running maximum at the destination, fetched early so that its latency hides
-        // behind the reductions: the maximum only grows, so a block whose own maximum does not
-        // exceed a value already seen there has nothing to add (the load bypasses non-coherent
-        // caches; an older value only makes the test more conservative).
-        uint32_t seen = 0;
-        if (threadIdx.x == 0)
-            seen = __hip_atomic_load(&out->amax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         uint32_t m = nan_seen ? 0x7FC00000u : f2u(amax);
         uint32_t nf = nonfinite, z = zero_codes - zero_inputs;
         reduce_wave(m, nf, z);

@@ -54,6 +54,19 @@ __device__ __forceinline__ uint32_t round4(float v[4], float scale, bool sat, Wo
     return pk;
 }
 
+// The same for U groups, all of which exist.
+template <int U, bool kSR, bool kStats>
+__device__ __forceinline__ void round_groups(float (&v)[U][4], float scale, bool sat, const Words4 (&r)[U], StatsAcc &st, uint32_t (&pk)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[u][j] *= scale;
+        if constexpr (kStats) pk[u] = e5m2_pack4_raw<kSR>(v[u], r[u].r01, r[u].r23, sat);
+        else pk[u] = e5m2_pack4<kSR>(v[u], r[u].r01, r[u].r23, sat);
+    }
+    if constexpr (kStats) st.add_raw(v, pk);
+}
+
 // Random words of U groups of four elements per lane, group u starting at element index i(u)
 // (a multiple of 4).  A group is half a Philox block.  With `paired`, lanes 2m and 2m + 1 hold the
 // two halves of the same block for every u (all lanes of the wave are here), and each computes every
@@ -84,9 +97,8 @@ __device__ __forceinline__ uint32_t round1(float x, float scale, bool sat, const
 constexpr int kFlatUnroll = 4;  // 16-byte loads in flight per thread
 constexpr int kStatsBlocks = 512;      // grid limit per tensor of a batch with statistics (256 threads)
 // The flat variant with statistics: one workgroup of 1024 threads per CU.  Every workgroup ends with
-// one to three atomics on the one mp8_stats (the maximum needs none where a larger one has been seen), which
-// the memory side serialises at 10 to 17 ns each: 2048 workgroups 142 us, 512 64 us, 256 57 us for the 67 M
-// elements of the Transformer-big error tensor, against 52 us without statistics.
+// one to three atomics on the one mp8_stats (the maximum needs none where a larger one had been seen), which
+// the memory side serialises at about 9 ns each (256 of them 2.3 us, 512 5.2 us).
 constexpr int kFlatStatsBlocks = 256;
 constexpr int64_t kFlatSmall = 256 * 1024;
 constexpr int64_t kTiny = 128 * 1024, kTinyRagged = 256 * 1024;  // transposing: element by element up to here
@@ -119,6 +131,8 @@ __device__ __forceinline__ void flat_body(const void *__restrict__ src, uint8_t 
                                           const FlatSplit &split) {
     const Philox rng(seed, offset);
     StatsAcc st;
+    uint32_t seen = 0;
+    if constexpr (kStats) seen = StatsAcc::peek(stats);
     const int64_t n4 = n >> 2;  // groups of four elements
     uint32_t *dst4 = reinterpret_cast<uint32_t *>(dst);
     int64_t at = 0, end = 0;
@@ -133,15 +147,17 @@ __device__ __forceinline__ void flat_body(const void *__restrict__ src, uint8_t 
         }
         Words4 w[U] = {};
         if constexpr (kSR) group_words<U>(rng, true, [&](int u) { return (base + u * NT) * 4; }, w);
+        uint32_t pk[U];
+        if constexpr (!decltype(guard)::value) round_groups<U, kSR, kStats>(v, scale, sat != 0, w, st, pk);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t g = base + u * NT;
             if (!decltype(guard)::value || g < end) {
-                uint32_t pk = round4<kSR, kStats>(v[u], scale, sat != 0, w[u], st);
+                if constexpr (decltype(guard)::value) pk[u] = round4<kSR, kStats>(v[u], scale, sat != 0, w[u], st);
                 // a plain store: the codes are what the next kernel (a GEMM) reads, and they are a
                 // quarter of the bytes -- left in the caches they were measured 7 % faster here and
                 // 11 us per step faster for the GEMM that follows than with a non-temporal store
-                dst4[g] = pk;
+                dst4[g] = pk[u];
             }
         }
         at += U * NT;
@@ -163,7 +179,7 @@ __device__ __forceinline__ void flat_body(const void *__restrict__ src, uint8_t 
         if (i < n)
             dst[i] = (uint8_t)round1<kSR, kStats>(load_src<kF16>(src, i), scale, sat != 0, rng, i, st);
     }
-    if constexpr (kStats) st.flush(stats);
+    if constexpr (kStats) st.flush(stats, seen);
 }
 
 template <bool kF16, bool kSR, bool kStats, int NT, bool kRounds>
@@ -250,7 +266,8 @@ constexpr int kPitch = kTile / 4 + 1;  // LDS row pitch in dwords
 // 128-byte line.  Requires cols % 4 == 0 and rows % 16 == 0.
 // With statistics two such 256-thread teams, each with tiles of its own, make one workgroup: the
 // workgroups end together, and their atomics on the one mp8_stats then queue up behind the last
-// stores (16384 x 1024: 512 workgroups 39 us, 256 34 us, no statistics 21.7 us).
+// stores (16384 x 1024, stochastic, 256 workgroups 23.1 us, no statistics 21.8 us; 33.8 us before the running maximum
+// was read early and groups without a remarkable code went uncounted, see StatsAcc).
 template <bool kF16, bool kSR, bool kStats>
 __global__ __launch_bounds__(kStats ? 512 : 256, kStats ? 1 : 2) void quantize_transpose_kernel(
     const void *__restrict__ src, uint8_t *__restrict__ dst, uint8_t *__restrict__ dst_t,
@@ -260,6 +277,8 @@ __global__ __launch_bounds__(kStats ? 512 : 256, kStats ? 1 : 2) void quantize_t
     __shared__ uint32_t tiles[TEAMS][2][kTile * kPitch];
     const Philox rng(seed, offset);
     StatsAcc st;
+    uint32_t seen = 0;
+    if constexpr (kStats) seen = StatsAcc::peek(stats);
     const int64_t tiles_c = (cols + kTile - 1) / kTile;
     const int64_t ntiles = ((rows + kTile - 1) / kTile) * tiles_c;
     const int team = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
@@ -285,20 +304,22 @@ __global__ __launch_bounds__(kStats ? 512 : 256, kStats ? 1 : 2) void quantize_t
     };
     auto phase1 = [&](int64_t t, uint32_t *tile, auto guard) {
         const int64_t r0 = (t / tiles_c) * kTile, c = (t % tiles_c) * kTile + 4 * cq;
-        Words4 w[2] = {};
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const int tr = tr0 + 8 * u;
-            const int64_t r = r0 + tr;
-            if constexpr (kSR)
-                if (u % 2 == 0) group_words<2>(rng, paired, [&](int d) { return (r + 8 * d) * cols + c; }, w);
-            uint32_t pk = 0;
-            if (!decltype(guard)::value || (r < rows && c < cols)) {
-                const int64_t i = r * cols + c;
-                pk = round4<kSR, kStats>(v[u], scale, sat != 0, w[u % 2], st);
-                __builtin_nontemporal_store(pk, reinterpret_cast<uint32_t *>(dst + i));
+        for (int u = 0; u < 16; u += 4) {
+            float (&x)[4][4] = *reinterpret_cast<float (*)[4][4]>(&v[u]);
+            auto row = [&](int d) { return r0 + tr0 + 8 * (u + d); };
+            Words4 w[4] = {};
+            if constexpr (kSR) group_words<4>(rng, paired, [&](int d) { return row(d) * cols + c; }, w);
+            uint32_t pk[4] = {0, 0, 0, 0};
+            if constexpr (!decltype(guard)::value) round_groups<4, kSR, kStats>(x, scale, sat != 0, w, st, pk);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                if (!decltype(guard)::value || (row(d) < rows && c < cols)) {
+                    if constexpr (decltype(guard)::value) pk[d] = round4<kSR, kStats>(x[d], scale, sat != 0, w[d], st);
+                    __builtin_nontemporal_store(pk[d], reinterpret_cast<uint32_t *>(dst + row(d) * cols + c));
+                }
+                tile[(tr0 + 8 * (u + d)) * kPitch + cq] = pk[d];
             }
-            tile[tr * kPitch + cq] = pk;
         }
     };
     auto phase2 = [&](int64_t t, const uint32_t *tile, auto guard) {
@@ -346,7 +367,7 @@ __global__ __launch_bounds__(kStats ? 512 : 256, kStats ? 1 : 2) void quantize_t
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         if (full) phase2(t, tile, Plain{}); else if (here) phase2(t, tile, Guarded{});
     }
-    if constexpr (kStats) st.flush(stats);
+    if constexpr (kStats) st.flush(stats, seen);
 }
 
 // One tile per block (no tile loop): with thousands of tiles many blocks per CU are resident at
@@ -361,6 +382,8 @@ __global__ __launch_bounds__(256) void quantize_transpose_oneshot_kernel(
     __shared__ uint32_t tile[kTile * kPitch];
     const Philox rng(seed, offset);
     StatsAcc st;
+    uint32_t seen = 0;
+    if constexpr (kStats) seen = StatsAcc::peek(stats);
     const int64_t tiles_c = (cols + kTile - 1) / kTile;
     const int64_t r0 = (int64_t)(blockIdx.x / tiles_c) * kTile;
     const int64_t c0 = (int64_t)(blockIdx.x % tiles_c) * kTile;
@@ -409,7 +432,7 @@ __global__ __launch_bounds__(256) void quantize_transpose_oneshot_kernel(
             }
         }
     }
-    if constexpr (kStats) st.flush(stats);
+    if constexpr (kStats) st.flush(stats, seen);
 }
 
 // Four consecutive elements of a row of any length and alignment: `have` (1 .. 4) of them exist.
@@ -473,6 +496,8 @@ __global__ __launch_bounds__((T / 4) * (T / 4)) void quantize_tile_kernel(
     __shared__ uint32_t tile[T * P];
     const Philox rng(seed, offset);
     StatsAcc st;
+    uint32_t seen = 0;
+    if constexpr (kStats) seen = StatsAcc::peek(stats);
     const int64_t tiles_c = (cols + T - 1) / T, tiles_r = (rows + T - 1) / T;
     const int64_t sup_c = (tiles_c + S - 1) / S, sup_r = (tiles_r + S - 1) / S;
     const int64_t ntiles = sup_c * sup_r * S * S;
@@ -569,7 +594,7 @@ __global__ __launch_bounds__((T / 4) * (T / 4)) void quantize_tile_kernel(
         r0 = rn;
         c0 = cn;
     }
-    if constexpr (kStats) st.flush(stats);
+    if constexpr (kStats) st.flush(stats, seen);
 }
 
 // Any shape: one element per thread and iteration.  For tensors so small that the shortest chain of
@@ -581,6 +606,8 @@ __global__ __launch_bounds__(256) void quantize_generic_kernel(
     mp8_stats *stats) {
     const Philox rng(seed, offset);
     StatsAcc st;
+    uint32_t seen = 0;
+    if constexpr (kStats) seen = StatsAcc::peek(stats);
     const int64_t n = rows * cols;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
@@ -591,7 +618,7 @@ __global__ __launch_bounds__(256) void quantize_generic_kernel(
             dst_t[(i - r * cols) * rows + r] = (uint8_t)c;
         }
     }
-    if constexpr (kStats) st.flush(stats);
+    if constexpr (kStats) st.flush(stats, seen);
 }
 
 __global__ __launch_bounds__(256) void sr_bits_kernel(uint16_t *out, int64_t n, uint64_t seed,
@@ -684,7 +711,7 @@ static hipError_t launch_quantize(const void *src, uint8_t *dst, uint8_t *dst_t,
             // both directions, super-tiles of 4x4 keep the lines written by concurrently
             // running blocks close together in both copies.  With statistics one block per CU:
             // every block ends in atomics on one address, and blocks that end together wait
-            // for each other there (512 of them: 16384 x 1024 39 us, against 22 us without atomics)
+            // for each other there
             tiles(std::integral_constant<int, 128>{}, wide ? 4 : 1, kStats ? kFlatStatsBlocks : kMaxTileBlocks);
         } else {
             // few tiles: smaller ones shorten the latency chain of the single round of blocks
