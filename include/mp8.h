@@ -344,13 +344,14 @@ mp8_status mp8_conv3x3_wgrad_update_fp16_sr(
  * The results are bit for bit those of the two separate calls.  When the layer has at most 128
  * output columns (N a multiple of 16, K a multiple of 128) the GEMM reads the activations only
  * once, and one kernel does both: it reads x, rounds it, writes x8_out (the weight gradient needs
- * it later) and multiplies from the codes it holds.  Every other shape runs as the two calls.
+ * it later) and multiplies from the codes it holds.  Small layers with more columns and a short
+ * contraction (K up to 512) take it as well.  Every other shape runs as the two calls.
  *   x          [M, K] FP32, dense, 16-byte aligned (device)
  *   x8_out     [M, K] 8-bit codes, dense, 16-byte aligned; always written
  *   w8         [K, N] 8-bit codes, row stride ldw >= N (the layout mp8_sgd_update_fp16_sr's
  *              w8_out produces); 16-byte aligned rows for the fused kernel
  *   flags      MP8_FLAG_SATURATE or 0, for the output rounding; x_flags the same for x8_out
- *   workspace  as mp8_gemm_fp8_workspace_bytes(MP8_FWD, M, N, K) says; the fused kernel needs none
+ *   workspace  as mp8_gemm_fp8_workspace_bytes(MP8_FWD, M, N, K) says; none for N <= 128 where one kernel does both
  * M*K == 0 or N == 0 is valid.  On error nothing is enqueued.
  */
 mp8_status mp8_quantize_gemm_fwd_fp8(int64_t M, int64_t N, int64_t K, const float *x, float x_scale,

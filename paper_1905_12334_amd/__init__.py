@@ -272,7 +272,7 @@ def quantize_gemm_fwd_fp8(M, N, K, x, x8_out, w8, out8=None, out8_t=None, acc=No
                           alpha=1.0, round=RNE, flags=0, seed=0, offset=0, stats=None, workspace=None,
                           ldw=None):
     """mp8_quantize_gemm_fwd_fp8: x8_out = Q(x * x_scale) [M, K] and out = x8_out . w8 [K, N] in one
-    call (one kernel when N <= 128)."""
+    call (one kernel when N <= 128 or the layer is small)."""
     (_nat or _native()).quantize_gemm_fwd_fp8(M, N, K, x, x8_out, w8, out8, out8_t, acc, acc_mode, x_scale, x_round,
                                               x_flags, x_seed, x_offset, x_stats, alpha, round, flags, seed, offset,
                                               stats, workspace, ldw)

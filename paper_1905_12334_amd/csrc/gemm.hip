@@ -887,14 +887,26 @@ extern "C" mp8_status mp8_quantize_gemm_fwd_fp8(int64_t M, int64_t N, int64_t K,
     if (N > 0 && K > 0 && (!w8 || ldw < N)) return MP8_ERR_INVALID_ARG;
     if (((uintptr_t)x | (uintptr_t)x8_out | (uintptr_t)acc | (uintptr_t)out8 | (uintptr_t)out8_t) & 15u)
         return MP8_ERR_ALIGNMENT;
-    const bool fused = N >= 16 && N <= 128 && (N & 15) == 0 && K > 0 && (K & (BK - 1)) == 0 &&
+    // Up to 128 columns the activations are read once.  More column tiles round them again each, which pays while it
+    // costs less than the launch it saves: short contractions with few tiles (256 x 256 x 256 4.8 us, two launches 5.4;
+    // 1024 x 1024 x 256 5.0 and 5.4; 4096 x 256 x 512 7.3 and 8.4; but 1024 x 2048 x 256 6.5 and 6.1, 256 x 256 x 1024 9.6 and 8.1,
+    // 64 x 1024 x 512 6.5 and 6.1).
+    const int64_t ctiles = (N + 127) / 128;
+    const bool narrow = N <= 128, small = K <= (M >= 256 ? 4 : 2) * BK && M <= 64 * 128 && ctiles <= 128 && (M + 63) / 64 * ctiles <= 128;
+    const bool fused = N >= 16 && (narrow || small) && (N & 15) == 0 && K > 0 && (K & (BK - 1)) == 0 &&
                        ((uintptr_t)w8 & 15u) == 0 && (ldw & 15) == 0 && ldw < (1 << 24) &&
                        M <= (INT64_MAX / 8) / K && (M + 63) / 64 <= 0x7FFFFFFFLL;
+    // (beyond 128 columns, the checks of the two calls this one stands for: what they refuse stays refused)
+    if (!narrow && N > 0 && K > 0) {
+        const mp8_status sv = gemm_validate(MP8_FWD, M, N, K, x8_out, K, w8, ldw, acc, acc_mode, out8, out8_t, round,
+                                            (flags & MP8_FLAG_SATURATE) | MP8_FLAG_B_CONTRACTION_MAJOR, workspace, workspace_bytes);
+        if (sv != MP8_OK) return sv;
+    }
     if (!fused) {
         // any other shape: the two calls this one stands for (the second one's checks first, so
         // that a rejected call has enqueued nothing)
         const int gflags = (flags & MP8_FLAG_SATURATE) | MP8_FLAG_B_CONTRACTION_MAJOR;
-        if (N > 0 && K > 0) {
+        if (narrow && N > 0 && K > 0) {
             const mp8_status sv = gemm_validate(MP8_FWD, M, N, K, x8_out, K, w8, ldw, acc, acc_mode, out8, out8_t,
                                                 round, gflags, workspace, workspace_bytes);
             if (sv != MP8_OK) return sv;
@@ -938,7 +950,7 @@ extern "C" mp8_status mp8_quantize_gemm_fwd_fp8(int64_t M, int64_t N, int64_t K,
                        out8 != nullptr;
     const bool qplain = !qa.sr && !qa.sat && x_stats == nullptr;
     // 128 rows per workgroup once that still gives every other CU a workgroup
-    const bool tall = (M + 127) / 128 >= 128;
+    const bool tall = narrow && (M + 127) / 128 >= 128;
     void (*kernel)(const GemmArgs, const QuantArgs);
     if (tall)
         kernel = plain ? (qplain ? gemm_qfwd_kernel<EPI_RNE, true, 128> : gemm_qfwd_kernel<EPI_RNE, false, 128>)
@@ -947,7 +959,7 @@ extern "C" mp8_status mp8_quantize_gemm_fwd_fp8(int64_t M, int64_t N, int64_t K,
         kernel = plain ? (qplain ? gemm_qfwd_kernel<EPI_RNE, true, 64> : gemm_qfwd_kernel<EPI_RNE, false, 64>)
                        : (qplain ? gemm_qfwd_kernel<EPI_FULL, true, 64> : gemm_qfwd_kernel<EPI_FULL, false, 64>);
     const int bm = tall ? 128 : 64;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((M + bm - 1) / bm)), dim3(4 * bm + 256), 0,
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((M + bm - 1) / bm), (unsigned)ctiles), dim3(4 * bm + 256), 0,
                        (hipStream_t)stream, ga, qa);
     return hipGetLastError() == hipSuccess ? MP8_OK : MP8_ERR_HIP;
 }

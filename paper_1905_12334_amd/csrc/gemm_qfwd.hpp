@@ -24,9 +24,11 @@ __device__ __forceinline__ void wait_vm_lds_fence() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(n) : "memory");
 }
 
-// y8[M, N] = Q(alpha * Q(x * scale)[M, K] . w8[K, N]) for N <= 128, writing Q(x * scale) as well.
-// With one column tile the activations are read exactly once by the GEMM, so the kernel that
-// rounds them can be the GEMM itself.  A workgroup owns 64 (or 128) rows and has eight (twelve) waves in two roles:
+// y8[M, N] = Q(alpha * Q(x * scale)[M, K] . w8[K, N]), writing Q(x * scale) as well.
+// With one column tile (N <= 128) the activations are read exactly once by the GEMM, so the kernel that
+// rounds them can be the GEMM itself.  Small layers take it with several column tiles too (blockIdx.y), each of which
+// rounds its rows again: at that size a launch costs more (256 x 256 x 256 4.8 us, Q node and GEMM 5.4, and the host's
+// time for a launch).  A workgroup owns 64 (or 128) rows and has eight (twelve) waves in two roles:
 //
 //   the first four (eight) waves, the readers: per 128-element stage of the contraction they load 64 x 128 FP32
 //     (16-byte loads, a wave's load covering 512 contiguous bytes of two rows, two or three
@@ -74,7 +76,8 @@ __global__ __launch_bounds__(4 * BM + 256, BM == 64 ? 2 : 1) void gemm_qfwd_kern
     uint8_t *lds_a = lds, *lds_b = lds + 2 * A_STAGE;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t row0 = (int64_t)blockIdx.x * BM;
+    const int64_t row0 = (int64_t)blockIdx.x * BM, col0 = (int64_t)blockIdx.y * 128;
+    const bool first_cols = blockIdx.y == 0;  // of several column tiles, which all round their rows, one stores and counts them
     const int ksteps = p.ksteps;
     const int64_t kc = (int64_t)ksteps * BK;
     StatsAcc stx, st;
@@ -95,7 +98,7 @@ __global__ __launch_bounds__(4 * BM + 256, BM == 64 ? 2 : 1) void gemm_qfwd_kern
             a_slot[u] = (uint32_t)(row * BK + ((((c4 >> 2) ^ ((row >> 1) & 7))) << 4) + 4 * (c4 & 3));
         }
         const Philox rng(q.seed, q.offset);
-        const bool x_stats = q.stats != nullptr;
+        const bool x_stats = q.stats != nullptr && first_cols;
         f32x4 f[DEPTH][8];
         // Stages beyond the last one are "loaded" too (the first 16 bytes of x in every lane): the
         // number of loads in flight is then the same in every iteration, and the compiler's
@@ -177,7 +180,7 @@ __global__ __launch_bounds__(4 * BM + 256, BM == 64 ? 2 : 1) void gemm_qfwd_kern
         uint32_t ob[4];
         {
             const int chunk = (lane & 3) ^ (((lane >> 4) & 1) << 1);
-            int64_t m = 64 * (v >> 1) + 16 * chunk;
+            int64_t m = col0 + 64 * (v >> 1) + 16 * chunk;
             m = m + 16 <= p.cols ? m : p.cols - 16;  // columns beyond the matrix: never stored
 #pragma unroll
             for (int qq = 0; qq < 4; ++qq)
@@ -256,15 +259,20 @@ __global__ __launch_bounds__(4 * BM + 256, BM == 64 ? 2 : 1) void gemm_qfwd_kern
                         acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bv[j], av, acc[i][j], 1, 1, 0, 0, 0, 0);
                 }
             }
+            if (first_cols) {
 #pragma unroll
-            for (int h = 0; h < PIECES; ++h) {
-                const u32x4 o = *reinterpret_cast<const u32x4 *>(sa + piece_lds[h]);
-                *reinterpret_cast<u32x4 *>(piece_dst[h] + (int64_t)s * BK) = o;
+                for (int h = 0; h < PIECES; ++h) {
+                    const u32x4 o = *reinterpret_cast<const u32x4 *>(sa + piece_lds[h]);
+                    *reinterpret_cast<u32x4 *>(piece_dst[h] + (int64_t)s * BK) = o;
+                }
             }
             // this wave's part of stage s + 1 of the weights, requested one iteration ago (before the
             // loop for s = 0); younger: the stores of stage s - 1 (not for s = 0), 4 direct loads, the
             // stores of stage s
-            if (s + 2 < ksteps) {
+            if (!first_cols) {
+                if (s + 2 < ksteps) wait_vm_lds_fence<4>();
+                else wait_vm_lds_fence<0>();
+            } else if (s + 2 < ksteps) {
                 if (s > 0) wait_vm_lds_fence<4 + 2 * PIECES>();
                 else wait_vm_lds_fence<4 + PIECES>();
             } else {  // no direct loads were issued in this iteration
@@ -292,13 +300,13 @@ __global__ __launch_bounds__(4 * BM + 256, BM == 64 ? 2 : 1) void gemm_qfwd_kern
                         vv[8 * g + e] = u2f(sw[0]);
                         vv[8 * g + 4 + e] = u2f(sw[1]);
                     }
-                const int64_t c = 64 * wc + 32 * j + 16 * fkb;
+                const int64_t c = col0 + 64 * wc + 32 * j + 16 * fkb;
                 if (r < p.rows && c < p.cols) emit16<EPI>(p, 0, r, c, vv, st, fast_cols);
             }
         }
     }
     if constexpr (!QPLAIN) {
-        if (q.stats != nullptr) {
+        if (q.stats != nullptr && first_cols) {
             stx.flush(q.stats);
             __syncthreads();  // the two reductions share their LDS words
         }
