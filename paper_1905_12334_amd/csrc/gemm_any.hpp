@@ -200,15 +200,27 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p) {
                     *reinterpret_cast<f32x4 *>(red + (wave * T + 32 * i + frow) * RED_LD + 32 * j + 8 * g + 4 * fkb) = o;
                 }
         __syncthreads();
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float *at = red + (threadIdx.x >> 2) * RED_LD + 16 * (threadIdx.x & 3) + 4 * q;
+        auto summed = [&](int row, int col) {  // four columns, in wave order
+            const float *at = red + row * RED_LD + col;
             f32x4 sum = *reinterpret_cast<const f32x4 *>(at);
 #pragma unroll
             for (int w = 1; w < 4; ++w) {
                 const f32x4 x = *reinterpret_cast<const f32x4 *>(at + w * T * RED_LD);
                 sum.x += x.x; sum.y += x.y; sum.z += x.z; sum.w += x.w;
             }
+            return sum;
+        };
+        if constexpr (EPI == EPI_PARTIAL) {
+#pragma unroll
+            for (int k = 0; k < T * T / 1024; ++k) {
+                const int item = threadIdx.x + 256 * k, rr = item >> 4, c4 = 4 * (item & 15);
+                emit_partial4(p, split, row0 + rr, col0 + c4, summed(rr, c4));
+            }
+            return;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const f32x4 sum = summed(threadIdx.x >> 2, 16 * (threadIdx.x & 3) + 4 * q);
             if (SLICES && slice > 0) {
                 v[4 * q] += sum.x; v[4 * q + 1] += sum.y; v[4 * q + 2] += sum.z; v[4 * q + 3] += sum.w;
             } else {
@@ -221,8 +233,7 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p) {
     StatsAcc st;
     const int64_t r = row0 + (threadIdx.x >> 2), c = col0 + 16 * (threadIdx.x & 3);
     if (r < p.rows && c < p.cols) {
-        if constexpr (EPI == EPI_PARTIAL) emit16<EPI_PARTIAL>(p, split, r, c, v, st, (p.cols & 15) == 0);
-        else if ((p.cols & 15) == 0) finish16(p.ep, r, c, v, st);
+        if ((p.cols & 15) == 0) finish16(p.ep, r, c, v, st);
         else finish16_ragged(p.ep, r, c, p.cols - c < 16 ? (int)(p.cols - c) : 16, v, st);
     }
     if constexpr (EPI == EPI_FULL) {

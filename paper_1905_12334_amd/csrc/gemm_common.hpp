@@ -291,27 +291,28 @@ __device__ __forceinline__ void map_block(const GemmArgs &p, int &split, int &tm
 // with s state words per weight (UpdateHook in gemm_finish.hpp).
 enum { EPI_PARTIAL = 0, EPI_RNE = 1, EPI_FULL = 2, EPI_UPDATE = 3 };
 
+// EPI_PARTIAL: four consecutive columns c .. c+3 (c % 4 == 0) of row r of an FP32 tile to slice `split` of the workspace.
+// To be called with neighbouring lanes side by side in a row, so that a store instruction of a wave covers whole lines:
+// with sixteen columns per lane, four stores of every fourth sixteen bytes, the tiles left at 1 TB/s (512 x 2048 in
+// two slices of 64x64 tiles over 4096: 17.5 us, half of it these stores).
+__device__ __forceinline__ void emit_partial4(const GemmArgs &p, int split, int64_t r, int64_t c, f32x4 v) {
+    if (r >= p.rows) return;
+    float *dst = p.partial + ((int64_t)split * p.rows + r) * p.cols + c;
+    if ((p.cols & 3) == 0) {
+        if (c < p.cols) *reinterpret_cast<f32x4 *>(dst) = v;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (c + e < p.cols) dst[e] = v[e];
+    }
+}
+
 // What a tile kernel does with sixteen consecutive columns c .. c+15 (c % 16 == 0) of output row
-// r, per epilogue variant (described at the main kernel): FP32 to slice `split` of the workspace, the RNE-only
-// conversion, or the complete epilogue.
+// r, per epilogue variant (described at the main kernel): the RNE-only conversion, or the complete epilogue.
 template <int EPI>
-__device__ __forceinline__ void emit16(const GemmArgs &p, int split, int64_t r, int64_t c,
-                                       float v[16], StatsAcc &st, bool fast_cols) {
-    if constexpr (EPI == EPI_PARTIAL) {
-        float *dst = p.partial + ((int64_t)split * p.rows + r) * p.cols + c;
-        if (fast_cols) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                f32x4 o = {v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
-                reinterpret_cast<f32x4 *>(dst)[q] = o;
-            }
-        } else {
-            // constant indices only: a run-time index would move v out of the registers
-#pragma unroll
-            for (int e = 0; e < 16; ++e)
-                if (c + e < p.cols) dst[e] = v[e];
-        }
-    } else if constexpr (EPI == EPI_RNE) {
+__device__ __forceinline__ void emit16(const GemmArgs &p, int64_t r, int64_t c, float v[16], StatsAcc &st) {
+    static_assert(EPI != EPI_PARTIAL, "see emit_partial4");
+    if constexpr (EPI == EPI_RNE) {
         // the host sends only row lengths that are multiples of 16 here
         uint32_t pk[4];
 #pragma unroll

@@ -103,22 +103,32 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs &p, const f32x16 (&
             update(band, EP_LD, st);
             break;
         }
+        if constexpr (EPI == EPI_PARTIAL) {
+            constexpr int F4 = WTN / 4;
+#pragma unroll 4
+            for (int item = lane; item < BANDS * 32 * F4; item += 64) {
+                const int br = item / F4, q = item - br * F4;
+                emit_partial4(p, split, row0 + wm * WTM + 32 * h + br, col0 + wn * WTN + 4 * q,
+                              *reinterpret_cast<const f32x4 *>(band + br * EP_LD + 4 * q));
+            }
+        } else {
 #pragma unroll 1
-        for (int item = lane; item < BANDS * 32 * CG; item += 64) {
-            const int br = item / CG, cg = item - br * CG;
-            const int64_t r = row0 + wm * WTM + 32 * h + br;
-            const int64_t c = col0 + wn * WTN + 16 * cg;
-            if (r < p.rows && c < p.cols) {
-                float v[16];
-                const f32x4 *src = reinterpret_cast<const f32x4 *>(band + br * EP_LD + 16 * cg);
+            for (int item = lane; item < BANDS * 32 * CG; item += 64) {
+                const int br = item / CG, cg = item - br * CG;
+                const int64_t r = row0 + wm * WTM + 32 * h + br;
+                const int64_t c = col0 + wn * WTN + 16 * cg;
+                if (r < p.rows && c < p.cols) {
+                    float v[16];
+                    const f32x4 *src = reinterpret_cast<const f32x4 *>(band + br * EP_LD + 16 * cg);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    f32x4 x = src[q];
-                    v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
+                    for (int q = 0; q < 4; ++q) {
+                        f32x4 x = src[q];
+                        v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
+                    }
+                    if (HALF && EPI == EPI_FULL && !fast_cols)
+                        finish16_ragged(p.ep, r, c, p.cols - c < 16 ? (int)(p.cols - c) : 16, v, st);
+                    else emit16<EPI>(p, r, c, v, st);
                 }
-                if (HALF && EPI == EPI_FULL && !fast_cols)
-                    finish16_ragged(p.ep, r, c, p.cols - c < 16 ? (int)(p.cols - c) : 16, v, st);
-                else emit16<EPI>(p, split, r, c, v, st, fast_cols);
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

@@ -284,7 +284,6 @@ __global__ __launch_bounds__(4 * BM + 256, BM == 64 ? 2 : 1) void gemm_qfwd_kern
 
         // acc[i][j][4g + e]: row (BM/2) wr + 32 i + lane%32, column 64 wc + 32 j + 8g + 4 (lane/32) + e;
         // one exchange between the wave's halves leaves lane (row, h) with columns 16h .. 16h+15
-        const bool fast_cols = (p.cols & 15) == 0;
 #pragma unroll
         for (int i = 0; i < RB; ++i) {
             const int64_t r = row0 + (BM / 2) * wr + 32 * i + frow;
@@ -301,7 +300,7 @@ __global__ __launch_bounds__(4 * BM + 256, BM == 64 ? 2 : 1) void gemm_qfwd_kern
                         vv[8 * g + 4 + e] = u2f(sw[1]);
                     }
                 const int64_t c = col0 + 64 * wc + 32 * j + 16 * fkb;
-                if (r < p.rows && c < p.cols) emit16<EPI>(p, 0, r, c, vv, st, fast_cols);
+                if (r < p.rows && c < p.cols) emit16<EPI>(p, r, c, vv, st);
             }
         }
     }

@@ -137,26 +137,52 @@ __global__ __launch_bounds__(256, EPI == EPI_FULL ? 4 : 5) void gemm_shortk_kern
         }
         return;
     }
-    StatsAcc stt;
-    const bool fast_cols = (p.cols & 15) == 0;
+    if constexpr (EPI == EPI_PARTIAL) {
+        // the FP32 tile through the same 4 KB, 32 columns at a time: a row is eight pieces of four columns, piece q of row rr
+        // in slot q ^ (rr & 7)
+        float *mine = reinterpret_cast<float *>(lds_dyn + 32 * wave * BK);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        float v[16];
+        for (int j = 0; j < 4; ++j) {
 #pragma unroll
-        for (int g = 0; g < 2; ++g)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                // lower half keeps its own columns 8g+e and receives the upper half's 8g+4+e;
-                // the upper half receives the lower half's 8(g+2)+e and keeps its 8(g+2)+4+e
-                const auto sw = __builtin_amdgcn_permlane32_swap(f2u(acc[j][4 * g + e]),
-                                                                 f2u(acc[j][4 * (g + 2) + e]), false, false);
-                v[8 * g + e] = u2f(sw[0]);
-                v[8 * g + 4 + e] = u2f(sw[1]);
+            for (int g = 0; g < 4; ++g) {
+                const f32x4 o = {acc[j][4 * g], acc[j][4 * g + 1], acc[j][4 * g + 2], acc[j][4 * g + 3]};
+                *reinterpret_cast<f32x4 *>(mine + frow * 32 + 4 * ((2 * g + fkb) ^ (frow & 7))) = o;
             }
-        const int64_t c = col0 + 32 * j + 16 * fkb;
-        if (r < p.rows && c < p.cols) emit16<EPI>(p, 0, r, c, v, stt, fast_cols);
+            // (private to this wave: order its writes before its reads, and these before the next columns' writes)
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int rr = 8 * k + (lane >> 3), q = lane & 7;
+                emit_partial4(p, 0, row0 + 32 * wave + rr, col0 + 32 * j + 4 * q,
+                              *reinterpret_cast<const f32x4 *>(mine + rr * 32 + 4 * (q ^ (rr & 7))));
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+        return;
     }
+    StatsAcc stt;
     if constexpr (EPI == EPI_FULL) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            float v[16];
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    // lower half keeps its own columns 8g+e and receives the upper half's 8g+4+e;
+                    // the upper half receives the lower half's 8(g+2)+e and keeps its 8(g+2)+4+e
+                    const auto sw = __builtin_amdgcn_permlane32_swap(f2u(acc[j][4 * g + e]),
+                                                                     f2u(acc[j][4 * (g + 2) + e]), false, false);
+                    v[8 * g + e] = u2f(sw[0]);
+                    v[8 * g + 4 + e] = u2f(sw[1]);
+                }
+            const int64_t c = col0 + 32 * j + 16 * fkb;
+            if (r < p.rows && c < p.cols) emit16<EPI>(p, r, c, v, stt);
+        }
         if (p.ep.stats != nullptr) stt.flush(p.ep.stats);
     }
 }

@@ -179,7 +179,6 @@ __global__ __launch_bounds__(256, 1) void gemm_wave128_kernel(const GemmArgs p) 
     // column 32j + 8g + 4*(lane/32) + e of this wave's tile.
     float *red = reinterpret_cast<float *>(lds);
     StatsAcc st;
-    const bool fast_cols = (p.cols & 15) == 0;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         __syncthreads();  // every wave is done with its buffer / the previous half has been read
@@ -194,24 +193,39 @@ __global__ __launch_bounds__(256, 1) void gemm_wave128_kernel(const GemmArgs p) 
                     *reinterpret_cast<f32x4 *>(red + (wave * 64 + 32 * ii + frow) * RED_LD + 32 * j + 8 * g + 4 * fkb) = o;
                 }
         __syncthreads();
+        if constexpr (EPI == EPI_PARTIAL) {
 #pragma unroll
-        for (int it = 0; it < 2; ++it) {
-            const int item = threadIdx.x + 256 * it;  // 64 rows x 8 groups of sixteen columns
-            const int rr = item >> 3, cg = item & 7;
-            const int64_t r = row0 + 64 * h + rr, c = col0 + 16 * cg;
-            float v[16];
+            for (int it = 0; it < 8; ++it) {
+                const int item = threadIdx.x + 256 * it, rr = item >> 5, q = item & 31;  // 64 rows x 32 groups of four columns
+                f32x4 t = {};
 #pragma unroll
-            for (int w = 0; w < 4; ++w)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const f32x4 x = *reinterpret_cast<const f32x4 *>(red + (w * 64 + rr) * RED_LD + 16 * cg + 4 * q);
-                    if (w == 0) {
-                        v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
-                    } else {
-                        v[4 * q] += x.x; v[4 * q + 1] += x.y; v[4 * q + 2] += x.z; v[4 * q + 3] += x.w;
-                    }
+                for (int w = 0; w < 4; ++w) {
+                    const f32x4 x = *reinterpret_cast<const f32x4 *>(red + (w * 64 + rr) * RED_LD + 4 * q);
+                    if (w == 0) t = x;
+                    else { t.x += x.x; t.y += x.y; t.z += x.z; t.w += x.w; }
                 }
-            if (r < p.rows && c < p.cols) emit16<EPI>(p, split, r, c, v, st, fast_cols);
+                emit_partial4(p, split, row0 + 64 * h + rr, col0 + 4 * q, t);
+            }
+        } else {
+#pragma unroll
+            for (int it = 0; it < 2; ++it) {
+                const int item = threadIdx.x + 256 * it;  // 64 rows x 8 groups of sixteen columns
+                const int rr = item >> 3, cg = item & 7;
+                const int64_t r = row0 + 64 * h + rr, c = col0 + 16 * cg;
+                float v[16];
+#pragma unroll
+                for (int w = 0; w < 4; ++w)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x4 x = *reinterpret_cast<const f32x4 *>(red + (w * 64 + rr) * RED_LD + 16 * cg + 4 * q);
+                        if (w == 0) {
+                            v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
+                        } else {
+                            v[4 * q] += x.x; v[4 * q + 1] += x.y; v[4 * q + 2] += x.z; v[4 * q + 3] += x.w;
+                        }
+                    }
+                if (r < p.rows && c < p.cols) emit16<EPI>(p, r, c, v, st);
+            }
         }
     }
     if constexpr (EPI == EPI_FULL) {

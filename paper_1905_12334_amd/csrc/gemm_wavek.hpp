@@ -205,6 +205,20 @@ __device__ __forceinline__ void gemm_wavek(const GemmArgs &p, const UpdateHook &
             v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
         };
         update_groups<STATES, 4>(p.ep, upd, updating, group, sum, st, uo, words);
+    } else if constexpr (EPI == EPI_PARTIAL) {
+        constexpr int F4 = BN / 4;
+#pragma unroll
+        for (int k = 0; k < BM * F4 / 256; ++k) {
+            const int item = threadIdx.x + 256 * k, rr = item / F4, q = item % F4;
+            f32x4 t = {};
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const f32x4 x = *reinterpret_cast<const f32x4 *>(red + (w * BM + rr) * RED_LD + 4 * q);
+                if (w == 0) t = x;
+                else { t.x += x.x; t.y += x.y; t.z += x.z; t.w += x.w; }
+            }
+            emit_partial4(p, split, row0 + rr, col0 + 4 * q, t);
+        }
     } else if (BM * BN == 64 * 64 || threadIdx.x < BM * BN / 16) {  // whole waves either way
         constexpr int CG = BN / 16;
         const int rr = threadIdx.x / CG, cg = threadIdx.x % CG;
@@ -224,7 +238,7 @@ __device__ __forceinline__ void gemm_wavek(const GemmArgs &p, const UpdateHook &
         if (r < p.rows && c < p.cols) {
             if (HALF && EPI == EPI_FULL && (p.cols & 15) != 0)
                 finish16_ragged(p.ep, r, c, p.cols - c < 16 ? (int)(p.cols - c) : 16, v, st);
-            else emit16<EPI>(p, split, r, c, v, st, (p.cols & 15) == 0);
+            else emit16<EPI>(p, r, c, v, st);
         }
     }
     if constexpr (EPI >= EPI_FULL) {
