@@ -416,21 +416,38 @@ extern "C" size_t mp8_gemm_fp8_workspace_bytes(mp8_op op, int64_t M, int64_t N, 
 
 namespace mp8 {
 
+// Outputs from which a transposed copy is a pass of its own (see transpose_codes_kernel).  Below, the epilogues store it:
+// neighbouring lanes hold neighbouring rows, and the caches put the bytes together (contraction 1024: 1024 x 1024 6.2 us,
+// by a pass 7.9; 2048 x 2048 11.8 and 12.3; 4096 x 4096 35.6 and 28.2).
+constexpr int64_t kTransposeFrom = 1 << 23;
+
 // Launch the MFMA kernel chosen by `pick` (indexed by EPI_*) for plan `pl`, and the finishing
 // kernel when the epilogue cannot be fused.  `ga` carries the operands; its tiling, slicing and
 // epilogue fields are filled in here.
-static mp8_status launch_mfma(GemmArgs ga, const Epilogue &ep, const Plan &pl, int64_t kc,
+static mp8_status launch_mfma(GemmArgs ga, Epilogue ep, const Plan &pl, int64_t kc,
                               void (*const pick[3])(const GemmArgs), void *workspace,
                               size_t workspace_bytes, hipStream_t s, const UpdateHook *upd = nullptr,
                               bool validate_only = false, UpdateKernel with_update = nullptr) {
     const int64_t rows = ep.rows, cols = ep.cols;
     const int acc_mode = ep.acc_mode;
     float *acc = ep.acc;
-    uint8_t *out8 = ep.out8, *out8_t = ep.out8_t;
-    // Fused epilogue or two passes?  (The master-weight update lives in the finishing pass or in an
-    // update kernel; the epilogues of gemm_any_kernel and the half-precision forms do everything else.)
+    uint8_t *out8 = ep.out8;
+    auto has_workspace = [&] {
+        return workspace != nullptr && workspace_bytes >= (size_t)pl.splits * (size_t)rows * (size_t)cols * sizeof(float);
+    };
+    // (the 8-bit kernels have always asked for a workspace with these outputs)
+    if (pl.mfma && !pl.half && (acc_mode == 2 || (ep.out8_t != nullptr && !(acc_mode == 1 && pl.splits == 1))) && !has_workspace())
+        return MP8_ERR_WORKSPACE;
+    // Fused epilogue or two passes?  An FP32 result alone is the tiles as the kernels write them; with codes the epilogues
+    // do both.  (The master-weight update lives in the finishing pass or in an update kernel; the epilogues
+    // of gemm_any_kernel and the half-precision forms take any row length.)
+    const bool acc_alone = acc_mode == 1 && out8 == nullptr && ep.out8_t == nullptr && ep.stats == nullptr;
     const bool two_pass = (pl.splits > 1 && !pl.in_turn) || (upd != nullptr && with_update == nullptr) ||
-                          (pl.mfma && !pl.half && ((cols & 15) != 0 || acc_mode != 0 || out8_t != nullptr));
+                          (pl.mfma && !pl.half && ((cols & 15) != 0 || acc_alone));
+    // The transposed copy of large results, and of those a finishing pass rounds, is made from the codes (if they are kept).
+    uint8_t *const copy_t = out8 != nullptr && cols >= 4 && (two_pass || rows * cols >= kTransposeFrom) ? ep.out8_t : nullptr;
+    if (copy_t != nullptr) ep.out8_t = nullptr;
+    uint8_t *const out8_t = ep.out8_t;
     float *partial = nullptr;
     Epilogue fin = ep;  // what the finishing kernel applies
     fin.want_codes = upd != nullptr;
@@ -440,8 +457,7 @@ static mp8_status launch_mfma(GemmArgs ga, const Epilogue &ep, const Plan &pl, i
             fin.acc = nullptr;
             fin.acc_mode = 0;
         } else {
-            const size_t need = (size_t)pl.splits * (size_t)rows * (size_t)cols * sizeof(float);
-            if (workspace == nullptr || workspace_bytes < need) return MP8_ERR_WORKSPACE;
+            if (!has_workspace()) return MP8_ERR_WORKSPACE;
             partial = (float *)workspace;
         }
     }
@@ -488,6 +504,12 @@ static mp8_status launch_mfma(GemmArgs ga, const Epilogue &ep, const Plan &pl, i
                                upd ? *upd : UpdateHook{});
             if (hipGetLastError() != hipSuccess) return MP8_ERR_HIP;
         }
+    }
+    if (copy_t != nullptr) {
+        const int64_t tiles = (rows + 127) / 128 * ((cols + 127) / 128);
+        hipLaunchKernelGGL(((rows | cols) & 15) == 0 ? transpose_codes_kernel<true> : transpose_codes_kernel<false>,
+                           dim3((unsigned)std::min<int64_t>(tiles, 1 << 20)), dim3(256), 0, s, out8, copy_t, rows, cols);
+        if (hipGetLastError() != hipSuccess) return MP8_ERR_HIP;
     }
     return MP8_OK;
 }

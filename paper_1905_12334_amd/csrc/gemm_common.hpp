@@ -143,10 +143,11 @@ __device__ __forceinline__ uint32_t finish1(const Epilogue &ep, int64_t r, int64
 // whose row length is a multiple of 16: 16-byte accesses, two Philox blocks, hardware
 // conversions.  Written to stay small: the rounding mode is a run-time flag and the rare
 // conversions are out of line.
+// (acc_done: v has been through ep.acc already)
 __device__ __forceinline__ void finish16(const Epilogue &ep, int64_t r, int64_t c, float v[16],
-                                         StatsAcc &st) {
+                                         StatsAcc &st, bool acc_done = false) {
     const int64_t i0 = r * ep.cols + c;
-    if (ep.acc_mode != 0) {
+    if (ep.acc_mode != 0 && !acc_done) {
         f32x4 *p = reinterpret_cast<f32x4 *>(ep.acc + i0);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -310,7 +311,7 @@ __device__ __forceinline__ void emit_partial4(const GemmArgs &p, int split, int6
 // What a tile kernel does with sixteen consecutive columns c .. c+15 (c % 16 == 0) of output row
 // r, per epilogue variant (described at the main kernel): the RNE-only conversion, or the complete epilogue.
 template <int EPI>
-__device__ __forceinline__ void emit16(const GemmArgs &p, int64_t r, int64_t c, float v[16], StatsAcc &st) {
+__device__ __forceinline__ void emit16(const GemmArgs &p, int64_t r, int64_t c, float v[16], StatsAcc &st, bool acc_done = false) {
     static_assert(EPI != EPI_PARTIAL, "see emit_partial4");
     if constexpr (EPI == EPI_RNE) {
         // the host sends only row lengths that are multiples of 16 here
@@ -325,7 +326,7 @@ __device__ __forceinline__ void emit16(const GemmArgs &p, int64_t r, int64_t c, 
         u32x4 o = {pk[0], pk[1], pk[2], pk[3]};
         *reinterpret_cast<u32x4 *>(p.ep.out8 + r * p.cols + c) = o;
     } else {
-        finish16(p.ep, r, c, v, st);
+        finish16(p.ep, r, c, v, st, acc_done);
     }
 }
 

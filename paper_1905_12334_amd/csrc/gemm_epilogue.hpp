@@ -112,6 +112,30 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs &p, const f32x16 (&
                               *reinterpret_cast<const f32x4 *>(band + br * EP_LD + 4 * q));
             }
         } else {
+            // The FP32 result leaves as the partial tiles do, neighbouring lanes side by side; the sums stay in the band.
+            const bool acc_done = EPI == EPI_FULL && p.ep.acc_mode != 0 && fast_cols;
+            if (acc_done) {
+                constexpr int F4 = WTN / 4;
+#pragma unroll 4
+                for (int item = lane; item < BANDS * 32 * F4; item += 64) {
+                    const int br = item / F4, q = item - br * F4;
+                    const int64_t r = row0 + wm * WTM + 32 * h + br, c = col0 + wn * WTN + 4 * q;
+                    if (r < p.rows && c < p.cols) {
+                        f32x4 *at = reinterpret_cast<f32x4 *>(band + br * EP_LD + 4 * q);
+                        f32x4 *to = reinterpret_cast<f32x4 *>(p.ep.acc + r * p.cols + c);
+                        f32x4 x = *at;
+                        if (p.ep.acc_mode == 2) {
+                            const f32x4 o = *to;
+                            x.x += o.x; x.y += o.y; x.z += o.z; x.w += o.w;
+                            *at = x;
+                        }
+                        *to = x;
+                    }
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
 #pragma unroll 1
             for (int item = lane; item < BANDS * 32 * CG; item += 64) {
                 const int br = item / CG, cg = item - br * CG;
@@ -127,7 +151,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs &p, const f32x16 (&
                     }
                     if (HALF && EPI == EPI_FULL && !fast_cols)
                         finish16_ragged(p.ep, r, c, p.cols - c < 16 ? (int)(p.cols - c) : 16, v, st);
-                    else emit16<EPI>(p, r, c, v, st);
+                    else emit16<EPI>(p, r, c, v, st, acc_done);
                 }
             }
         }

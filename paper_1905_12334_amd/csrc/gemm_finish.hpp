@@ -270,6 +270,75 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float *__restr
     if (ep.stats != nullptr) st.flush(ep.stats);
 }
 
+// The transposed copy of finished codes: dst [cols, rows] from src [rows, cols].  A pass of its own over 2 bytes per
+// element: a finishing pass would store it byte by byte, its lanes lying along the rows of src, each into a line of its
+// own (4096 x 4096 x 2048 with it 124 us, now 37).  Tiles of 128 x 128 through LDS; 16-byte pieces, eight lanes to a line, where both
+// counts are multiples of 16 (WHOLE), else pieces of any alignment and length (at least four columns).
+template <bool WHOLE>
+__global__ __launch_bounds__(256) void transpose_codes_kernel(const uint8_t *__restrict__ src, uint8_t *__restrict__ dst,
+                                                              int64_t rows, int64_t cols) {
+    constexpr int T = 128, P = T / 4 + 1;  // LDS row pitch in dwords
+    __shared__ uint32_t tile[T * P];
+    const int64_t tiles_c = (cols + T - 1) / T, ntiles = ((rows + T - 1) / T) * tiles_c;
+    const int tid = threadIdx.x, k = tid & 7, cg = tid >> 3;
+    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        const int64_t r0 = t / tiles_c * T, c0 = t % tiles_c * T;
+        if constexpr (WHOLE) {
+            u32x4 x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int64_t r = r0 + 32 * i + cg, c = c0 + 16 * k;
+                x[i] = r < rows && c < cols ? *reinterpret_cast<const u32x4 *>(src + r * cols + c) : u32x4{0, 0, 0, 0};
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) tile[(32 * i + cg) * P + 4 * k + e] = x[i][e];
+        } else {
+            // (rows and pieces beyond the matrix are read from its last ones: at least four columns)
+            const int g = tid & 31;
+            const int64_t c = c0 + 4 * g, cl = c + 4 <= cols ? c : cols - 4;
+            const int shift = c - cl < 4 ? 8 * (int)(c - cl) : 0;
+            uint32_t x[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int64_t r = r0 + 8 * i + (tid >> 5);
+                __builtin_memcpy(&x[i], src + (r < rows ? r : rows - 1) * cols + cl, 4);
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) tile[(8 * i + (tid >> 5)) * P + g] = x[i] >> shift;
+        }
+        __syncthreads();
+        uint32_t colw[4][4];  // [column][row block of 4]
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            uint32_t rr[4], cc[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) rr[j] = tile[(16 * k + 4 * b + j) * P + cg];
+            transpose4x4(rr, cc);
+#pragma unroll
+            for (int col = 0; col < 4; ++col) colw[col][b] = cc[col];
+        }
+        const int64_t orow = r0 + 16 * k;
+#pragma unroll
+        for (int col = 0; col < 4; ++col) {
+            const int64_t oc = c0 + 4 * cg + col;
+            if (orow < rows && oc < cols) {
+                uint8_t *to = dst + oc * rows + orow;
+                const u32x4 o = {colw[col][0], colw[col][1], colw[col][2], colw[col][3]};
+                if (WHOLE) *reinterpret_cast<u32x4 *>(to) = o;
+                else if (orow + 16 <= rows) __builtin_memcpy(to, &o, 16);
+                else {
+#pragma unroll
+                    for (int e = 0; e < 15; ++e)
+                        if (orow + e < rows) to[e] = (uint8_t)(colw[col][e >> 2] >> (8 * (e & 3)));
+                }
+            }
+        }
+        __syncthreads();  // the next tile overwrites this one
+    }
+}
+
 // Any-shape fallback: one thread per output element, operands decoded one by one, FP32 fused
 // multiply-adds in contraction order.  Used for what gemm_any_kernel cannot take: contractions shorter
 // than 16, contraction-major operands with fewer than 16 rows or columns, enormous leading dimensions.

@@ -238,20 +238,6 @@ __global__ __launch_bounds__(256) void quantize_batch_kernel(const BatchArgs b) 
 #undef MP8_B
 }
 
-// Transpose a 4x4 byte block held as four row dwords into four column dwords
-// (byte k of row j becomes byte j of column k).  v_perm_b32 picks bytes 0-3 from its second
-// operand and 4-7 from its first.
-__device__ __forceinline__ void transpose4x4(const uint32_t r[4], uint32_t c[4]) {
-    const uint32_t t0 = __builtin_amdgcn_perm(r[1], r[0], 0x05010400u);  // r0.0 r1.0 r0.1 r1.1
-    const uint32_t t1 = __builtin_amdgcn_perm(r[3], r[2], 0x05010400u);  // r2.0 r3.0 r2.1 r3.1
-    const uint32_t t2 = __builtin_amdgcn_perm(r[1], r[0], 0x07030602u);  // r0.2 r1.2 r0.3 r1.3
-    const uint32_t t3 = __builtin_amdgcn_perm(r[3], r[2], 0x07030602u);  // r2.2 r3.2 r2.3 r3.3
-    c[0] = __builtin_amdgcn_perm(t1, t0, 0x05040100u);
-    c[1] = __builtin_amdgcn_perm(t1, t0, 0x07060302u);
-    c[2] = __builtin_amdgcn_perm(t3, t2, 0x05040100u);
-    c[3] = __builtin_amdgcn_perm(t3, t2, 0x07060302u);
-}
-
 constexpr int kTile = 128;
 constexpr int kPitch = kTile / 4 + 1;  // LDS row pitch in dwords
 
