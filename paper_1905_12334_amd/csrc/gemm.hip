@@ -345,6 +345,21 @@ static UpdateKernel update_kernel(const Plan &pl, int64_t cols, int layout, int 
     return nullptr;
 }
 
+// The same for gemm_any_kernel, contraction-major operands.  Two launches against one, SGD / momentum / ADAM, us:
+//     12 tiles (65 x 200 x 130)      8.7  9.0 10.0    9.3  9.6 10.0: the kernel's chain of latencies has nothing beside it
+//     32       (300 x 104 x 1001)    8.9  9.3 10.2    8.6  8.8 10.2
+//    256       (1000 x 1000 x 1000) 12.6 12.8 14.5   12.0 12.5 14.9: with ADAM, one wave per SIMD divides and takes roots
+//    512       (256 x 1000 x 2048)  12.6 13.7 16.1   11.6 12.6 15.6
+//   1024       (700 x 2008 x 2001)  27.3 30.9 37.6   26.9 28.1 34.0
+//   4032       (200 x 4088 x 4001)  61.2 80.1 101.6  65.0 69.4 90.1: SGD has the least to read, and streams faster by itself
+static UpdateKernel any_update_kernel(const Plan &pl, int64_t cols, int layout, int states) {
+    static const UpdateKernel kernels[3] = {gemm_any_update_kernel<0>, gemm_any_update_kernel<1>, gemm_any_update_kernel<2>};
+    const int64_t nt = (int64_t)pl.tiles_m * pl.tiles_n;
+    if (pl.splits != 1 || layout != 3 || (cols & 7) != 0) return nullptr;
+    if (nt < (states == 2 ? 2 * kCUs : 32) || (states == 0 && nt > 4 * kCUs)) return nullptr;
+    return kernels[states];
+}
+
 // Upper bound of the workspace: one FP32 tile set per contraction slice.  (The MFMA kernel
 // finishes its tiles itself only for an unsplit contraction, a row length that is a multiple
 // of 16 and no FP32 / transposed output; otherwise it writes FP32 tiles and the finishing
@@ -577,8 +592,9 @@ static mp8_status gemm_impl(mp8_op op, int64_t M, int64_t N, int64_t K, const ui
         pl = any_plan(rows, cols, kc);
         // it never needs a workspace: without one a split contraction takes its slices in turn
         pl.in_turn = pl.splits == 1 || !has_workspace(pl.splits);
-        // (the update goes with the finishing pass only: otherwise two launches)
-        if (upd != nullptr && pl.in_turn) return MP8_ERR_UNSUPPORTED;
+        // (the update goes with the finishing pass or an unsplit call's epilogue: otherwise two launches)
+        const UpdateKernel with_update = upd != nullptr && out8 != nullptr ? any_update_kernel(pl, cols, layout, upd->states) : nullptr;
+        if (upd != nullptr && pl.in_turn && with_update == nullptr) return MP8_ERR_UNSUPPORTED;
         GemmArgs ga{};
         ga.a = a;
         ga.b = b;
@@ -586,7 +602,7 @@ static mp8_status gemm_impl(mp8_op op, int64_t M, int64_t N, int64_t K, const ui
         ga.ldb = ldb;
         void (*const *kern)(const GemmArgs) = kAny[atn ? 2 : btn ? 1 : 0];
         void (*const pick[3])(const GemmArgs) = {kern[0], nullptr, kern[pl.splits > 1 ? 2 : 1]};
-        return launch_mfma(ga, ep, pl, kc, pick, workspace, workspace_bytes, s, upd, validate_only);
+        return launch_mfma(ga, ep, pl, kc, pick, workspace, workspace_bytes, s, upd, validate_only, with_update);
     }
     if (!pl.mfma || kc == 0) {
         if (upd != nullptr) return MP8_ERR_UNSUPPORTED;
@@ -694,9 +710,8 @@ namespace mp8 {
 // body the three optimizer variants share.  `hook` is the rule as the finishing pass applies it,
 // `update_from(codes)` launches the same rule's stand-alone kernel on codes in memory.  Three ways,
 // all with the same results: the update inside the finishing pass of a split contraction, or inside the
-// GEMM's own epilogue (small unsplit outputs, see update_kernel), or the GEMM followed by the
-// update kernel (larger ones, unaligned operands, and a skip flag that lives inside `stats` -- see
-// flag_inside_stats).  Whatever
+// GEMM's own epilogue (unsplit outputs, see update_kernel and any_update_kernel), or the GEMM followed by the
+// update kernel (larger ones, and a skip flag that lives inside `stats` -- see flag_inside_stats).  Whatever
 // can be checked is checked before the first launch.
 template <class UpdateFrom>
 static mp8_status wgrad_with_update(int64_t M, int64_t N, int64_t K, const uint8_t *a, int64_t lda,

@@ -4,6 +4,7 @@
 #pragma once
 
 #include "gemm_common.hpp"
+#include "gemm_finish.hpp"
 
 namespace mp8 {
 
@@ -23,14 +24,20 @@ namespace mp8 {
 // the slices of its tile one after the other (SLICES) and adds them up in the same order.
 //
 // What bounds it: a 64x64 tile pulls 128 bytes per clock and CU at the 8-bit matrix rate and 64 at the
-// half-precision one, which is what the path from L2 carries; unaligned rows cost more requests.  A layer of
+// half-precision one, which is what the path from L2 carries; unaligned rows cost more requests: a CU needs about
+// 0.4 us per 16 KB stage however many tiles or waves there are (eight waves per tile: 256 x 1001, contraction 2003,
+// row-major 12.1 us instead of 11.1, both contraction-major 10.5 instead of 10.7).  A layer of
 // 256 x 1000 x 2048, back to back: forward 10.4 us, backward data 7.1, weight gradient 7.2 (one thread per output
 // element 639 each).
+// EPI_UPDATE: an unsplit weight gradient applies the master-weight update itself (columns a multiple of eight:
+// neighbouring lanes share random blocks), with the code of the other kernels' epilogues: no launch and no pass
+// over the gradient codes.  256 x 1000 x 2048 with momentum 13.7 -> 12.6 us, its training step 40.0 -> 37.2.
 // Needs a contraction of at least 16, and 16 rows / columns of a contraction-major operand (an edge
 // chunk is read as the last 16 bytes of its row and shifted into place).
 template <int EPI, bool ATN, bool BTN, bool SLICES>
-__device__ __forceinline__ void gemm_any(const GemmArgs &p) {
-    static_assert(EPI != EPI_PARTIAL || !SLICES, "FP32 tiles are written slice by slice");
+__device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &upd) {
+    constexpr int STATES = EPI >= EPI_UPDATE ? EPI - EPI_UPDATE : 0;
+    static_assert(EPI == EPI_FULL || !SLICES, "only a plain call takes its slices in turn");
     static_assert(BTN || !ATN, "a alone contraction-major is not built");
     constexpr int T = 64, SLAB = T * BK, WAVE_LDS = 2 * SLAB;
     constexpr int RED_LD = T + 4;  // floats per row of a tile parked for the reduction
@@ -186,6 +193,21 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p) {
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
 
+        // what this thread updates: four groups of four weights, 16 lanes side by side in a row of the tile
+        auto group = [&](int q) {
+            const int item = threadIdx.x + 256 * q;
+            const int64_t r = row0 + (item >> 4), c = col0 + 4 * (item & 15);
+            return GroupAt{r, c, r < p.rows && c < p.cols};
+        };
+        UpdateOperands4 uo[4];
+        GroupWords<4> words;
+        bool updating = false;
+        if constexpr (EPI >= EPI_UPDATE) {  // (not earlier: the next stage's 64 registers are free now)
+            load_groups<STATES, 4>(p.ep, upd, group, uo);
+            updating = !(upd.skip != nullptr && *upd.skip != 0u);
+            draw_groups<4>(p.ep, upd, group, words);
+        }
+
         // The four tiles meet in LDS: acc[i][j][4g + e] is row 32i + lane%32, column
         // 32j + 8g + 4*(lane/32) + e of this wave's tile; each thread then sums sixteen columns of a row.
         const int frow = lane & 31, fkb = lane >> 5;
@@ -210,7 +232,17 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p) {
             }
             return sum;
         };
-        if constexpr (EPI == EPI_PARTIAL) {
+        if constexpr (EPI >= EPI_UPDATE) {
+            StatsAcc st;
+            auto sum = [&](int q, float out[4]) {
+                const int item = threadIdx.x + 256 * q;
+                const f32x4 t = summed(item >> 4, 4 * (item & 15));
+                out[0] = t.x; out[1] = t.y; out[2] = t.z; out[3] = t.w;
+            };
+            update_groups<STATES, 4>(p.ep, upd, updating, group, sum, st, uo, words);
+            if (p.ep.stats != nullptr) st.flush(p.ep.stats);
+            return;
+        } else if constexpr (EPI == EPI_PARTIAL) {
 #pragma unroll
             for (int k = 0; k < T * T / 1024; ++k) {
                 const int item = threadIdx.x + 256 * k, rr = item >> 4, c4 = 4 * (item & 15);
@@ -243,7 +275,11 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p) {
 
 template <int EPI, bool ATN, bool BTN, bool SLICES = false>
 __global__ __launch_bounds__(256, SLICES ? 1 : 2) void gemm_any_kernel(const GemmArgs p) {
-    gemm_any<EPI, ATN, BTN, SLICES>(p);
+    gemm_any<EPI, ATN, BTN, SLICES>(p, UpdateHook{});
+}
+template <int STATES>
+__global__ __launch_bounds__(256, 2) void gemm_any_update_kernel(const GemmArgs p, const UpdateHook upd) {
+    gemm_any<EPI_UPDATE + STATES, true, true, false>(p, upd);
 }
 
 }  // namespace mp8
