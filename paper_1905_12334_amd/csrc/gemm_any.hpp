@@ -24,10 +24,11 @@ namespace mp8 {
 // the slices of its tile one after the other (SLICES) and adds them up in the same order.
 //
 // What bounds it: a 64x64 tile pulls 128 bytes per clock and CU at the 8-bit matrix rate and 64 at the
-// half-precision one, which is what the path from L2 carries; unaligned rows cost more requests: a CU needs about
+// half-precision one, which is what the path from L2 carries; unaligned rows cost more requests.  A CU needs about
 // 0.4 us per 16 KB stage however many tiles or waves there are (eight waves per tile: 256 x 1001, contraction 2003,
-// row-major 12.1 us instead of 11.1, both contraction-major 10.5 instead of 10.7).  A layer of
-// 256 x 1000 x 2048, back to back: forward 10.4 us, backward data 7.1, weight gradient 7.2 (one thread per output
+// row-major 12.1 us instead of 11.1, both contraction-major 10.5 instead of 10.7; two 8-byte loads for one of 16
+// 10.7 instead of 10.2 at 256 x 1000, contraction 2048).  A layer of
+// 256 x 1000 x 2048, back to back: forward 10.2 us, backward data 7.1, weight gradient 7.2 (one thread per output
 // element 639 each).
 // EPI_UPDATE: an unsplit weight gradient applies the master-weight update itself (columns a multiple of eight:
 // neighbouring lanes share random blocks), with the code of the other kernels' epilogues: no launch and no pass
