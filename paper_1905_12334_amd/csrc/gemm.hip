@@ -361,9 +361,8 @@ static UpdateKernel any_update_kernel(const Plan &pl, int64_t cols, int layout, 
 }
 
 // Upper bound of the workspace: one FP32 tile set per contraction slice.  (The MFMA kernel
-// finishes its tiles itself only for an unsplit contraction, a row length that is a multiple
-// of 16 and no FP32 / transposed output; otherwise it writes FP32 tiles and the finishing
-// kernel takes over.)
+// finishes its tiles itself for an unsplit contraction with a row length that is a multiple
+// of 16; otherwise it writes FP32 tiles and the finishing kernel takes over.)
 static size_t plan_workspace(const Plan &pl, int64_t rows, int64_t cols) {
     if (!pl.mfma) return 0;
     return (size_t)pl.splits * (size_t)rows * (size_t)cols * sizeof(float);
