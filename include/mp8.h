@@ -346,7 +346,8 @@ mp8_status mp8_conv3x3_wgrad_update_fp16_sr(
  * output columns (N a multiple of 16, K a multiple of 128) the GEMM reads the activations only
  * once, and one kernel does both: it reads x, rounds it, writes x8_out (the weight gradient needs
  * it later) and multiplies from the codes it holds.  Small layers with more columns and a short
- * contraction (K up to 512) take it as well.  Every other shape runs as the two calls.
+ * contraction (K up to 512) take it as well where rounding the activations once per 128 columns costs less than a
+ * launch (rounding to nearest without saturation).  Every other call runs as the two calls.
  *   x          [M, K] FP32, dense, 16-byte aligned (device)
  *   x8_out     [M, K] 8-bit codes, dense, 16-byte aligned; always written
  *   w8         [K, N] 8-bit codes, row stride ldw >= N (the layout mp8_sgd_update_fp16_sr's

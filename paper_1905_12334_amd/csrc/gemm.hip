@@ -924,11 +924,30 @@ extern "C" mp8_status mp8_quantize_gemm_fwd_fp8(int64_t M, int64_t N, int64_t K,
     if (((uintptr_t)x | (uintptr_t)x8_out | (uintptr_t)acc | (uintptr_t)out8 | (uintptr_t)out8_t) & 15u)
         return MP8_ERR_ALIGNMENT;
     // Up to 128 columns the activations are read once.  More column tiles round them again each, which pays while it
-    // costs less than the launch it saves: short contractions with few tiles (256 x 256 x 256 4.8 us, two launches 5.4;
-    // 1024 x 1024 x 256 5.0 and 5.4; 4096 x 256 x 512 7.3 and 8.4; but 1024 x 2048 x 256 6.5 and 6.1, 256 x 256 x 1024 9.6 and 8.1,
-    // 64 x 1024 x 512 6.5 and 6.1).
+    // costs less than the launch it saves: few tiles, short contractions, and a rounding that is cheap to repeat (GPU time, us, two
+    // launches / one kernel):
+    //   nearest, codes only     1 x 1024 x 128 4.3 / 3.7, 1024 x 1024 x 128 5.0 / 4.1; 1 x 4096 x 256 4.55 / 4.7, 16 x 1024 x 256 5.0 / 4.65, 256 x 256 x
+    //                           256 5.2 / 4.8, 4096 x 256 x 256 5.6 / 5.0; 256 x 1024 x 512 6.2 / 6.1, 4096 x 256 x 512 7.2 / 6.5; 64 x 1024 x 512 6.1 / 6.5
+    //   stochastic x            1024 x 1024 x 128 5.15 / 6.3, 256 x 256 x 256 5.45 / 8.3, 1024 x 1024 x 512 6.8 / 13.3: never
+    //   saturated x             1024 x 1024 x 128 5.1 / 5.3, 256 x 256 x 256 5.3 / 7.1: never
+    //   statistics of x         64 x 1024 x 128 5.4 / 5.6, 1024 x 1024 x 128 6.9 / 6.1, 256 x 256 x 256 6.5 / 8.0, 1024 x 1024 x 256 8.9 / 8.2,
+    //                           4096 x 256 x 512 10.7 / 12.5 (statistics make the Q node slow, but only once)
+    //   complete epilogue       stochastic 64 x 1024 x 128 5.5 / 5.2, 256 x 256 x 256 6.1 / 6.1, 1024 x 1024 x 256 6.4 / 6.3, 1024 x 1024 x 512
+    //                           7.5 / 7.7, 4096 x 256 x 512 8.2 / 7.8; FP32 beside codes 1024 x 1024 x 512 8.0 / 8.0, 4096 x 256 x 512 8.7 / 8.3;
+    //                           transposed 1024 x 1024 x 128 6.2 / 5.8, 1024 x 1024 x 256 6.7 / 6.8, 4096 x 256 x 512 8.5 / 8.2; saturated
+    //                           64 x 1024 x 128 5.5 / 5.2, 4096 x 256 x 256 6.6 / 6.7; acc += 1024 x 1024 x 128 6.9 / 7.3: never; FP32 alone 1024 x 1024 x 128
+    //                           5.4 / 5.4, 1024 x 1024 x 256 5.9 / 6.3
     const int64_t ctiles = (N + 127) / 128;
-    const bool narrow = N <= 128, small = K <= (M >= 256 ? 4 : 2) * BK && M <= 64 * 128 && ctiles <= 128 && (M + 63) / 64 * ctiles <= 128;
+    const bool narrow = N <= 128;
+    const bool plain = acc_mode == 0 && out8_t == nullptr && round == MP8_RNE && !(flags & MP8_FLAG_SATURATE) && stats == nullptr &&
+                       out8 != nullptr;
+    const bool qplain = x_round == MP8_RNE && !(x_flags & MP8_FLAG_SATURATE) && x_stats == nullptr;
+    const bool few = K <= 4 * BK && M <= 64 * 128 && ctiles <= 128 && (M + 63) / 64 * ctiles <= 128 &&
+                     M >= (K <= BK ? 1 : K <= 2 * BK ? 16 : 256);
+    const bool cheap_x = qplain || (x_round == MP8_RNE && !(x_flags & MP8_FLAG_SATURATE) && M >= 1024 && K <= 2 * BK);
+    const bool cheap_out = plain || (acc_mode != 2 && (K <= BK || (out8 != nullptr && !(flags & MP8_FLAG_SATURATE) &&
+                                                                   M >= (out8_t != nullptr ? 8 : 4) * K)));
+    const bool small = few && cheap_x && cheap_out;
     const bool fused = N >= 16 && (narrow || small) && (N & 15) == 0 && K > 0 && (K & (BK - 1)) == 0 &&
                        ((uintptr_t)w8 & 15u) == 0 && (ldw & 15) == 0 && ldw < (1 << 24) &&
                        M <= (INT64_MAX / 8) / K && (M + 63) / 64 <= 0x7FFFFFFFLL;
@@ -982,9 +1001,6 @@ extern "C" mp8_status mp8_quantize_gemm_fwd_fp8(int64_t M, int64_t N, int64_t K,
     qa.seed = x_seed;
     qa.offset = x_offset;
     qa.stats = x_stats;
-    const bool plain = acc_mode == 0 && out8_t == nullptr && !ep.sr && !ep.sat && stats == nullptr &&
-                       out8 != nullptr;
-    const bool qplain = !qa.sr && !qa.sat && x_stats == nullptr;
     // 128 rows per workgroup once that still gives every other CU a workgroup
     const bool tall = narrow && (M + 127) / 128 >= 128;
     void (*kernel)(const GemmArgs, const QuantArgs);
