@@ -105,6 +105,14 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs &p, const f32x16 (&
         }
         if constexpr (EPI == EPI_PARTIAL) {
             constexpr int F4 = WTN / 4;
+            const int64_t c0 = col0 + wn * WTN, left = p.cols - c0;
+            if (2 * left <= WTN) {  // lanes side by side in as many rows as fit, not most of them beyond the matrix (64 x 3 x 256 5.3 -> 4.85 us)
+                const int lg = left <= 4 ? 0 : 32 - __builtin_clz((int)(left - 1) >> 2);
+                const int c = 4 * (lane & ((1 << lg) - 1));
+#pragma unroll 2
+                for (int br = lane >> lg; br < BANDS * 32; br += 64 >> lg)
+                    emit_partial4(p, split, row0 + wm * WTM + 32 * h + br, c0 + c, *reinterpret_cast<const f32x4 *>(band + br * EP_LD + c));
+            } else
 #pragma unroll 4
             for (int item = lane; item < BANDS * 32 * F4; item += 64) {
                 const int br = item / F4, q = item - br * F4;
@@ -113,7 +121,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs &p, const f32x16 (&
             }
         } else {
             // The FP32 result leaves as the partial tiles do, neighbouring lanes side by side; the sums stay in the band.
-            const bool acc_done = EPI == EPI_FULL && p.ep.acc_mode != 0 && fast_cols;
+            const bool acc_done = EPI == EPI_FULL && p.ep.acc_lines != 0;
             if (acc_done) {
                 constexpr int F4 = WTN / 4;
 #pragma unroll 4

@@ -152,6 +152,13 @@ __global__ __launch_bounds__(256, EPI == EPI_FULL ? 4 : 5) void gemm_shortk_kern
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            if (p.cols - col0 <= 16) {  // four lanes to a row, and no more columns (200000 x 3 x 256 22.5 -> 17.3 us)
+#pragma unroll
+                for (int rr = lane >> 2; rr < 32; rr += 16)
+                    emit_partial4(p, 0, row0 + 32 * wave + rr, col0 + 4 * (lane & 3),
+                                  *reinterpret_cast<const f32x4 *>(mine + rr * 32 + 4 * ((lane & 3) ^ (rr & 7))));
+                return;
+            }
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int rr = 8 * k + (lane >> 3), q = lane & 7;
