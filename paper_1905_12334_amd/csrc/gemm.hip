@@ -18,9 +18,9 @@
 //   gemm_epilogue.hpp  from a tile's accumulators to its outputs
 //   gemm_finish.hpp   second pass for split contractions and unfused epilogues, optionally with
 //                     the master-weight update; the any-shape fallback kernel
-// Split contraction, FP32 / transposed outputs, ragged column counts: the MFMA kernels write
-// FP32 tiles and the second pass sums the slices in order and applies the epilogue -- the sum
-// is rounded exactly once.
+// Split contraction, ragged column counts, FP32 results alone, and FP32 or transposed results of poorly filled tiles: the
+// MFMA kernels write FP32 tiles and the second pass sums the slices in order and applies the epilogue -- the sum is
+// rounded exactly once.  Everything else leaves in the kernels' own epilogues.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
@@ -430,10 +430,53 @@ extern "C" size_t mp8_gemm_fp8_workspace_bytes(mp8_op op, int64_t M, int64_t N, 
 
 namespace mp8 {
 
-// Outputs from which a transposed copy is a pass of its own (see transpose_codes_kernel).  Below, the epilogues store it:
-// neighbouring lanes hold neighbouring rows, and the caches put the bytes together (contraction 1024: 1024 x 1024 6.2 us,
-// by a pass 7.9; 2048 x 2048 11.8 and 12.3; 4096 x 4096 35.6 and 28.2).
+// Outputs from which a transposed copy can be a pass of its own (see copied_from_codes).
 constexpr int64_t kTransposeFrom = 1 << 23;
+
+// Is the transposed copy made from the finished codes by a pass of its own (transpose_codes_kernel), or stored with them byte
+// by byte?  With them / by the pass, us:
+//   rounded by a finishing pass, whose lanes lie along the rows: 64 x 64 (contraction 16384) 8.7 / 10.4, 600 x 600 8.7 / 11.1, 512 x 512 12.6 / 13.7,
+//         1000 x 1000 13.7 / 13.1, 3000 x 3000 83 / 32, 64000 x 100 32 / 24; but 200000 x 20 28.4 / 29.2, 1000 x 48 8.7 / 12.4: tiles of 128
+//         columns and rows that are not there
+//   256x256 tiles: codes alone leave them much faster.  To nearest 4096 x 4096 x 1024 37.3 / 29.3, 131072 x 64 x 1024 66.1 / 45.0; stochastic
+//         4096 x 4096 x 1024 40.1 / 39.9, 8192 x 4096 x 1024 76.8 / 73.3
+//   other aligned kernels, to nearest: 4096 x 4096 x 256 19.2 / 21.0, 8192 x 4096 x 256 32.7 / 30.0, x 128 34.3 / 30.8, in one load of the whole
+//         contraction 23.7 / 28.5; 4096 x 2048 x 1024 17.8 / 18.6, x 4096 36.3 / 34.8; few columns or rows 131072 x 64 x 256 20.2 / 16.9, 256 x
+//         65536 x 256 21.1 / 19.3, 262144 x 32 x 128 29.3 / 20.9; half-precision 4096 x 4096 x 144 24.2 / 25.1, 8192 x 4096 x 144 42.6 / 37.5, 4096 x 2048 x 2064 40.5 / 39.3
+//   with another rounding the complete epilogue runs either way: half-precision stochastic 6000 x 6000 x 1040 100 / 106
+//   gemm_any_kernel, which has one epilogue: 4096 x 4088 x 200 43.9 / 49.5, 2900 x 2900 x 500 28.6 / 35.7
+static bool copied_from_codes(const Plan &pl, int64_t rows, int64_t cols, int64_t kc, bool two_pass, bool nearest_codes) {
+    const int64_t n = rows * cols;
+    if (two_pass) return n >= 3 << 18 && rows >= 64 && cols >= 64;
+    if (!pl.mfma || n < kTransposeFrom) return false;
+    const TileConfig &t = kTiles[pl.tile];
+    if (!pl.half && t.bm * t.bn == 256 * 256) return true;
+    if (!nearest_codes || (t.max_ksteps > 0 && kc <= BK)) return false;
+    const double products = (double)n * (double)kc;
+    if (pl.half) return n >= 1 << 25 || products >= 0x1p32;
+    return n >= 1 << 25 || products >= (n >= 1 << 24 ? 0x1p33 : 0x1p35) || std::min(rows, cols) <= 256;
+}
+
+// Tiles so much of which lies beyond the matrix that their epilogue, which walks all of it, takes longer with an FP32 or a
+// transposed result than a finishing pass over what there is (us, finishing pass / epilogue):
+//   256x256   65536 rows, contraction 1024: FP32 beside the codes 48 columns 29.2 / 35.0, 80 34.8 / 35.9, 96 36.3 / 35.9; added to
+//             64 35.5 / 52.1, 160 53.5 / 55.6, 320 95.9 / 102.7, 400 124.9 / 106.1; transposed 48 32.0 / 34.1, 64 37.6 / 34.5
+//   128x128   16 columns: one tile per CU (32768 x 512) transposed, stochastic 9.5 / 10.9; two 65536 x 512 13.9 / 12.5, beside 13.3 / 12.1, added
+//             to 14.1 / 18.2; many 262144 x 128 transposed, stochastic 26.8 / 33.5, beside 24.9 / 30.3; 32 columns: many 262144 x 128 added to
+//             37.9 / 51.5, beside 34.0 / 33.7; 32768 x 2048 added to 21.3 / 24.6, x 512 11.1 / 11.2; 16 rows by 524288 x 128 added to 45.3 / 49.4
+//   contractions of one or two stages, whose lanes lie along the rows: 7 by 200000 transposed 19.6 / 26.0, 16 by 524288 63 / 26, added to 39.6 / 43.5
+static bool poorly_filled(const Plan &pl, int64_t rows, int64_t cols, int acc_mode, bool transposed, int64_t ksteps) {
+    const TileConfig &t = kTiles[pl.tile];
+    if (t.max_ksteps > 0) return (transposed && rows <= 8) || (acc_mode == 2 && rows <= 16);
+    const int64_t nt = (int64_t)pl.tiles_m * pl.tiles_n;
+    const double of_cols = (double)cols / ((double)pl.tiles_n * t.bn), of_tile = of_cols * (double)rows / ((double)pl.tiles_m * t.bm);
+    if (t.bm * t.bn == 256 * 256) return acc_mode == 2 ? of_tile < 0.7 : of_cols < (acc_mode == 1 ? 0.375 : 0.25);
+    if (t.bm * t.bn == 128 * 128) {
+        if (acc_mode == 2) return of_cols <= 0.125 || (of_cols <= 0.25 && ksteps >= 16) || (nt > 2 * kCUs && of_tile <= 0.25);
+        return of_cols <= 0.125 && (nt <= kCUs || nt > 2 * kCUs);
+    }
+    return false;
+}
 
 // Launch the MFMA kernel chosen by `pick` (indexed by EPI_*) for plan `pl`, and the finishing
 // kernel when the epilogue cannot be fused.  `ga` carries the operands; its tiling, slicing and
@@ -456,10 +499,15 @@ static mp8_status launch_mfma(GemmArgs ga, Epilogue ep, const Plan &pl, int64_t 
     // do both.  (The master-weight update lives in the finishing pass or in an update kernel; the epilogues
     // of gemm_any_kernel and the half-precision forms take any row length.)
     const bool acc_alone = acc_mode == 1 && out8 == nullptr && ep.out8_t == nullptr && ep.stats == nullptr;
+    const bool nearest_codes = acc_mode == 0 && out8 != nullptr && !ep.sr && !ep.sat && ep.stats == nullptr;
+    const bool poor = pl.mfma && !pl.half && pl.conv_rows == 0 && ep.mask == 0 && (acc_mode != 0 || ep.out8_t != nullptr) &&
+                      poorly_filled(pl, rows, cols, acc_mode, ep.out8_t != nullptr, kc / BK);
+    // (of a large result codes to nearest alone, and the copy from them, are shorter still: 524288 x 16 x 128 34 us, by a finishing pass 42)
+    const bool codes_first = poor && nearest_codes && rows * cols >= kTransposeFrom;
     const bool two_pass = (pl.splits > 1 && !pl.in_turn) || (upd != nullptr && with_update == nullptr) ||
-                          (pl.mfma && !pl.half && ((cols & 15) != 0 || acc_alone));
-    // The transposed copy of large results, and of those a finishing pass rounds, is made from the codes (if they are kept).
-    uint8_t *const copy_t = out8 != nullptr && cols >= 4 && (two_pass || rows * cols >= kTransposeFrom) ? ep.out8_t : nullptr;
+                          (pl.mfma && !pl.half && ((cols & 15) != 0 || acc_alone)) || (poor && !codes_first);
+    uint8_t *const copy_t = out8 != nullptr && (codes_first || copied_from_codes(pl, rows, cols, kc, two_pass, nearest_codes))
+                                ? ep.out8_t : nullptr;
     if (copy_t != nullptr) ep.out8_t = nullptr;
     uint8_t *const out8_t = ep.out8_t;
     float *partial = nullptr;

@@ -1,5 +1,5 @@
-// Second pass of a GEMM whose epilogue is not fused (split contraction, FP32 / transposed
-// outputs, ragged columns), optionally with the master-weight update of Figure 1b applied to the
+// Second pass of a GEMM whose epilogue is not fused (split contraction, ragged columns, poorly filled tiles
+// with an FP32 or transposed result), optionally with the master-weight update of Figure 1b applied to the
 // codes it has just rounded; and the any-shape fallback kernel.
 #pragma once
 
@@ -272,7 +272,7 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float *__restr
 
 // The transposed copy of finished codes: dst [cols, rows] from src [rows, cols].  A pass of its own over 2 bytes per
 // element: a finishing pass would store it byte by byte, its lanes lying along the rows of src, each into a line of its
-// own (4096 x 4096 x 2048 with it 124 us, now 37).  Tiles of 128 x 128 through LDS; 16-byte pieces, eight lanes to a line, where both
+// own (4096 x 4096 x 2048 with it 124 us, now 37; where it pays: copied_from_codes).  Tiles of 128 x 128 through LDS; 16-byte pieces, eight lanes to a line, where both
 // counts are multiples of 16 (WHOLE), else pieces of any alignment and length (at least four columns).
 template <bool WHOLE>
 __global__ __launch_bounds__(256) void transpose_codes_kernel(const uint8_t *__restrict__ src, uint8_t *__restrict__ dst,
