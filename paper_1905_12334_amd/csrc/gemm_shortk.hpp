@@ -188,7 +188,7 @@ __global__ __launch_bounds__(256, EPI == EPI_FULL ? 4 : 5) void gemm_shortk_kern
                     v[8 * g + 4 + e] = u2f(sw[1]);
                 }
             const int64_t c = col0 + 32 * j + 16 * fkb;
-            if (r < p.rows && c < p.cols) emit16<EPI>(p, r, c, v, stt);
+            if (r < p.rows && c < p.cols) emit16<EPI, true>(p, r, c, v, stt);
         }
         if (p.ep.stats != nullptr) stt.flush(p.ep.stats);
     }

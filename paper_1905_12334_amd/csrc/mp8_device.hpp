@@ -270,47 +270,62 @@ struct StatsAcc {
     float amax = 0.0f;      // max |y| over non-NaN values
     uint32_t nan_seen = 0;  // any NaN among the values
     uint32_t nonfinite = 0, zero_codes = 0, zero_inputs = 0;
-    // Bit 7 of the bytes of four packed codes that are zero, Inf or NaN.  In a loss-scaled tensor few groups hold
-    // one, and only those are counted: with everything counted without a branch a Q node with statistics spent 25
-    // instructions per four values on them, as many as on the rest of its work.
-    static __device__ __forceinline__ uint32_t remarkable(uint32_t packed) {
-        const uint32_t top = (packed & 0x7C7C7C7Cu) + 0x04040404u;   // bit 7: the exponent field is all ones
-        const uint32_t some = (packed & 0x7F7F7F7Fu) + 0x7F7F7F7Fu;  // bit 7: the magnitude is not zero
-        return (top | ~some) & 0x80808080u;
-    }
-    __device__ __forceinline__ void add_amax4(const float y[4]) {  // ignores NaN operands
-        amax = __builtin_fmaxf(__builtin_fmaxf(amax, __builtin_fabsf(y[0])), __builtin_fabsf(y[1]));
-        amax = __builtin_fmaxf(__builtin_fmaxf(amax, __builtin_fabsf(y[2])), __builtin_fabsf(y[3]));
-    }
-    __device__ __forceinline__ void count4(const float y[4], uint32_t packed) {
+    // Of U times four values and their codes: the maximum, and a test of the values that decides whether anything is counted.
+    // A code is Inf or NaN only if its value is beyond the largest normal, and a non-zero value becomes zero only below the
+    // smallest subnormal; with its bits shifted left by one and one subtracted, a zero is the largest number and does
+    // not look like one.  Two instructions per value and no dependence on the codes, whatever share of the values is
+    // zero (behind a ReLU half of them; a test for zero codes, which was here before, met one in every wave).  With everything
+    // counted without a test a Q node spent 25 instructions per four values, as many as on the rest of its work.
+    // kRaw: the codes are as the conversion instructions give them, and are made canonical where there is a NaN.
+    template <int U, bool kRaw>
+    __device__ __forceinline__ void add(const float (*y)[4], uint32_t *packed) {
+        float hi = 0.0f;
+        uint32_t lo = ~0u;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) zero_inputs += (y[j] == 0.0f) ? 1u : 0u;
-        nan_seen |= any_nan4(y) ? 1u : 0u;
-        nonfinite += __builtin_popcount(((packed & 0x7C7C7C7Cu) + 0x04040404u) & 0x80808080u);
-        zero_codes += 4u - __builtin_popcount(((packed & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) & 0x80808080u);
-    }
-    // four values before rounding and their packed codes
-    __device__ __forceinline__ void add4(const float y[4], uint32_t packed) {
-        add_amax4(y);
-        if (remarkable(packed)) count4(y, packed);
-    }
-    // U times four values and their codes as the conversion instructions give them: one test for all, and the NaN codes
-    // made canonical behind it
-    template <int U>
-    __device__ __forceinline__ void add_raw(const float (&y)[U][4], uint32_t (&packed)[U]) {
-        uint32_t any = 0;
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            add_amax4(y[u]);
-            any |= remarkable(packed[u]);
-        }
-        if (any) {
+            for (int j = 0; j < 4; ++j) {
+                hi = __builtin_elementwise_maximum(hi, __builtin_fabsf(y[u][j]));  // (a NaN stays)
+                const uint32_t bits = (f2u(y[u][j]) << 1) - 1u;
+                lo = bits < lo ? bits : lo;
+            }
+        amax = __builtin_fmaxf(amax, hi);  // (ignores a NaN)
+        constexpr uint32_t kSmallestSubnormal = ((127u - 16u) << 24) - 1u;
+        const bool flushed = lo < kSmallestSubnormal, large = !(hi <= 57344.0f);
+        if (flushed | large) {
+            if (flushed) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                packed[u] = canonical_nan_codes(packed[u]);
-                count4(y[u], packed[u]);
+                for (int u = 0; u < U; ++u) count_zeros(y[u], packed[u]);
+            }
+            if (large) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if constexpr (kRaw) packed[u] = canonical_nan_codes(packed[u]);
+                    count_large(y[u], packed[u]);
+                }
             }
         }
+    }
+    __device__ __forceinline__ void count_zeros(const float y[4], uint32_t packed) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) zero_inputs += (y[j] == 0.0f) ? 1u : 0u;
+        zero_codes += 4u - __builtin_popcount(((packed & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) & 0x80808080u);
+    }
+    __device__ __forceinline__ void count_large(const float y[4], uint32_t packed) {
+        nan_seen |= any_nan4(y) ? 1u : 0u;
+        nonfinite += __builtin_popcount(((packed & 0x7C7C7C7Cu) + 0x04040404u) & 0x80808080u);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) amax = __builtin_fmaxf(amax, __builtin_fabsf(y[j]));  // (ignores a NaN)
+    }
+    // four values before rounding and their packed (canonical) codes
+    __device__ __forceinline__ void add4(const float y[4], uint32_t packed) {
+        add<1, false>(reinterpret_cast<const float (*)[4]>(y), &packed);
+    }
+    // the same without the test, for code that gains less from it than the branches cost (finish16_ragged: 1000 x 1000 x 1000
+    // stochastic, contraction-major 14.5 us with it, 13.9 without)
+    __device__ __forceinline__ void add4_always(const float y[4], uint32_t packed) {
+        count_zeros(y, packed);
+        count_large(y, packed);
     }
     __device__ __forceinline__ void add1(float y, uint32_t code) {
         if (y != y) nan_seen = 1u;
@@ -322,7 +337,8 @@ struct StatsAcc {
     // The running maximum at the destination, for flush: the maximum only grows, so a block whose own does not
     // exceed a value seen there has nothing to add (an older value only makes the test more conservative).
     // To be called when the kernel starts: at its end this load would meet the other blocks' additions to the same line,
-    // which then go to and fro between the caches (16384 x 1024, transposed, 256 blocks: 34.0 us, loaded early 25.5).
+    // which then go to and fro between the caches (16384 x 1024, transposed, stochastic, 256 blocks: read at the end 31.8 us where a larger
+    // maximum stands and 31.6 into a cleared slot, to which then every block adds; read early 23.2 and 23.6).
     static __device__ __forceinline__ uint32_t peek(const mp8_stats *out) {
         uint32_t seen = 0;
         if (threadIdx.x == 0) seen = __hip_atomic_load(&out->amax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

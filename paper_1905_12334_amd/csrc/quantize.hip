@@ -64,7 +64,7 @@ __device__ __forceinline__ void round_groups(float (&v)[U][4], float scale, bool
         if constexpr (kStats) pk[u] = e5m2_pack4_raw<kSR>(v[u], r[u].r01, r[u].r23, sat);
         else pk[u] = e5m2_pack4<kSR>(v[u], r[u].r01, r[u].r23, sat);
     }
-    if constexpr (kStats) st.add_raw(v, pk);
+    if constexpr (kStats) st.add<U, true>(v, pk);
 }
 
 // Random words of U groups of four elements per lane, group u starting at element index i(u)
@@ -98,15 +98,16 @@ constexpr int kFlatUnroll = 4;  // 16-byte loads in flight per thread
 constexpr int kStatsBlocks = 512;      // grid limit per tensor of a batch with statistics (256 threads)
 // The flat variant with statistics: one workgroup of 1024 threads per CU.  Every workgroup ends with
 // one to three atomics on the one mp8_stats (the maximum needs none where a larger one had been seen), which
-// the memory side serialises at about 9 ns each (256 of them 2.3 us, 512 5.2 us).
+// the memory side serialises at about 9 ns each.  512 of them: 4096 x 2048 stochastic into a cleared slot 14.2 us, 256 12.7; where a
+// larger maximum stands 8.8 and 9.5.
 constexpr int kFlatStatsBlocks = 256;
 constexpr int64_t kFlatSmall = 256 * 1024;
 constexpr int64_t kTiny = 128 * 1024, kTinyRagged = 256 * 1024;  // transposing: element by element up to here
 constexpr int64_t kTileSwitch = 256;   // transposing: tiles of 128 x 128 from this many on, else of 64 x 64
 // With statistics earlier, where tiles of 64 would be more workgroups than CUs; stochastic rounding, which they speed up
-// more, at two per CU.  (us in tiles of 128 / of 64, where no value of the tensor is flushed to zero, and where
-// every workgroup counts some: to nearest 1024 x 1280 7.0 / 6.9 and 7.5 / 11.8, 1920 x 2048 8.0 / 16.6 and 9.6 / 36;
-// stochastic 1024 x 1280 8.3 / 6.5 and 8.8 / 9.8, 1024 x 2048 8.6 / 8.4 and 9.3 / 13.6.)
+// more, at two per CU.  (us in tiles of 128 / of 64, where a larger maximum stands, and into a cleared slot, to which every
+// workgroup adds: to nearest 512 x 1280 6.7 / 4.95 and 7.0 / 6.6, 1024 x 1024 6.8 / 5.15 and 7.4 / 7.95, 1920 x 2048 8.0 / 16.6 and 10.5 / 36;
+// stochastic 1024 x 1280 8.2 / 6.0 and 9.0 / 9.2, 1280 x 1280 8.3 / 6.2 and 9.3 / 10.2.)
 constexpr int64_t kTileSwitchStats = 65, kTileSwitchStatsSR = 128;
 constexpr int64_t kMaxTileBlocks = 1 << 21;  // a launch has fewer than 2^32 threads; tiles beyond it by striding
 constexpr int kStatsThreads = 1024;
@@ -252,8 +253,8 @@ constexpr int kPitch = kTile / 4 + 1;  // LDS row pitch in dwords
 // 128-byte line.  Requires cols % 4 == 0 and rows % 16 == 0.
 // With statistics two such 256-thread teams, each with tiles of its own, make one workgroup: the
 // workgroups end together, and their atomics on the one mp8_stats then queue up behind the last
-// stores (16384 x 1024, stochastic, 256 workgroups 23.1 us, no statistics 21.8 us; 33.8 us before the running maximum
-// was read early and groups without a remarkable code went uncounted, see StatsAcc).
+// stores (16384 x 1024, stochastic, 256 workgroups 23.2 us, no statistics 21.4 us; 34.4 us before the running maximum
+// was read early, which is most of it, and values were tested before they are counted, see StatsAcc).
 template <bool kF16, bool kSR, bool kStats>
 __global__ __launch_bounds__(kStats ? 512 : 256, kStats ? 1 : 2) void quantize_transpose_kernel(
     const void *__restrict__ src, uint8_t *__restrict__ dst, uint8_t *__restrict__ dst_t,
