@@ -300,7 +300,8 @@ mp8_status mp8_adam_fp16_sr(uint16_t *w16, float *m, float *v, const uint8_t *g8
  *   - it is not split and the output takes 64x64 tiles (N a multiple of 16, both operands row-major or
  *     both contraction-major; with ADAM from 128 tiles on): in the GEMM's own epilogue, without a
  *     workspace; the same for operands that the aligned kernels cannot take, contraction-major, N a
- *     multiple of 8, from 32 tiles on (SGD up to 1024, ADAM from 512 on);
+ *     multiple of 8, with a g8_out, where one launch takes less time than two (from 32 tiles on; with ADAM
+ *     from 512);
  *   - otherwise in a launch of its own after the GEMM, which is cheaper than a finishing pass that
  *     writes and reads the FP32 result.  The codes lie in g8_out, or in the first K*N bytes of the
  *     workspace if the caller passes no g8_out and the workspace is that large.

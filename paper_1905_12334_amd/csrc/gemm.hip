@@ -345,19 +345,38 @@ static UpdateKernel update_kernel(const Plan &pl, int64_t cols, int layout, int 
     return nullptr;
 }
 
-// The same for gemm_any_kernel, contraction-major operands.  Two launches against one, SGD / momentum / ADAM, us:
+// The same for gemm_any_kernel, contraction-major operands.  Its tiles run 2 kCUs at a time, and the update is a serial tail of each
+// (with ADAM one wave per SIMD divides and takes roots), so a last round that is nearly empty pays for all of it.  Two launches
+// against one, SGD / momentum / ADAM, us:
 //     12 tiles (65 x 200 x 130)      8.7  9.0 10.0    9.3  9.6 10.0: the kernel's chain of latencies has nothing beside it
 //     32       (300 x 104 x 1001)    8.9  9.3 10.2    8.6  8.8 10.2
-//    256       (1000 x 1000 x 1000) 12.6 12.8 14.5   12.0 12.5 14.9: with ADAM, one wave per SIMD divides and takes roots
-//    512       (256 x 1000 x 2048)  12.6 13.7 16.1   11.6 12.6 15.6
-//   1024       (700 x 2008 x 2001)  27.3 30.9 37.6   26.9 28.1 34.0
-//   4032       (200 x 4088 x 4001)  61.2 80.1 101.6  65.0 69.4 90.1: SGD has the least to read, and streams faster by itself
-static UpdateKernel any_update_kernel(const Plan &pl, int64_t cols, int layout, int states) {
+//    256       (1000 x 1000 x 1000) 12.6 12.8 14.5   12.0 12.5 14.9
+//    512       (256 x 1000 x 2048)  12.1 14.2 15.9   11.2 12.7 16.0
+//    533       (1000 x 2584 x 772)  20.7 23.1 25.6   21.7 23.9 28.5
+//    567       (200 x 520 x 4000)   15.7 17.6 20.4   17.5 18.9 27.1
+//    644       (64 x 1736 x 1455)   16.2 17.8 21.8   16.3 17.6 23.1
+//    800       (500 x 2520 x 1263)  21.1 23.9 29.1   21.5 23.6 29.9
+//    882       (256 x 3128 x 1149)  19.3 23.4 28.9   19.7 21.5 27.4: a second round three eighths full is enough, for SGD three quarters
+//   1003       (64 x 3736 x 1088)   19.0 23.3 29.5   18.3 20.6 27.7
+//   1107       (500 x 2600 x 1711)  26.0 30.2 36.9   25.9 29.5 37.7
+//   1612       (129 x 3944 x 1661)  30.7 37.1 46.6   30.6 32.9 41.9
+//   3995       (64 x 3000 x 5440)   61.7 78.8 102.0  61.6 67.2 90.3: SGD has the least to read, and streams as fast by itself
+// With statistics of the gradient every tile ends in atomics on one address.  Where all tiles end together that takes longer after the
+// updates (256 x 1000 x 2048 17.2 with momentum, in one launch 20.1; 129 x 2360 x 431 14.6 and 16.7), else it overlaps with
+// them (64 x 2872 x 196 13.2 and 10.6; 129 x 3288 x 644 20.9 and 19.0, with ADAM 24.7 and 27.5; 500 x 3112 x 815 with ADAM 32.1 and 26.5).  A few tiles
+// whose last column is eight wide end later in one launch when they round stochastically (256 x 520 x 256 8.5 9.0, in one 9.6
+// 10.0, to nearest 7.8 and 7.7; 536 wide 8.3 8.8 and 8.3 8.5; why, is not known).
+static UpdateKernel any_update_kernel(const Plan &pl, int64_t cols, int layout, const UpdateHook &upd, bool with_stats, bool stochastic) {
     static const UpdateKernel kernels[3] = {gemm_any_update_kernel<0>, gemm_any_update_kernel<1>, gemm_any_update_kernel<2>};
-    const int64_t nt = (int64_t)pl.tiles_m * pl.tiles_n;
-    if (pl.splits != 1 || layout != 3 || (cols & 7) != 0) return nullptr;
-    if (nt < (states == 2 ? 2 * kCUs : 32) || (states == 0 && nt > 4 * kCUs)) return nullptr;
-    return kernels[states];
+    const int64_t nt = (int64_t)pl.tiles_m * pl.tiles_n, round = 2 * kCUs;
+    if (pl.splits != 1 || layout != 3 || (cols & 7) != 0 || nt < 32) return nullptr;
+    if (stochastic && (cols & 63) == 8 && nt < kCUs / 2) return nullptr;
+    if (with_stats && nt > kCUs && nt <= round) return nullptr;
+    bool pays = true;
+    if (upd.states == 0) pays = nt <= round || (nt >= round + round * 3 / 4 && nt <= 2 * round);
+    else if (upd.states == 1) pays = nt <= round || nt > round + round / 4 || with_stats;
+    else pays = nt == round || nt >= round + round * 3 / 8 || (with_stats && nt > round + round / 4);
+    return pays ? kernels[upd.states] : nullptr;
 }
 
 // Upper bound of the workspace: one FP32 tile set per contraction slice.  (The MFMA kernel
@@ -645,7 +664,8 @@ static mp8_status gemm_impl(mp8_op op, int64_t M, int64_t N, int64_t K, const ui
         // it never needs a workspace: without one a split contraction takes its slices in turn
         pl.in_turn = pl.splits == 1 || !has_workspace(pl.splits);
         // (the update goes with the finishing pass or an unsplit call's epilogue: otherwise two launches)
-        const UpdateKernel with_update = upd != nullptr && out8 != nullptr ? any_update_kernel(pl, cols, layout, upd->states) : nullptr;
+        const UpdateKernel with_update =
+            upd != nullptr && out8 != nullptr ? any_update_kernel(pl, cols, layout, *upd, stats != nullptr, ep.sr || upd->sr) : nullptr;
         if (upd != nullptr && pl.in_turn && with_update == nullptr) return MP8_ERR_UNSUPPORTED;
         GemmArgs ga{};
         ga.a = a;

@@ -11,7 +11,8 @@ from test_gpu_gemm_ragged import TN, mp8  # noqa: F401 (the fixture)
 pytestmark = pytest.mark.gpu
 
 
-# Tiles: 4 (two launches), 32 (the fewest), 144 and 128, 512 and 544 (ADAM too), 1088 (SGD no more); one stage, incomplete ones; rows and columns at the edge of a tile and of a pair of groups.
+# Tiles: 4, 32, 144 and 128, 512, 544, 1088; one stage, incomplete ones; rows and columns at the edge of a tile and of a pair of groups.  (With statistics
+# of the gradient some of them take two launches; test_gpu_any_update_rule has calls without, and reads which call takes which.)
 @pytest.mark.parametrize("dims", [(100, 72, 65), (300, 104, 1001), (129, 24, 2048), (257, 1000, 520), (1100, 1000, 500), (65, 1000, 2047),
                                   (1200, 2040, 1040), (130, 2040, 2113)])
 @pytest.mark.parametrize("rule", ["sgd", "momentum", "adam"])
