@@ -379,9 +379,10 @@ static UpdateKernel any_update_kernel(const Plan &pl, int64_t cols, int layout, 
     return pays ? kernels[upd.states] : nullptr;
 }
 
-// Upper bound of the workspace: one FP32 tile set per contraction slice.  (The MFMA kernel
-// finishes its tiles itself for an unsplit contraction with a row length that is a multiple
-// of 16; otherwise it writes FP32 tiles and the finishing kernel takes over.)
+// Upper bound of the workspace: one FP32 tile set per contraction slice.  (The MFMA kernels
+// finish their tiles themselves for an unsplit contraction with a row length that is a multiple
+// of 16, unless most of a tile lies beyond the matrix (poorly_filled); otherwise they write FP32
+// tiles and the finishing kernel takes over.)
 static size_t plan_workspace(const Plan &pl, int64_t rows, int64_t cols) {
     if (!pl.mfma) return 0;
     return (size_t)pl.splits * (size_t)rows * (size_t)cols * sizeof(float);
@@ -511,7 +512,8 @@ static mp8_status launch_mfma(GemmArgs ga, Epilogue ep, const Plan &pl, int64_t 
     auto has_workspace = [&] {
         return workspace != nullptr && workspace_bytes >= (size_t)pl.splits * (size_t)rows * (size_t)cols * sizeof(float);
     };
-    // (the 8-bit kernels have always asked for a workspace with these outputs)
+    // With these outputs some tiles are finished by a second pass (poorly_filled); which ones is not the caller's concern, so
+    // the 8-bit kernels ask for a workspace with all of them, as the header says.
     if (pl.mfma && !pl.half && (acc_mode == 2 || (ep.out8_t != nullptr && !(acc_mode == 1 && pl.splits == 1))) && !has_workspace())
         return MP8_ERR_WORKSPACE;
     // Fused epilogue or two passes?  An FP32 result alone is the tiles as the kernels write them; with codes the epilogues
@@ -1116,6 +1118,11 @@ static Plan conv_plan(mp8_op op, const ConvDims &d, int64_t Ci, int64_t W) {
     // Forward and backward data: the kernel that keeps a tile's pixel rows in LDS, while they fit.  256 rows per tile from
     // one and a half tiles per CU on: 32 x 56 x 56 x 64 (421) 7.7 us, in tiles of 128 8.3, 17 x 33 x 33, 128 to 512 (656) 16.8 and 17.5,
     // 41 x 17 x 17, 192 to 320 (290) 13.5 and 12.6.
+    // Never in slices, also where tiles are few and the contraction is long: codes alone are faster whole (forward, general
+    // kernel in slices / this one: 2 x 7 x 7, 512 to 512 12.5 / 11.0, 512 to 128 11.6 / 10.9, 256 to 256 11.6 / 7.0), and slices
+    // would ask for a workspace.  What is slower are complete epilogues on some 30 workgroups and less with 512 contracted
+    // channels, whose latency nothing covers (2 x 7 x 7, 512 to 128: with statistics 12.0 / 12.3, an FP32 result 11.6 / 12.1,
+    // added to 11.7 / 13.8, with all of it 12.6 / 15.1; 256 to 256 added to 11.8 / 9.8).
     if (op != MP8_WGRAD && 2 * (W + 3) <= kConvHalo) {
         Plan pl{};
         pl.mfma = true;

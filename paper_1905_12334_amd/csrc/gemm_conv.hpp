@@ -14,10 +14,12 @@ namespace mp8 {
 // it in LDS at once, and the nine taps are multiplied from there.  256 threads, wave w owns rows w BM/4 .. and
 // all 64 output columns.
 //   BM = 128  53 KB: three workgroups on a CU cover each other's loads
-//   BM = 256  61 KB: two; half the LDS reads of weights per product, for grids that still give every CU one or two
+//   BM = 256  60 KB, where the epilogue takes FP32 bands 68 KB: two; half the LDS reads of weights per product, for grids
+//             that still give every CU one or two
 // While a chunk is multiplied, the weights of the next one take the place of the filter rows that are done; the
 // slab follows at its end.  (A second slab for the next chunk leaves room for two workgroups of BM = 128 only: 26 x 56 x
-// 56, 256 to 64 channels 14.2 us, with it 16.7.  No refill at all: 2 x 28 x 28, 512 to 512 12.2 and 13.4.)
+// 56, 256 to 64 channels 14.2 us, with it 16.7.  No refill at all: 2 x 28 x 28, 512 to 512 12.2 and 13.4.)  The plan
+// takes the contraction whole (see conv_plan).
 // Measured, forward / backward data, before and after: 32 x 28 x 28 x 128 9.5 / 9.2 and 8.2 / 8.0 us, 32 x 56 x 56 x 64 12.6
 // / 12.7 and 7.7 / 7.6, 26 x 56 x 56, 256 to 64 27.5 / 24.9 and 14.2 / 17.0, 45 x 7 x 7, 64 to 128 7.0 / 8.0 and 4.1 / 5.1.
 // BTN: forward (w [9 Cin, Cout] contraction-major); else backward data (w [tap][Cin][Cout], rows of a tap's slab).

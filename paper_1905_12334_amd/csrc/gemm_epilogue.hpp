@@ -17,8 +17,9 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs &p, const f32x16 (&
     // Epilogue.  acc[i][j][4g + e] is output row  wm*WTM + 32i + lane%32  and column
     // wn*WTN + 32j + 8g + 4*(lane/32) + e.  Each wave passes its tile through LDS one band
     // of 32 rows at a time, so that afterwards every lane owns 16 consecutive columns of one
-    // row: full 16-byte stores of codes, 64-byte runs of FP32, one Philox block per eight
-    // elements.
+    // row: full 16-byte stores of codes, one Philox block per eight elements.  FP32 leaves
+    // before that, 16 bytes per lane, neighbouring lanes side by side (partial tiles, and acc where
+    // acc_lines says so; else 64-byte runs per lane).
     constexpr int EP_LD = WTN + 4;                 // floats per band row (+4: bank spread)
     constexpr int CG = WTN / 16;                   // 16-column groups per band row
     constexpr int BANDS = MT >= 2 ? 2 : 1;         // bands staged per pass
