@@ -146,7 +146,8 @@ __device__ __forceinline__ uint32_t finish1(const Epilogue &ep, int64_t r, int64
 // conversions are out of line.
 // acc_done: v has been through ep.acc already.  kAlways: statistics without a test (see StatsAcc::add4_always), which gemm_shortk_kernel
 // alone is better off with (4096 x 4096 x 128 to nearest 35.8 us with it, 33.2 without; everywhere else the test is worth 2 to 6 %).
-template <bool kAlways = false>
+// kThrough: the codes by store_through, for callers whose neighbouring lanes complete a line.
+template <bool kAlways = false, bool kThrough = false>
 __device__ __forceinline__ void finish16(const Epilogue &ep, int64_t r, int64_t c, float v[16],
                                          StatsAcc &st, bool acc_done = false) {
     const int64_t i0 = r * ep.cols + c;
@@ -184,7 +185,8 @@ __device__ __forceinline__ void finish16(const Epilogue &ep, int64_t r, int64_t 
     if (!kAlways && ep.stats != nullptr && !padding) st.add<4, false>(y, pk);
     if (ep.out8 != nullptr) {
         u32x4 o = {pk[0], pk[1], pk[2], pk[3]};
-        *reinterpret_cast<u32x4 *>(ep.out8 + i0) = o;
+        if constexpr (kThrough) store_through(reinterpret_cast<u32x4 *>(ep.out8 + i0), o);
+        else *reinterpret_cast<u32x4 *>(ep.out8 + i0) = o;
     }
     if (ep.out8_t != nullptr) {
         uint8_t *t = ep.out8_t + c * ep.rows + r;
@@ -305,7 +307,7 @@ __device__ __forceinline__ void emit_partial4(const GemmArgs &p, int split, int6
     if (r >= p.rows) return;
     float *dst = p.partial + ((int64_t)split * p.rows + r) * p.cols + c;
     if ((p.cols & 3) == 0) {
-        if (c < p.cols) *reinterpret_cast<f32x4 *>(dst) = v;
+        if (c < p.cols) store_through(reinterpret_cast<f32x4 *>(dst), v);
     } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -315,7 +317,7 @@ __device__ __forceinline__ void emit_partial4(const GemmArgs &p, int split, int6
 
 // What a tile kernel does with sixteen consecutive columns c .. c+15 (c % 16 == 0) of output row
 // r, per epilogue variant (described at the main kernel): the RNE-only conversion, or the complete epilogue.
-template <int EPI, bool kAlways = false>
+template <int EPI, bool kThrough = false, bool kAlways = false>
 __device__ __forceinline__ void emit16(const GemmArgs &p, int64_t r, int64_t c, float v[16], StatsAcc &st, bool acc_done = false) {
     static_assert(EPI != EPI_PARTIAL, "see emit_partial4");
     if constexpr (EPI == EPI_RNE) {
@@ -329,9 +331,10 @@ __device__ __forceinline__ void emit16(const GemmArgs &p, int64_t r, int64_t c, 
         }
         if (p.ep.mask && conv_padding_row(p.ep, r)) pk[0] = pk[1] = pk[2] = pk[3] = 0;
         u32x4 o = {pk[0], pk[1], pk[2], pk[3]};
-        *reinterpret_cast<u32x4 *>(p.ep.out8 + r * p.cols + c) = o;
+        if constexpr (kThrough) store_through(reinterpret_cast<u32x4 *>(p.ep.out8 + r * p.cols + c), o);
+        else *reinterpret_cast<u32x4 *>(p.ep.out8 + r * p.cols + c) = o;
     } else {
-        finish16<kAlways>(p.ep, r, c, v, st, acc_done);
+        finish16<kAlways, kThrough>(p.ep, r, c, v, st, acc_done);
     }
 }
 

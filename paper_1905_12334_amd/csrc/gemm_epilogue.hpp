@@ -75,7 +75,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs &p, const f32x16 (&
             const int64_t r = row0 + rr;
             if (r < p.rows && c < p.cols) {
                 if (p.ep.mask && conv_padding_row(p.ep, r)) o = u32x4{0u, 0u, 0u, 0u};
-                *reinterpret_cast<u32x4 *>(p.ep.out8 + r * p.cols + c) = o;
+                store_through(reinterpret_cast<u32x4 *>(p.ep.out8 + r * p.cols + c), o);
             }
         }
         return;
@@ -138,7 +138,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs &p, const f32x16 (&
                             x.x += o.x; x.y += o.y; x.z += o.z; x.w += o.w;
                             *at = x;
                         }
-                        *to = x;
+                        store_through(to, x);
                     }
                 }
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -160,7 +160,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs &p, const f32x16 (&
                     }
                     if (HALF && EPI == EPI_FULL && !fast_cols)
                         finish16_ragged(p.ep, r, c, p.cols - c < 16 ? (int)(p.cols - c) : 16, v, st);
-                    else emit16<EPI>(p, r, c, v, st, acc_done);
+                    else emit16<EPI, true>(p, r, c, v, st, acc_done);
                 }
             }
         }

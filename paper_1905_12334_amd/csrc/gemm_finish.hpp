@@ -33,7 +33,7 @@ __device__ __forceinline__ uint32_t finish4(const Epilogue &ep, int64_t r, int64
     uint32_t pk = e5m2_pack4_rt(y, r01, r23, ep.sr != 0, ep.sat != 0);
     if (ep.mask && conv_padding_row(ep, r)) pk = 0;
     else if (ep.stats != nullptr) st.add4(y, pk);
-    if (ep.out8 != nullptr) *reinterpret_cast<uint32_t *>(ep.out8 + i0) = pk;
+    if (ep.out8 != nullptr) store_through(reinterpret_cast<uint32_t *>(ep.out8 + i0), pk);
     if (ep.out8_t != nullptr) {
         uint8_t *t = ep.out8_t + c * ep.rows + r;
         t[0] = (uint8_t)pk;
@@ -122,15 +122,15 @@ __device__ __forceinline__ void update4(const UpdateHook &u, int64_t i0, uint32_
     });
     if constexpr (STATES >= 1) {
         const f32x4 x = {st[0][0], st[1][0], st[2][0], st[3][0]};
-        *reinterpret_cast<f32x4 *>(u.state0 + i0) = x;
+        store_through(reinterpret_cast<f32x4 *>(u.state0 + i0), x);
     }
     if constexpr (STATES == 2) {
         const f32x4 x = {st[0][1], st[1][1], st[2][1], st[3][1]};
-        *reinterpret_cast<f32x4 *>(u.state1 + i0) = x;
+        store_through(reinterpret_cast<f32x4 *>(u.state1 + i0), x);
     }
     const u32x2 o = {w[0], w[1]};
-    *reinterpret_cast<u32x2 *>(u.w16 + i0) = o;
-    if (u.w8_out != nullptr) *reinterpret_cast<uint32_t *>(u.w8_out + i0) = e5m2_of_halves(w);
+    store_through(reinterpret_cast<u32x2 *>(u.w16 + i0), o);
+    if (u.w8_out != nullptr) store_through(reinterpret_cast<uint32_t *>(u.w8_out + i0), e5m2_of_halves(w));
 }
 
 // The update inside a GEMM's own epilogue.  A thread finishes Q groups of four consecutive weights; group
@@ -188,7 +188,7 @@ __device__ __forceinline__ void update_groups(const Epilogue &ep, const UpdateHo
             for (int e = 0; e < 4; ++e) v[e] *= ep.alpha;
             const uint32_t pk = e5m2_pack4_rt(v, words.g[0].r01, words.g[0].r23, ep.sr != 0, ep.sat != 0);
             if (ep.stats != nullptr) st.add4(v, pk);
-            if (ep.out8 != nullptr) *reinterpret_cast<uint32_t *>(ep.out8 + i0) = pk;
+            if (ep.out8 != nullptr) store_through(reinterpret_cast<uint32_t *>(ep.out8 + i0), pk);
             if (updating) update4<STATES>(u, i0, pk, in[0], words.w[0]);
         }
 #pragma unroll

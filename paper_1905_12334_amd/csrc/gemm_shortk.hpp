@@ -133,7 +133,7 @@ __global__ __launch_bounds__(256, EPI == EPI_FULL ? 4 : 5) void gemm_shortk_kern
             const int rr = 8 * k + (lane >> 3);
             const u32x4 o = *reinterpret_cast<const u32x4 *>(mine + rr * BK + (((lane & 7) ^ ((rr >> 1) & 7)) << 4));
             const int64_t ro = row0 + 32 * wave + rr;
-            if (ro < p.rows && c < p.cols) *reinterpret_cast<u32x4 *>(p.ep.out8 + ro * p.cols + c) = o;
+            if (ro < p.rows && c < p.cols) store_through(reinterpret_cast<u32x4 *>(p.ep.out8 + ro * p.cols + c), o);
         }
         return;
     }
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(256, EPI == EPI_FULL ? 4 : 5) void gemm_shortk_kern
                     v[8 * g + 4 + e] = u2f(sw[1]);
                 }
             const int64_t c = col0 + 32 * j + 16 * fkb;
-            if (r < p.rows && c < p.cols) emit16<EPI, true>(p, r, c, v, stt);
+            if (r < p.rows && c < p.cols) emit16<EPI, false, true>(p, r, c, v, stt);
         }
         if (p.ep.stats != nullptr) stt.flush(p.ep.stats);
     }

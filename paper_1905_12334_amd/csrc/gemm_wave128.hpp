@@ -224,7 +224,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wave128_kernel(const GemmArgs p) 
                             v[4 * q] += x.x; v[4 * q + 1] += x.y; v[4 * q + 2] += x.z; v[4 * q + 3] += x.w;
                         }
                     }
-                if (r < p.rows && c < p.cols) emit16<EPI>(p, r, c, v, st);
+                if (r < p.rows && c < p.cols) emit16<EPI, true>(p, r, c, v, st);
             }
         }
     }
