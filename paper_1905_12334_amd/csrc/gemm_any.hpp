@@ -32,7 +32,8 @@ namespace mp8 {
 // element 639 each).
 // EPI_UPDATE: an unsplit weight gradient applies the master-weight update itself (columns a multiple of eight:
 // neighbouring lanes share random blocks), with the code of the other kernels' epilogues: no launch and no pass
-// over the gradient codes.  256 x 1000 x 2048 with momentum 13.7 -> 12.6 us, its training step 40.0 -> 37.2.
+// over the gradient codes.  256 x 1000 x 2048 with momentum 13.7 -> 12.6 us, its training step 40.0 -> 37.2; with the weights, the state
+// and the random words fetched behind the first stage's loads instead of after the contraction 12.7 -> 10.1, 37.0 -> 34.4.
 // Needs a contraction of at least 16, and 16 rows / columns of a contraction-major operand (an edge
 // chunk is read as the last 16 bytes of its row and shifted into place).
 template <int EPI, bool ATN, bool BTN, bool SLICES>
@@ -148,6 +149,16 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
         }
     };
 
+    // what this thread updates: four groups of four weights, 16 lanes side by side in a row of the tile
+    auto group = [&](int q) {
+        const int item = threadIdx.x + 256 * q;
+        const int64_t r = row0 + (item >> 4), c = col0 + 4 * (item & 15);
+        return GroupAt{r, c, r < p.rows && c < p.cols};
+    };
+    UpdateOperands4 uo[4];
+    GroupWords<4> words;
+    uint32_t flag = 0;
+
     uint8_t *slab_a = lds + wave * WAVE_LDS, *slab_b = slab_a + SLAB;
     float *red = reinterpret_cast<float *>(lds);
     float v[16];
@@ -165,7 +176,15 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
         // stage s is fetched into registers in the round before the one that multiplies it (the rounds
         // are written so that the code of each step exists once: the incomplete stage makes it long)
         const int first = ks_begin + wave;
-        for (int s = first; s < ks_end + 4; s += 4) {
+        if constexpr (EPI >= EPI_UPDATE) {  // the weights, the state and the random words behind the first stage's loads
+            if (first < ks_end) {
+                load_stage(ATN, oa, first, xa);
+                load_stage(BTN, ob, first, xb);
+            }
+            load_groups<STATES, 4>(p.ep, upd, group, uo, flag);
+            draw_groups<4>(p.ep, upd, group, words);
+        }
+        for (int s = EPI >= EPI_UPDATE ? first + 4 : first; s < ks_end + 4; s += 4) {
             if (s > first) {
                 store_stage(ATN, oa, xa, slab_a);
                 store_stage(BTN, ob, xb, slab_b);
@@ -192,21 +211,6 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        }
-
-        // what this thread updates: four groups of four weights, 16 lanes side by side in a row of the tile
-        auto group = [&](int q) {
-            const int item = threadIdx.x + 256 * q;
-            const int64_t r = row0 + (item >> 4), c = col0 + 4 * (item & 15);
-            return GroupAt{r, c, r < p.rows && c < p.cols};
-        };
-        UpdateOperands4 uo[4];
-        GroupWords<4> words;
-        bool updating = false;
-        if constexpr (EPI >= EPI_UPDATE) {  // (not earlier: the next stage's 64 registers are free now)
-            load_groups<STATES, 4>(p.ep, upd, group, uo);
-            updating = !(upd.skip != nullptr && *upd.skip != 0u);
-            draw_groups<4>(p.ep, upd, group, words);
         }
 
         // The four tiles meet in LDS: acc[i][j][4g + e] is row 32i + lane%32, column
@@ -240,7 +244,7 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
                 const f32x4 t = summed(item >> 4, 4 * (item & 15));
                 out[0] = t.x; out[1] = t.y; out[2] = t.z; out[3] = t.w;
             };
-            update_groups<STATES, 4>(p.ep, upd, updating, group, sum, st, uo, words);
+            update_groups<STATES, 4>(p.ep, upd, flag, group, sum, st, uo, words);
             if (p.ep.stats != nullptr) st.flush(p.ep.stats);
             return;
         } else if constexpr (EPI == EPI_PARTIAL) {

@@ -137,18 +137,28 @@ __device__ __forceinline__ void update4(const UpdateHook &u, int64_t i0, uint32_
 // q of neighbouring lanes lies side by side (runs of 128 or 256 bytes of FP32 state; sixteen consecutive
 // weights per lane, as the plain epilogues have them, cost 6 us more here for 1 M weights with ADAM).  Lanes
 // 2m and 2m + 1 hold the halves of one random block.  where(q): row, column (a multiple of 4), and whether
-// it exists; value(q, v): the four sums.  `in`: what load_groups fetched, ahead of the contraction.
+// it exists; value(q, v): the four sums.  `in`: what load_groups fetched.  The fetch goes out behind the loads of the
+// first stages, in front of which it held them up (4096 x 2048 x 512 with ADAM: 4700 cycles from the start of the kernel to
+// its first operand load, 350 now), as always the same kLoads instructions, whether a group exists or not, so that hand-counted waits know them.
 struct GroupAt {
     int64_t r, c;
     bool valid;
 };
+// The skip flag is fetched with them, into a vector register: as a scalar it would be waited for at once.
+template <int STATES, int Q>
+constexpr int kGroupLoads = Q * (1 + STATES) + 1;
 template <int STATES, int Q, class Where>
-__device__ __forceinline__ void load_groups(const Epilogue &ep, const UpdateHook &u, Where where, UpdateOperands4 (&in)[Q]) {
+__device__ __forceinline__ void load_groups(const Epilogue &ep, const UpdateHook &u, Where where, UpdateOperands4 (&in)[Q], uint32_t &flag) {
+    uint32_t zero = 0;
+    asm("" : "+v"(zero));
+    asm volatile("" ::: "memory");
+    flag = (u.skip != nullptr ? u.skip : reinterpret_cast<const uint32_t *>(u.w16))[zero];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         const GroupAt g = where(q);
-        if (g.valid) in[q] = load_update4<STATES>(u, g.r * ep.cols + g.c);
+        in[q] = load_update4<STATES>(u, g.valid ? g.r * ep.cols + g.c : 0);
     }
+    asm volatile("" ::: "memory");
 }
 // The random words of the two roundings (gradient, weight).  Drawn while the first operands are on their
 // way: one workgroup has nothing else to do then, and 1 - 2 us of multiplications to do after the
@@ -173,19 +183,23 @@ __device__ __forceinline__ void draw_groups(const Epilogue &ep, const UpdateHook
     if (u.sr) draw(u.seed, u.offset, out.w);
 }
 // A rolled loop, the register arrays shifted down by one group per turn: straight-line code for four groups
-// of ADAM is 19 KB that every launch would fetch through a cold instruction cache.
+// of ADAM is 19 KB that every launch would fetch through a cold instruction cache.  The sums of all groups
+// are read ahead of it: one latency of the LDS instead of Q.
 template <int STATES, int Q, class Where, class Value>
-__device__ __forceinline__ void update_groups(const Epilogue &ep, const UpdateHook &u, bool updating, Where where, Value value,
+__device__ __forceinline__ void update_groups(const Epilogue &ep, const UpdateHook &u, uint32_t flag, Where where, Value value,
                                               StatsAcc &st, UpdateOperands4 (&in)[Q], GroupWords<Q> &words) {
+    const bool updating = u.skip == nullptr || flag == 0;
+    float sums[Q][4];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) value(q, sums[q]);
 #pragma unroll 1
     for (int q = 0; q < Q; ++q) {
         const GroupAt g = where(q);
         if (g.valid) {
             const int64_t i0 = g.r * ep.cols + g.c;
             float v[4];
-            value(q, v);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] *= ep.alpha;
+            for (int e = 0; e < 4; ++e) v[e] = sums[0][e] * ep.alpha;
             const uint32_t pk = e5m2_pack4_rt(v, words.g[0].r01, words.g[0].r23, ep.sr != 0, ep.sat != 0);
             if (ep.stats != nullptr) st.add4(v, pk);
             if (ep.out8 != nullptr) store_through(reinterpret_cast<uint32_t *>(ep.out8 + i0), pk);
@@ -196,6 +210,8 @@ __device__ __forceinline__ void update_groups(const Epilogue &ep, const UpdateHo
             in[k] = in[k + 1];
             words.g[k] = words.g[k + 1];
             words.w[k] = words.w[k + 1];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sums[k][e] = sums[k + 1][e];
         }
     }
 }

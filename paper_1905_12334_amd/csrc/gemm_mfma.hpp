@@ -76,19 +76,15 @@ __device__ __forceinline__ void gemm_mfma(const GemmArgs &p, const UpdateHook &u
     const int64_t row0 = (int64_t)tm * BM, col0 = (int64_t)tn * BN;
 
     // what this thread updates (EPI_UPDATE): four groups of four weights of the wave's 32x32 tile, eight
-    // lanes side by side in a row, fetched before the contraction
+    // lanes side by side in a row, fetched behind the loads of the first stages
     constexpr int STATES = EPI >= EPI_UPDATE ? EPI - EPI_UPDATE : 0;
     auto group = [&](int q) {
         const int64_t r = row0 + wm * WTM + 8 * q + (lane >> 3), c = col0 + wn * WTN + 4 * (lane & 7);
         return GroupAt{r, c, r < p.rows && c < p.cols};
     };
+    static_assert(EPI < EPI_UPDATE || (WTM == 32 && WTN == 32 && NSTAGE == 2), "one 32x32 tile per wave; the first wait is counted for two stages");
     UpdateOperands4 uo[4];
-    bool updating = false;
-    if constexpr (EPI >= EPI_UPDATE) {
-        static_assert(WTM == 32 && WTN == 32, "one 32x32 tile per wave");
-        load_groups<STATES, 4>(p.ep, upd, group, uo);
-        updating = !(upd.skip != nullptr && *upd.skip != 0u);
-    }
+    uint32_t flag = 0;
 
     // contraction slice of this workgroup, in stages of 128
     const int per = p.ks_per, extra = p.ks_extra;
@@ -346,8 +342,13 @@ __device__ __forceinline__ void gemm_mfma(const GemmArgs &p, const UpdateHook &u
             else issue_loads(st);
         }
     GroupWords<4> words;
-    if constexpr (EPI >= EPI_UPDATE) draw_groups<4>(p.ep, upd, group, words);
-    wait_stage(-1);
+    if constexpr (EPI >= EPI_UPDATE) {
+        load_groups<STATES, 4>(p.ep, upd, group, uo, flag);
+        draw_groups<4>(p.ep, upd, group, words);
+        wait_vm_lds<kGroupLoads<STATES, 4>>();  // (both stages: the loads of the update lie behind them)
+    } else {
+        wait_stage(-1);
+    }
     __syncthreads();
 #pragma unroll
     for (int n = 0; n < 2 * F; ++n) read_half(0, 0, frag_order(n / 2), n & 1, f0);
@@ -442,7 +443,7 @@ __device__ __forceinline__ void gemm_mfma(const GemmArgs &p, const UpdateHook &u
                 const f32x4 x = *reinterpret_cast<const f32x4 *>(band + (8 * q + (lane >> 3)) * ld + 4 * (lane & 7));
                 v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
             };
-            update_groups<STATES, 4>(p.ep, upd, updating, group, sum, st, uo, words);
+            update_groups<STATES, 4>(p.ep, upd, flag, group, sum, st, uo, words);
         }
     });
 }

@@ -22,7 +22,8 @@ namespace mp8 {
 // outputs with so few 64x64 tiles that most CUs would idle while the busy ones wait for their
 // own loads (a CU takes 64 bytes per clock however few of them work).
 // With EPI_UPDATE the master weights and the optimizer's state that a thread will need at the end are
-// fetched before the first stage: one workgroup per CU leaves each lane 512 registers.
+// fetched behind the loads of its first two stages: one workgroup per CU leaves each lane 512 registers.  (4096 x 2048 x 512
+// with ADAM 16.9 us, ahead of them 17.6.)
 // HALF: as in the general kernel.
 template <int EPI, bool ATN, bool BTN, int CONV, int BM = 64, int BN = 64, bool HALF = false>
 __device__ __forceinline__ void gemm_wavek(const GemmArgs &p, const UpdateHook &upd) {
@@ -55,13 +56,9 @@ __device__ __forceinline__ void gemm_wavek(const GemmArgs &p, const UpdateHook &
         const int64_t r = row0 + (item >> 4), c = col0 + 4 * (item & 15);
         return GroupAt{r, c, r < p.rows && c < p.cols};
     };
+    static_assert(EPI < EPI_UPDATE || (BM == 64 && BN == 64), "four groups per thread");
     UpdateOperands4 uo[4];
-    bool updating = false;
-    if constexpr (EPI >= EPI_UPDATE) {
-        static_assert(BM == 64 && BN == 64, "four groups per thread");
-        load_groups<STATES, 4>(p.ep, upd, group, uo);
-        updating = !(upd.skip != nullptr && *upd.skip != 0u);
-    }
+    uint32_t flag = 0;
     const int per = p.ks_per, extra = p.ks_extra;
     const int ks_begin = split * per + (split < extra ? split : extra);
     const int ks_count = per + (split < extra ? 1 : 0);
@@ -152,10 +149,22 @@ __device__ __forceinline__ void gemm_wavek(const GemmArgs &p, const UpdateHook &
     else if (mine > 0) issue(0);
     if (mine > 1) issue(1);
     GroupWords<4> words;
-    if constexpr (EPI >= EPI_UPDATE) draw_groups<4>(p.ep, upd, group, words);
+    constexpr int UL = EPI >= EPI_UPDATE ? kGroupLoads<STATES, 4> : 0;
+    if constexpr (EPI >= EPI_UPDATE) {
+        load_groups<STATES, 4>(p.ep, upd, group, uo, flag);
+        draw_groups<4>(p.ep, upd, group, words);
+    }
+#pragma clang loop unroll(disable)
     for (int j = 0; j < mine; ++j) {
-        if (j + 1 < mine) wait_vm_lds<QA + QB>();  // the loads of the next stage may fly
-        else wait_vm_lds<0>();
+        // the loads of the next stage may fly, and during the first two stages those of the update, which lie behind them
+        if (UL > 0 && j < 2) {
+            if (j + 1 < mine) wait_vm_lds<QA + QB + UL>();
+            else wait_vm_lds<UL>();
+        } else if (j + 1 < mine) {
+            wait_vm_lds<QA + QB>();
+        } else {
+            wait_vm_lds<0>();
+        }
         const uint8_t *s = ring + (j & 1) * STAGE;
 #pragma unroll
         for (int sub = 0; sub < 2; ++sub) {
@@ -204,7 +213,7 @@ __device__ __forceinline__ void gemm_wavek(const GemmArgs &p, const UpdateHook &
             }
             v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
         };
-        update_groups<STATES, 4>(p.ep, upd, updating, group, sum, st, uo, words);
+        update_groups<STATES, 4>(p.ep, upd, flag, group, sum, st, uo, words);
     } else if constexpr (EPI == EPI_PARTIAL) {
         constexpr int F4 = BN / 4;
 #pragma unroll
