@@ -131,6 +131,9 @@ static void (*const kAny[3][3])(const GemmArgs) = {
     {gemm_any_kernel<EPI_PARTIAL, false, true>, gemm_any_kernel<EPI_FULL, false, true>, gemm_any_kernel<EPI_FULL, false, true, true>},
     {gemm_any_kernel<EPI_PARTIAL, true, true>, gemm_any_kernel<EPI_FULL, true, true>, gemm_any_kernel<EPI_FULL, true, true, true>}};
 
+// ... and in tiles of 32 rows, unsplit: [b contraction-major]
+static void (*const kAny32[2])(const GemmArgs) = {gemm_any_kernel<EPI_FULL, false, false, false, 32>, gemm_any_kernel<EPI_FULL, false, true, false, 32>};
+
 // Half-precision forms of the direct-to-LDS kernels, for contractions that are not whole stages: [64x64, 64x64
 // divided among the waves, 128x128][operand layout as above][EPI_*] (they never write FP32 tiles)
 #define MP8_HALF_64(ATN, BTN)                                                                                    \
@@ -329,6 +332,16 @@ static Plan any_plan(int64_t rows, int64_t cols, int64_t kc) {
     if (ksteps * (s - 1) <= ANY_FINISH_STAGES * s) s = 1;
     pl.splits = (int)s;
     return pl;
+}
+
+// Tiles of 32 rows (row-major a, unsplit): twice as many CUs share the work while half of them would idle, and up to three
+// stages they also end sooner on all of them.  In 64 rows / in 32, us, b row-major and contraction-major: 256 x 1000 x 2048
+// (64 tiles of 64) contraction-major 8.9 / 8.0, 1000 x 500 x 1001 (128) 7.2 7.1 / 6.8 6.8, 17 x 100 x 200 (2) 4.7 4.9 / 4.5 4.6; 600 x 1000
+// (160) x 300 5.5 5.9 / 5.2 5.6, x 2000 8.2 10.5 / 8.2 11.0; 1000 x 1000 (256) x 200 5.5 5.9 / 5.3 5.7, x 1000 7.0 8.0 / 7.3 8.8; 1500 x 1000
+// (384) x 300 6.5 6.8 / 6.0 6.6, x 1500 11.8 12.8 / 11.4 13.6; 4000 x 500 (504) x 777 10.8 11.0 / 12.6 12.3.
+static bool any_in_32_rows(const Plan &pl, int64_t kc, int layout) {
+    const int64_t nt = (int64_t)pl.tiles_m * pl.tiles_n;
+    return pl.splits == 1 && !(layout & 1) && (nt <= kCUs / 2 || (nt <= kCUs + kCUs / 2 && kc <= 3 * BK));
 }
 
 // The kernel that computes an unsplit weight gradient and applies the update in its epilogue, or null.  Such
@@ -675,7 +688,12 @@ static mp8_status gemm_impl(mp8_op op, int64_t M, int64_t N, int64_t K, const ui
         ga.lda = lda;
         ga.ldb = ldb;
         void (*const *kern)(const GemmArgs) = kAny[atn ? 2 : btn ? 1 : 0];
-        void (*const pick[3])(const GemmArgs) = {kern[0], nullptr, kern[pl.splits > 1 ? 2 : 1]};
+        void (*whole)(const GemmArgs) = kern[pl.splits > 1 ? 2 : 1];
+        if (any_in_32_rows(pl, kc, layout)) {  // (the same bits: the order of the additions does not depend on the tile)
+            whole = kAny32[btn];
+            pl.tiles_m = (int)((rows + 31) / 32);
+        }
+        void (*const pick[3])(const GemmArgs) = {kern[0], nullptr, whole};
         return launch_mfma(ga, ep, pl, kc, pick, workspace, workspace_bytes, s, upd, validate_only, with_update);
     }
     if (!pl.mfma || kc == 0) {

@@ -23,27 +23,32 @@ namespace mp8 {
 // workspace they run side by side (EPI_PARTIAL and a finishing pass), without one a workgroup takes
 // the slices of its tile one after the other (SLICES) and adds them up in the same order.
 //
-// What bounds it: a 64x64 tile pulls 128 bytes per clock and CU at the 8-bit matrix rate and 64 at the
-// half-precision one, which is what the path from L2 carries; unaligned rows cost more requests.  A CU needs about
-// 0.4 us per 16 KB stage however many tiles or waves there are (eight waves per tile: 256 x 1001, contraction 2003,
-// row-major 12.1 us instead of 11.1, both contraction-major 10.5 instead of 10.7; two 8-byte loads for one of 16
-// 10.7 instead of 10.2 at 256 x 1000, contraction 2048).  A layer of
-// 256 x 1000 x 2048, back to back: forward 10.2 us, backward data 7.1, weight gradient 7.2 (one thread per output
-// element 639 each).
+// BM = 32: tiles of 32 rows for small outputs (any_in_32_rows); the order of the additions is the same.
+//
+// What bounds it: with one tile per CU the chain of a wave -- a stage's loads, their way through the registers into LDS,
+// conversion, multiplication -- of which the loads overlap with the rest; with more tiles the path from L2, of which a
+// 64-column piece of a contraction-major row uses half of each 128-byte line.  256 x 1000 x 2048, back to back: forward 10.3 us while the
+// multiplications waited for the next stage's loads (a branch for the incomplete stage made the compiler wait there), 8.9
+// without the wait, 8.0 in tiles of 32 rows; backward data 6.8, 5.7; one thread per output element 639.  1500 x 1000 x 1500, whose tiles share
+// three CUs out of four unevenly, is slower for it (11.0 -> 11.6, contraction-major 12.3 -> 12.8), 500 x 2000 x 3000 faster (12.4 -> 12.3, 14.4 -> 13.2).
+// Eight waves per tile instead of four (256 x 1001, contraction 2003: row-major 12.1 us instead of 11.1) and two 8-byte loads for
+// one of 16 (10.7 instead of 10.2 at 256 x 1000, contraction 2048) were slower.
 // EPI_UPDATE: an unsplit weight gradient applies the master-weight update itself (columns a multiple of eight:
 // neighbouring lanes share random blocks), with the code of the other kernels' epilogues: no launch and no pass
 // over the gradient codes.  256 x 1000 x 2048 with momentum 13.7 -> 12.6 us, its training step 40.0 -> 37.2; with the weights, the state
 // and the random words fetched behind the first stage's loads instead of after the contraction 12.7 -> 10.1, 37.0 -> 34.4.
 // Needs a contraction of at least 16, and 16 rows / columns of a contraction-major operand (an edge
 // chunk is read as the last 16 bytes of its row and shifted into place).
-template <int EPI, bool ATN, bool BTN, bool SLICES>
+template <int EPI, bool ATN, bool BTN, bool SLICES, int BM = 64>
 __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &upd) {
     constexpr int STATES = EPI >= EPI_UPDATE ? EPI - EPI_UPDATE : 0;
     static_assert(EPI == EPI_FULL || !SLICES, "only a plain call takes its slices in turn");
     static_assert(BTN || !ATN, "a alone contraction-major is not built");
-    constexpr int T = 64, SLAB = T * BK, WAVE_LDS = 2 * SLAB;
+    static_assert(BM == 64 || (BM == 32 && !ATN && EPI == EPI_FULL && !SLICES), "the 32-row tile takes a row-major a and the whole contraction");
+    constexpr int T = 64, SLAB_A = BM * BK, WAVE_LDS = SLAB_A + T * BK;
+    constexpr int MI = BM / 32;    // 32x32 accumulator tiles along the rows
     constexpr int RED_LD = T + 4;  // floats per row of a tile parked for the reduction
-    constexpr int RED_BYTES = 4 * T * RED_LD * 4;
+    constexpr int RED_BYTES = 4 * BM * RED_LD * 4;
     __shared__ __attribute__((aligned(1024))) uint8_t lds[RED_BYTES > 4 * WAVE_LDS ? RED_BYTES : 4 * WAVE_LDS];
 
     int split, tm, tn;
@@ -53,7 +58,7 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
     tn = __builtin_amdgcn_readfirstlane(tn);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t row0 = (int64_t)tm * T, col0 = (int64_t)tn * T;
+    const int64_t row0 = (int64_t)tm * BM, col0 = (int64_t)tn * T;
     // One operand: its tile's first row `first` of `limit`, leading dimension ld.
     //   row-major: load q brings tile rows 8q .. 8q+7, lane l sixteen contraction bytes of row
     //   8q + l/8, chunk l%8; rows beyond the matrix are clamped to its last row (never stored)
@@ -78,7 +83,8 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
             const int64_t m = 16 * (lane & 3), last = limit - 16 - first;
             o.shift = m > last ? (int)(m - last < 15 ? m - last : 15) : 0;
             // (last is negative in a tile narrower than sixteen columns: the sum is not)
-            o.off[0] = (uint32_t)((lane >> 2) * ld + (m > last ? last : m) + 16);
+            o.off[1] = (uint32_t)((m > last ? last : m) + 16);  // in the first contraction row
+            o.off[0] = (uint32_t)((lane >> 2) * ld) + o.off[1];
         } else {
             o.base = uniform_ptr(x + first * ld);
 #pragma unroll
@@ -102,46 +108,60 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
     };
     // x shifted down by 0 .. 15 bytes, zeros above
     auto shift_down = [](u32x4 x, int bytes) {
-        uint64_t lo = ((uint64_t)x.y << 32) | x.x, hi = ((uint64_t)x.w << 32) | x.z;
-        if (bytes & 8) {
-            lo = hi;
-            hi = 0;
-        }
+        const uint32_t whole = (bytes & 8) ? ~0u : 0u;  // (masks: with `?:` the compiler branches around every shift)
+        const uint32_t w0 = (x.z & whole) | (x.x & ~whole), w1 = (x.w & whole) | (x.y & ~whole);
+        uint64_t lo = ((uint64_t)w1 << 32) | w0, hi = ((uint64_t)(x.w & ~whole) << 32) | (x.z & ~whole);
         const int s = 8 * (bytes & 7);
         lo = (lo >> s) | ((hi << 1) << (63 - s));
         hi >>= s;
         return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
     };
-    auto load_stage = [&](bool km, const Operand &o, int s, u32x4 x[8]) {
+    // A stage into registers: the same loads whether it is complete or not, so that nothing but the next round waits for them.
+    // (With a branch for the incomplete stage the compiler joined the two ways behind a wait for all loads.)  What lies beyond
+    // the contraction is read from its first row or chunk, and a partial chunk as the last sixteen bytes of its row:
+    // store_stage puts zeros there, and shifts the partial chunk down.
+    auto left_of = [&](int s) {
+        const int64_t left = p.kc - (int64_t)s * BK;
+        return left < BK ? (int)left : BK;
+    };
+    auto load_stage = [&](bool km, const Operand &o, int s, auto &x) {
+        constexpr int N = sizeof(x) / sizeof(x[0]);  // loads: eight rows or sixteen contraction rows each
         const uint8_t *k0 = o.base + (int64_t)s * o.kstep;
-        const int64_t left64 = p.kc - (int64_t)s * BK;
-        auto load = [&](int q) { return km ? load16(k0 + 16 * q * o.ld, o.off[0]) : load16(k0, o.off[q]); };
-        if (left64 >= BK) {
+        const int left = left_of(s);
+        if (km) {
+            const int last = (left - 1) >> 4;  // the last load with anything in it: the others repeat it
+            const uint32_t off = 16 * last + (lane >> 2) < left ? o.off[0] : o.off[1];
+            const int64_t step = 16 * o.ld;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) x[q] = load(q);
-        } else if (km) {  // the last, incomplete stage: contraction rows beyond it are zero
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                x[q] = u32x4{0, 0, 0, 0};
-                if (16 * q + (lane >> 2) < (int)left64) x[q] = load(q);
+            for (int q = 0; q < N; ++q) {
+                x[q] = load16(k0, q < last ? o.off[0] : off);
+                k0 += q < last ? step : 0;
             }
-        } else {  // bytes beyond it are zero; a partial chunk is the row's last sixteen bytes, shifted down
-            const int n = (int)left64 - 16 * (lane & 7), back = n < 16 ? 16 - n : 0;
+        } else {
+            const int chunk = 16 * (lane & 7), n = left - chunk, short0 = left < 16 ? 16 - left : 0;
+            const uint32_t back = n <= 0 ? chunk + short0 : n < 16 ? 16 - n : 0;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) x[q] = u32x4{0, 0, 0, 0};
-            if (n > 0) {
-#pragma unroll
-                for (int q = 0; q < 8; ++q) x[q] = shift_down(load16(k0, o.off[q] - back), back);
-            }
+            for (int q = 0; q < N; ++q) x[q] = load16(k0, o.off[q] - back);
         }
     };
-    auto store_stage = [&](bool km, const Operand &o, u32x4 x[8], uint8_t *slab) {
+    auto store_stage = [&](bool km, const Operand &o, int s, auto &x, uint8_t *slab) {
+        constexpr int N = sizeof(x) / sizeof(x[0]);
+        const int left = left_of(s);
+        if (left < BK) {
+            const int n = left - 16 * (lane & 7), shift = n >= 16 ? 0 : n > 0 ? 16 - n : 15;
+#pragma unroll
+            for (int q = 0; q < N; ++q) {
+                const uint32_t mask = (km ? 16 * q + (lane >> 2) < left : n > 0) ? ~0u : 0u;
+                if (!km) x[q] = shift_down(x[q], shift);
+                x[q].x &= mask; x[q].y &= mask; x[q].z &= mask; x[q].w &= mask;
+            }
+        }
         if (km && o.edge) {
 #pragma unroll
-            for (int q = 0; q < 8; ++q) x[q] = shift_down(x[q], o.shift);
+            for (int q = 0; q < N; ++q) x[q] = shift_down(x[q], o.shift);
         }
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
+        for (int q = 0; q < N; ++q) {
             const int row = km ? 16 * q + (lane >> 2) : 8 * q + (lane >> 3);
             const int at = km ? row * 64 + (((lane & 3) ^ (((row >> 2) & 1) << 1)) << 4)
                               : row * BK + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
@@ -159,20 +179,20 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
     GroupWords<4> words;
     uint32_t flag = 0;
 
-    uint8_t *slab_a = lds + wave * WAVE_LDS, *slab_b = slab_a + SLAB;
+    uint8_t *slab_a = lds + wave * WAVE_LDS, *slab_b = slab_a + SLAB_A;
     float *red = reinterpret_cast<float *>(lds);
     float v[16];
     for (int slice = SLICES ? 0 : split; slice < (SLICES ? p.splits : split + 1); ++slice) {
         const int ks_begin = slice * p.ks_per + (slice < p.ks_extra ? slice : p.ks_extra);
         const int ks_end = ks_begin + p.ks_per + (slice < p.ks_extra ? 1 : 0);
-        f32x16 acc[2][2];
+        f32x16 acc[MI][2];
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
             for (int j = 0; j < 2; ++j)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-        u32x4 xa[8], xb[8];
+        u32x4 xa[BM / 8], xb[8];
         // stage s is fetched into registers in the round before the one that multiplies it (the rounds
         // are written so that the code of each step exists once: the incomplete stage makes it long)
         const int first = ks_begin + wave;
@@ -186,8 +206,8 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
         }
         for (int s = EPI >= EPI_UPDATE ? first + 4 : first; s < ks_end + 4; s += 4) {
             if (s > first) {
-                store_stage(ATN, oa, xa, slab_a);
-                store_stage(BTN, ob, xb, slab_b);
+                store_stage(ATN, oa, s - 4, xa, slab_a);
+                store_stage(BTN, ob, s - 4, xb, slab_b);
             }
             if (s < ks_end) {
                 load_stage(ATN, oa, s, xa);
@@ -200,9 +220,9 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
             for (int sub = 0; sub < 2; ++sub) {
-                i32x8 af[2], bf[2];
+                i32x8 af[MI], bf[2];
 #pragma unroll
-                for (int i = 0; i < 2; ++i) af[i] = slab64_fragment<ATN>(slab_a, sub, i, lane);
+                for (int i = 0; i < MI; ++i) af[i] = slab64_fragment<ATN>(slab_a, sub, i, lane);
 #pragma unroll
                 for (int j = 0; j < 2; ++j) bf[j] = slab64_fragment<BTN>(slab_b, sub, j, lane);
                 // b as the "row" matrix: a lane gets consecutive output columns
@@ -218,13 +238,13 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
         const int frow = lane & 31, fkb = lane >> 5;
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
             for (int j = 0; j < 2; ++j)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     f32x4 o = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-                    *reinterpret_cast<f32x4 *>(red + (wave * T + 32 * i + frow) * RED_LD + 32 * j + 8 * g + 4 * fkb) = o;
+                    *reinterpret_cast<f32x4 *>(red + (wave * BM + 32 * i + frow) * RED_LD + 32 * j + 8 * g + 4 * fkb) = o;
                 }
         __syncthreads();
         auto summed = [&](int row, int col) {  // four columns, in wave order
@@ -232,7 +252,7 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
             f32x4 sum = *reinterpret_cast<const f32x4 *>(at);
 #pragma unroll
             for (int w = 1; w < 4; ++w) {
-                const f32x4 x = *reinterpret_cast<const f32x4 *>(at + w * T * RED_LD);
+                const f32x4 x = *reinterpret_cast<const f32x4 *>(at + w * BM * RED_LD);
                 sum.x += x.x; sum.y += x.y; sum.z += x.z; sum.w += x.w;
             }
             return sum;
@@ -255,6 +275,7 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
             }
             return;
         }
+        if (BM < 64 && (int)threadIdx.x >= BM * T / 16) break;  // (whole waves; nothing but the statistics is left for them)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const f32x4 sum = summed(threadIdx.x >> 2, 16 * (threadIdx.x & 3) + 4 * q);
@@ -269,7 +290,7 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
 
     StatsAcc st;
     const int64_t r = row0 + (threadIdx.x >> 2), c = col0 + 16 * (threadIdx.x & 3);
-    if (r < p.rows && c < p.cols) {
+    if (r < p.rows && c < p.cols && (int)threadIdx.x < BM * T / 16) {
         if ((p.cols & 15) == 0) finish16(p.ep, r, c, v, st);
         else finish16_ragged(p.ep, r, c, p.cols - c < 16 ? (int)(p.cols - c) : 16, v, st);
     }
@@ -278,9 +299,9 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
     }
 }
 
-template <int EPI, bool ATN, bool BTN, bool SLICES = false>
+template <int EPI, bool ATN, bool BTN, bool SLICES = false, int BM = 64>
 __global__ __launch_bounds__(256, SLICES ? 1 : 2) void gemm_any_kernel(const GemmArgs p) {
-    gemm_any<EPI, ATN, BTN, SLICES>(p, UpdateHook{});
+    gemm_any<EPI, ATN, BTN, SLICES, BM>(p, UpdateHook{});
 }
 template <int STATES>
 __global__ __launch_bounds__(256, 2) void gemm_any_update_kernel(const GemmArgs p, const UpdateHook upd) {
