@@ -598,9 +598,13 @@ static mp8_status launch_mfma(GemmArgs ga, Epilogue ep, const Plan &pl, int64_t 
         if (!only_acc) {
             const int64_t items = (cols & 3) == 0 ? rows * cols / 4 : rows * cols;
             int64_t blocks = std::min<int64_t>((items + 255) / 256, 256 * 16);
-            const int states = upd ? upd->states : 0;
-            hipLaunchKernelGGL(states == 2 ? splitk_finish_kernel<2>
-                                           : states == 1 ? splitk_finish_kernel<1> : splitk_finish_kernel<0>,
+            const int states = upd ? upd->states : -1;
+            static void (*const finish[4][3])(const float *, int, const Epilogue, const UpdateHook) = {
+                {splitk_finish_kernel<-1, 1>, splitk_finish_kernel<-1, 4>, splitk_finish_kernel<-1, 8>},
+                {splitk_finish_kernel<0, 1>, splitk_finish_kernel<0, 4>, splitk_finish_kernel<0, 8>},
+                {splitk_finish_kernel<1, 1>, splitk_finish_kernel<1, 4>, splitk_finish_kernel<1, 8>},
+                {splitk_finish_kernel<2, 1>, splitk_finish_kernel<2, 4>, splitk_finish_kernel<2, 8>}};
+            hipLaunchKernelGGL(finish[states + 1][pl.splits == 1 ? 0 : pl.splits <= 4 ? 1 : 2],
                                dim3((unsigned)blocks), dim3(256), 0, s, (const float *)partial, pl.splits, fin,
                                upd ? *upd : UpdateHook{});
             if (hipGetLastError() != hipSuccess) return MP8_ERR_HIP;
