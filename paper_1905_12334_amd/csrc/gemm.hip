@@ -9,6 +9,7 @@
 //   gemm_common.hpp   argument structs, the epilogue of a run of outputs, direct-to-LDS loads
 //   gemm_mfma.hpp     the general kernel: block tile BM x BN, ring of 2-4 stages of 128 bytes of
 //                     contraction, slot-scheduled MFMA loop, every operand layout, 3x3 convolutions
+//   gemm_stream.hpp   several 256x256 tiles per CU: the operand stream goes on from tile to tile
 //   gemm_shortk.hpp   contractions of one or two stages (all start-up and epilogue)
 //   gemm_wavek.hpp    small outputs with long contractions (contraction divided among waves)
 //   gemm_wave128.hpp  about one 128x128 tile per CU and a long contraction (every wave the whole tile)
@@ -38,6 +39,7 @@
 #include "gemm_finish.hpp"
 #include "gemm_mfma.hpp"
 #include "gemm_shortk.hpp"
+#include "gemm_stream.hpp"
 #include "gemm_wavek.hpp"
 #include "gemm_wave128.hpp"
 #include "gemm_qfwd.hpp"
@@ -286,6 +288,21 @@ static Plan make_plan(int64_t rows, int64_t cols, int64_t kc, int tile_config, i
     return pl;
 }
 
+// Outputs of more 256x256 tiles than CUs whose codes are rounded to nearest and nothing else is asked for: does
+// gemm_stream_kernel, which starts once and not per tile, beat the tile that make_plan names?  128x128 tiles (contractions of two stages: their
+// own kernel) / 256x256, us, b row-major, contraction-major; fill = tiles over whole rounds of 256:
+//   fill 1.00   16384 x 4096 x 256 31.6 30.7 / 28.5 26.8, x 512 43.3 43.8 / 37.1 37.6, x 768 59.0 59.8 / 50.7 48.5
+//        0.96   25088 x 1152 x 256 13.2 15.0 / 14.1 13.9, x 384 17.9 17.7 / 16.1 16.3, x 768 28.0 27.4 / 24.6 24.6
+//        0.77   25088 x 1024 x 256 13.0 14.6 / 13.9 13.7, x 384 17.5 17.3 / 15.9 16.0, x 1024 32.5 32.8 / 30.0 30.3, x 2048 55.2 55.4 / 46.8 47.6
+//        0.75   16384 x 1536 x 384 15.2 14.9 / 15.8 15.9, x 768 23.2 23.1 / 23.0 23.2, x 1024 27.6 27.8 / 27.2 28.4, x 2048 47.4 49.7 / 47.9 50.3
+//        0.62   16384 x 1280 x 1024 23.4 23.7 / 26.9 27.5, x 2048 44.2 43.6 / 45.1 46.1
+static bool stream_pays(int64_t rows, int64_t cols, int64_t ksteps, int layout) {
+    const int64_t nt = (rows + 255) / 256 * ((cols + 255) / 256);
+    if (nt <= kCUs || ksteps < 2 || (ksteps == 2 && layout == 0 && nt <= 3 * kCUs)) return false;
+    const double fill = (double)nt / (double)((nt + kCUs - 1) / kCUs * kCUs);
+    return fill >= 0.765;
+}
+
 // Can the direct-to-LDS kernels fetch (aligned) operands of a contraction that is not whole stages?  Row-major
 // ones have to end with a whole 16-byte chunk.
 static bool half_takes(int64_t rows, int64_t cols, int64_t kc, int layout) {
@@ -511,6 +528,15 @@ static bool poorly_filled(const Plan &pl, int64_t rows, int64_t cols, int acc_mo
     return false;
 }
 
+// More 256x256 tiles than CUs, codes to nearest: the kernel whose workgroups take several of them (null: another kernel).
+static void (*stream_kernel(void (*const pick[3])(const GemmArgs), bool unit))(const GemmArgs) {
+    const TileConfig &t = kTiles[T256x256];
+    if (pick == t.kernel) return unit ? gemm_stream_kernel<false, false, true> : gemm_stream_kernel<false, false, false>;
+    if (pick == t.kernel_bt) return unit ? gemm_stream_kernel<false, true, true> : gemm_stream_kernel<false, true, false>;
+    if (pick == t.kernel_tn) return unit ? gemm_stream_kernel<true, true, true> : gemm_stream_kernel<true, true, false>;
+    return nullptr;
+}
+
 // Launch the MFMA kernel chosen by `pick` (indexed by EPI_*) for plan `pl`, and the finishing
 // kernel when the epilogue cannot be fused.  `ga` carries the operands; its tiling, slicing and
 // epilogue fields are filled in here.
@@ -590,7 +616,10 @@ static mp8_status launch_mfma(GemmArgs ga, Epilogue ep, const Plan &pl, int64_t 
         hipLaunchKernelGGL(with_update, dim3((unsigned)nblocks), dim3(256), 0, s, ga, *upd);
         return hipGetLastError() == hipSuccess ? MP8_OK : MP8_ERR_HIP;
     }
-    hipLaunchKernelGGL(pick[epi], dim3((unsigned)nblocks), dim3(256), dyn_lds, s, ga);
+    if (const auto stream = epi == EPI_RNE && nblocks > kCUs && ga.ksteps >= 2 ? stream_kernel(pick, ep.alpha == 1.0f) : nullptr)
+        hipLaunchKernelGGL(stream, dim3(kCUs), dim3(256), 0, s, ga);
+    else
+        hipLaunchKernelGGL(pick[epi], dim3((unsigned)nblocks), dim3(256), dyn_lds, s, ga);
     if (hipGetLastError() != hipSuccess) return MP8_ERR_HIP;
     if (two_pass) {
         const bool only_acc = fin.acc_mode == 0 && fin.out8 == nullptr && fin.out8_t == nullptr &&
@@ -674,6 +703,13 @@ static mp8_status gemm_impl(mp8_op op, int64_t M, int64_t N, int64_t K, const ui
         pl.mfma = false;
     }
     if (tile_config > 0 && !pl.mfma) return MP8_ERR_UNSUPPORTED;
+    const bool codes_alone = acc_mode == 0 && out8 != nullptr && out8_t == nullptr && stats == nullptr && !ep.sr && !ep.sat && (cols & 15) == 0;
+    if (pl.mfma && tile_config == 0 && split_k == 0 && pl.splits == 1 && upd == nullptr && codes_alone &&
+        stream_pays(rows, cols, kc / BK, layout)) {
+        pl.tile = T256x256;
+        pl.tiles_m = (int)((rows + 255) / 256);
+        pl.tiles_n = (int)((cols + 255) / 256);
+    }
     if (!pl.mfma && aligned) pl = half_plan(rows, cols, kc, layout);
     auto has_workspace = [&](int splits) {
         return workspace != nullptr && workspace_bytes >= (size_t)splits * (size_t)rows * (size_t)cols * sizeof(float);

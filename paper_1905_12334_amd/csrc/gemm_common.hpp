@@ -271,12 +271,11 @@ __device__ __forceinline__ void finish16_ragged(const Epilogue &ep, int64_t r, i
     }
 }
 
-// Map the linear workgroup id to (slice, tile row, tile column).  Consecutive ids go to
+// Map workgroup bid of nb to (slice, tile row, tile column).  Consecutive ids go to
 // different XCDs (round robin), so ids are first regrouped so that each XCD works on a
 // contiguous range of tiles and its L2 sees operand reuse; inside the range, tiles are
 // walked in bands of 8 tile-rows.
-__device__ __forceinline__ void map_block(const GemmArgs &p, int &split, int &tm, int &tn) {
-    const uint32_t nb = gridDim.x, bid = blockIdx.x;
+__device__ __forceinline__ void map_tile(const GemmArgs &p, uint32_t nb, uint32_t bid, int &split, int &tm, int &tn) {
     const uint32_t xcd = bid & 7, idx = bid >> 3;
     const uint32_t per = nb >> 3, rem = nb & 7;
     const uint32_t pid = xcd * per + (xcd < rem ? xcd : rem) + idx;
@@ -294,6 +293,7 @@ __device__ __forceinline__ void map_block(const GemmArgs &p, int &split, int &tm
         tm = (int)(first + r);
     }
 }
+__device__ __forceinline__ void map_block(const GemmArgs &p, int &split, int &tm, int &tn) { map_tile(p, gridDim.x, blockIdx.x, split, tm, tn); }
 
 // EPI_UPDATE + s: EPI_FULL (without FP32 and transposed outputs), then the master-weight update of a rule
 // with s state words per weight (UpdateHook in gemm_finish.hpp).
