@@ -363,39 +363,37 @@ static bool any_in_32_rows(const Plan &pl, int64_t kc, int layout) {
 
 // The kernel that computes an unsplit weight gradient and applies the update in its epilogue, or null.  Such
 // an update costs neither a launch nor a pass over the gradient codes.  Built for the 64x64 tiles, whose
-// outputs are small: larger ones stream their weights and state faster in a kernel of its own.  Measured
-// against the two kernels (GPU time): 256^3 SGD 5.6 us, was 6.2; 4096 x 2048 x 512 SGD 15.8, was 16.7; ADAM
-// 19.3, was 19.8 there, but with 64 tiles (1024 x 512 x 512) 11.0 against 9.8: its divisions and square
-// roots then run on a quarter of the CUs, so it wants half of them to have a tile.
-static UpdateKernel update_kernel(const Plan &pl, int64_t cols, int layout, int states) {
+// outputs are small: larger ones stream their weights and state faster in a kernel of its own.  Whole training steps
+// (Q nodes, three GEMMs, update) in two launches against one, us, weights from the Infinity Cache / from memory: 256^3 SGD 15.5 against 14.8;
+// ADAM 256^3 17.1 20.0 against 17.0 19.4, 1024 x 512 x 256 (32 tiles) 23.2 24.2 against 21.8 23.2, 1280 x 768 x 512 (96) 28.7 28.5 against 27.2 27.9,
+// 4096 x 512 x 512 (64) 34.2 36.2 against 33.6 35.6, 640 x 1024 x 448 (112) 26.4 26.4 against 24.7 26.5.  (Without a gradient
+// to keep, ADAM on less than half of the CUs has its codes in the workspace, which such a call is asked for.)
+static UpdateKernel update_kernel(const Plan &pl, int64_t cols, int layout, int states, bool keeps_codes) {
     if (!pl.mfma || pl.splits != 1 || (cols & 15) != 0 || (layout != 0 && layout != 3)) return nullptr;
-    if (states == 2 && pl.tiles_m * pl.tiles_n < kCUs / 2) return nullptr;
+    if (states == 2 && !keeps_codes && pl.tiles_m * pl.tiles_n < kCUs / 2) return nullptr;
     if (pl.tile == T64x64w) return kWavekUpdate[pl.half][layout != 0][states];
     if (pl.tile == T64x64s2) return k64x64Update[pl.half][layout != 0][states];
     return nullptr;
 }
 
-// The same for gemm_any_kernel, contraction-major operands.  Its tiles run 2 kCUs at a time, and the update is a serial tail of each
-// (with ADAM one wave per SIMD divides and takes roots), so a last round that is nearly empty pays for all of it.  Two launches
-// against one, SGD / momentum / ADAM, us:
-//     12 tiles (65 x 200 x 130)      8.7  9.0 10.0    9.3  9.6 10.0: the kernel's chain of latencies has nothing beside it
-//     32       (300 x 104 x 1001)    8.9  9.3 10.2    8.6  8.8 10.2
-//    256       (1000 x 1000 x 1000) 12.6 12.8 14.5   12.0 12.5 14.9
-//    512       (256 x 1000 x 2048)  12.1 14.2 15.9   11.2 12.7 16.0
-//    533       (1000 x 2584 x 772)  20.7 23.1 25.6   21.7 23.9 28.5
-//    567       (200 x 520 x 4000)   15.7 17.6 20.4   17.5 18.9 27.1
-//    644       (64 x 1736 x 1455)   16.2 17.8 21.8   16.3 17.6 23.1
-//    800       (500 x 2520 x 1263)  21.1 23.9 29.1   21.5 23.6 29.9
-//    882       (256 x 3128 x 1149)  19.3 23.4 28.9   19.7 21.5 27.4: a second round three eighths full is enough, for SGD three quarters
-//   1003       (64 x 3736 x 1088)   19.0 23.3 29.5   18.3 20.6 27.7
-//   1107       (500 x 2600 x 1711)  26.0 30.2 36.9   25.9 29.5 37.7
-//   1612       (129 x 3944 x 1661)  30.7 37.1 46.6   30.6 32.9 41.9
-//   3995       (64 x 3000 x 5440)   61.7 78.8 102.0  61.6 67.2 90.3: SGD has the least to read, and streams as fast by itself
-// With statistics of the gradient every tile ends in atomics on one address.  Where all tiles end together that takes longer after the
-// updates (256 x 1000 x 2048 17.2 with momentum, in one launch 20.1; 129 x 2360 x 431 14.6 and 16.7), else it overlaps with
-// them (64 x 2872 x 196 13.2 and 10.6; 129 x 3288 x 644 20.9 and 19.0, with ADAM 24.7 and 27.5; 500 x 3112 x 815 with ADAM 32.1 and 26.5).  A few tiles
-// whose last column is eight wide end later in one launch when they round stochastically (256 x 520 x 256 8.5 9.0, in one 9.6
-// 10.0, to nearest 7.8 and 7.7; 536 wide 8.3 8.8 and 8.3 8.5; why, is not known).
+// The same for gemm_any_kernel, contraction-major operands.  Whole training steps in two launches against one, SGD / momentum / ADAM, us,
+// weights from the Infinity Cache:
+//      9 tiles (200 x 216 x 130)      21.9 22.3 22.6   19.9 20.4 22.1
+//     32       (300 x 104 x 1001)     24.0 24.4 25.5   22.0 22.4 24.2
+//    256       (1000 x 1000 x 1000)   35.8 36.6 38.6   32.4 33.1 34.9
+//    512       (256 x 1000 x 2048)    33.5 35.3 38.0   29.2 30.3 33.5
+//    533       (1000 x 2584 x 772)    57.3 59.6 62.1   54.2 55.6 60.7
+//    567       (200 x 536 x 4000)     43.9 44.9 47.9   39.9 42.9 45.4
+//    837       (64 x 1928 x 1700)     39.7 43.9 48.4   34.7 37.6 44.6
+//   1504       (129 x 3000 x 2002)    56.5 61.7 70.1   48.8 52.7 61.6
+//   3995       (64 x 3000 x 5440)     86.0 105.6 128.5 78.7 89.3 111.1
+// and from memory 256 tiles ADAM 38.9 and 37.8, 533 momentum 60.6 and 60.8, ADAM 64.2 and 66.0, 567 momentum 44.9 and 46.7, 1504 58.0 64.2 73.3 and
+// 54.1 62.9 77.3, 2820 (129 x 3000 x 3800) 82.8 95.4 and 83.0 101.3.  The update is a serial tail of each tile, 2 kCUs at a time, and a last round
+// that is nearly empty pays for all of it.  The lines below are those of the first kernel, whose update fetched its operands only
+// after the contraction: one launch was 20 % slower with ADAM on half-empty rounds, and with statistics, whose atomics on one address follow the updates,
+// where all tiles end together.  Today it would be the shorter on most of them, but which call is one kernel is part of what callers test.
+// With ADAM, tiles whose last column is eight wide end 4 us later (200 x 264 x 130 22.7, in one launch 25.8; 256 and 528 wide as above;
+// why, is not known).
 static UpdateKernel any_update_kernel(const Plan &pl, int64_t cols, int layout, const UpdateHook &upd, bool with_stats, bool stochastic) {
     static const UpdateKernel kernels[3] = {gemm_any_update_kernel<0>, gemm_any_update_kernel<1>, gemm_any_update_kernel<2>};
     const int64_t nt = (int64_t)pl.tiles_m * pl.tiles_n, round = 2 * kCUs;
@@ -750,7 +748,7 @@ static mp8_status gemm_impl(mp8_op op, int64_t M, int64_t N, int64_t K, const ui
     ga.b = b;
     ga.lda = lda;
     ga.ldb = ldb;
-    const UpdateKernel with_update = upd != nullptr ? update_kernel(pl, cols, layout, upd->states) : nullptr;
+    const UpdateKernel with_update = upd != nullptr ? update_kernel(pl, cols, layout, upd->states, out8 != nullptr) : nullptr;
     if (pl.half) {
         if (upd != nullptr && with_update == nullptr) return MP8_ERR_UNSUPPORTED;  // (two launches)
         const int form = pl.tile == T64x64s2 ? 0 : pl.tile == T64x64w ? 1 : 2;
@@ -817,7 +815,7 @@ static uint8_t *codes_for_separate_update(int64_t M, int64_t N, int64_t K, int f
     if ((atn && !btn) || (N & 15) != 0 || K > (INT64_MAX / 8) / std::max<int64_t>(N, 1)) return nullptr;
     const Plan pl = make_plan(K, N, M, 0, 0, (atn ? 1 : 0) | (btn ? 2 : 0));
     if (!pl.mfma || pl.splits != 1) return nullptr;
-    if (own_epilogue && update_kernel(pl, N, (atn ? 1 : 0) | (btn ? 2 : 0), states) != nullptr) return nullptr;
+    if (own_epilogue && update_kernel(pl, N, (atn ? 1 : 0) | (btn ? 2 : 0), states, g8_out != nullptr) != nullptr) return nullptr;
     if (g8_out != nullptr) return g8_out;
     return workspace != nullptr && workspace_bytes >= (size_t)(K * N) ? (uint8_t *)workspace : nullptr;
 }

@@ -92,3 +92,23 @@ def test_which_calls_update_in_the_epilogue(mp8, dims, rule, own):
     else:
         with pytest.raises(mp8.Mp8Error):
             call()
+
+
+@pytest.mark.parametrize("dims", [(256, 64, 64), (400, 208, 80), (512, 1024, 448), (2048, 1024, 960), (2100, 1024, 1008)])   # 1 tile, 8, 112, 240, 256
+@pytest.mark.parametrize("contraction_major", [True, False])
+def test_adam_with_a_gradient_buffer_is_one_kernel(mp8, dims, contraction_major):
+    """However few tiles there are, with whole and with incomplete stages, and with no workspace."""
+    import torch
+
+    from captured import launches
+    M, N, K = dims
+    M -= 0 if contraction_major else M % 16
+    a, b = (torch.full(s, 0x38, dtype=torch.uint8, device="cuda") for s in ((M, K), (M, N)))
+    w, m, v = (torch.zeros(K * N, dtype=t, device="cuda") for t in (torch.float16, torch.float32, torch.float32))
+    g = torch.empty(K * N, dtype=torch.uint8, device="cuda")
+    call = lambda: mp8.wgrad_adam_fp16_sr(M, N, K, a, b, w, m, v, 1e-3, 1.0, 1, g8_out=g,
+                                          flags=mp8.FLAG_CONTRACTION_MAJOR if contraction_major else 0)
+    call()
+    torch.cuda.synchronize()
+    names = launches(call)
+    assert len(names) == 1 and "update" in names[0], names
