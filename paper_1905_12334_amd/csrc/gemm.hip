@@ -951,8 +951,8 @@ extern "C" mp8_status mp8_wgrad_adam_fp16_sr(int64_t M, int64_t N, int64_t K, co
     upd.omb1 = 1.0f - beta1;
     upd.omb2 = 1.0f - beta2;
     // bias corrections as in mp8_adam_fp16_sr: the powers in double, the result as FP32
-    upd.c1 = (float)(1.0 - std::pow((double)beta1, (double)step));
-    upd.c2 = (float)(1.0 - std::pow((double)beta2, (double)step));
+    upd.ric1 = 1.0 / (double)(float)(1.0 - std::pow((double)beta1, (double)step));
+    upd.ric2 = 1.0 / (double)(float)(1.0 - std::pow((double)beta2, (double)step));
     upd.eps = eps;
     return wgrad_with_update(M, N, K, a, lda, b, ldb, alpha, g8_out, g_round, flags, g_seed, g_offset, stats, upd,
                              workspace, workspace_bytes, stream, [&](const uint8_t *codes) {

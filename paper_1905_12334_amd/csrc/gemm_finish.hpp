@@ -57,7 +57,8 @@ struct UpdateHook {
     int states;
     float *state0, *state1;
     float mu, wd;                            // momentum; L2 regularisation of either rule
-    float b1, b2, omb1, omb2, c1, c2, eps;   // ADAM
+    float b1, b2, omb1, omb2, eps;           // ADAM
+    double ric1, ric2;
 };
 
 // The hook's update rule: f(rule) with the rule object the stand-alone update kernels use.
@@ -65,7 +66,7 @@ template <int STATES, class F>
 __device__ __forceinline__ void with_rule(const UpdateHook &u, F f) {
     if constexpr (STATES == 0) f(SgdRule{u.neg_lr});
     else if constexpr (STATES == 1) f(MomentumRule{u.neg_lr, u.mu, u.wd});
-    else f(AdamRule{u.neg_lr, u.b1, u.b2, u.omb1, u.omb2, u.c1, u.c2, u.eps, u.wd});
+    else f(AdamRule{u.neg_lr, u.b1, u.b2, u.omb1, u.omb2, u.eps, u.wd, u.ric1, u.ric2});
 }
 
 template <int STATES>

@@ -250,7 +250,7 @@ extern "C" mp8_status mp8_adam_fp16_sr(uint16_t *w16, float *m, float *v, const 
     // bias corrections: the powers in double, the result as FP32
     const float c1 = (float)(1.0 - std::pow((double)beta1, (double)step));
     const float c2 = (float)(1.0 - std::pow((double)beta2, (double)step));
-    const mp8::AdamRule rule{-lr, beta1, beta2, 1.0f - beta1, 1.0f - beta2, c1, c2, eps, weight_decay};
+    const mp8::AdamRule rule{-lr, beta1, beta2, 1.0f - beta1, 1.0f - beta2, eps, weight_decay, 1.0 / (double)c1, 1.0 / (double)c2};
     return mp8::launch_state_update(w16, m, v, g8, n, rule, inv_loss_scale, round, seed, offset,
                                     skip_if_nonzero, w8_out, stats, stream);
 }
