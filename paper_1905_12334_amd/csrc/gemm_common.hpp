@@ -315,6 +315,15 @@ __device__ __forceinline__ void emit_partial4(const GemmArgs &p, int split, int6
     }
 }
 
+// EPI_RNE: the codes of such a group (the host sends only row lengths that are multiples of 16 here).
+__device__ __forceinline__ void emit_nearest4(const GemmArgs &p, int64_t r, int64_t c, f32x4 v) {
+    if (r >= p.rows || c >= p.cols) return;
+    const float y[4] = {v.x * p.ep.alpha, v.y * p.ep.alpha, v.z * p.ep.alpha, v.w * p.ep.alpha};
+    uint32_t pk = e5m2_pack4<false>(y, 0u, 0u, false);
+    if (p.ep.mask && conv_padding_row(p.ep, r)) pk = 0;
+    *reinterpret_cast<uint32_t *>(p.ep.out8 + r * p.cols + c) = pk;
+}
+
 // What a tile kernel does with sixteen consecutive columns c .. c+15 (c % 16 == 0) of output row
 // r, per epilogue variant (described at the main kernel): the RNE-only conversion, or the complete epilogue.
 template <int EPI, bool kThrough = false, bool kAlways = false>

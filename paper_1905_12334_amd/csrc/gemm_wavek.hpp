@@ -228,6 +228,19 @@ __device__ __forceinline__ void gemm_wavek(const GemmArgs &p, const UpdateHook &
             }
             emit_partial4(p, split, row0 + rr, col0 + 4 * q, t);
         }
+    } else if constexpr (EPI == EPI_RNE && BM * BN == 4 * 256) {
+        // Four columns per thread: sixteen would leave three of the four waves idle behind one wave's chain of LDS reads, sums and
+        // conversions (128 x 2048 x 4096 4.75 -> 4.56 us, 512 x 512 x 2048 3.54 -> 3.35).  Tiles of 32x64 are no faster with
+        // it, row-major 4.30 -> 4.39 (128 x 4096 x 2048), 64x64 slower, 7.64 -> 8.01 (1000 x 1024 x 4096).
+        const int rr = threadIdx.x / (BN / 4), q = threadIdx.x % (BN / 4);
+        f32x4 t = {};
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const f32x4 x = *reinterpret_cast<const f32x4 *>(red + (w * BM + rr) * RED_LD + 4 * q);
+            if (w == 0) t = x;
+            else { t.x += x.x; t.y += x.y; t.z += x.z; t.w += x.w; }
+        }
+        emit_nearest4(p, row0 + rr, col0 + 4 * q, t);
     } else if (BM * BN == 64 * 64 || threadIdx.x < BM * BN / 16) {  // whole waves either way
         constexpr int CG = BN / 16;
         const int rr = threadIdx.x / CG, cg = threadIdx.x % CG;
