@@ -366,7 +366,8 @@ static bool any_in_32_rows(const Plan &pl, int64_t kc, int layout) {
 // outputs are small: larger ones stream their weights and state faster in a kernel of its own.  Whole training steps
 // (Q nodes, three GEMMs, update) in two launches against one, us, weights from the Infinity Cache / from memory: 256^3 SGD 15.5 against 14.8;
 // ADAM 256^3 17.1 20.0 against 17.0 19.4, 1024 x 512 x 256 (32 tiles) 23.2 24.2 against 21.8 23.2, 1280 x 768 x 512 (96) 28.7 28.5 against 27.2 27.9,
-// 4096 x 512 x 512 (64) 34.2 36.2 against 33.6 35.6, 640 x 1024 x 448 (112) 26.4 26.4 against 24.7 26.5.  (Without a gradient
+// 4096 x 512 x 512 (64) 34.2 36.2 against 33.6 35.6, 640 x 1024 x 448 (112) 26.4 26.4 against 24.7 26.5 (with ADAM's
+// corrections still divisions: since then one launch takes 0.3 to 0.8 less).  (Without a gradient
 // to keep, ADAM on less than half of the CUs has its codes in the workspace, which such a call is asked for.)
 static UpdateKernel update_kernel(const Plan &pl, int64_t cols, int layout, int states, bool keeps_codes) {
     if (!pl.mfma || pl.splits != 1 || (cols & 15) != 0 || (layout != 0 && layout != 3)) return nullptr;
@@ -388,7 +389,7 @@ static UpdateKernel update_kernel(const Plan &pl, int64_t cols, int layout, int 
 //   1504       (129 x 3000 x 2002)    56.5 61.7 70.1   48.8 52.7 61.6
 //   3995       (64 x 3000 x 5440)     86.0 105.6 128.5 78.7 89.3 111.1
 // and from memory 256 tiles ADAM 38.9 and 37.8, 533 momentum 60.6 and 60.8, ADAM 64.2 and 66.0, 567 momentum 44.9 and 46.7, 1504 58.0 64.2 73.3 and
-// 54.1 62.9 77.3, 2820 (129 x 3000 x 3800) 82.8 95.4 and 83.0 101.3.  The update is a serial tail of each tile, 2 kCUs at a time, and a last round
+// 54.1 62.9 77.3, 2820 (129 x 3000 x 3800) 82.8 95.4 and 83.0 101.3 (ADAM's corrections still divisions).  The update is a serial tail of each tile, 2 kCUs at a time, and a last round
 // that is nearly empty pays for all of it.  The lines below are those of the first kernel, whose update fetched its operands only
 // after the contraction: one launch was 20 % slower with ADAM on half-empty rounds, and with statistics, whose atomics on one address follow the updates,
 // where all tiles end together.  Today it would be the shorter on most of them, but which call is one kernel is part of what callers test.
