@@ -353,9 +353,10 @@ static Plan any_plan(int64_t rows, int64_t cols, int64_t kc) {
 
 // Tiles of 32 rows (row-major a, unsplit): twice as many CUs share the work while half of them would idle, and up to three
 // stages they also end sooner on all of them.  In 64 rows / in 32, us, b row-major and contraction-major: 256 x 1000 x 2048
-// (64 tiles of 64) contraction-major 8.9 / 8.0, 1000 x 500 x 1001 (128) 7.2 7.1 / 6.8 6.8, 17 x 100 x 200 (2) 4.7 4.9 / 4.5 4.6; 600 x 1000
-// (160) x 300 5.5 5.9 / 5.2 5.6, x 2000 8.2 10.5 / 8.2 11.0; 1000 x 1000 (256) x 200 5.5 5.9 / 5.3 5.7, x 1000 7.0 8.0 / 7.3 8.8; 1500 x 1000
-// (384) x 300 6.5 6.8 / 6.0 6.6, x 1500 11.8 12.8 / 11.4 13.6; 4000 x 500 (504) x 777 10.8 11.0 / 12.6 12.3.
+// (64 tiles of 64) contraction-major 9.4 / 7.2, 1000 x 500 x 1001 (128) 7.9 7.7 / 6.6 6.2, 17 x 100 x 200 (2) 5.1 5.1 / 4.4 4.3; 600 x 1000
+// (160) x 300 5.2 5.4 / 4.9 5.1, x 2000 8.3 9.9 / 8.3 11.6; 1000 x 1000 (256) x 200 5.3 5.4 / 5.0 5.2, x 380 5.3 5.5 / 5.1 5.5, x 500 5.4 5.6 /
+// 5.3 5.9, x 1000 6.8 7.2 / 6.9 7.9; 1500 x 1000 (384) x 300 6.0 6.3 / 5.8 6.0, x 1500 11.4 12.5 / 11.3 13.1; 4000 x 500 (504) x 380
+// 6.3 6.7 / 8.4 8.7.
 static bool any_in_32_rows(const Plan &pl, int64_t kc, int layout) {
     const int64_t nt = (int64_t)pl.tiles_m * pl.tiles_n;
     return pl.splits == 1 && !(layout & 1) && (nt <= kCUs / 2 || (nt <= kCUs + kCUs / 2 && kc <= 3 * BK));
@@ -595,7 +596,6 @@ static mp8_status launch_mfma(GemmArgs ga, Epilogue ep, const Plan &pl, int64_t 
     ga.cols = cols;
     ga.ksteps = (int)((kc + BK - 1) / BK);
     ga.tail = (int)(kc % BK);
-    ga.kc = kc;
     ga.splits = pl.splits;
     ga.tiles_m = pl.tiles_m;
     ga.tiles_n = pl.tiles_n;

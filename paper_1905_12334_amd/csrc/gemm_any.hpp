@@ -26,17 +26,17 @@ namespace mp8 {
 // BM = 32: tiles of 32 rows for small outputs (any_in_32_rows); the order of the additions is the same.
 //
 // What bounds it: with one tile per CU the chain of a wave -- a stage's loads, their way through the registers into LDS,
-// conversion, multiplication -- of which the loads overlap with the rest; with more tiles the path from L2, of which a
-// 64-column piece of a contraction-major row uses half of each 128-byte line.  256 x 1000 x 2048, back to back: forward 10.3 us while the
-// multiplications waited for the next stage's loads (a branch for the incomplete stage made the compiler wait there), 8.9
-// without the wait, 8.0 in tiles of 32 rows; backward data 6.8, 5.7; one thread per output element 639.  1500 x 1000 x 1500, whose tiles share
-// three CUs out of four unevenly, is slower for it (11.0 -> 11.6, contraction-major 12.3 -> 12.8), 500 x 2000 x 3000 faster (12.4 -> 12.3, 14.4 -> 13.2).
-// Eight waves per tile instead of four (256 x 1001, contraction 2003: row-major 12.1 us instead of 11.1) and two 8-byte loads for
-// one of 16 (10.7 instead of 10.2 at 256 x 1000, contraction 2048) were slower.
+// conversion, multiplication -- of which the loads overlap with the rest; with two tiles per CU every instruction of that chain, and the
+// path from L2, of which a 64-column piece of a contraction-major row uses half of each 128-byte line.  Back to back, us, loads that the
+// multiplications wait for (a branch for the incomplete stage made the compiler wait there) / loads whose addresses every stage works
+// out / now: 256 x 1000 x 2048 forward 10.4 / 8.0 / 7.4 (tiles of 32 rows but for the first), backward data 6.5 / 5.3 / 5.2, one thread
+// per output element 639; 1500 x 1000 x 1500 11.8 / 12.0 / 11.3, b contraction-major 12.7 / 13.2 / 12.5, both 14.7 / 14.8 / 14.1; 500 x 2000 x 3000
+// 13.4 13.1 12.1, 15.7 13.8 13.4, 16.7 15.3 14.4.  A few tiles more than CUs, both operands contraction-major and more than 15 stages are what
+// the first form did better: 1100 x 1000 x 3000 21.9 / 24.2 / 23.3, 1300 x 1000 x 2003 17.3 / 18.5 / 17.7.
 // EPI_UPDATE: an unsplit weight gradient applies the master-weight update itself (columns a multiple of eight:
 // neighbouring lanes share random blocks), with the code of the other kernels' epilogues: no launch and no pass
-// over the gradient codes.  256 x 1000 x 2048 with momentum 13.7 -> 12.6 us, its training step 40.0 -> 37.2; with the weights, the state
-// and the random words fetched behind the first stage's loads instead of after the contraction 12.7 -> 10.1, 37.0 -> 34.4.
+// over the gradient codes: 256 x 1000 x 2048 with momentum 13.7 -> 12.6 us; with the weights, the state
+// and the random words fetched behind the first stage's loads instead of after the contraction 12.7 -> 10.1, now 9.5.
 // Needs a contraction of at least 16, and 16 rows / columns of a contraction-major operand (an edge
 // chunk is read as the last 16 bytes of its row and shifted into place).
 template <int EPI, bool ATN, bool BTN, bool SLICES, int BM = 64>
@@ -63,12 +63,12 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
     //   row-major: load q brings tile rows 8q .. 8q+7, lane l sixteen contraction bytes of row
     //   8q + l/8, chunk l%8; rows beyond the matrix are clamped to its last row (never stored)
     //   contraction-major: load q brings contraction rows 16q .. 16q+15 of 64 bytes, lane l chunk l%4
-    //   of row 16q + l/4 (one lane offset serves all loads: the rest of their addresses is uniform); a chunk
-    //   that would leave the row is read as its last sixteen bytes and shifted down by `shift` bytes
+    //   of row 16q + l/4 (one lane offset, off[0], serves all loads: the rest of their addresses, at[q], is uniform); a
+    //   chunk that would leave the row is read as its last sixteen bytes and shifted down by `shift` bytes
     struct Operand {
         const uint8_t *base;
         int64_t ld, kstep;
-        uint32_t off[8];
+        uint32_t off[8], at[8];
         int shift;
         bool edge;
     };
@@ -79,12 +79,13 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
         o.shift = 0;
         o.edge = km && first + T > limit;
         if (km) {
-            o.base = uniform_ptr(x + first);
+            o.base = uniform_ptr(x + first - 16 * ld);
             const int64_t m = 16 * (lane & 3), last = limit - 16 - first;
             o.shift = m > last ? (int)(m - last < 15 ? m - last : 15) : 0;
             // (last is negative in a tile narrower than sixteen columns: the sum is not)
-            o.off[1] = (uint32_t)((m > last ? last : m) + 16);  // in the first contraction row
-            o.off[0] = (uint32_t)((lane >> 2) * ld) + o.off[1];
+            o.off[0] = (uint32_t)((lane >> 2) * ld + (m > last ? last : m) + 16);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) o.at[q] = (uint32_t)((16 * q + 16) * ld);
         } else {
             o.base = uniform_ptr(x + first * ld);
 #pragma unroll
@@ -94,10 +95,10 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
                 o.off[q] = (uint32_t)(r * ld) + 16 * (lane & 7) + 16;
             }
         }
-        o.base -= 16;  // (what is subtracted from a lane offset leaves it non-negative: they are unsigned)
+        o.base -= 16;  // (16 bytes, and 16 contraction rows above: what is subtracted leaves off and at, which are unsigned, non-negative)
         return o;
     };
-    const Operand oa = operand(ATN, p.a, p.lda, row0, p.rows), ob = operand(BTN, p.b, p.ldb, col0, p.cols);
+    Operand oa = operand(ATN, p.a, p.lda, row0, p.rows), ob = operand(BTN, p.b, p.ldb, col0, p.cols);
 
     // (address space 1: the base pointers have been through integers, and the compiler has to know
     // that they point to global memory)
@@ -116,57 +117,67 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
         hi >>= s;
         return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
     };
-    // A stage into registers: the same loads whether it is complete or not, so that nothing but the next round waits for them.
-    // (With a branch for the incomplete stage the compiler joined the two ways behind a wait for all loads.)  What lies beyond
-    // the contraction is read from its first row or chunk, and a partial chunk as the last sixteen bytes of its row:
-    // store_stage puts zeros there, and shifts the partial chunk down.
-    auto left_of = [&](int s) {
-        const int64_t left = p.kc - (int64_t)s * BK;
-        return left < BK ? (int)left : BK;
-    };
-    auto load_stage = [&](bool km, const Operand &o, int s, auto &x) {
+    // A stage into registers: the same loads whether it is complete or not, so that nothing but the next round waits for them
+    // (with a branch around them the compiler joined the two ways behind a wait for all loads).  The incomplete stage, the last one of
+    // all, only changes where they read, in a branch of its own: complete ones go without an instruction for it.  Its partial chunk is read as the last
+    // sixteen bytes of the row and its partial sixteen contraction rows as the last sixteen of all, what lies beyond it as something that
+    // exists: store_stage puts them in place, and zeros behind them.
+    auto left_of = [&](int s) { return p.tail != 0 && s == p.ksteps - 1 ? p.tail : BK; };
+    auto load_stage = [&](bool km, Operand &o, int s, auto &x) {
         constexpr int N = sizeof(x) / sizeof(x[0]);  // loads: eight rows or sixteen contraction rows each
-        const uint8_t *k0 = o.base + (int64_t)s * o.kstep;
         const int left = left_of(s);
-        if (km) {
-            const int last = (left - 1) >> 4;  // the last load with anything in it: the others repeat it
-            const uint32_t off = 16 * last + (lane >> 2) < left ? o.off[0] : o.off[1];
-            const int64_t step = 16 * o.ld;
+        if (left < BK) {
+            if (km) {
 #pragma unroll
-            for (int q = 0; q < N; ++q) {
-                x[q] = load16(k0, q < last ? o.off[0] : off);
-                k0 += q < last ? step : 0;
+                for (int q = 0; q < N; ++q)
+                    if (16 * q + 16 > left) o.at[q] = (uint32_t)(left * o.ld);
+            } else {
+                const int chunk = 16 * (lane & 7), n = left - chunk, short0 = left < 16 ? 16 - left : 0;
+                const uint32_t back = n <= 0 ? chunk + short0 : n < 16 ? 16 - n : 0;
+#pragma unroll
+                for (int q = 0; q < N; ++q) o.off[q] -= back;
             }
-        } else {
-            const int chunk = 16 * (lane & 7), n = left - chunk, short0 = left < 16 ? 16 - left : 0;
-            const uint32_t back = n <= 0 ? chunk + short0 : n < 16 ? 16 - n : 0;
+        }
+        const uint8_t *k0 = o.base + (int64_t)s * o.kstep;
 #pragma unroll
-            for (int q = 0; q < N; ++q) x[q] = load16(k0, o.off[q] - back);
+        for (int q = 0; q < N; ++q) {
+            const uint8_t *from = km ? k0 + o.at[q] : k0;
+            if (km) asm("" : "+s"(from));  // (a scalar base: left alone, the compiler adds in vector registers)
+            x[q] = load16(from, o.off[km ? 0 : q]);
         }
     };
     auto store_stage = [&](bool km, const Operand &o, int s, auto &x, uint8_t *slab) {
         constexpr int N = sizeof(x) / sizeof(x[0]);
         const int left = left_of(s);
-        if (left < BK) {
-            const int n = left - 16 * (lane & 7), shift = n >= 16 ? 0 : n > 0 ? 16 - n : 15;
-#pragma unroll
-            for (int q = 0; q < N; ++q) {
-                const uint32_t mask = (km ? 16 * q + (lane >> 2) < left : n > 0) ? ~0u : 0u;
-                if (!km) x[q] = shift_down(x[q], shift);
-                x[q].x &= mask; x[q].y &= mask; x[q].z &= mask; x[q].w &= mask;
-            }
-        }
+        auto put = [&](int row, u32x4 v) {
+            const int at = km ? row * 64 + (((lane & 3) ^ (((row >> 2) & 1) << 1)) << 4)
+                              : row * BK + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+            *reinterpret_cast<u32x4 *>(slab + at) = v;
+        };
+        auto row = [&](int q) { return km ? 16 * q + (lane >> 2) : 8 * q + (lane >> 3); };
         if (km && o.edge) {
 #pragma unroll
             for (int q = 0; q < N; ++q) x[q] = shift_down(x[q], o.shift);
         }
+        if (left < BK && km) {  // (LDS operations of a wave are done in order)
 #pragma unroll
-        for (int q = 0; q < N; ++q) {
-            const int row = km ? 16 * q + (lane >> 2) : 8 * q + (lane >> 3);
-            const int at = km ? row * 64 + (((lane & 3) ^ (((row >> 2) & 1) << 1)) << 4)
-                              : row * BK + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
-            *reinterpret_cast<u32x4 *>(slab + at) = x[q];
+            for (int q = 0; q < N; ++q) put(row(q), 16 * q + 16 <= left ? x[q] : u32x4{});
+            const int r = left - 16 + (lane >> 2);
+            put(r & (BK - 1), r >= 0 ? x[N - 1] : u32x4{});
+            asm volatile("");  // (or the compiler joins the stores of both ways)
+            return;
         }
+        if (left < BK) {
+            const int n = left - 16 * (lane & 7), shift = n >= 16 ? 0 : n > 0 ? 16 - n : 15;
+            const uint32_t mask = n > 0 ? ~0u : 0u;
+#pragma unroll
+            for (int q = 0; q < N; ++q) {
+                x[q] = shift_down(x[q], shift);
+                x[q].x &= mask; x[q].y &= mask; x[q].z &= mask; x[q].w &= mask;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < N; ++q) put(row(q), x[q]);
     };
 
     // what this thread updates: four groups of four weights, 16 lanes side by side in a row of the tile
@@ -218,6 +229,9 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            // A wave that multiplies goes ahead of one that fetches: two workgroups of a CU otherwise fetch and multiply in step
+            // (1500 x 1000, contraction 1500 11.8 -> 11.2 us, 700 8.6 -> 8.1, 100 5.1 -> 5.0; one workgroup per CU as before).
+            __builtin_amdgcn_s_setprio(1);
 #pragma unroll
             for (int sub = 0; sub < 2; ++sub) {
                 i32x8 af[MI], bf[2];
@@ -228,6 +242,7 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
                 // b as the "row" matrix: a lane gets consecutive output columns
                 mma64_tiles<true>(bf, af, acc);
             }
+            __builtin_amdgcn_s_setprio(0);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");

@@ -95,7 +95,6 @@ struct GemmArgs {
     // nothing in their loops, knows of it: global stage 0 is the incomplete one and stage s > 0 covers
     // indices BK (s - 1) ...  What lies beyond the contraction reads as zero (see dma16_or_zero).
     int tail;
-    int64_t kc;         // contraction length (gemm_any_kernel)
     int splits;         // number of contraction slices
     int tiles_m, tiles_n;
     // host-side precomputation for the workgroup -> (slice, tile) map, so that the kernel's
