@@ -194,8 +194,9 @@ size_t mp8_gemm_fp8_workspace_bytes_tuned(mp8_op op, int64_t M, int64_t N, int64
 /* Host only: which tile configuration (1-based, *tile_out) and how many contraction slices (*splits_out) an
  * aligned call with these arguments would take; 0 and 1 where it takes a kernel that is not among the tile
  * configurations (contractions that are not a multiple of 128, and contraction-major operands whose row length
- * is not a multiple of 16).  Calls that ask for nothing but codes to nearest take 256x256 tiles more often than this says.
- * For tests and tuning. */
+ * is not a multiple of 16).  The call meant is one that asks for nothing but 8-bit codes to nearest; one that
+ * also asks for anything else (a flag, stochastic rounding, another result, statistics, an update) takes what is
+ * reported with MP8_FLAG_SATURATE, which is another tile for some large outputs.  For tests and tuning. */
 mp8_status mp8_gemm_fp8_plan(mp8_op op, int64_t M, int64_t N, int64_t K, int flags, int tile_config,
                              int split_k, int *tile_out, int *splits_out);
 int mp8_gemm_num_tile_configs(void);

@@ -355,8 +355,8 @@ def conv3x3_wgrad_momentum_fp16_sr(B, H, W, Cin, Cout, x8, e8, w16, velocity, lr
 
 
 def gemm_fp8_plan(op, M, N, K, flags=0, tile_config=0, split_k=0):
-    """(tile configuration name, contraction slices) of an aligned call; (None, 1) where it takes a kernel that is not
-    among the tile configurations."""
+    """(tile configuration name, contraction slices) of an aligned call that asks for codes to nearest alone (any other: with
+    FLAG_SATURATE); (None, 1) where it takes a kernel that is not among the tile configurations."""
     t, s = C.c_int(0), C.c_int(0)
     _check(lib().mp8_gemm_fp8_plan(op, M, N, K, flags, tile_config, split_k, C.byref(t), C.byref(s)),
            "mp8_gemm_fp8_plan")

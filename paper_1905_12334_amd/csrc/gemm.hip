@@ -289,18 +289,35 @@ static Plan make_plan(int64_t rows, int64_t cols, int64_t kc, int tile_config, i
 }
 
 // Outputs of more 256x256 tiles than CUs whose codes are rounded to nearest and nothing else is asked for: does
-// gemm_stream_kernel, which starts once and not per tile, beat the tile that make_plan names?  128x128 tiles (contractions of two stages: their
-// own kernel) / 256x256, us, b row-major, contraction-major; fill = tiles over whole rounds of 256:
-//   fill 1.00   16384 x 4096 x 256 31.6 30.7 / 28.5 26.8, x 512 43.3 43.8 / 37.1 37.6, x 768 59.0 59.8 / 50.7 48.5
-//        0.96   25088 x 1152 x 256 13.2 15.0 / 14.1 13.9, x 384 17.9 17.7 / 16.1 16.3, x 768 28.0 27.4 / 24.6 24.6
-//        0.77   25088 x 1024 x 256 13.0 14.6 / 13.9 13.7, x 384 17.5 17.3 / 15.9 16.0, x 1024 32.5 32.8 / 30.0 30.3, x 2048 55.2 55.4 / 46.8 47.6
-//        0.75   16384 x 1536 x 384 15.2 14.9 / 15.8 15.9, x 768 23.2 23.1 / 23.0 23.2, x 1024 27.6 27.8 / 27.2 28.4, x 2048 47.4 49.7 / 47.9 50.3
-//        0.62   16384 x 1280 x 1024 23.4 23.7 / 26.9 27.5, x 2048 44.2 43.6 / 45.1 46.1
+// gemm_stream_kernel, which starts once and not per tile, beat the tile that make_plan names?  Both deal whole tiles to the CUs, 256 of them or
+// 512 of 128x128 at a time, and what counts is how many rounds that makes: a round of 256x256 tiles takes as long as 1.6 to 2 of 128x128,
+// so two of them have to stand for four, four for seven.  128x128 tiles (contractions of two stages: their own kernel) / 256x256, us, b
+// row-major, contraction-major, both operands contraction-major:
+//   rounds 4 / 2   25088 x 1024 (392 tiles of 256x256) x 384 17.4 17.4 17.9 / 17.0 17.0 17.2, x 1024 32.1 32.2 32.5 / 29.0 29.5 30.0, x 2048 56.3 54.3 54.8 / 47.5 47.5 48.6
+//          4 / 2   25088 x 960 (as many) x 384 17.2 18.1 18.6 / 17.2 17.5 17.4, x 1024 31.9 33.6 34.2 / 29.2 29.3 30.1
+//          8 / 4   16384 x 4096 (1024) x 512 46.2 47.5 45.6 / 38.9 40.4 40.1, x 768 58.1 59.2 58.8 / 48.7 51.0 50.4
+//          3 / 2   25088 x 896 (392) x 384 14.4 14.5 15.4 / 17.0 17.0 17.1, x 1024 27.6 27.3 28.1 / 29.6 29.9 30.4, x 2048 45.8 45.5 47.5 / 49.0 49.9 51.5
+//          3 / 2   25088 x 832 (392) x 384 14.4 14.8 15.4 / 16.9 17.1 17.4, 65536 x 272 (512) 16.4 17.1 17.1 / 18.1 18.7 18.5, 6016 x 4096 (384) 14.9 15.0 15.6 / 16.8 17.1 17.1
+//          2 / 2   100352 x 64 (392) x 384 12.2 12.0 12.2 / 18.5 18.6 18.7, 131072 x 16 (512) 13.0 13.1 13.3 / 19.0 19.4 19.2
+// Below 392 tiles the two differ by less than 5 % either way.  Two stages, row-major: 25088 x 1024 x 256 12.7 / 14.5, 38400 x 1536 (rows
+// that end inside a tile) 25.0 / 27.1, but 16384 x 4096 26.9 / 27.8, 16384 x 4000 27.7 / 27.0, 43504 x 2560 45.8 / 44.8.
 static bool stream_pays(int64_t rows, int64_t cols, int64_t ksteps, int layout) {
-    const int64_t nt = (rows + 255) / 256 * ((cols + 255) / 256);
-    if (nt <= kCUs || ksteps < 2 || (ksteps == 2 && layout == 0 && nt <= 3 * kCUs)) return false;
-    const double fill = (double)nt / (double)((nt + kCUs - 1) / kCUs * kCUs);
-    return fill >= 0.765;
+    auto tiles = [&](int64_t t) { return (rows + t - 1) / t * ((cols + t - 1) / t); };
+    const int64_t nt = tiles(256), rounds = (nt + kCUs - 1) / kCUs, rounds128 = (tiles(128) + 2 * kCUs - 1) / (2 * kCUs);
+    const double round = (double)rounds * kCUs;
+    if (nt <= kCUs || ksteps < 2 || nt < 0.765 * round || 4 * rounds128 < 7 * rounds) return false;
+    return ksteps > 2 || layout != 0 || (nt > 3 * kCUs && (double)rows * (double)cols >= 0.95 * 256 * 256 * round);
+}
+
+// The plan of an aligned call.  codes_alone: it asks for codes to nearest, in rows of a multiple of 16, and nothing else.
+static Plan plan_of(int64_t rows, int64_t cols, int64_t kc, int tile_config, int split_k, int layout, bool codes_alone) {
+    Plan pl = make_plan(rows, cols, kc, tile_config, split_k, layout);
+    if (codes_alone && pl.mfma && tile_config == 0 && split_k == 0 && pl.splits == 1 && stream_pays(rows, cols, kc / BK, layout)) {
+        pl.tile = T256x256;
+        pl.tiles_m = (int)((rows + 255) / 256);
+        pl.tiles_n = (int)((cols + 255) / 256);
+    }
+    return pl;
 }
 
 // Can the direct-to-LDS kernels fetch (aligned) operands of a contraction that is not whole stages?  Row-major
@@ -468,7 +485,8 @@ extern "C" mp8_status mp8_gemm_fp8_plan(mp8_op op, int64_t M, int64_t N, int64_t
     if (atn && !btn) return MP8_ERR_UNSUPPORTED;
     int64_t rows, cols, kc;
     op_dims(op, M, N, K, rows, cols, kc);
-    const Plan pl = make_plan(rows, cols, kc, tile_config, split_k, (atn ? 1 : 0) | (btn ? 2 : 0));
+    const Plan pl = plan_of(rows, cols, kc, tile_config, split_k, (atn ? 1 : 0) | (btn ? 2 : 0),
+                            (flags & MP8_FLAG_SATURATE) == 0 && (cols & 15) == 0);
     if (tile_out) *tile_out = pl.mfma ? pl.tile + 1 : 0;
     if (splits_out) *splits_out = pl.splits;
     return MP8_OK;
@@ -693,7 +711,9 @@ static mp8_status gemm_impl(mp8_op op, int64_t M, int64_t N, int64_t K, const ui
     hipStream_t s = (hipStream_t)stream;
 
     const int layout = (atn ? 1 : 0) | (btn ? 2 : 0);
-    Plan pl = make_plan(rows, cols, kc, tile_config, split_k, layout);
+    const bool codes_alone = upd == nullptr && acc_mode == 0 && out8 != nullptr && out8_t == nullptr && stats == nullptr && !ep.sr && !ep.sat &&
+                             (cols & 15) == 0;
+    Plan pl = plan_of(rows, cols, kc, tile_config, split_k, layout, codes_alone);
     // the direct-to-LDS kernels want 16-byte aligned rows and 32-bit offsets inside a 256-row tile
     const bool aligned = (((uintptr_t)a | (uintptr_t)b) & 15u) == 0 && (lda & 15) == 0 &&
                          (ldb & 15) == 0 && lda < (1 << 24) && ldb < (1 << 24);
@@ -702,13 +722,6 @@ static mp8_status gemm_impl(mp8_op op, int64_t M, int64_t N, int64_t K, const ui
         pl.mfma = false;
     }
     if (tile_config > 0 && !pl.mfma) return MP8_ERR_UNSUPPORTED;
-    const bool codes_alone = acc_mode == 0 && out8 != nullptr && out8_t == nullptr && stats == nullptr && !ep.sr && !ep.sat && (cols & 15) == 0;
-    if (pl.mfma && tile_config == 0 && split_k == 0 && pl.splits == 1 && upd == nullptr && codes_alone &&
-        stream_pays(rows, cols, kc / BK, layout)) {
-        pl.tile = T256x256;
-        pl.tiles_m = (int)((rows + 255) / 256);
-        pl.tiles_n = (int)((cols + 255) / 256);
-    }
     if (!pl.mfma && aligned) pl = half_plan(rows, cols, kc, layout);
     auto has_workspace = [&](int splits) {
         return workspace != nullptr && workspace_bytes >= (size_t)splits * (size_t)rows * (size_t)cols * sizeof(float);
