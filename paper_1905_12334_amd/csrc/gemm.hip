@@ -607,6 +607,10 @@ static mp8_status launch_mfma(GemmArgs ga, Epilogue ep, const Plan &pl, int64_t 
     // 512 x 512 4.5 -> 4.3; where it is added to, only half-precision) and, half-precision, in rows that fill no tile (65536 x 32 x 272 13.4 -> 12.6).
     ep.acc_lines = acc_mode != 0 && (cols & 15) == 0 &&
                    (pl.half ? nblocks > kCUs / 2 && std::min(rows, cols) >= (ep.sr && acc_mode == 1 ? 65 : 64) : acc_mode == 2 || nblocks > kCUs / 2);
+    // What is added to by the next call as well stays in the L2s while they hold it (32 MB).  Past them / into them, us: added to, with
+    // codes, 64 x 64 x 128 4.3 / 3.7, 128 x 512 x 256 5.0 / 4.2, 2048 x 2048 x 256 (16 MB) 13.8 / 12.0; 4096 x 4096 x 512 (64 MB) as fast,
+    // 8192 x 8192 x 512 194 / 201.
+    if (ep.acc_lines != 0 && acc_mode == 2 && rows * cols <= (int64_t)1 << 23) ep.acc_lines = 2;
     if (nblocks > 0x7FFFFFFFLL) return MP8_ERR_UNSUPPORTED;
     if (validate_only) return MP8_OK;  // every check has passed; nothing is enqueued
 

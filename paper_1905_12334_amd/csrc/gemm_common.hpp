@@ -44,7 +44,7 @@ struct Epilogue {
     float alpha;
     float *acc;
     int acc_mode;
-    int acc_lines;   // tile_epilogue: the FP32 result by a pass of its own ahead of the codes (see launch_mfma)
+    int acc_lines;   // tile_epilogue: the FP32 result by a pass of its own ahead of the codes, past the L2 (1) or into it (2; see launch_mfma)
     uint8_t *out8;
     uint8_t *out8_t;
     int sr;

@@ -125,22 +125,27 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs &p, const f32x16 (&
             const bool acc_done = EPI == EPI_FULL && p.ep.acc_lines != 0;
             if (acc_done) {
                 constexpr int F4 = WTN / 4;
+                auto lines = [&](auto plain) {
 #pragma unroll 4
-                for (int item = lane; item < BANDS * 32 * F4; item += 64) {
-                    const int br = item / F4, q = item - br * F4;
-                    const int64_t r = row0 + wm * WTM + 32 * h + br, c = col0 + wn * WTN + 4 * q;
-                    if (r < p.rows && c < p.cols) {
-                        f32x4 *at = reinterpret_cast<f32x4 *>(band + br * EP_LD + 4 * q);
-                        f32x4 *to = reinterpret_cast<f32x4 *>(p.ep.acc + r * p.cols + c);
-                        f32x4 x = *at;
-                        if (p.ep.acc_mode == 2) {
-                            const f32x4 o = *to;
-                            x.x += o.x; x.y += o.y; x.z += o.z; x.w += o.w;
-                            *at = x;
+                    for (int item = lane; item < BANDS * 32 * F4; item += 64) {
+                        const int br = item / F4, q = item - br * F4;
+                        const int64_t r = row0 + wm * WTM + 32 * h + br, c = col0 + wn * WTN + 4 * q;
+                        if (r < p.rows && c < p.cols) {
+                            f32x4 *at = reinterpret_cast<f32x4 *>(band + br * EP_LD + 4 * q);
+                            f32x4 *to = reinterpret_cast<f32x4 *>(p.ep.acc + r * p.cols + c);
+                            f32x4 x = *at;
+                            if (decltype(plain)::value || p.ep.acc_mode == 2) {
+                                const f32x4 o = *to;
+                                x.x += o.x; x.y += o.y; x.z += o.z; x.w += o.w;
+                                *at = x;
+                            }
+                            if constexpr (decltype(plain)::value) *to = x;
+                            else store_through(to, x);
                         }
-                        store_through(to, x);
                     }
-                }
+                };
+                if (p.ep.acc_lines == 2) lines(std::true_type{});  // (added to)
+                else lines(std::false_type{});
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
