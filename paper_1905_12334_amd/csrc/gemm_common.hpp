@@ -44,7 +44,9 @@ struct Epilogue {
     float alpha;
     float *acc;
     int acc_mode;
-    int acc_lines;   // tile_epilogue: the FP32 result by a pass of its own ahead of the codes, past the L2 (1) or into it (2; see launch_mfma)
+    // tile_epilogue (see launch_mfma): the FP32 result by a pass of its own ahead of the codes, past the L2 (1) or
+    // into it (2); the codes into the L2
+    int acc_lines, codes_plain;
     uint8_t *out8;
     uint8_t *out8_t;
     int sr;
@@ -145,7 +147,7 @@ __device__ __forceinline__ uint32_t finish1(const Epilogue &ep, int64_t r, int64
 // conversions are out of line.
 // acc_done: v has been through ep.acc already.  kAlways: statistics without a test (see StatsAcc::add4_always), which gemm_shortk_kernel
 // alone is better off with (4096 x 4096 x 128 to nearest 35.8 us with it, 33.2 without; everywhere else the test is worth 2 to 6 %).
-// kThrough: the codes by store_through, for callers whose neighbouring lanes complete a line.
+// kThrough: the codes by store_through, unless ep.codes_plain.
 template <bool kAlways = false, bool kThrough = false>
 __device__ __forceinline__ void finish16(const Epilogue &ep, int64_t r, int64_t c, float v[16],
                                          StatsAcc &st, bool acc_done = false) {
