@@ -611,6 +611,11 @@ static mp8_status launch_mfma(GemmArgs ga, Epilogue ep, const Plan &pl, int64_t 
     // codes, 64 x 64 x 128 4.3 / 3.7, 128 x 512 x 256 5.0 / 4.2, 2048 x 2048 x 256 (16 MB) 13.8 / 12.0; 4096 x 4096 x 512 (64 MB) as fast,
     // 8192 x 8192 x 512 194 / 201.
     if (ep.acc_lines != 0 && acc_mode == 2 && rows * cols <= (int64_t)1 << 23) ep.acc_lines = 2;
+    // The codes of the complete epilogue of 64x64 tiles, whose waves store them 32 bytes of a line at a time, go past the L2 where tiles of a second
+    // round overlap with that, and where statistics follow them.  Past it / into it: beside an FP32 result 64 x 64 x 128 3.05 / 2.86, 512 x 512
+    // x 256 3.64 / 3.50; added to 3.83 / 3.65 and 4.48 / 4.32; stochastic 1024 x 1024 (256 tiles) 1.5 % longer, 1024 x 2048 2 % shorter; with statistics
+    // 3 % shorter (1024 x 512) to 6 % (1024 x 2048).
+    ep.codes_plain = pl.mfma && kTiles[pl.tile].bm * kTiles[pl.tile].bn == 64 * 64 && nblocks <= kCUs && (acc_mode != 0 || ep.stats == nullptr);
     if (nblocks > 0x7FFFFFFFLL) return MP8_ERR_UNSUPPORTED;
     if (validate_only) return MP8_OK;  // every check has passed; nothing is enqueued
 

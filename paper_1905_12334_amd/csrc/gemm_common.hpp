@@ -186,7 +186,7 @@ __device__ __forceinline__ void finish16(const Epilogue &ep, int64_t r, int64_t 
     if (!kAlways && ep.stats != nullptr && !padding) st.add<4, false>(y, pk);
     if (ep.out8 != nullptr) {
         u32x4 o = {pk[0], pk[1], pk[2], pk[3]};
-        if constexpr (kThrough) store_through(reinterpret_cast<u32x4 *>(ep.out8 + i0), o);
+        if (kThrough && !ep.codes_plain) store_through(reinterpret_cast<u32x4 *>(ep.out8 + i0), o);
         else *reinterpret_cast<u32x4 *>(ep.out8 + i0) = o;
     }
     if (ep.out8_t != nullptr) {

@@ -36,3 +36,17 @@ def run(mp8, rows, cols, kc, layout, alpha, accumulate, stats):  # noqa: F811
 @pytest.mark.parametrize("layout", [ROW, TN])
 def test_added_to(mp8, rows, cols, kc, layout):  # noqa: F811
     run(mp8, rows, cols, kc, layout, 2.0 ** -4, True, False)
+
+
+# one round of 64x64 tiles, and one tile more
+@pytest.mark.parametrize("rows,cols,kc", [(64, 64, 128), (1024, 1024, 256), (1088, 1024, 256), (512, 496, 400), (1088, 976, 400)])
+@pytest.mark.parametrize("accumulate,stats", [(False, False), (False, True), (True, False), (True, True)])
+def test_codes_of_64x64_tiles(mp8, rows, cols, kc, accumulate, stats):  # noqa: F811
+    import torch
+    once, a, b = run(mp8, rows, cols, kc, TN, 2.0 ** -5, accumulate, stats)
+    out, want = (torch.zeros(rows * cols, dtype=torch.uint8, device="cuda") for _ in range(2))
+    kw = dict(round=mp8.SR, seed=3, offset=9)
+    mp8.gemm_fp8(mp8.FWD, rows, cols, kc, a, b, out8=out, alpha=2.0 ** -5, flags=TN, stats=mp8.new_stats() if stats else None, **kw)
+    mp8.quantize_e5m2(once.view(rows, cols), want.view(rows, cols), scale=2.0 ** -5, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
