@@ -31,8 +31,7 @@ namespace mp8 {
 // multiplications wait for (a branch for the incomplete stage made the compiler wait there) / loads whose addresses every stage works
 // out / now: 256 x 1000 x 2048 forward 10.4 / 8.0 / 7.4 (tiles of 32 rows but for the first), backward data 6.5 / 5.3 / 5.2, one thread
 // per output element 639; 1500 x 1000 x 1500 11.8 / 12.0 / 11.3, b contraction-major 12.7 / 13.2 / 12.5, both 14.7 / 14.8 / 14.1; 500 x 2000 x 3000
-// 13.4 13.1 12.1, 15.7 13.8 13.4, 16.7 15.3 14.4.  A few tiles more than CUs, both operands contraction-major and more than 15 stages are what
-// the first form did better: 1100 x 1000 x 3000 21.9 / 24.2 / 23.3, 1300 x 1000 x 2003 17.3 / 18.5 / 17.7.
+// 13.4 13.1 12.1, 15.7 13.8 13.4, 16.7 15.3 14.4.  (Where only some CUs have two tiles, see `paced`.)
 // EPI_UPDATE: an unsplit weight gradient applies the master-weight update itself (columns a multiple of eight:
 // neighbouring lanes share random blocks), with the code of the other kernels' epilogues: no launch and no pass
 // over the gradient codes: 256 x 1000 x 2048 with momentum 13.7 -> 12.6 us; with the weights, the state
@@ -180,6 +179,16 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
         for (int q = 0; q < N; ++q) put(row(q), x[q]);
     };
 
+    // Some CUs have two workgroups and the others one: over a long contraction those run away from these, which then find nothing in the
+    // L2 any more of what all of them read.  Loads that are waited for, one operand at a time, keep both operands' readers together.  Both
+    // contraction-major, us, running free / so: 1100 x 1000 x 3000 23.2 / 21.9, x 9001 63 / 54, 1088 x 1024 x 17364 (aligned rows) 104 / 80,
+    // 1300 x 1000 x 4099 32 / 30, 1500 x 1000 x 9001 59 / 55; 129 x 7001 x 3000 24.5 / 25.3, x 9001 63 / 64.  Shorter ones are better off without
+    // (777 x 1333 x 2003 19.8 / 20.8), and so are those of more than two rounds (1500 x 1500 x 3000 33 / 37) and with a row-major a.
+    const bool paced = ATN && gridDim.x > 256 && gridDim.x <= 512 && p.ks_per >= 24;
+    auto pace = [&](bool on) {
+        if (paced && on) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    };
+
     // what this thread updates: four groups of four weights, 16 lanes side by side in a row of the tile
     auto group = [&](int q) {
         const int item = threadIdx.x + 256 * q;
@@ -222,7 +231,9 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
             }
             if (s < ks_end) {
                 load_stage(ATN, oa, s, xa);
+                pace(s > first);
                 load_stage(BTN, ob, s, xb);
+                pace(s > first);
             }
             if (s == first) continue;
             // the slabs are private to this wave: order its LDS writes before its reads
