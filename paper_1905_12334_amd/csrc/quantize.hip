@@ -125,7 +125,7 @@ struct FlatSplit {
 // The flat loop of one tensor for workgroup `block` (NT threads each).  In a whole pass all loads of a thread
 // are in flight before the first is used, without guards; the end of a run takes two groups per thread, then
 // one (guarded).
-template <bool kF16, bool kSR, bool kStats, int NT, bool kRounds = false>
+template <bool kF16, bool kSR, bool kStats, int NT, bool kRounds = false, bool kPlain = false>
 __device__ __forceinline__ void flat_body(const void *__restrict__ src, uint8_t *__restrict__ dst,
                                           int64_t n, float scale, int sat, uint64_t seed,
                                           uint64_t offset, mp8_stats *stats, int64_t block,
@@ -159,7 +159,8 @@ __device__ __forceinline__ void flat_body(const void *__restrict__ src, uint8_t 
                 // quarter of the bytes -- left in the 256 MB cache they were measured 7 % faster here and
                 // 11 us per step faster for the GEMM that follows.  Past the L2, see store_through: 128 x 2048 2.25 -> 2.09 us,
                 // 4096 x 2048 with statistics 6.97 -> 6.59, 16384 x 1024 12.8 -> 11.5
-                store_through(dst4 + g, pk[u]);
+                if constexpr (kPlain) dst4[g] = pk[u];
+                else store_through(dst4 + g, pk[u]);
             }
         }
         at += U * NT;
@@ -184,11 +185,11 @@ __device__ __forceinline__ void flat_body(const void *__restrict__ src, uint8_t 
     if constexpr (kStats) st.flush(stats, seen);
 }
 
-template <bool kF16, bool kSR, bool kStats, int NT, bool kRounds>
+template <bool kF16, bool kSR, bool kStats, int NT, bool kRounds, bool kPlain>
 __global__ __launch_bounds__(NT) void quantize_flat_kernel(const void *__restrict__ src, uint8_t *__restrict__ dst,
                                                            int64_t n, float scale, int sat, uint64_t seed,
                                                            uint64_t offset, mp8_stats *stats, const FlatSplit split) {
-    flat_body<kF16, kSR, kStats, NT, kRounds>(src, dst, n, scale, sat, seed, offset, stats, blockIdx.x, split);
+    flat_body<kF16, kSR, kStats, NT, kRounds, kPlain>(src, dst, n, scale, sat, seed, offset, stats, blockIdx.x, split);
 }
 
 // Several tensors in one launch: a step that quantises activations and errors (and whatever
@@ -628,10 +629,18 @@ static hipError_t launch_quantize(const void *src, uint8_t *dst, uint8_t *dst_t,
     const int64_t n = rows * cols;
     if (dst_t == nullptr) {
         const int64_t n4 = n >> 2;
+        // Codes that replace those a GEMM has just read: stores past the L2 clear the lines that the other XCDs still hold, and from about 4 MB on
+        // that takes longer than writing dirty lines back does (Q node and forward GEMM into one buffer, us, past / into the L2: 1835 x 256
+        // x 2048, 3.8 MB, 11.8 / 11.2, 2165 16.2 / 13.8, 2555 17.4 / 14.9, 3015 18.1 / 16.3, 3558, 7.3 MB, 17.2 / 17.6; 3110 x 144 x 1024, 3.2 MB, 10.0 / 9.9,
+        // 3670 10.7 / 11.3, 5111 15.4 / 13.0, 9909 18.4 / 19.2; training steps 3379 x 128 x 1728 with momentum 45.7 / 41.6, 3123 x 384 x 1600 46.5 / 43.4;
+        // the node alone 4.58 / 4.57 at 5.2 M).  Stochastic ones and those with statistics, which take longer than their stores, gain nothing.
+        constexpr bool kPlain = !kSR && !kStats;
+        const bool plain = n > (7 << 19) && n <= (13 << 19);
         auto launch = [&](auto threads, auto in_rounds, int64_t blocks, const FlatSplit &split) {
             constexpr int NT = decltype(threads)::value;
-            hipLaunchKernelGGL((quantize_flat_kernel<kF16, kSR, kStats, NT, decltype(in_rounds)::value>), dim3((unsigned)blocks),
-                               dim3(NT), 0, s, src, dst, n, scale, sat, seed, offset, stats, split);
+            hipLaunchKernelGGL((kPlain && plain ? quantize_flat_kernel<kF16, kSR, kStats, NT, decltype(in_rounds)::value, kPlain>
+                                                : quantize_flat_kernel<kF16, kSR, kStats, NT, decltype(in_rounds)::value, false>),
+                               dim3((unsigned)blocks), dim3(NT), 0, s, src, dst, n, scale, sat, seed, offset, stats, split);
         };
         auto runs = [&](auto threads, int64_t chunk) {
             launch(threads, std::false_type{}, std::max<int64_t>(1, (n4 + chunk - 1) / chunk), FlatSplit{chunk, 0, 0, 0});

@@ -57,6 +57,13 @@ def test_flat_run_lengths(mp8, n, rnd, with_stats):
     check(mp8, data(n, (1, n), False), rnd, False, with_stats)
 
 
+# to nearest without statistics the stores change at 7 * 2^19 and behind 13 * 2^19 elements
+@pytest.mark.parametrize("n", [7 * 2 ** 19, 7 * 2 ** 19 + 1, 7 * 2 ** 19 + 1027, 13 * 2 ** 19, 13 * 2 ** 19 + 1])
+@pytest.mark.parametrize("half", [False, True])
+def test_flat_stores(mp8, n, half):
+    check(mp8, data(n, (1, n), half), oracle.RNE, False, False)
+
+
 @pytest.mark.parametrize("shape", [(1, 1), (2, 3), (63, 65), (66, 127), (600, 450), (130, 2061), (517, 523), (2049, 2051), (2050, 2052), (2052, 2050)])
 @pytest.mark.parametrize("rnd", [oracle.RNE, oracle.SR])
 @pytest.mark.parametrize("half,with_stats", [(False, True), (True, False)])
