@@ -124,7 +124,9 @@ struct FlatSplit {
 
 // The flat loop of one tensor for workgroup `block` (NT threads each).  In a whole pass all loads of a thread
 // are in flight before the first is used, without guards; the end of a run takes two groups per thread, then
-// one (guarded).
+// one at a time (guarded), or, stochastic, what is left at once: with its random words a second pass takes longer than
+// one of two groups, whose lanes share the generator's blocks (us, one at a time / at once: 0.6 M elements 2.56 / 2.23, 1 M 2.73 / 2.35; with statistics
+// 0.6 M 3.17 / 2.91, 1.9 M 4.93 / 3.91, 6.2 M 8.39 / 7.28; to nearest the other way round, 3.5 M with statistics 4.16 / 4.30).
 template <bool kF16, bool kSR, bool kStats, int NT, bool kRounds = false, bool kPlain = false>
 __device__ __forceinline__ void flat_body(const void *__restrict__ src, uint8_t *__restrict__ dst,
                                           int64_t n, float scale, int sat, uint64_t seed,
@@ -175,7 +177,12 @@ __device__ __forceinline__ void flat_body(const void *__restrict__ src, uint8_t 
     end = at + split.chunk < n4 ? at + split.chunk : n4;
     while (at + kFlatUnroll * NT <= end) pass(std::integral_constant<int, kFlatUnroll>{}, std::false_type{});
     if (at + 2 * NT <= end) pass(std::integral_constant<int, 2>{}, std::false_type{});
-    while (at < end) pass(std::integral_constant<int, 1>{}, std::true_type{});
+    if constexpr (kSR) {
+        if (at + NT < end) pass(std::integral_constant<int, 2>{}, std::true_type{});
+        else if (at < end) pass(std::integral_constant<int, 1>{}, std::true_type{});
+    } else {
+        while (at < end) pass(std::integral_constant<int, 1>{}, std::true_type{});
+    }
     // ragged tail (< 4 elements)
     if (block == 0 && threadIdx.x < 4) {
         const int64_t i = (n4 << 2) + threadIdx.x;

@@ -64,6 +64,13 @@ def test_flat_stores(mp8, n, half):
     check(mp8, data(n, (1, n), half), oracle.RNE, False, False)
 
 
+# the guarded end of a run: one pass or two of 256 threads' groups, and of 1024 with statistics (runs of 64 r groups in 256 workgroups)
+@pytest.mark.parametrize("n,with_stats", [(4 * (2 ** 18 + 256 + d), False) for d in (-1, 0, 1, 255, 256, 257, 511)] +
+                         [(4 * 256 * 64 * r - 8, True) for r in (5, 7, 8, 9, 15, 16, 17, 31, 33, 47, 48, 49)])
+def test_stochastic_ends_of_runs(mp8, n, with_stats):
+    check(mp8, data(n, (1, n), False), oracle.SR, False, with_stats)
+
+
 @pytest.mark.parametrize("shape", [(1, 1), (2, 3), (63, 65), (66, 127), (600, 450), (130, 2061), (517, 523), (2049, 2051), (2050, 2052), (2052, 2050)])
 @pytest.mark.parametrize("rnd", [oracle.RNE, oracle.SR])
 @pytest.mark.parametrize("half,with_stats", [(False, True), (True, False)])
