@@ -183,8 +183,10 @@ __device__ __forceinline__ void gemm_any(const GemmArgs &p, const UpdateHook &up
     // L2 any more of what all of them read.  Loads that are waited for, one operand at a time, keep both operands' readers together.  Both
     // contraction-major, us, running free / so: 1100 x 1000 x 3000 23.2 / 21.9, x 9001 63 / 54, 1088 x 1024 x 17364 (aligned rows) 104 / 80,
     // 1300 x 1000 x 4099 32 / 30, 1500 x 1000 x 9001 59 / 55; 129 x 7001 x 3000 24.5 / 25.3, x 9001 63 / 64.  Shorter ones are better off without
-    // (777 x 1333 x 2003 19.8 / 20.8), and so are those of more than two rounds (1500 x 1500 x 3000 33 / 37) and with a row-major a.
-    const bool paced = ATN && gridDim.x > 256 && gridDim.x <= 512 && p.ks_per >= 24;
+    // (777 x 1333 x 2003 19.8 / 20.8), and so are those of more than two rounds (1500 x 1500 x 3000 33 / 37).  With a row-major a from
+    // some 7000 on: 1100 x 1000 x 4099 31 / 31, x 7008 41 / 37, x 8752 52 / 45, x 16016 92 / 76, 1500 x 1000 x 10000 56 / 51, x 10001 67 / 66;
+    // 777 x 1333 x 6001 44 / 45, 2000 x 1000 x 13001 86 / 90.  Both row-major: never (1100 x 1000 x 8752 44 / 44).
+    const bool paced = BTN && gridDim.x > 256 && gridDim.x <= 512 && p.ks_per >= (ATN ? 24 : 56);
     auto pace = [&](bool on) {
         if (paced && on) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     };
