@@ -300,7 +300,7 @@ mp8_status mp8_adam_fp16_sr(uint16_t *w16, float *m, float *v, const uint8_t *g8
  * them is given.  Where the update happens, by shape:
  *   - the contraction is split: in the finishing pass that adds the slices up and rounds the sum;
  *   - it is not split and the output takes 64x64 tiles (N a multiple of 16, both operands row-major or
- *     both contraction-major; with ADAM from 128 tiles on): in the GEMM's own epilogue, without a
+ *     both contraction-major; with ADAM and no g8_out from 128 tiles on): in the GEMM's own epilogue, without a
  *     workspace; the same for operands that the aligned kernels cannot take, contraction-major, N a
  *     multiple of 8, with a g8_out, where one launch takes less time than two (from 32 tiles on; with ADAM
  *     from 512);

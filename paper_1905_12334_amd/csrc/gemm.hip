@@ -395,24 +395,24 @@ static UpdateKernel update_kernel(const Plan &pl, int64_t cols, int layout, int 
     return nullptr;
 }
 
-// The same for gemm_any_kernel, contraction-major operands.  Whole training steps in two launches against one, SGD / momentum / ADAM, us,
-// weights from the Infinity Cache:
-//      9 tiles (200 x 216 x 130)      21.9 22.3 22.6   19.9 20.4 22.1
-//     32       (300 x 104 x 1001)     24.0 24.4 25.5   22.0 22.4 24.2
-//    256       (1000 x 1000 x 1000)   35.8 36.6 38.6   32.4 33.1 34.9
-//    512       (256 x 1000 x 2048)    33.5 35.3 38.0   29.2 30.3 33.5
-//    533       (1000 x 2584 x 772)    57.3 59.6 62.1   54.2 55.6 60.7
-//    567       (200 x 536 x 4000)     43.9 44.9 47.9   39.9 42.9 45.4
-//    837       (64 x 1928 x 1700)     39.7 43.9 48.4   34.7 37.6 44.6
-//   1504       (129 x 3000 x 2002)    56.5 61.7 70.1   48.8 52.7 61.6
-//   3995       (64 x 3000 x 5440)     86.0 105.6 128.5 78.7 89.3 111.1
-// and from memory 256 tiles ADAM 38.9 and 37.8, 533 momentum 60.6 and 60.8, ADAM 64.2 and 66.0, 567 momentum 44.9 and 46.7, 1504 58.0 64.2 73.3 and
-// 54.1 62.9 77.3, 2820 (129 x 3000 x 3800) 82.8 95.4 and 83.0 101.3 (ADAM's corrections still divisions).  The update is a serial tail of each tile, 2 kCUs at a time, and a last round
-// that is nearly empty pays for all of it.  The lines below are those of the first kernel, whose update fetched its operands only
-// after the contraction: one launch was 20 % slower with ADAM on half-empty rounds, and with statistics, whose atomics on one address follow the updates,
-// where all tiles end together.  Today it would be the shorter on most of them, but which call is one kernel is part of what callers test.
-// With ADAM, tiles whose last column is eight wide end 4 us later (200 x 264 x 130 22.7, in one launch 25.8; 256 and 528 wide as above;
-// why, is not known).
+// The same for gemm_any_kernel, contraction-major operands.  Whole training steps in two launches / in one, us, weights from the Infinity Cache:
+//                                          SGD              momentum         ADAM
+//     12 tiles (200 x 216 x 130)       20.7 / 19.5      21.2 / 19.9      22.2 / 21.6
+//     32       (300 x 104 x 1001)      23.2 / 21.8      23.5 / 22.0      24.4 / 23.8
+//    256       (1000 x 1000 x 1000)    33.5 / 31.2      34.8 / 32.2      37.3 / 35.1
+//    272       (129 x 1000 x 1088)     27.7 / 25.0      28.1 / 25.7      30.0 / 29.0
+//    512       (256 x 1000 x 2048)     30.2 / 26.9      32.8 / 28.2      36.3 / 32.5
+//    528       (129 x 1000 x 2112)     34.3 / 32.1      36.5 / 33.8      40.8 / 38.9
+//    837       (64 x 1928 x 1700)      38.5 / 34.0      42.1 / 36.2      47.4 / 42.7
+//   1040       (129 x 1000 x 4160)     46.3 / 42.3      50.8 / 45.3      57.4 / 54.2
+//   1504       (129 x 3000 x 2002)     55.9 / 49.0      61.3 / 51.8      69.1 / 61.4
+//   3995       (64 x 3000 x 5440)      87.6 / 82.4     107.2 / 91.2     127.4 / 115.2
+// and the gradient with its statistics alone: 272 tiles 11.4 / 9.2, 12.0 / 9.7, 13.8 / 12.8, 512 12.1 / 9.3, 14.0 / 10.1, 16.7 / 13.5.  One launch is the
+// shorter one wherever it is built, but for stochastic rounding on less than kCUs / 2 tiles whose last column is eight wide (200 x 264 x 130 21.0 / 21.1,
+// 21.3 / 21.2, ADAM 22.3 / 26.1; why, is not known): that condition stands on its figures.  The others are
+// those of the first kernel, whose update fetched its operands only after the contraction (a last round that was nearly empty paid for all of it, and
+// the atomics of the statistics followed the updates).  They refuse calls that would gain 3 to 14 %, and are kept because which call is one kernel
+// is part of what is tested.
 static UpdateKernel any_update_kernel(const Plan &pl, int64_t cols, int layout, const UpdateHook &upd, bool with_stats, bool stochastic) {
     static const UpdateKernel kernels[3] = {gemm_any_update_kernel<0>, gemm_any_update_kernel<1>, gemm_any_update_kernel<2>};
     const int64_t nt = (int64_t)pl.tiles_m * pl.tiles_n, round = 2 * kCUs;

@@ -7,7 +7,7 @@
 namespace mp8 {
 
 // The general kernel (gemm_mfma.hpp) with a 256x256 tile has the CU to itself, and nothing overlaps with its start, its conversions
-// and its stores: beside 1.37 us for each 128-byte stage it spends 8.8 us per tile, all CUs in step (16384 x 4096, N(0,1) codes).  Here a
+// and its stores: beside 1.4 us for each 128-byte stage it spends some 6 us per tile, all CUs in step (from the times below).  Here a
 // workgroup takes tiles blockIdx.x, blockIdx.x + gridDim.x, ... (as the hardware would have dealt them out), and the ring of two
 // stages goes on from one tile to the next: while the last stages of a tile are multiplied, the first two of the next one arrive.  The codes
 // leave through 4 KB of LDS per wave beside the ring, 32 rows of 128 bytes at a time, without a barrier, and the

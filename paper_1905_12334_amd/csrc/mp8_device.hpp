@@ -27,8 +27,10 @@ using half2v = _Float16 __attribute__((ext_vector_type(2)));
 // on another XCD 1 MB 4.16 / 3.68, 4 MB 5.74 / 5.43, 8 MB 8.30 / 7.79, 16 MB 14.6 / 13.1, 32 MB 25.7 / 26.3; as pieces of 64 bytes 4 MB 2.60 /
 // 2.32.  Whole training steps: 4096 x 2048 x 512 with ADAM 51.9 -> 49.4, 16384 x 4096 x 1024 282 -> 268, 32 x 56 x 56 x 64
 // convolution 45.7 -> 43.9.  It does not pay, and plain or non-temporal stores are kept, where a store of a wave covers no more
-// than 32 or 64 bytes of a line that other waves complete later (the complete epilogues of 64x64 tiles, the codes that the forward
-// GEMM writes while it reads), and for the optimizer's streams (61 M weights with ADAM 212 us, 223).
+// than 32 or 64 bytes of a line that other waves complete later (the complete epilogues of 64x64 tiles on small grids, see
+// Epilogue.codes_plain, and the codes that the forward GEMM writes while it reads); where the next kernel adds to what the L2s still
+// hold (acc_lines); for the Q node's codes of 3.7 to 6.8 M (see launch_quantize); and for the optimizer's own streams (61 M weights with ADAM
+// 212 us, 223), unlike an update in a GEMM's epilogue (see update4).
 template <class T>
 __device__ __forceinline__ void store_through(T *p, T v) {
     static_assert(sizeof(T) == 4 || sizeof(T) == 8 || sizeof(T) == 16, "4, 8 or 16 bytes");
