@@ -640,8 +640,10 @@ static hipError_t launch_quantize(const void *src, uint8_t *dst, uint8_t *dst_t,
         // that takes longer than writing dirty lines back does (Q node and forward GEMM into one buffer, us, past / into the L2: 1835 x 256
         // x 2048, 3.8 MB, 11.8 / 11.2, 2165 16.2 / 13.8, 2555 17.4 / 14.9, 3015 18.1 / 16.3, 3558, 7.3 MB, 17.2 / 17.6; 3110 x 144 x 1024, 3.2 MB, 10.0 / 9.9,
         // 3670 10.7 / 11.3, 5111 15.4 / 13.0, 9909 18.4 / 19.2; training steps 3379 x 128 x 1728 with momentum 45.7 / 41.6, 3123 x 384 x 1600 46.5 / 43.4;
-        // the node alone 4.58 / 4.57 at 5.2 M).  Stochastic ones and those with statistics, which take longer than their stores, gain nothing.
-        constexpr bool kPlain = !kSR && !kStats;
+        // the node alone 4.58 / 4.57 at 5.2 M).  Half-precision sources leave less to hide the write-back behind (alone 4.1 M 2.59 / 2.91, 6.4 M 3.01 / 3.81).
+        // With statistics the node itself would gain from 4.2 to 8.0 M (6.0 M 6.97 / 6.39), but the GEMMs behind it lose more (training
+        // steps 15390 x 512 x 128 33.9 / 35.5, 3759 x 1792 x 128 39.2 / 41.1, 100 of them 1 % longer).  Stochastic ones gain nothing.
+        constexpr bool kPlain = !kF16 && !kSR && !kStats;
         const bool plain = n > (7 << 19) && n <= (13 << 19);
         auto launch = [&](auto threads, auto in_rounds, int64_t blocks, const FlatSplit &split) {
             constexpr int NT = decltype(threads)::value;
