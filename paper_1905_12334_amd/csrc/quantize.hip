@@ -126,7 +126,8 @@ struct FlatSplit {
 // are in flight before the first is used, without guards; the end of a run takes two groups per thread, then
 // one at a time (guarded), or, stochastic, what is left at once: with its random words a second pass takes longer than
 // one of two groups, whose lanes share the generator's blocks (us, one at a time / at once: 0.6 M elements 2.56 / 2.23, 1 M 2.73 / 2.35; with statistics
-// 0.6 M 3.17 / 2.91, 1.9 M 4.93 / 3.91, 6.2 M 8.39 / 7.28; to nearest the other way round, 3.5 M with statistics 4.16 / 4.30).
+// 0.6 M 3.17 / 2.91, 1.9 M 4.93 / 3.91, 6.2 M 8.39 / 7.28; half-precision sources below 0.2 M 1.92 / 1.95, with statistics
+// 2.13 / 2.20; to nearest the other way round, 3.5 M with statistics 4.16 / 4.30).
 template <bool kF16, bool kSR, bool kStats, int NT, bool kRounds = false, bool kPlain = false>
 __device__ __forceinline__ void flat_body(const void *__restrict__ src, uint8_t *__restrict__ dst,
                                           int64_t n, float scale, int sat, uint64_t seed,
